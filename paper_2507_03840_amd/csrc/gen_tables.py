@@ -432,14 +432,144 @@ def generate():
     return "\n".join(out) + "\n"
 
 
+# ------------------------------------------------------------------ node-wise form of the SO(2) message sums
+def so2_beta(lo, li, L):
+    """beta[m], m = 0..4:  D_lo^T P^m D_li = sum_L beta_L^m sum_M C^(lo li L)[:, :, M] Yhat_LM(r_hat), where P^m has ones
+    at (+m, +m) and (-m, -m); for odd lo + li + L the same with Q^m, which has -1 at (+m, -m) and +1 at (-m, +m).
+    (Both matrices commute with rotations about z, so the product depends on r_hat only; at r_hat = z, where
+    Yhat_LM = sqrt(2 L + 1) delta_M0, the orthogonality of the coupling tensors gives beta.)"""
+    C0 = coupling_real(lo, li, L)[:, :, L]
+    beta = np.zeros(LMAX + 1)
+    for m in range(min(lo, li) + 1):
+        F = np.zeros_like(C0)
+        if (lo + li + L) % 2 == 0:
+            F[lo + m, li + m] = F[lo - m, li - m] = 1.0
+        elif m:
+            F[lo + m, li - m], F[lo - m, li + m] = -1.0, 1.0
+        beta[m] = (F * C0).sum() / sqrt(2 * L + 1)
+    return beta
+
+
+def so2_harmonic_constants():
+    """start[m], a[l][m], b[l][m]: Pbar_m^m = start, Pbar_l^m = a z Pbar_{l-1}^m - b Pbar_{l-2}^m;
+    Yhat_{l,+m} / Yhat_{l,-m} = Pbar_l^m(z) times the real / imaginary part of (x + i y)^m."""
+    n = 2 * LMAX + 1
+    start, a, b = np.zeros(n), np.zeros((n, n)), np.zeros((n, n))
+    for m in range(n):
+        v = sqrt(2 * m + 1.0) * (sqrt(2.0) if m else 1.0)
+        for k in range(1, m + 1):
+            v *= (2 * k - 1) / sqrt((2 * k - 1) * (2 * k))
+        start[m] = v
+        for l in range(m + 1, n):
+            a[l, m] = sqrt((4.0 * l * l - 1.0) / (l * l - m * m))
+            if l > m + 1:
+                b[l, m] = sqrt((2.0 * l + 1) * ((l - 1.0) ** 2 - m * m) / ((2.0 * l - 3) * (l * l - m * m)))
+    return start, a, b
+
+
+def eval_harmonics(v):
+    start, a, b = so2_harmonic_constants()
+    n = len(start)
+    out = np.zeros((len(v), n * n))
+    for m in range(n):
+        P = {m: np.full(len(v), start[m])}
+        for l in range(m + 1, n):
+            P[l] = a[l, m] * v[:, 2] * P[l - 1] - b[l, m] * P.get(l - 2, 0.0)
+        w = (v[:, 0] + 1j * v[:, 1]) ** m
+        for l in range(m, n):
+            out[:, l * l + l + m] = P[l] * w.real
+            if m:
+                out[:, l * l + l - m] = P[l] * w.imag
+    return out
+
+
+def check_so2_path_form(Jm):
+    """The path form against rotation matrices, and the harmonics against scipy's."""
+    rng = np.random.default_rng(11)
+    v = rng.standard_normal((3, 3))
+    v[2] = (0.0, 0.0, -1.0)
+    v /= np.linalg.norm(v, axis=1, keepdims=True)
+    Y = eval_harmonics(v)
+    for l in range(2 * LMAX + 1):
+        assert np.allclose(Y[:, l * l:(l + 1) ** 2], sqrt(4 * pi) * real_sh(l, v), atol=1e-12)
+    for q in range(3):
+        x, y, z = v[q]
+        phi, theta = np.arctan2(y, x), np.arctan2(sqrt(x * x + y * y), z)
+        D = [Jm[l].T @ z_block(l, -theta) @ Jm[l] @ z_block(l, -phi) for l in range(LMAX + 1)]
+        for lo in range(LMAX + 1):
+            for li in range(LMAX + 1):
+                for m in range(min(lo, li) + 1):
+                    for odd in (0, 1):
+                        F = np.zeros((2 * lo + 1, 2 * li + 1))
+                        if odd == 0:
+                            F[lo + m, li + m] = F[lo - m, li - m] = 1.0
+                        elif m:
+                            F[lo + m, li - m], F[lo - m, li + m] = -1.0, 1.0
+                        got = sum(so2_beta(lo, li, L)[m] * coupling_real(lo, li, L) @ Y[q, L * L:(L + 1) ** 2]
+                                  for L in range(abs(lo - li), lo + li + 1) if (lo + li + L) % 2 == odd)
+                        assert np.allclose(D[lo].T @ F @ D[li], got, atol=1e-11), (lo, li, m, odd)
+
+
+def generate_so2():
+    """so2_node_gen.inc: harmonics to degree 2 LMAX, path weights beta, and the coupling of a harmonic of degree L with
+    a feature block of degree li to every degree lo, one straight run of multiply-adds per (li, L)."""
+    Jm = {l: (np.ones((1, 1)) if l == 0 else j_matrix(l)) for l in range(LMAX + 1)}
+    check_so2_path_form(Jm)
+    n = 2 * LMAX + 1
+    start, a, b = so2_harmonic_constants()
+    out = ["// GENERATED by gen_tables.py -- do not edit.", "#pragma once", "",
+           f"#define SO2N_NL {n}   // harmonics of degree 0 .. SO2N_NL - 1"]
+    row = lambda r: "{" + ", ".join(f32(x) for x in r) + "}"
+    out.append(f"static constexpr float SO2N_START[{n}] = {row(start)};")
+    for name, M in (("A", a), ("B", b)):
+        out.append(f"static constexpr float SO2N_{name}[{n}][{n}] = {{")
+        out += ["  " + row(M[l]) + "," for l in range(n)]
+        out.append("};")
+    out.append("// beta[lo][li][L - |lo - li|][m]")
+    out.append(f"static __device__ const float SO2N_BETA[{LMAX + 1}][{LMAX + 1}][{n}][{LMAX + 1}] = {{")
+    for lo in range(LMAX + 1):
+        out.append("  {")
+        for li in range(LMAX + 1):
+            rows = [so2_beta(lo, li, L) for L in range(abs(lo - li), lo + li + 1)]
+            rows += [np.zeros(LMAX + 1)] * (n - len(rows))
+            out.append("    {" + ", ".join(row(r) for r in rows) + "},")
+        out.append("  },")
+    out.append("};")
+    out.append("// o[lo * lo + lo + m_o] += sum over M, m_i of C^(lo li L)[m_o][m_i][M] v_M[li + m_i] for every lo <= LMAX that li")
+    out.append("// and L couple to; row(L + M, v) supplies v_M.  The next row is requested before the products of the current one,")
+    out.append("// and no further ahead: left to itself the compiler fetches all of them first and runs out of registers.")
+    out.append("template <int LMAX, int LI, int L> struct So2Couple;")
+    for li in range(LMAX + 1):
+        for L in range(0, LMAX + li + 1):
+            los = [lo for lo in range(LMAX + 1) if abs(lo - li) <= L <= lo + li]
+            C = {lo: coupling_real(lo, li, L) for lo in los}
+            out.append(f"template <int LMAX> struct So2Couple<LMAX, {li}, {L}> {{")
+            out.append("  template <class R> __device__ __forceinline__ static void run(R&& row, float* o) {")
+            out.append(f"    float v0[{2 * li + 1}]" + (f", v1[{2 * li + 1}];" if L else ";"))
+            out.append("    row(0, v0);")
+            for M in range(2 * L + 1):
+                v = f"v{M & 1}"
+                if M < 2 * L:
+                    out.append(f"    row({M + 1}, v{1 - (M & 1)});")
+                for lo in los:
+                    t = [f"o[{lo * lo + mo}] += {f32(C[lo][mo, mi, M])} * {v}[{mi}];" for mi in range(2 * li + 1)
+                         for mo in range(2 * lo + 1) if C[lo][mo, mi, M] != 0.0]
+                    if t:
+                        out.append(f"    if constexpr ({lo} <= LMAX) {{ {' '.join(t)} }}")
+                out.append("    __builtin_amdgcn_sched_barrier(0);")
+            out.append("  }")
+            out.append("};")
+    return "\n".join(out) + "\n"
+
+
 def main():
     here = os.path.dirname(os.path.abspath(__file__))
     target = sys.argv[1] if len(sys.argv) > 1 else os.path.join(here, "egnn_gen.inc")
-    text = generate()
-    if not os.path.exists(target) or open(target).read() != text:
-        with open(target, "w") as f:
-            f.write(text)
-    print(f"wrote {target} ({len(text.splitlines())} lines)")
+    for path, text in ((target, generate()), (os.path.join(os.path.dirname(target), "so2_node_gen.inc"), generate_so2())):
+        if not os.path.exists(path) or open(path).read() != text:
+            with open(path, "w") as f:
+                f.write(text)
+        print(f"wrote {path} ({len(text.splitlines())} lines)")
 
 
 if __name__ == "__main__":

@@ -17,10 +17,13 @@
 //                          192 columns per workgroup: a row of A is fetched and cut once for all its column blocks;
 //   4. so2_scatter_kernel  one workgroup per destination node, lane = (edge slot, channel): m-major rows of Y back to
 //                          (l, m) order, rotated back, times f_c, summed; slots added in fixed order (no atomics).
+// The plain sum of messages mixes its channels per node instead where nodes have enough edges (so2_node.hip); this per-edge
+// form serves sparse graphs and the two blocks, whose messages hold a tensor of the edge's own or are not summed.
 #include <type_traits>
 #include "egnn_internal.h"
 #include "bond_frame.h"
 #include "stream_gemm.h"
+#include "so2_node.h"
 
 struct So2Bufs {
   float* A[5];
@@ -591,6 +594,19 @@ static int so2_transform(egnn_ctx* ctx, const egnn_graph* g, const float* pos, c
   return EGNN_OK;
 }
 
+// Whether the message sum mixes channels per node (so2_node.hip): what that costs per node has to be worth the edges' part
+// of the per-edge products.  3,000 nodes, us per call per edge -> per node: lmax 4, 32 channels, 14.9 edges a node 350 -> 427,
+// 22.6 536 -> 416, 37.8 694 -> 433; lmax 3, 64 channels, 14.9 521 -> 464; lmax 2, 16 channels, 9.5 82 -> 88, 14.9 121 -> 87.
+// Its buffers must fit the workspace the caller was asked for (about 15 edges a node; many halo rows may not), and byte
+// offsets of feature rows 32 bits.
+#define SO2N_MIN_DEGREE 20
+static bool so2_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
+  const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels * 4;
+  return g->n_owned > 0 && g->n_edges >= (int64_t)SO2N_MIN_DEGREE * g->n_owned && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
+         so2_a256((size_t)g->n_edges * 16) + so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, true, nullptr, nullptr) <=
+             so2_ws(ctx, g->n_edges, false, false, nullptr, nullptr, nullptr, nullptr, nullptr);
+}
+
 static int so2_scatter(egnn_ctx* ctx, const egnn_graph* g, const So2Call& call, const float* alpha, float scale, float* a,
                        hipStream_t st) {
   if (g->n_owned == 0) return EGNN_OK;
@@ -619,9 +635,18 @@ extern "C" int egnn_so2_message_sum(egnn_ctx* ctx, const egnn_graph* g, const fl
   int rc = so2_check(ctx, g, ws, ws_bytes, false, "so2_message_sum");
   if (rc) return rc;
   hipStream_t st = (hipStream_t)stream;
+  const float scale = 1.0f / sqrtf(ctx->desc.agg_norm);
+  if (so2_use_nodes(ctx, g)) {
+    So2nCall c;
+    float* rhat_d = (float*)ws;
+    so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, true, (char*)ws + so2_a256((size_t)g->n_edges * 16), &c);
+    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, 64, 0, st))) return rc;
+    if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st))) return rc;
+    return so2n_message_sum(ctx, g, rhat_d, x, W_e, W_so2, scale, a, c, st);
+  }
   So2Call call;
   if ((rc = so2_transform(ctx, g, pos, box, x, W_e, false, W_so2, ws, &call, st))) return rc;
-  return so2_scatter(ctx, g, call, nullptr, 1.0f / sqrtf(ctx->desc.agg_norm), a, st);
+  return so2_scatter(ctx, g, call, nullptr, scale, a, st);
 }
 
 extern "C" int egnn_edge_embed_init(egnn_ctx* ctx, const egnn_graph* g, const float* pos, const float box[3],
@@ -1365,6 +1390,17 @@ static int so2_backward_check(egnn_ctx* ctx, const egnn_graph* g, const void* ws
   return EGNN_OK;
 }
 
+// As so2_use_nodes, per node of any kind: the sums over outgoing edges are taken for the halo nodes as well.  Per edge -> per
+// node, lmax 4, 32 channels: 7.4 edges a node 896 -> 895 us, 12.4 1247 -> 1227, 21.1 1807 -> 1269; lmax 3, 64 channels: 7.4
+// 1200 -> 1278, 12.4 1714 -> 1319.
+#define SO2N_MIN_DEGREE_BACKWARD 12
+static bool so2_use_nodes_backward(const egnn_ctx* ctx, const egnn_graph* g) {
+  const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels * 4;
+  return g->n_owned > 0 && g->n_edges >= (int64_t)SO2N_MIN_DEGREE_BACKWARD * g->n_total && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
+         so2_a256((size_t)g->n_edges * 16) + so2n_backward_carve(ctx, g->n_owned, g->n_total, nullptr, nullptr) <=
+             so2_bwd_ws(ctx, g->n_edges, g->n_owned, false, false, nullptr, nullptr);
+}
+
 extern "C" int egnn_so2_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t* col_ptr,
                                              const int32_t* perm, const float* pos, const float box[3], const float* x,
                                              const float* W_e, const float* W_so2, const float* da, float* dx,
@@ -1384,6 +1420,15 @@ extern "C" int egnn_so2_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g,
     if ((rc = egnn_launch_fill_int(ctx, (int*)dx, (long)g->n_total * D * E, 0, st))) return rc;
     if ((rc = egnn_launch_fill_int(ctx, (int*)dW_e, (long)E * n_rbf, 0, st))) return rc;
     return egnn_launch_fill_int(ctx, (int*)dW_so2, (long)so2_w_offset(lmax, E, lmax + 1), 0, st);
+  }
+  if (so2_use_nodes_backward(ctx, g)) {
+    So2nCall c;
+    float* rhat_d = (float*)ws;
+    so2n_backward_carve(ctx, g->n_owned, g->n_total, (char*)ws + so2_a256((size_t)n * 16), &c);
+    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, 64, 0, st))) return rc;
+    if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st))) return rc;
+    return so2n_message_sum_backward(ctx, g, col_ptr, perm, rhat_d, x, W_e, W_so2, da, 1.0f / sqrtf(ctx->desc.agg_norm), dx, dW_e,
+                                     dW_so2, c, st);
   }
   So2Call call;
   if ((rc = so2_transform(ctx, g, pos, box, x, W_e, false, W_so2, ws, &call, st, false))) return rc;

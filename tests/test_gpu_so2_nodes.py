@@ -1,0 +1,94 @@
+"""SO(2) message sums whose channels are mixed per node: sizes at which the gathering kernel changes behaviour."""
+import numpy as np
+import pytest
+
+from oracle import so2_oracle as S
+from paper_2507_03840_amd import synth
+from tests import gpu_util as U
+
+pytestmark = pytest.mark.gpu
+
+# Operands are cut to 22 bits twice (harmonics x features, coupled sums x weights), relative error 2^-22 per operand and
+# product at most, four operands: 4 * 2.4e-7; as much again for the 32-bit sums over up to 300 edges and 3,300 products.
+TOL = 2e-6
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2507_03840_amd import binding
+    binding.load_library()
+    return binding
+
+
+def case(lmax, E, n, n_owned, n_rbf):
+    """Every atom within the cutoff of every other: degree n - 1."""
+    w = synth.small_cluster(n, n_owned, lmax, E, n_rbf, 30.0, 300 + n)
+    g = U.oracle_graph(w)
+    assert len(g[0]) == n_owned * (n - 1)
+    rng = np.random.default_rng([n, lmax, E])
+    x = synth.node_features(rng, w.n_total, lmax, E)
+    W_e, W0, Wr, Wi = synth.so2_weights(rng, lmax, E, n_rbf)
+    return w, g, x, W_e, W0, Wr, Wi
+
+
+@pytest.mark.parametrize("lmax,E,n,n_owned,n_rbf", [
+    # around a step of 16 edges and the smallest degree of this route; one node, ragged numbers of nodes
+    (4, 32, 25, 1, 2), (4, 32, 32, 9, 16), (4, 32, 33, 31, 16), (4, 32, 34, 5, 31),
+    # around a batch of 256 staged edges
+    (4, 32, 256, 3, 16), (4, 32, 257, 2, 32), (4, 32, 258, 3, 16), (2, 32, 300, 4, 8),
+    # every degree and slice width (a partial tile of columns at 0/8, 0/16, 2/8, 2/16, 4/8, 4/16), several slices
+    (0, 8, 40, 33, 5), (0, 16, 40, 8, 6), (0, 32, 30, 7, 6), (1, 8, 40, 9, 6), (1, 16, 33, 11, 6), (1, 64, 40, 9, 6),
+    (2, 8, 30, 17, 6), (2, 16, 41, 16, 6), (3, 8, 29, 10, 6), (3, 16, 65, 10, 6), (3, 32, 49, 10, 6), (4, 8, 40, 13, 6),
+    (4, 16, 47, 12, 6), (4, 64, 48, 11, 16), (3, 128, 31, 9, 8), (4, 128, 30, 5, 16)])
+def test_message_sum_per_node(B, lmax, E, n, n_owned, n_rbf):
+    import torch
+    print("case", lmax, E, n, n_owned, n_rbf, flush=True)
+    w, g, x, W_e, W0, Wr, Wi = case(lmax, E, n, n_owned, n_rbf)
+    agg = 7.0
+    ref = S.so2_message_sum(g, w.pos, w.box, x, W_e, W0, Wr, Wi, lmax, E, n_rbf, w.r_cut, agg)
+    m = B.Egnn(lmax, E, n_rbf, w.r_cut, agg)
+    graph = m.egnn_nlist(B.to_device(w.pos), n_owned, w.box, w.pbc)
+    args = (graph, B.to_device(w.pos), w.box, B.to_device(x), B.to_device(W_e), B.to_device(S.so2_pack(W0, Wr, Wi)))
+    # the workspace holds garbage at first: nothing of it may reach the result
+    ws = torch.full((m.egnn_so2_workspace_bytes(graph.n_edges),), 0xFF, dtype=torch.uint8, device="cuda")
+    a = m.egnn_so2_message_sum(*args, ws).cpu().numpy()
+    e = U.rel_err(a, ref)
+    print(f"  {graph.n_edges} edges, rel err {e:.2e}", flush=True)
+    assert e < TOL
+    assert np.array_equal(a, m.egnn_so2_message_sum(*args, ws).cpu().numpy())
+
+
+# Weight gradients are differences of sums over all edges: the fp32 rounding of the terms enters with the ratio of their
+# size to the result's, a few times at these shapes.
+TOL_BWD = 5e-6
+
+
+@pytest.mark.parametrize("lmax,E,n,n_owned,n_rbf", [
+    (4, 32, 34, 31, 16), (4, 32, 40, 28, 31), (4, 32, 270, 30, 16), (0, 8, 40, 33, 5), (0, 32, 30, 29, 6), (1, 8, 40, 30, 6),
+    (1, 64, 41, 36, 6), (2, 16, 51, 49, 2), (2, 32, 47, 47, 32), (3, 8, 33, 30, 6), (3, 32, 49, 40, 6), (4, 8, 40, 33, 6),
+    (4, 16, 35, 33, 6), (4, 64, 36, 31, 16), (3, 128, 31, 29, 8), (4, 128, 30, 27, 16)])
+def test_message_sum_backward_per_node(B, lmax, E, n, n_owned, n_rbf):
+    import torch
+    from tests.test_gpu_so2_backward import check, unpack
+    print("case", lmax, E, n, n_owned, n_rbf, flush=True)
+    assert n_owned * (n - 1) >= 24 * n     # (otherwise the per-edge route)
+    w, g, x, W_e, W0, Wr, Wi = case(lmax, E, n, n_owned, n_rbf)
+    agg = 7.0
+    da = np.random.default_rng(n).standard_normal((n_owned, (lmax + 1) ** 2, E)).astype(np.float32)
+    ref = S.so2_message_sum_backward(g, w.pos, w.box, x, W_e, W0, Wr, Wi, lmax, E, n_rbf, w.r_cut, agg, da)
+    m = B.Egnn(lmax, E, n_rbf, w.r_cut, agg)
+    graph = m.egnn_nlist(B.to_device(w.pos), n_owned, w.box, w.pbc)
+    ws = torch.full((max(m.egnn_so2_backward_workspace_bytes(graph.n_edges, n_owned),
+                         m.egnn_backward_workspace_bytes(graph.n_edges, n_owned, n)),), 0xFF, dtype=torch.uint8, device="cuda")
+    col_ptr, perm = m.egnn_graph_transpose(graph, ws)
+    args = (graph, col_ptr, perm, B.to_device(w.pos), w.box, B.to_device(x), B.to_device(W_e),
+            B.to_device(S.so2_pack(W0, Wr, Wi)), B.to_device(da))
+    ws.fill_(0xFF)
+    dx, dW_e, dW = m.egnn_so2_message_sum_backward(*args, ws)
+    g0, gr, gi = unpack(dW.cpu().numpy(), lmax, E)
+    got, want = dict(dx=dx.cpu().numpy(), dW_e=dW_e.cpu().numpy(), dW0=g0), dict(dx=ref[0], dW_e=ref[1], dW0=ref[2])
+    for i in range(lmax):
+        got[f"dWr{i + 1}"], got[f"dWi{i + 1}"], want[f"dWr{i + 1}"], want[f"dWi{i + 1}"] = gr[i], gi[i], ref[3][i], ref[4][i]
+    print(f"  {graph.n_edges} edges, worst rel err {check(got, want, TOL_BWD):.2e}", flush=True)
+    again = m.egnn_so2_message_sum_backward(*args, ws)
+    assert all(torch.equal(a, b) for a, b in zip((dx, dW_e, dW), again))
