@@ -23,14 +23,36 @@ __global__ void fill_src_kernel(const int* __restrict__ src, long n_edges, const
 }
 
 // One wavefront per source: rank sort of its bucket (ascending edge id = ascending destination), so the
-// order in which the reverse pass adds up the edges of a source is fixed.
+// order in which the reverse pass adds up the edges of a source is fixed.  The bucket is compared from LDS (from memory, one
+// word at a time for every lane, it took 173 instead of 45 us at 20,000 sources and 2.35 million edges); longer ones than
+// SORT_LDS from memory.
+#define SORT_LDS 1024
 __global__ __launch_bounds__(256) void sort_bucket_kernel(const int* __restrict__ col_ptr,
                                                           const int* __restrict__ bucket, int* __restrict__ perm,
                                                           int n_total) {
-  const int lane = threadIdx.x & 63;
-  const int i = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (i >= n_total) return;
-  const int c0 = col_ptr[i], c1 = col_ptr[i + 1];
+  __shared__ int4 s_bucket[4][SORT_LDS / 4];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int i = blockIdx.x * 4 + wave;
+  const int c0 = i < n_total ? col_ptr[i] : 0, c1 = i < n_total ? col_ptr[i + 1] : 0;
+  const int n = c1 - c0;
+  if (n <= SORT_LDS) {
+    int* mine = reinterpret_cast<int*>(s_bucket[wave]);
+    for (int a = lane; a < (n + 3) / 4 * 4; a += 64) mine[a] = a < n ? bucket[c0 + a] : 2147483647;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+    for (int a = lane; a < n; a += 64) {
+      const int e = mine[a];
+      int rank = 0;
+#pragma unroll 4
+      for (int b = 0; b < (n + 3) / 4; ++b) {
+        const int4 v = s_bucket[wave][b];
+        rank += (v.x < e ? 1 : 0) + (v.y < e ? 1 : 0) + (v.z < e ? 1 : 0) + (v.w < e ? 1 : 0);
+      }
+      perm[c0 + rank] = e;
+    }
+    return;
+  }
   for (int a = c0 + lane; a < c1; a += 64) {
     const int e = bucket[a];
     int rank = 0;

@@ -19,8 +19,9 @@
 // have an absolute sum of 100; it grows like the 4.7th power of that sum, so a device-side switch (rg_route_kernel)
 // leaves the work to the exact route beyond 256, where it would pass 1e-6.
 //
-// Determinism: the edges of an interval are visited in ascending edge id (a counting sort by interval with integer
-// atomics, then a rank sort inside each interval), every sum has a fixed order, no floating-point atomics.
+// Determinism: the edges of an interval are visited in ascending edge id (a stable counting sort by interval), every sum
+// has a fixed order, no floating-point atomics.
+#include <algorithm>
 #include "egnn_internal.h"
 
 #define RG_BINS 2048
@@ -50,41 +51,101 @@ __device__ __forceinline__ int rg_bin(float d, float inv_h) {
   return m < 0 ? 0 : (m > RG_BINS - 1 ? RG_BINS - 1 : m);
 }
 
-// key[k] = interval of edge k; cnt[m + 1] += 1
-__global__ __launch_bounds__(256) void rg_key_kernel(const float4* __restrict__ rhat_d, long n_edges, float inv_h,
-                                                     int* __restrict__ key, int* __restrict__ cnt,
-                                                     const int* __restrict__ route) {
-  if (route && !route[0]) return;
-  const long k = (long)blockIdx.x * 256 + threadIdx.x;
-  if (k >= n_edges) return;
-  const int m = rg_bin(rhat_d[k].w, inv_h);
-  key[k] = m;
-  atomicAdd(&cnt[m + 1], 1);    // integer: the result does not depend on the order
+// The edges grouped by interval are a stable counting sort: the edges are cut into chunks in id order, one wavefront each.
+// Counters in memory that all edges share (and a sort inside the intervals afterwards, as they fill in no particular order)
+// cost 0.60 + 0.61 + 2.09 ms at 2.35 million edges; counters per chunk in LDS and ranks by ballots 0.07 ms in all.
+__device__ __forceinline__ long rg_chunk_end(long begin, long per_chunk, long n) {
+  return begin + per_chunk < n ? begin + per_chunk : n;
 }
 
-__global__ __launch_bounds__(256) void rg_fill_kernel(const int* __restrict__ key, long n_edges,
-                                                      const int* __restrict__ bin_ptr, int* __restrict__ cursor,
-                                                      int* __restrict__ bucket, const int* __restrict__ route) {
+// key[k] = interval of edge k; hist[chunk][m] = edges of the chunk in interval m
+__global__ __launch_bounds__(64) void rg_count_kernel(const float4* __restrict__ rhat_d, long n_edges, long per_chunk, float inv_h,
+                                                      int* __restrict__ key, int* __restrict__ hist,
+                                                      const int* __restrict__ route) {
   if (route && !route[0]) return;
-  const long k = (long)blockIdx.x * 256 + threadIdx.x;
-  if (k >= n_edges) return;
-  const int m = key[k];
-  bucket[bin_ptr[m] + atomicAdd(&cursor[m], 1)] = (int)k;
+  __shared__ int s_cnt[RG_BINS];
+  for (int m = threadIdx.x; m < RG_BINS; m += 64) s_cnt[m] = 0;
+  __syncthreads();
+  const long k0 = (long)blockIdx.x * per_chunk, k1 = rg_chunk_end(k0, per_chunk, n_edges);
+#pragma unroll 4
+  for (long k = k0 + threadIdx.x; k < k1; k += 64) {
+    const int m = rg_bin(rhat_d[k].w, inv_h);
+    key[k] = m;
+    atomicAdd(&s_cnt[m], 1);
+  }
+  __syncthreads();
+  for (int m = threadIdx.x; m < RG_BINS; m += 64) hist[(size_t)blockIdx.x * RG_BINS + m] = s_cnt[m];
 }
 
-// One workgroup per interval: rank sort of its edges (ascending id), so that the binning pass adds them in a fixed order.
-__global__ __launch_bounds__(256) void rg_sort_kernel(const int* __restrict__ bin_ptr, const int* __restrict__ bucket,
-                                                      int* __restrict__ perm, const int* __restrict__ route) {
+// hist[chunk][m] -> edges of interval m in the chunks before; bin_ptr[m + 1] = edges of interval m in all.  A workgroup takes
+// 64 intervals, its 16 waves a sixteenth of the chunks each.
+__global__ __launch_bounds__(1024) void rg_offsets_kernel(int* __restrict__ hist, int n_chunks, int* __restrict__ bin_ptr,
+                                                          const int* __restrict__ route) {
   if (route && !route[0]) return;
-  const int m = blockIdx.x;
-  const int c0 = bin_ptr[m], c1 = bin_ptr[m + 1];
-  for (int a = c0 + threadIdx.x; a < c1; a += 256) {
-    const int e = bucket[a];
-    int rank = 0;
-    for (int b = c0; b < c1; ++b) rank += bucket[b] < e ? 1 : 0;
-    perm[c0 + rank] = e;
+  __shared__ int s_sum[16][64];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, m = blockIdx.x * 64 + lane;
+  const int per = (n_chunks + 15) / 16, c0 = min(wave * per, n_chunks), c1 = min(c0 + per, n_chunks);
+  int sum = 0;
+#pragma unroll 8
+  for (int c = c0; c < c1; ++c) sum += hist[(size_t)c * RG_BINS + m];
+  s_sum[wave][lane] = sum;
+  __syncthreads();
+  int before = 0, all = 0;
+  for (int q = 0; q < 16; ++q) {
+    if (q < wave) before += s_sum[q][lane];
+    all += s_sum[q][lane];
+  }
+  if (wave == 0) bin_ptr[m + 1] = all;
+  int c = c0;
+  for (; c + 8 <= c1; c += 8) {
+    int v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = hist[(size_t)(c + u) * RG_BINS + m];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      hist[(size_t)(c + u) * RG_BINS + m] = before;
+      before += v[u];
+    }
+  }
+  for (; c < c1; ++c) {
+    const int v = hist[(size_t)c * RG_BINS + m];
+    hist[(size_t)c * RG_BINS + m] = before;
+    before += v;
   }
 }
+
+// perm: the edges of the chunk to their places, in ascending id: 64 at a time, the rank among the lanes of the same interval
+// from ballots over the bits of the interval's number
+__global__ __launch_bounds__(64) void rg_place_kernel(const int* __restrict__ key, long n_edges, long per_chunk,
+                                                      const int* __restrict__ bin_ptr, const int* __restrict__ hist,
+                                                      int* __restrict__ perm, const int* __restrict__ route) {
+  if (route && !route[0]) return;
+  __shared__ int s_next[RG_BINS];
+  const int lane = threadIdx.x;
+  for (int m = lane; m < RG_BINS; m += 64) s_next[m] = bin_ptr[m] + hist[(size_t)blockIdx.x * RG_BINS + m];
+  __syncthreads();
+  volatile int* next = s_next;
+  const long k0 = (long)blockIdx.x * per_chunk, k1 = rg_chunk_end(k0, per_chunk, n_edges);
+  int ahead = k0 + lane < k1 ? key[k0 + lane] : 0;
+  for (long k = k0 + lane; k - lane < k1; k += 64) {
+    const bool live = k < k1;
+    const int m = ahead;
+    ahead = k + 64 < k1 ? key[k + 64] : 0;
+    unsigned long long same = __ballot(live);
+#pragma unroll
+    for (int bit = 0; bit < 11; ++bit) {
+      const unsigned long long set = __ballot((m >> bit) & 1);
+      same &= ((m >> bit) & 1) ? set : ~set;
+    }
+    const int rank = __popcll(same & ((1ull << lane) - 1ull));
+    if (live) {
+      const int at = next[m] + rank;
+      perm[at] = (int)k;
+      if ((same >> lane) == 1ull) next[m] = at + 1;       // the last lane of its interval
+    }
+  }
+}
+static_assert(RG_BINS == 1 << 11, "rg_place_kernel ranks by 11 bits");
 
 // Lagrange weights of the six grid points -2 .. 3 around an interval, at position t in [0, 1) inside it
 __device__ __forceinline__ void rg_weights(float t, float (&phi)[RG_PTS]) {
@@ -362,16 +423,20 @@ int egnn_launch_length_bins(egnn_ctx* ctx, const float4* rd, int64_t n_edges, in
   const float inv_h = (float)RG_BINS / ctx->desc.r_cut;
   int rc;
   if ((rc = egnn_launch_fill_int(ctx, bin_ptr, RG_BINS + 1, 0, st))) return rc;
-  if ((rc = egnn_launch_fill_int(ctx, cursor, RG_BINS, 0, st))) return rc;
   if (n_edges == 0) return EGNN_OK;
-  const dim3 ge((unsigned)((n_edges + 255) / 256)), b256(256);
-  hipLaunchKernelGGL(rg_key_kernel, ge, b256, 0, st, rd, (long)n_edges, inv_h, key, bin_ptr, route);
-  EGNN_LAUNCH_CHECK(ctx, "rg_key_kernel");
+  // chunks of 2,048 edges or more: their counters fit the scratch of one word per edge (a single chunk's the cursors), and at
+  // most 1,024, four wavefronts per compute unit
+  const long most = std::min<long>(std::max<long>((long)n_edges / RG_BINS, 1), 1024);
+  const long per = (((long)n_edges + most - 1) / most + 63) / 64 * 64;
+  const int chunks = (int)(((long)n_edges + per - 1) / per);
+  int* hist = chunks == 1 ? cursor : bucket;
+  hipLaunchKernelGGL(rg_count_kernel, dim3(chunks), dim3(64), 0, st, rd, (long)n_edges, per, inv_h, key, hist, route);
+  EGNN_LAUNCH_CHECK(ctx, "rg_count_kernel");
+  hipLaunchKernelGGL(rg_offsets_kernel, dim3(RG_BINS / 64), dim3(1024), 0, st, hist, chunks, bin_ptr, route);
+  EGNN_LAUNCH_CHECK(ctx, "rg_offsets_kernel");
   if ((rc = egnn_launch_row_scan(ctx, bin_ptr, RG_BINS, st))) return rc;
-  hipLaunchKernelGGL(rg_fill_kernel, ge, b256, 0, st, key, (long)n_edges, bin_ptr, cursor, bucket, route);
-  EGNN_LAUNCH_CHECK(ctx, "rg_fill_kernel");
-  hipLaunchKernelGGL(rg_sort_kernel, dim3(RG_BINS), b256, 0, st, bin_ptr, bucket, perm, route);
-  EGNN_LAUNCH_CHECK(ctx, "rg_sort_kernel");
+  hipLaunchKernelGGL(rg_place_kernel, dim3(chunks), dim3(64), 0, st, key, (long)n_edges, per, bin_ptr, hist, perm, route);
+  EGNN_LAUNCH_CHECK(ctx, "rg_place_kernel");
   return EGNN_OK;
 }
 
