@@ -6,6 +6,7 @@
 // S3: w[k][p][c] = fc(d_k) alpha_p (W_r2 SiLU(W_r1 B(d_k)))[p*E + c] -- a dense [n_edges x 64] x [64 x P*E]
 //     contraction on the matrix cores, with the 64-wide hidden activation of 64 edges per wavefront held in
 //     registers as the A operand for the whole row.
+#include <algorithm>
 #include "egnn_internal.h"
 
 // ------------------------------------------------------------------------------------------------ S2
@@ -145,58 +146,81 @@ __device__ __forceinline__ void rw_split(float x, uint32_t& hi, uint32_t& lo) {
   lo = __builtin_bit_cast(unsigned short, l);
 }
 
-// scales[0] = s_w, scales[1] = s_g (powers of two, see above), scales[2] = 1 / (s_w s_g).  One workgroup of 1,024
-// threads, 16-byte loads: a few microseconds for the 10^5 values of W_r2.
-#define HS_THREADS 1024
-__global__ __launch_bounds__(HS_THREADS) void half_scales_kernel(const float* __restrict__ W_r1,
-                                                                 const float* __restrict__ W_r2, int n_rbf, int PE,
-                                                                 int log2E, PathAlpha alpha, float* __restrict__ scales) {
-  __shared__ float red[HS_THREADS];
+// scales[0] = s_w, scales[1] = s_g (powers of two, see above), scales[2] = 1 / (s_w s_g).  In two steps: the largest
+// |alpha W_r2| of each of HS_BLOCKS parts and, by the first workgroup, the largest row sum of |W_r1| go to scales[HS_PART ..]
+// and scales[3]; whoever reads the scales first (half_scales_of) takes the maximum.  One workgroup for all of W_r2 took 10.7 us
+// at 1,344 rows and 19 us at 2,688, the parts take 3.
+// (The parts end at word 32: the reverse pass keeps another word behind its first 128 bytes of scales.)
+#define HS_BLOCKS 24
+#define HS_PART 8
+static_assert(HS_PART + HS_BLOCKS <= 32, "see above");
+__global__ __launch_bounds__(256) void half_scales_part_kernel(const float* __restrict__ W_r1, const float* __restrict__ W_r2,
+                                                               int n_rbf, int PE, int log2E, PathAlpha alpha,
+                                                               float* __restrict__ scales) {
+  __shared__ float red[4];
   float mw = 0.0f;
   const float4* W4 = reinterpret_cast<const float4*>(W_r2);
-#pragma unroll 4   // (several loads in flight: the kernel is one workgroup, its time is load latency)
-  for (int i = threadIdx.x; i < PE * (EGNN_HIDDEN / 4); i += HS_THREADS) {
+#pragma unroll 4
+  for (int i = blockIdx.x * 256 + threadIdx.x; i < PE * (EGNN_HIDDEN / 4); i += HS_BLOCKS * 256) {
     const float4 v = W4[i];
     const float al = fabsf(alpha.a[(i / (EGNN_HIDDEN / 4)) >> log2E]);
     mw = fmaxf(mw, al * fmaxf(fmaxf(fabsf(v.x), fabsf(v.y)), fmaxf(fabsf(v.z), fabsf(v.w))));
   }
-  float mg = 0.0f;
-  if (threadIdx.x < EGNN_HIDDEN) {
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
+  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = mw;
+  __syncthreads();
+  if (threadIdx.x == 0) scales[HS_PART + blockIdx.x] = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+  if (blockIdx.x == 0 && threadIdx.x < EGNN_HIDDEN) {
+    float mg = 0.0f;
     for (int b = 0; b < n_rbf; ++b) mg += fabsf(W_r1[threadIdx.x * n_rbf + b]);
-  }
-  auto block_max = [&](float v) {
-    red[threadIdx.x] = v;
-    __syncthreads();
-    for (int st = HS_THREADS / 2; st > 0; st >>= 1) {
-      if ((int)threadIdx.x < st) red[threadIdx.x] = fmaxf(red[threadIdx.x], red[threadIdx.x + st]);
-      __syncthreads();
-    }
-    const float r = red[0];
-    __syncthreads();
-    return r;
-  };
-  mw = block_max(mw);
-  mg = block_max(mg);
-  if (threadIdx.x == 0) {
-    // (zero, infinite or NaN weights: no scaling; the result then shows them as it would without)
-    auto exp_of = [](float m) { return (m > 0.0f && m < 3.0e38f) ? ilogbf(m) : 13; };
-    int ew = 13 - exp_of(mw), eg = 13 - exp_of(mg);
-    ew = ew < -60 ? -60 : (ew > 60 ? 60 : ew);
-    eg = eg < -60 ? -60 : (eg > 60 ? 60 : eg);
-    scales[0] = ldexpf(1.0f, ew);
-    scales[1] = ldexpf(1.0f, eg);
-    scales[2] = ldexpf(1.0f, -ew - eg);
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) mg = fmaxf(mg, __shfl_xor(mg, off));
+    if (threadIdx.x == 0) scales[3] = mg;
   }
 }
 
-int egnn_launch_half_scales(egnn_ctx* ctx, int which, const float* W_r1, const float* W_r2, float* scales,
-                            hipStream_t stream) {
+// s_w, s_g and 1 / (s_w s_g) from the parts; by a whole wavefront
+__device__ __forceinline__ void half_scales_of(const float* __restrict__ scales, float& s_w, float& s_g, float& inv) {
+  const int lane = threadIdx.x & 63;
+  float mw = lane < HS_BLOCKS ? scales[HS_PART + lane] : 0.0f;
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mw = fmaxf(mw, __shfl_xor(mw, off));
+  const float mg = scales[3];
+  // (zero, infinite or NaN weights: no scaling; the result then shows them as it would without)
+  auto exp_of = [](float m) { return (m > 0.0f && m < 3.0e38f) ? ilogbf(m) : 13; };
+  int ew = 13 - exp_of(mw), eg = 13 - exp_of(mg);
+  ew = ew < -60 ? -60 : (ew > 60 ? 60 : ew);
+  eg = eg < -60 ? -60 : (eg > 60 ? 60 : eg);
+  s_w = ldexpf(1.0f, ew);
+  s_g = ldexpf(1.0f, eg);
+  inv = ldexpf(1.0f, -ew - eg);
+}
+
+__global__ __launch_bounds__(64) void half_scales_final_kernel(float* __restrict__ scales) {
+  float s_w, s_g, inv;
+  half_scales_of(scales, s_w, s_g, inv);
+  if (threadIdx.x == 0) { scales[0] = s_w; scales[1] = s_g; scales[2] = inv; }
+}
+
+static int launch_half_scales_part(egnn_ctx* ctx, int which, const float* W_r1, const float* W_r2, float* scales,
+                                   hipStream_t stream) {
   const int P = ctx->n_paths[which];
   PathAlpha al;
   for (int p = 0; p < EGNN_MAX_PATHS; ++p) al.a[p] = p < P ? ctx->alpha[which][p] : 0.0f;
-  hipLaunchKernelGGL(half_scales_kernel, dim3(1), dim3(HS_THREADS), 0, stream, W_r1, W_r2, ctx->desc.n_rbf,
+  hipLaunchKernelGGL(half_scales_part_kernel, dim3(HS_BLOCKS), dim3(256), 0, stream, W_r1, W_r2, ctx->desc.n_rbf,
                      P * ctx->desc.channels, ctx->log2_channels, al, scales);
-  EGNN_LAUNCH_CHECK(ctx, "half_scales_kernel");
+  EGNN_LAUNCH_CHECK(ctx, "half_scales_part_kernel");
+  return EGNN_OK;
+}
+
+// (128 bytes of `scales`)
+int egnn_launch_half_scales(egnn_ctx* ctx, int which, const float* W_r1, const float* W_r2, float* scales,
+                            hipStream_t stream) {
+  int rc = launch_half_scales_part(ctx, which, W_r1, W_r2, scales, stream);
+  if (rc) return rc;
+  hipLaunchKernelGGL(half_scales_final_kernel, dim3(1), dim3(64), 0, stream, scales);
+  EGNN_LAUNCH_CHECK(ctx, "half_scales_final_kernel");
   return EGNN_OK;
 }
 
@@ -213,15 +237,20 @@ __global__ __launch_bounds__(256) void split_w2_kernel(const float* __restrict__
   o[2 * EGNN_HIDDEN] = (uint16_t)(s.lo >> 16);
 }
 
-// W_r2 times alpha_p times s_w cut into two half-precision pieces: out[n][piece][64].
+// W_r2 times alpha_p times s_w cut into two half-precision pieces: out[n][piece][64].  Takes the scales from their parts; the
+// first workgroup leaves them in scales[0 .. 2].
 __global__ __launch_bounds__(256) void split_w2_half_kernel(const float* __restrict__ W_r2, uint16_t* __restrict__ out,
                                                             int PE, int log2E, PathAlpha alpha,
-                                                            const float* __restrict__ scales) {
+                                                            float* __restrict__ scales) {
   const int i = blockIdx.x * 256 + threadIdx.x;
+  const float x = i < PE * EGNN_HIDDEN ? W_r2[i] : 0.0f;
+  float s_w, s_g, inv;
+  half_scales_of(scales, s_w, s_g, inv);
+  if (i == 0) { scales[0] = s_w; scales[1] = s_g; scales[2] = inv; }
   if (i >= PE * EGNN_HIDDEN) return;
   const int n = i >> 6, j = i & 63;
   uint32_t hi, lo;
-  rw_split(W_r2[i] * alpha.a[n >> log2E] * scales[0], hi, lo);
+  rw_split(x * alpha.a[n >> log2E] * s_w, hi, lo);
   uint16_t* o = out + (size_t)n * 2 * EGNN_HIDDEN + j;
   o[0] = (uint16_t)hi;
   o[EGNN_HIDDEN] = (uint16_t)lo;
@@ -323,7 +352,7 @@ __global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(c
                                                              const uint16_t* __restrict__ W2s,
                                                              const float* __restrict__ scales,
                                                              float* __restrict__ w, int n_rbf, int PE,
-                                                             float r_cut, int rows_per_wave) {
+                                                             float r_cut, int rows_per_wave, int split_blocks) {
   __shared__ float sW1[32 * EGNN_HIDDEN];  // [b][j], n_rbf <= 32
   __shared__ uint4 sB[2][32 * RW_BROW4];
   const int tid = threadIdx.x;
@@ -334,12 +363,15 @@ __global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(c
   __syncthreads();
 
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_blocks = (PE + 31) >> 5;
+  // this workgroup's column blocks (few rows: several workgroups share them out, see egnn_launch_radial; an even first one,
+  // which the buffers and the half-precision pairs count on)
+  const int nb_first = (int)blockIdx.y * split_blocks;
+  const int n_blocks = min(nb_first + split_blocks, (PE + 31) >> 5);
 
   if (wave == RW_COMPUTE_WAVES) {
     // ---- loader: block nb -> sB[nb & 1]; rows past the end repeat row 0 (their columns are never stored)
     const uint4* src = reinterpret_cast<const uint4*>(W2s);
-    for (int nb = 0; nb < n_blocks; ++nb) {
+    for (int nb = nb_first; nb < n_blocks; ++nb) {
       uint4 v[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
@@ -374,6 +406,12 @@ __global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(c
   const float s_g = scales[1], unscale = scales[2];
 #pragma unroll
   for (int mb = 0; mb < RW_MB; ++mb) {
+    if (!HALF && mb > 0 && mb * 32 >= rows_here) {
+      // (a wave that owns 32 rows or fewer: the second block's rows are not stored)
+#pragma unroll
+      for (int t = 0; t < 4; ++t) a_frag[mb][0][t] = a_frag[mb][1][t] = make_uint4(0u, 0u, 0u, 0u);
+      continue;
+    }
     long e = e_base + mb * 32 + m;
     if (e >= n_edges) e = n_edges - 1;
     const float d = rhat_d[e].w;
@@ -442,7 +480,7 @@ __global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(c
 #if RW_PIPELINE
     float16v acc0[RW_MB], acc1[RW_MB];
     rw_block<false>(sB[0], a_frag, m, hh, acc0, acc0, no_rows, 0, 0, 0, unscale);
-    int nb = 1;
+    int nb = nb_first + 1;
     for (; nb + 1 < n_blocks; nb += 2) {
       step(acc1, acc0, nb);
       step(acc0, acc1, nb + 1);
@@ -455,7 +493,7 @@ __global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(c
     }
 #else
     (void)step;
-    for (int nb = 0; nb < n_blocks; ++nb) {
+    for (int nb = nb_first; nb < n_blocks; ++nb) {
       float16v acc[RW_MB];
       rw_block<false>(sB[nb & 1], a_frag, m, hh, acc, acc, no_rows, 0, 0, 0, unscale);
       if ((nb + 1) * 32 <= PE) {
@@ -476,7 +514,7 @@ __global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(c
     const __amdgpu_buffer_rsrc_t no_rows = __builtin_amdgcn_make_buffer_rsrc((void*)w, 0, 0, 0x00020000);
     const int row_words = w_half_row_words(PE);
     uint32_t* const out_base = reinterpret_cast<uint32_t*>(w) + (size_t)(e_base + 4 * hh) * row_words + m;
-    for (int nb = 0; nb < n_blocks; nb += 2) {
+    for (int nb = nb_first; nb < n_blocks; nb += 2) {
       float16v acc[RW_MB];
       uint32_t word[RW_MB][16];
       rw_block<false>(sB[0], a_frag, m, hh, acc, acc, no_rows, 0, 0, 0, unscale);   // nb is even
@@ -540,7 +578,7 @@ int egnn_launch_radial(egnn_ctx* ctx, int which, const float* rhat_d, int64_t n_
   const int PE = P * ctx->desc.channels;
   float* scales = (float*)scratch;
   uint16_t* W2s = (uint16_t*)((char*)scratch + 256);
-  int rc = egnn_launch_half_scales(ctx, which, W_r1, W_r2, scales, stream);
+  int rc = launch_half_scales_part(ctx, which, W_r1, W_r2, scales, stream);
   if (rc) return rc;
   {
     PathAlpha al;
@@ -558,13 +596,26 @@ int egnn_launch_radial(egnn_ctx* ctx, int which, const float* rhat_d, int64_t n_
     n_wg = (n_wg + EGNN_CUS - 1) / EGNN_CUS * EGNN_CUS;
     rows_per_wave = (int)((n_edges + n_wg * RW_COMPUTE_WAVES - 1) / (n_wg * RW_COMPUTE_WAVES));
   }
-  dim3 grid((unsigned)n_wg), block(RW_THREADS);
+  // Very few rows: 32 per wave, since the hidden layer of 64 takes longer than their products (1,387 rows x 176 columns: 13.1
+  // -> 9.1 us; a whole layer of 12,800 rows x 2,688 columns, 29 workgroups: 131 -> 138; the half-precision stores do not know
+  // such shares).
+  if (!half && n_wg <= EGNN_CUS / 16) {
+    rows_per_wave = RW_ROWS / 2;
+    n_wg = (n_edges + per_wg / 2 - 1) / (per_wg / 2);
+  }
+  // Few rows: the column blocks are shared out over the workgroups, two blocks each at least, up to half as many workgroups as
+  // there are compute units.  Every share repeats the hidden layer of its rows, and beyond that the stores of all together are
+  // what takes the time: 1,387 rows x 176 columns, 4 -> 12 workgroups, 16.5 -> 13.1 us; 53,000 x 736, 119 -> 238: 44 -> 48 us.
+  const int n_blocks = (PE + 31) / 32;
+  const long splits = std::max<long>(1, std::min<long>(EGNN_CUS / 2 / n_wg, (n_blocks + 1) / 2));
+  const int split_blocks = (int)(((n_blocks + splits - 1) / splits + 1) / 2 * 2);
+  dim3 grid((unsigned)n_wg, (unsigned)((n_blocks + split_blocks - 1) / split_blocks)), block(RW_THREADS);
   if (half)
     hipLaunchKernelGGL(radial_weights_kernel<true>, grid, block, 0, stream, reinterpret_cast<const float4*>(rhat_d),
-                       (long)n_edges, W_r1, W2s, scales, w, ctx->desc.n_rbf, PE, ctx->desc.r_cut, rows_per_wave);
+                       (long)n_edges, W_r1, W2s, scales, w, ctx->desc.n_rbf, PE, ctx->desc.r_cut, rows_per_wave, split_blocks);
   else
     hipLaunchKernelGGL(radial_weights_kernel<false>, grid, block, 0, stream, reinterpret_cast<const float4*>(rhat_d),
-                       (long)n_edges, W_r1, W2s, scales, w, ctx->desc.n_rbf, PE, ctx->desc.r_cut, rows_per_wave);
+                       (long)n_edges, W_r1, W2s, scales, w, ctx->desc.n_rbf, PE, ctx->desc.r_cut, rows_per_wave, split_blocks);
   EGNN_LAUNCH_CHECK(ctx, "radial_weights_kernel");
   return EGNN_OK;
 }

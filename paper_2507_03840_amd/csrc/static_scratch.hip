@@ -7,7 +7,7 @@
 // of the memory goes through that pointer.  Nothing in this file allocates or frees device memory.
 //
 // Every byte of the array that the kernels read for a given shape is written earlier in the same call (the scalings
-// by half_scales_kernel, rows 0 .. P*channels-1 of the pieces by split_w2_half_kernel); the loader wave of
+// by half_scales_part_kernel and split_w2_half_kernel, rows 0 .. P*channels-1 of the pieces by the latter); the loader wave of
 // radial_weights_kernel may copy rows past P*channels when that is not a multiple of 32, which here are stale rows of
 // an earlier, larger call -- their products land in columns the kernel never stores.  Nothing has to start at zero.
 // All calls on one GPU share the array: two calls that overlap in time on one GPU (two streams, two threads) race.
