@@ -160,6 +160,7 @@ __global__ __launch_bounds__(256) void padding_kernel(float* __restrict__ H, lon
 
 // ------------------------------------------------------------------------------------------------ L1 + L2 loss
 #define HL_PER_WG 4096
+typedef float ham_f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ double wg_sum(double v, double* red) {
   red[threadIdx.x] = v;
   __syncthreads();
@@ -204,6 +205,9 @@ __global__ __launch_bounds__(256) void sum_partials_kernel(const double* __restr
   if (threadIdx.x == 0) out[0] = s;
 }
 
+// VEC: 16-byte accesses (all three arrays and the workgroup's first value 16-byte aligned): 625,000 blocks of 13 x 13 take 230
+// us = 5.5 TB/s with them, 327 without.
+template <bool VEC>
 __global__ __launch_bounds__(256) void l1l2_partial_kernel(const float* __restrict__ H, const float* __restrict__ T,
                                                            long n_blocks, int n_orb, int bpw,
                                                            const int* __restrict__ row_atom,
@@ -219,18 +223,30 @@ __global__ __launch_bounds__(256) void l1l2_partial_kernel(const float* __restri
   const uint32_t all = n_orb >= 32 ? 0xffffffffu : ((1u << n_orb) - 1u);
   const long blk0 = (long)blockIdx.x * bpw;
   const int nb = (int)min((long)bpw, n_blocks - blk0);
-  ham_stage_masks(blk0, nb, row_atom, col_atom, species, orb_bits, n_species, all, s_rb, s_cb);
-  const double cnt = n_present[0];
-  const float inv_n = cnt > 0.0 ? (float)(1.0 / cnt) : 0.0f;
-  const float inv_nq = 1.0f / (float)nq, inv_no = 1.0f / (float)n_orb;
   const float* Hb = H + blk0 * nq;
   const float* Tb = T + blk0 * nq;
   float* gb = dH ? dH + blk0 * nq : nullptr;
   const int n_local = nb * nq;
+  constexpr int W = VEC ? 4 : 1, U = 4;
+  // the first values are requested before the masks are looked up
+  ham_f4 h[U], t[U];
+  auto load = [&](int base) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int i = base + (u * 256 + (int)threadIdx.x) * 4;
+      if (VEC && i + 3 < n_local) {
+        h[u] = __builtin_nontemporal_load(reinterpret_cast<const ham_f4*>(Hb + i));
+        t[u] = __builtin_nontemporal_load(reinterpret_cast<const ham_f4*>(Tb + i));
+      }
+    }
+  };
+  if (VEC) load(0);
+  ham_stage_masks(blk0, nb, row_atom, col_atom, species, orb_bits, n_species, all, s_rb, s_cb);
+  const double cnt = n_present[0];
+  const float inv_n = cnt > 0.0 ? (float)(1.0 / cnt) : 0.0f;
+  const float inv_nq = 1.0f / (float)nq, inv_no = 1.0f / (float)n_orb;
   double a1 = 0.0, a2 = 0.0;
-#pragma unroll 4
-  for (int idx = threadIdx.x; idx < n_local; idx += 256) {
-    const float d = Hb[idx] - Tb[idx];
+  auto entry = [&](int idx, float d) {
     const int bl = (int)(((float)idx + 0.5f) * inv_nq);
     const int r = idx - bl * nq;
     const int a = (int)(((float)r + 0.5f) * inv_no), b = r - a * n_orb;
@@ -240,6 +256,27 @@ __global__ __launch_bounds__(256) void l1l2_partial_kernel(const float* __restri
       a2 += (double)d * (double)d;
       g = ((d > 0.0f ? 1.0f : (d < 0.0f ? -1.0f : 0.0f)) + 2.0f * d) * inv_n;
     }
+    return g;
+  };
+  if (VEC) {
+    for (int base = 0; base < n_local; base += U * 1024) {
+      if (base > 0) load(base);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int i = base + (u * 256 + (int)threadIdx.x) * 4;
+        if (i + 3 < n_local) {
+          ham_f4 g;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) g[q] = entry(i + q, h[u][q] - t[u][q]);
+          if (gb) __builtin_nontemporal_store(g, reinterpret_cast<ham_f4*>(gb + i));
+        }
+      }
+    }
+  }
+  // (without 16-byte accesses all of it, with them the last one to three values)
+#pragma unroll 4
+  for (int idx = (VEC ? n_local / W * W : 0) + (int)threadIdx.x; idx < n_local; idx += 256) {
+    const float g = entry(idx, Hb[idx] - Tb[idx]);
     if (gb) gb[idx] = g;
   }
   const double s1 = wg_sum(a1, red);
@@ -250,18 +287,30 @@ __global__ __launch_bounds__(256) void l1l2_partial_kernel(const float* __restri
   }
 }
 
-__global__ __launch_bounds__(256) void l1l2_final_kernel(const double* __restrict__ partial1,
+// (one workgroup: 16 waves and four independent loads per thread, 26,000 pairs of partial sums 44 -> 9 us)
+#define HL_FINAL 1024
+__global__ __launch_bounds__(HL_FINAL) void l1l2_final_kernel(const double* __restrict__ partial1,
                                                          const double* __restrict__ partial2, int n_partials,
                                                          const double* __restrict__ n_present,
                                                          float* __restrict__ loss) {
-  __shared__ double red[256];
+  __shared__ double red1[HL_FINAL], red2[HL_FINAL];
   double a1 = 0.0, a2 = 0.0;
-  for (int b = threadIdx.x; b < n_partials; b += 256) {
+#pragma unroll 4
+  for (int b = threadIdx.x; b < n_partials; b += HL_FINAL) {
     a1 += partial1[b];
     a2 += partial2[b];
   }
-  const double s1 = wg_sum(a1, red);
-  const double s2 = wg_sum(a2, red);
+  red1[threadIdx.x] = a1;
+  red2[threadIdx.x] = a2;
+  __syncthreads();
+  for (int off = HL_FINAL / 2; off > 0; off >>= 1) {
+    if ((int)threadIdx.x < off) {
+      red1[threadIdx.x] += red1[threadIdx.x + off];
+      red2[threadIdx.x] += red2[threadIdx.x + off];
+    }
+    __syncthreads();
+  }
+  const double s1 = red1[0], s2 = red2[0];
   if (threadIdx.x == 0) {
     const double cnt = n_present[0];
     const double inv = cnt > 0.0 ? 1.0 / cnt : 0.0;
@@ -283,7 +332,8 @@ __global__ __launch_bounds__(256) void orb_count_kernel(const int* __restrict__ 
 
 // Per owned atom j: the blocks of its columns are its incoming edges (sources ascending) with its own on-site block
 // inserted where j falls among the sources.  Row offset of every block inside a column, the column length, and the
-// number of stored entries of the atom's columns.
+// number of stored entries of the atom's columns.  A wavefront per atom, 64 sources at a time by prefix sums: one thread per
+// atom walking its 200 sources took 264 us at 3,000 atoms (a chain of dependent loads on 12 workgroups), this 8.
 __global__ __launch_bounds__(256) void column_layout_kernel(const int* __restrict__ row_ptr,
                                                             const int* __restrict__ src,
                                                             const int* __restrict__ species,
@@ -294,31 +344,52 @@ __global__ __launch_bounds__(256) void column_layout_kernel(const int* __restric
                                                             int* __restrict__ edge_off, int* __restrict__ self_pos,
                                                             int* __restrict__ self_idx, int* __restrict__ col_len,
                                                             long* __restrict__ col_start) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  const int lane = threadIdx.x & 63, j = blockIdx.x * 4 + (threadIdx.x >> 6);
   if (j >= n_owned) return;
   const int k0 = row_ptr[j], k1 = row_ptr[j + 1];
   const int n_j = orb_off[j + 1] - orb_off[j];
   int run = 0, sidx = -1;
-  for (int k = k0; k < k1; ++k) {
-    const int i = src[k];
-    if (sidx < 0 && i > j) {
-      sidx = k - k0;
+  for (int base = k0; base < k1; base += 64) {
+    const int k = base + lane;
+    const bool live = k < k1;
+    const int i = live ? src[k] : 0;
+    const int first = live ? orb_off[i] : 0;
+    const int n_i = live ? orb_off[i + 1] - first : 0;
+    // the atom's own block goes before the first source above it
+    const unsigned long long above = __ballot(live && i > j);
+    int at = n_i;
+#pragma unroll
+    for (int off = 1; off < 64; off <<= 1) {
+      const int add = __shfl_up(at, off);
+      if (lane >= off) at += add;
+    }
+    const int total = __shfl(at, 63);
+    at += run - n_i;
+    run += total;
+    if (sidx < 0 && above) {
+      const int f = __ffsll((unsigned long long)above) - 1;
+      const int pos = __shfl(at, f);
+      sidx = base - k0 + f;
+      if (lane == 0) self_pos[j] = pos;
+      if (lane >= f) at += n_j;
+      run += n_j;
+    }
+    if (live) {
+      edge_pos[k] = at;
+      edge_bits[k] = ham_bits(species, orb_bits, n_species, i, all);
+      edge_off[k] = first;
+    }
+  }
+  if (lane == 0) {
+    if (sidx < 0) {
+      sidx = k1 - k0;
       self_pos[j] = run;
       run += n_j;
     }
-    edge_pos[k] = run;
-    edge_bits[k] = ham_bits(species, orb_bits, n_species, i, all);
-    edge_off[k] = orb_off[i];
-    run += orb_off[i + 1] - orb_off[i];
+    self_idx[j] = sidx;
+    col_len[j] = run;
+    col_start[j + 1] = (long)n_j * (long)run;
   }
-  if (sidx < 0) {
-    sidx = k1 - k0;
-    self_pos[j] = run;
-    run += n_j;
-  }
-  self_idx[j] = sidx;
-  col_len[j] = run;
-  col_start[j + 1] = (long)n_j * (long)run;
 }
 
 // In-place inclusive scan of v[1..n] by one workgroup; v[0] = 0.
@@ -364,9 +435,13 @@ __global__ __launch_bounds__(256) void col_ptr_kernel(const int* __restrict__ or
 // One workgroup per owned atom.  A tile of consecutive blocks of its columns is staged in LDS: the edge blocks of a
 // tile are one contiguous stretch of H_edge (edges are sorted by destination) and are copied flat, eight loads in
 // flight per thread; the on-site block, if it falls into the tile, goes to a slot of its own.  Then, column by
-// column, consecutive threads write consecutive rows of the column.
+// column, consecutive threads write consecutive rows of the column.  Bound by its reads and writes (1.27 GB for 600,000
+// blocks of 13 x 13 with the indices: 207 us, 6.1 TB/s).  The stores are ordinary ones: columns begin anywhere in a
+// line, and non-temporal stores of the part lines at both ends of a wave's row cost 293 us instead of 222; eight waves
+// instead of four hide more of the tile's copy (222 -> 207), smaller tiles do not (346 us with a quarter of the LDS).
 #define HAM_COPY_UNROLL 8
-__global__ __launch_bounds__(256) void csc_fill_kernel(const int* __restrict__ row_ptr, const int* __restrict__ species,
+#define HAM_FILL_THREADS 512
+__global__ __launch_bounds__(HAM_FILL_THREADS) void csc_fill_kernel(const int* __restrict__ row_ptr, const int* __restrict__ species,
                                                        const uint32_t* __restrict__ orb_bits, int n_species,
                                                        const int* __restrict__ orb_off,
                                                        const int* __restrict__ edge_pos,
@@ -428,25 +503,25 @@ __global__ __launch_bounds__(256) void csc_fill_kernel(const int* __restrict__ r
     {
       const int n = ne * nq;
       const float* gsrc = H_edge + (size_t)(k0 + eA) * nq;     // (not dereferenced when n == 0)
-      for (int base = 0; base < n; base += 256 * HAM_COPY_UNROLL) {
+      for (int base = 0; base < n; base += HAM_FILL_THREADS * HAM_COPY_UNROLL) {
         float v[HAM_COPY_UNROLL];
 #pragma unroll
         for (int u = 0; u < HAM_COPY_UNROLL; ++u) {
-          const int idx = base + u * 256 + tid;
+          const int idx = base + u * HAM_FILL_THREADS + tid;
           v[u] = idx < n ? __builtin_nontemporal_load(gsrc + idx) : 0.0f;
         }
 #pragma unroll
         for (int u = 0; u < HAM_COPY_UNROLL; ++u) {
-          const int idx = base + u * 256 + tid;
+          const int idx = base + u * HAM_FILL_THREADS + tid;
           if (idx < n) tile[idx] = v[u];
         }
       }
       if (self_here)
-        for (int e = tid; e < nq; e += 256) tile[tile_blocks * nq + e] = H_node[(size_t)j * nq + e];
+        for (int e = tid; e < nq; e += HAM_FILL_THREADS) tile[tile_blocks * nq + e] = H_node[(size_t)j * nq + e];
     }
     __syncthreads();
     const int r0 = s_pos[0], r1 = s_pos[nt];
-    for (int r = r0 + tid; r < r1; r += 256) {
+    for (int r = r0 + tid; r < r1; r += HAM_FILL_THREADS) {
       int lo = 0, hi = nt - 1;            // largest t with s_pos[t] <= r (blocks without orbitals are skipped over)
       while (lo < hi) {
         const int mid = (lo + hi + 1) >> 1;
@@ -458,8 +533,8 @@ __global__ __launch_bounds__(256) void csc_fill_kernel(const int* __restrict__ r
       const int grow = s_off[lo] + ap;
       for (int b = 0; b < n_j; ++b) {
         const long at = cstart + (long)b * len + r;
-        __builtin_nontemporal_store(trow[s_colmap[b]], values + at);
-        if (row_idx) __builtin_nontemporal_store(grow, row_idx + at);
+        values[at] = trow[s_colmap[b]];
+        if (row_idx) row_idx[at] = grow;
       }
     }
   }
@@ -689,10 +764,15 @@ extern "C" int egnn_loss_l1l2(egnn_ctx* ctx, const float* H, const float* T, int
   EGNN_LAUNCH_CHECK(ctx, "present_partial_kernel");
   hipLaunchKernelGGL(sum_partials_kernel, dim3(1), dim3(256), 0, st, p0, (int)nb_b, count);
   EGNN_LAUNCH_CHECK(ctx, "sum_partials_kernel");
-  hipLaunchKernelGGL(l1l2_partial_kernel, dim3((unsigned)nb_v), dim3(256), 0, st, H, T, (long)n_blocks, ctx->n_orb, bpw,
-                     row_atom, col_atom, species, orb_bits, n_species, count, dH, p1, p2);
+  const bool vec = (((uintptr_t)H | (uintptr_t)T | (uintptr_t)dH) & 15) == 0 && (bpw * ctx->n_orb * ctx->n_orb) % 4 == 0;
+  if (vec)
+    hipLaunchKernelGGL(l1l2_partial_kernel<true>, dim3((unsigned)nb_v), dim3(256), 0, st, H, T, (long)n_blocks, ctx->n_orb,
+                       bpw, row_atom, col_atom, species, orb_bits, n_species, count, dH, p1, p2);
+  else
+    hipLaunchKernelGGL(l1l2_partial_kernel<false>, dim3((unsigned)nb_v), dim3(256), 0, st, H, T, (long)n_blocks, ctx->n_orb,
+                       bpw, row_atom, col_atom, species, orb_bits, n_species, count, dH, p1, p2);
   EGNN_LAUNCH_CHECK(ctx, "l1l2_partial_kernel");
-  hipLaunchKernelGGL(l1l2_final_kernel, dim3(1), dim3(256), 0, st, p1, p2, (int)nb_v, count, loss);
+  hipLaunchKernelGGL(l1l2_final_kernel, dim3(1), dim3(HL_FINAL), 0, st, p1, p2, (int)nb_v, count, loss);
   EGNN_LAUNCH_CHECK(ctx, "l1l2_final_kernel");
   return EGNN_OK;
 }
@@ -730,7 +810,7 @@ extern "C" int egnn_hamiltonian_structure(egnn_ctx* ctx, const egnn_graph* g, co
   if ((rc = egnn_launch_row_scan(ctx, orb_off, n_total, st))) return rc;
   if (n_owned > 0) {
     const uint32_t all = ctx->n_orb >= 32 ? 0xffffffffu : ((1u << ctx->n_orb) - 1u);
-    hipLaunchKernelGGL(column_layout_kernel, dim3((n_owned + 255) / 256), dim3(256), 0, st, g->row_ptr, g->src, species,
+    hipLaunchKernelGGL(column_layout_kernel, dim3((n_owned + 3) / 4), dim3(256), 0, st, g->row_ptr, g->src, species,
                        orb_bits, n_species, all, orb_off, n_owned, p.edge_pos, p.edge_bits, p.edge_off, p.self_pos,
                        p.self_idx, p.col_len, p.col_start);
     EGNN_LAUNCH_CHECK(ctx, "column_layout_kernel");
@@ -771,7 +851,7 @@ extern "C" int egnn_hamiltonian_fill(egnn_ctx* ctx, const egnn_graph* g, const i
   // tile [tile+1][nq], s_pos [tile+1], s_off [tile], s_base [tile], s_map [tile][32]
   const size_t shmem = (size_t)(tile_blocks + 1) * nq * sizeof(float) + (size_t)(3 * tile_blocks + 1) * sizeof(int) +
                        (size_t)tile_blocks * 32;
-  hipLaunchKernelGGL(csc_fill_kernel, dim3(g->n_owned), dim3(256), shmem, (hipStream_t)stream, g->row_ptr, species,
+  hipLaunchKernelGGL(csc_fill_kernel, dim3(g->n_owned), dim3(HAM_FILL_THREADS), shmem, (hipStream_t)stream, g->row_ptr, species,
                      orb_bits, n_species, orb_off, p.edge_pos, p.edge_bits, p.edge_off, p.self_pos, p.self_idx,
                      p.col_len, p.col_start, H_edge, H_node, ctx->n_orb, tile_blocks, row_idx, values);
   EGNN_LAUNCH_CHECK(ctx, "csc_fill_kernel");
