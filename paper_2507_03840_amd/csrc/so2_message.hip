@@ -17,8 +17,9 @@
 //                          192 columns per workgroup: a row of A is fetched and cut once for all its column blocks;
 //   4. so2_scatter_kernel  one workgroup per destination node, lane = (edge slot, channel): m-major rows of Y back to
 //                          (l, m) order, rotated back, times f_c, summed; slots added in fixed order (no atomics).
-// The plain sum of messages mixes its channels per node instead where nodes have enough edges (so2_node.hip); this per-edge
-// form serves sparse graphs and the two blocks, whose messages hold a tensor of the edge's own or are not summed.
+// The sums of messages (plain and attention-weighted) mix their channels per node instead where nodes have enough edges
+// (so2_node.hip); this per-edge form serves sparse graphs, the edge block, whose messages are not summed, and the adjoints
+// of the two blocks.
 #include <type_traits>
 #include "egnn_internal.h"
 #include "bond_frame.h"
@@ -603,8 +604,30 @@ static int so2_transform(egnn_ctx* ctx, const egnn_graph* g, const float* pos, c
 static bool so2_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
   const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels * 4;
   return g->n_owned > 0 && g->n_edges >= (int64_t)SO2N_MIN_DEGREE * g->n_owned && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
-         so2_a256((size_t)g->n_edges * 16) + so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, true, nullptr, nullptr) <=
+         so2_a256((size_t)g->n_edges * 16) + so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, SO2N_GAUSS, nullptr, nullptr) <=
              so2_ws(ctx, g->n_edges, false, false, nullptr, nullptr, nullptr, nullptr, nullptr);
+}
+
+// The node block by the same means, with a pass over all edges for the attention scores first and a second gathering launch
+// for the edges' own rows.  3,000 nodes, us per call per edge -> per node: lmax 4, 32 channels, 22.6 edges a node 674 -> 797,
+// 37.8 910 -> 867, 209 4,500 -> 1,900; lmax 3, 64 channels, 22.6 916 -> 926, 37.8 1,319 -> 1,061; lmax 2, 16 channels, 13.7
+// 117 -> 153, 22.6 171 -> 163.  128 channels stay per edge (the score kernel's sums are laid out for two blocks of 32).
+static size_t so2_block_nodes_ws(const egnn_ctx* ctx, const egnn_graph* g, char* base, float** rhat_d, float** alpha, So2nCall* c) {
+  size_t used = 0;
+  auto take = [&](size_t bytes) { char* q = base ? base + used : nullptr; used += so2_a256(bytes); return q; };
+  float* rd = (float*)take((size_t)g->n_edges * 16);
+  float* al = (float*)take((size_t)g->n_edges * 4);
+  if (rhat_d) *rhat_d = rd;
+  if (alpha) *alpha = al;
+  return used + so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, SO2N_EDGES, base ? base + used : nullptr, c);
+}
+#define SO2N_MIN_DEGREE_BLOCK 32
+static bool so2_block_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
+  const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels * 4;
+  return g->n_owned > 0 && ctx->desc.channels <= 64 && g->n_edges >= (int64_t)SO2N_MIN_DEGREE_BLOCK * g->n_owned &&
+         ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
+         so2_block_nodes_ws(ctx, g, nullptr, nullptr, nullptr, nullptr) <=
+             so2_ws(ctx, g->n_edges, true, false, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
 static int so2_scatter(egnn_ctx* ctx, const egnn_graph* g, const So2Call& call, const float* alpha, float scale, float* a,
@@ -639,7 +662,7 @@ extern "C" int egnn_so2_message_sum(egnn_ctx* ctx, const egnn_graph* g, const fl
   if (so2_use_nodes(ctx, g)) {
     So2nCall c;
     float* rhat_d = (float*)ws;
-    so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, true, (char*)ws + so2_a256((size_t)g->n_edges * 16), &c);
+    so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, SO2N_GAUSS, (char*)ws + so2_a256((size_t)g->n_edges * 16), &c);
     if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, 64, 0, st))) return rc;
     if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st))) return rc;
     return so2n_message_sum(ctx, g, rhat_d, x, W_e, W_so2, scale, a, c, st);
@@ -678,6 +701,14 @@ extern "C" int egnn_so2_node_block(egnn_ctx* ctx, const egnn_graph* g, const flo
   if (rc) return rc;
   if (g->n_edges > 0 && !T_edge) return egnn_fail(ctx, EGNN_EINVAL, "so2_node_block: null edge embeddings");
   hipStream_t st = (hipStream_t)stream;
+  if (so2_block_use_nodes(ctx, g)) {
+    float *rhat_d, *alpha;
+    So2nCall c;
+    so2_block_nodes_ws(ctx, g, (char*)ws, &rhat_d, &alpha, &c);
+    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, 64, 0, st))) return rc;
+    if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st))) return rc;
+    return so2n_node_block(ctx, g, rhat_d, x, T_edge, W_so2, w_att, alpha, a, c, st);
+  }
   So2Call call;
   if ((rc = so2_transform(ctx, g, pos, box, x, T_edge, true, W_so2, ws, &call, st))) return rc;
   if (g->n_owned == 0) return EGNN_OK;

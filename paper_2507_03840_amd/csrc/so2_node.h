@@ -13,14 +13,16 @@ __host__ __device__ constexpr int so2n_path_base(int lo, int li) {
 __host__ __device__ constexpr int so2n_paths(int lmax, int lo) { return so2n_path_base(lo, lmax + 1); }
 
 // The coupled sums T: per node (lmax+1)^2 rows (lo, mo) of so2n_ld(lo) floats, columns (group, path, channel) with group
-// 0 = neighbours, 1 = the node itself, then SO2N_AUX columns of the Gaussian basis if aux.
-__host__ __device__ constexpr int so2n_ld(int lmax, int E, int lo, bool aux) {
-  return 2 * so2n_paths(lmax, lo) * E + (aux ? SO2N_AUX : 0);
+// 0 = neighbours, 1 = the node itself, 2 = the edges' own rows; then, if asked for, SO2N_AUX columns of the Gaussian basis.
+enum So2nForm { SO2N_PLAIN = 0, SO2N_GAUSS = 1, SO2N_EDGES = 2 };   // two groups; with the basis; three groups
+__host__ __device__ constexpr int so2n_groups(int form) { return form == SO2N_EDGES ? 3 : 2; }
+__host__ __device__ constexpr int so2n_ld(int lmax, int E, int lo, int form) {
+  return so2n_groups(form) * so2n_paths(lmax, lo) * E + (form == SO2N_GAUSS ? SO2N_AUX : 0);
 }
 // first float of degree lo within a node; lo = lmax + 1: floats of a node
-__host__ __device__ constexpr int so2n_node_off(int lmax, int E, int lo, bool aux) {
+__host__ __device__ constexpr int so2n_node_off(int lmax, int E, int lo, int form) {
   int n = 0;
-  for (int q = 0; q < lo; ++q) n += (2 * q + 1) * so2n_ld(lmax, E, q, aux);
+  for (int q = 0; q < lo; ++q) n += (2 * q + 1) * so2n_ld(lmax, E, q, form);
   return n;
 }
 
@@ -31,13 +33,15 @@ struct So2nCall {
   float* g;              // [n_owned][(2 lmax + 1)^2] weighted sums of the harmonics over the incoming edges
   float* wpath;          // path weights, fp32
   uint4* wpack;          // the same cut into pieces in operand order
-  unsigned* maxima;      // bit patterns: 0 features, 1 path weights, 2 T
+  unsigned* maxima;      // bit patterns: 0 features, 1 path weights, 2 T, 3 edge rows
 };
 
 // base = NULL: bytes only.  n_rows feature rows, T for n_t nodes.
-size_t so2n_carve(const egnn_ctx*, int32_t n_owned, int32_t n_rows, int32_t n_t, bool aux, char* base, So2nCall* out);
+size_t so2n_carve(const egnn_ctx*, int32_t n_owned, int32_t n_rows, int32_t n_t, int form, char* base, So2nCall* out);
 int so2n_message_sum(egnn_ctx*, const egnn_graph*, const float* rhat_d, const float* x, const float* W_e, const float* W,
                      float scale, float* a, const So2nCall&, hipStream_t);
+int so2n_node_block(egnn_ctx*, const egnn_graph*, const float* rhat_d, const float* x, const float* T_edge, const float* W,
+                    const float* w_att, float* alpha, float* a, const So2nCall&, hipStream_t);
 size_t so2n_backward_carve(const egnn_ctx*, int32_t n_owned, int32_t n_total, char* base, So2nCall* out);
 int so2n_message_sum_backward(egnn_ctx*, const egnn_graph*, const int32_t* col_ptr, const int32_t* perm, const float* rhat_d,
                               const float* x, const float* W_e, const float* W, const float* da, float scale, float* dx,

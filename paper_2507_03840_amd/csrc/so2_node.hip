@@ -10,7 +10,8 @@
 //     a[(lo, mo)][c_out]    = sum_{li, L, c} (sum_m beta_L^m W_m)[c_out][c] T        (so2n_mix_kernel, matrix cores)
 // The destination's own embedding is the same for all of the edges: its S is the outer product of x_j with
 // g_j[LM] = sum_k f_k Yhat_LM(r_k).  The L = 0 plane of the initial edge embedding, W_e B(d), enters through
-// sum_k f_k Yhat_LM(r_k) B_b(d_k), L <= lmax.
+// sum_k f_k Yhat_LM(r_k) B_b(d_k), L <= lmax; persistent edge embeddings (node block) are gathered like the sources', each
+// edge its own row.
 #include "so2_node.h"
 #include "stream_gemm.h"
 #include "so2_node_gen.inc"
@@ -47,6 +48,7 @@ __host__ __device__ constexpr size_t so2n_lds_bytes(int lmax, int E) {
 }
 
 typedef _Float16 so2n_h2 __attribute__((ext_vector_type(2)));
+typedef float so2n_f4u __attribute__((ext_vector_type(4), aligned(4)));   // (a caller's array: any alignment of its type)
 typedef __amdgpu_buffer_rsrc_t so2n_rsrc;
 
 __device__ __forceinline__ uint32_t so2n_split(float x) {   // high piece in the low half, rest in the high half
@@ -136,6 +138,7 @@ struct So2nArgs {
   const float* alpha;        // optional further weight per edge
   const uint32_t* packed;    // feature rows in pieces
   unsigned packed_bytes;
+  const float* rows;         // OWN: the edges' own rows (fp32)
   const float* x_self;       // rows of the nodes themselves (fp32); NULL: that group is zero
   const float* g_in;         // sums of the harmonics for the self group; NULL: those of this list
   float* g_out;              // NULL: not kept
@@ -143,7 +146,7 @@ struct So2nArgs {
   unsigned* maxima;
   int j_begin, j_end;        // nodes of this launch; T starts at j_begin
   int n_self;                // nodes that have a self group
-  int per_xcd, E, n_slices, n_rbf;
+  int per_xcd, E, n_slices, n_rbf, form;
   float r_cut;
 };
 
@@ -160,7 +163,9 @@ struct So2nArgs {
 // per compute unit cannot overlap (loads of the node's edges, barriers, starting the next workgroup).  Matrix cores at the
 // contraction alone: 92 us.  Coupling on the matrix cores as well, with tables in memory: 630 us (chains of dependent loads);
 // persistent workgroups that request the next node's edges early: 532 us (67 registers spilled).
-template <int LMAX, int CS>
+// OWN: the rows are the edges' own, fp32 and read once from memory (2 GB: 560 us), cut into pieces on the way to the matrix
+// cores, for the third group alone.
+template <int LMAX, int CS, bool OWN>
 __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p) {
   constexpr int D = (LMAX + 1) * (LMAX + 1), NL = 2 * LMAX + 1, NLM = NL * NL, MT = so2n_mt(LMAX);
   constexpr int STEP = so2n_step_bytes(LMAX);
@@ -207,7 +212,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
       g_own = p.rhat_d[k];
       f_own = e_own < nb ? egnn_envelope(g_own.w, p.r_cut) * (p.alpha ? p.alpha[k] : 1.0f) : 0.0f;
       if (tid < SO2N_BATCH) {
-        s_off[e_own] = (unsigned)p.index[k] * (unsigned)(D * E * 4);
+        s_off[e_own] = (unsigned)(OWN ? at - k0 - b0 : p.index[k]) * (unsigned)(D * E * 4);
         s_d[e_own] = g_own.w;
       }
     }
@@ -227,9 +232,15 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   for (int q = 0; q < 8; ++q) wmax = fmaxf(wmax, s_red[q]);
   // |Yhat_LM| <= sqrt(17): three bits below the range the scaling of a maximum aims at
   const int ey = sgh_scale_exp(__float_as_uint(wmax)) - 3;
-  const int ex = sgh_scale_exp(p.maxima[0]);
+  const int ex = sgh_scale_exp(p.maxima[OWN ? 3 : 0]);
   const float y_scale = ldexpf(1.0f, ey), unscale = ldexpf(1.0f, -ex) * ldexpf(1.0f, -ey);
-  const so2n_rsrc xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.packed), 0, (int)p.packed_bytes, 0x00020000);
+  // (rows of the edges themselves lie together: those of a batch are addressed from its first)
+  auto rows_of = [&](int b0) SO2N_INLINE {
+    if (!OWN) return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint32_t*>(p.packed), 0, (int)p.packed_bytes, 0x00020000);
+    const int nb = deg - b0 < SO2N_BATCH ? deg - b0 : SO2N_BATCH;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.rows + (size_t)(k0 + b0) * (D * E)), 0, nb * (D * E * 4), 0x00020000);
+  };
+  const float x_scale = ldexpf(1.0f, ex);
   const unsigned lane_col = (unsigned)(slice * 32 + l32) * 4u;
   const unsigned tile_bytes = (unsigned)(CS == 32 ? E : 32) * 4u;
   float amax = 0.0f;
@@ -256,8 +267,8 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   // coupling of the blocks this wave owns: lane = (group, channel), group 0 reads S, group 1 forms g x on the spot
   const int c = lane % CS, grp = lane / CS;
   const float from_s = grp == 0 ? 1.0f : 0.0f, from_x = grp == 1 ? 1.0f : 0.0f;
-  const bool has_aux = p.n_rbf > 0;
-  const int node_floats = so2n_node_off(LMAX, E, LMAX + 1, has_aux);
+  const int form = p.form;
+  const int node_floats = so2n_node_off(LMAX, E, LMAX + 1, form);
   float* T = p.T + (size_t)node * node_floats;
   const so2n_rsrc tr = __builtin_amdgcn_make_buffer_rsrc(T, 0, node_floats * 4, 0x00020000);
   auto couple = [&](auto li_c, auto L_c) SO2N_INLINE {
@@ -286,10 +297,10 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
     for (int lo = 0; lo <= LMAX; ++lo) {
       if (L >= (lo > li ? lo - li : li - lo) && L <= lo + li) {
         const int path = so2n_path_base(lo, li) + L - (lo > li ? lo - li : li - lo);
-        const int np = so2n_paths(LMAX, lo), ld = so2n_ld(LMAX, E, lo, has_aux);
-        const int at0 = so2n_node_off(LMAX, E, lo, has_aux) + path * E + slice * 32;
+        const int np = so2n_paths(LMAX, lo), ld = so2n_ld(LMAX, E, lo, form);
+        const int at0 = so2n_node_off(LMAX, E, lo, form) + path * E + slice * 32;
         // (lanes past the two groups: an offset the range check drops)
-        const int lane_at = grp < 2 ? (grp * np * E + c) * 4 : node_floats * 4;
+        const int lane_at = grp < (OWN ? 1 : 2) ? ((OWN ? 2 : grp) * np * E + c) * 4 : node_floats * 4;
 #pragma unroll
         for (int mo = 0; mo < 2 * lo + 1; ++mo) {
           const float v = o[lo * lo + mo];
@@ -324,6 +335,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
         load_edge(b0);
         so2n_barrier();
       }
+      const so2n_rsrc xr = rows_of(b0);
       uint32_t w[N][8];
       unsigned o[8];
       auto offsets = [&](int s) SO2N_INLINE {
@@ -350,7 +362,14 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
 #pragma unroll
         for (int i = 0; i < N; ++i) {
           uint4 bh, bl;
-          so2n_pieces(w[i], bh, bl);
+          if (OWN) {
+            float v[8];
+#pragma unroll
+            for (int q = 0; q < 8; ++q) v[q] = __uint_as_float(w[i][q]);
+            sgh_split8(v, x_scale, bh, bl);
+          } else {
+            so2n_pieces(w[i], bh, bl);
+          }
           fetch(i);
           __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -459,10 +478,10 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
       for (int i = 0; i < 16; ++i) {
         const int lm = 8 * (i >> 2) + 4 * hh + (i & 3);
         if (lm < D) {
-          const int lo = lm < 1 ? 0 : lm < 4 ? 1 : lm < 9 ? 2 : lm < 16 ? 3 : 4, ld = so2n_ld(LMAX, E, lo, true);
+          const int lo = lm < 1 ? 0 : lm < 4 ? 1 : lm < 9 ? 2 : lm < 16 ? 3 : 4, ld = so2n_ld(LMAX, E, lo, SO2N_GAUSS);
           const float v = u * acc[i];
           amax = fmaxf(amax, fabsf(v));
-          T[so2n_node_off(LMAX, E, lo, true) + (lm - lo * lo + 1) * ld - SO2N_AUX + l32] = v;
+          T[so2n_node_off(LMAX, E, lo, SO2N_GAUSS) + (lm - lo * lo + 1) * ld - SO2N_AUX + l32] = v;
         }
       }
     }
@@ -508,6 +527,138 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   if (tid == 0) atomicMax(p.maxima + 2, __float_as_uint(s_red[8]));   // (no result is waited for)
 }
 
+// ---------------------------------------------------------------------------------------------- attention scores
+// score[k] = sum_c w_att[c] leaky(y0[k][c]) with y0 = the L = 0 plane of edge k's message: that plane needs only the m = 0
+// component of every degree in the bond frame, sum_M Yhat_lM x_lM / sqrt(2 l + 1), of the three rows (edge, source,
+// destination), and the first E rows of W_0.  A workgroup takes 32 consecutive edges and the three groups one after
+// another: threads (edge, channel) form the components in LDS, four waves share the contraction over (l, channel)
+// (v_mfma_f32_32x32x2_f32, lane = edge).  Bound: the edge rows, read here and once more by the gathering kernel, because
+// the softmax stands in between; 628,000 edges, lmax 4, 32 channels: 660 us, of which matrix cores 122 and vector ALU about
+// 235 (all three groups in LDS at once, two workgroups per compute unit: 937).  The largest magnitude among them is kept
+// for that kernel's scaling.
+template <int LMAX>
+__global__ __launch_bounds__(256) void so2n_score_kernel(const int* __restrict__ src, const int* __restrict__ dst,
+                                                         const float4* __restrict__ rhat_d, const float* __restrict__ x,
+                                                         unsigned x_bytes, const float* __restrict__ T_edge, const float* __restrict__ W,
+                                                         const float* __restrict__ w_att, float* __restrict__ score,
+                                                         long n_edges, int log2E, unsigned* __restrict__ t_max) {
+  constexpr int D = (LMAX + 1) * (LMAX + 1), NL = LMAX + 1;
+  extern __shared__ float so2n_sf[];
+  __shared__ float s_h[32][D + 1];
+  __shared__ float s_part[4][32];
+  __shared__ float s_mx[4];
+  const int E = 1 << log2E, K = NL * E, ldq = K + 4;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, l32 = lane & 31, hh = lane >> 5;
+  const long e0 = (long)blockIdx.x * 32;
+  const int ne = n_edges - e0 < 32 ? (int)(n_edges - e0) : 32;
+  if (tid < 32) {
+    const float4 g = rhat_d[e0 + (tid < ne ? tid : ne - 1)];
+    so2n_harmonics<NL, 0, LMAX>(g.x, g.y, g.z, 1.0f, [&](int lm, float v) SO2N_INLINE { s_h[tid][lm] = v; });
+  }
+  __syncthreads();
+  const int c = tid & (E - 1), slot = tid >> log2E, n_slots = 256 >> log2E;
+  float mx = 0.0f;
+  // The contraction runs in steps of 8 columns, four of them per half-wave.  Up to 32 channels the waves share the columns and
+  // their sums meet in LDS before the non-linearity; with 64, waves 0 and 1 (2 and 3) share those of a block of 32 channels.
+  const int n_cb = E > 32 ? 2 : 1, cb = E > 32 ? wave >> 1 : 0, part = E > 32 ? wave & 1 : wave, parts = 4 / n_cb;
+  const int n_steps = K / 8, per = (n_steps + parts - 1) / parts;
+  const int s1 = (part + 1) * per < n_steps ? (part + 1) * per : n_steps;
+  float16v acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+  const bool live = cb * 32 + l32 < E;
+  const float* w_row = W + (size_t)(live ? cb * 32 + l32 : 0) * (3 * K) + 4 * hh;
+  const float* q_row = so2n_sf + (size_t)l32 * ldq + 4 * hh;
+  constexpr int U = 5;
+  const so2n_rsrc xr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(x), 0, (int)x_bytes, 0x00020000);
+  const so2n_rsrc tr = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(T_edge + (((size_t)e0 * D) << log2E)), 0,
+                                                         (ne * D) << (log2E + 2), 0x00020000);
+  auto group = [&](auto grp_c) SO2N_INLINE {
+    constexpr int GRP = decltype(grp_c)::value;         // as in the weights: 0 source, 1 destination, 2 edge
+    for (int e = slot; e < 32; e += n_slots) {
+      const long k = e0 + (e < ne ? e : ne - 1);        // (the copies of the last edge are not stored)
+      // (buffer loads: the 25 offsets within a row are scalars; formed per lane they were half of the kernel's instructions)
+      const unsigned row = GRP == 2 ? (unsigned)(k - e0) : (unsigned)(GRP == 0 ? src[k] : dst[k]);
+      const int at = (int)(((row * D) << (log2E + 2)) + 4 * c);
+      float v[D];
+#pragma unroll
+      for (int i = 0; i < D; ++i)
+        v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(GRP == 2 ? tr : xr, at, i << (log2E + 2), GRP == 2 ? 2 : 0));
+      float* q = so2n_sf + (size_t)e * ldq + c;
+#pragma unroll
+      for (int l = 0; l <= LMAX; ++l) {
+        constexpr float inv[5] = {1.0f, 0.57735026918962576f, 0.44721359549995794f, 0.37796447300922722f, 0.33333333333333333f};
+        float a = 0.0f;
+#pragma unroll
+        for (int i = l * l; i < (l + 1) * (l + 1); ++i) {
+          a += s_h[e][i] * v[i];
+          if (GRP == 2) mx = fmaxf(mx, fabsf(v[i]));
+        }
+        q[l << log2E] = a * inv[l];
+      }
+    }
+    __syncthreads();
+    for (int s = part * per; s < s1; s += U) {
+      sg_f4 wv[U], qv[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int su = s + u < s1 ? s + u : s1 - 1, l = (su * 8) >> log2E;
+        wv[u] = *reinterpret_cast<const so2n_f4u*>(w_row + su * 8 + (2 * l + GRP) * E);
+        qv[u] = *reinterpret_cast<const sg_f4*>(q_row + su * 8);
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u)
+        if (s + u < s1)
+#pragma unroll
+          for (int t = 0; t < 4; ++t)
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(live ? wv[u][t] : 0.0f, qv[u][t], acc, 0, 0, 0);
+    }
+    __syncthreads();
+  };
+  group(std::integral_constant<int, 2>{});
+  group(std::integral_constant<int, 0>{});
+  group(std::integral_constant<int, 1>{});
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  if (lane == 0) s_mx[wave] = mx;
+  // (the components are consumed: partial sums take their place)
+#pragma unroll
+  for (int i = 0; i < 16; ++i) so2n_sf[(wave * 16 + i) * 64 + lane] = acc[i];
+  __syncthreads();
+  if (tid == 0) egnn_raise_max(t_max, fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3])));
+  float sc = 0.0f;
+  for (int r = wave; r < 16 * n_cb; r += 4) {
+    const int b = r >> 4, i = r & 15, co = b * 32 + 8 * (i >> 2) + 4 * hh + (i & 3);
+    float v = 0.0f;
+    for (int z = 0; z < parts; ++z) v += so2n_sf[((b * parts + z) * 16 + i) * 64 + lane];
+    if (co < E) sc += w_att[co] * (v > 0.0f ? v : 0.2f * v);
+  }
+  sc += __shfl_xor(sc, 32);
+  if (hh == 0) s_part[wave][l32] = sc;
+  __syncthreads();
+  if (tid < ne) score[e0 + tid] = (s_part[0][tid] + s_part[1][tid]) + (s_part[2][tid] + s_part[3][tid]);
+}
+
+// scores -> attention weights, in place; a wavefront per node
+__global__ __launch_bounds__(256) void so2n_softmax_kernel(const int* __restrict__ row_ptr, float* __restrict__ alpha, int n_owned) {
+  const int lane = threadIdx.x & 63;
+  const int j = blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (j >= n_owned) return;
+  const int k0 = row_ptr[j], k1 = row_ptr[j + 1];
+  float mx = -3.0e38f;
+  for (int k = k0 + lane; k < k1; k += 64) mx = fmaxf(mx, alpha[k]);
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  float sum = 0.0f;
+  for (int k = k0 + lane; k < k1; k += 64) {
+    const float e = __expf(alpha[k] - mx);
+    alpha[k] = e;                               // read again by this lane alone
+    sum += e;
+  }
+  for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+  const float inv = 1.0f / sum;
+  for (int k = k0 + lane; k < k1; k += 64) alpha[k] *= inv;
+}
+
 // ---------------------------------------------------------------------------------------------- features in pieces
 // (one atomic per workgroup: from every wavefront at once they cost 80 us on 2.4 million values)
 __global__ __launch_bounds__(256) void so2n_max_kernel(const float* __restrict__ x, long n, unsigned* __restrict__ out) {
@@ -538,10 +689,10 @@ struct So2nW {
 // input degree of the forward pass, the paths run over its output degrees; swapping the two degrees of a coupling tensor
 // changes its sign with the parity of the degrees.
 __device__ float so2n_weight(const float* __restrict__ W, const float* __restrict__ W_e, const So2nW& s, int lmax, int E, int a,
-                             int k, int col, int n_rbf, bool transposed) {
+                             int k, int col, int n_rbf, int form, bool transposed) {
   const int np = so2n_paths(lmax, a);
-  if (k >= 2 * np * E) {
-    const int b = k - 2 * np * E;
+  if (k >= so2n_groups(form) * np * E) {
+    const int b = k - so2n_groups(form) * np * E;
     if (b >= n_rbf) return 0.0f;
     const float* row = W + (size_t)(a * E + col) * ((lmax + 1) * 3 * E) + 2 * E;   // W_0, edge columns of degree 0
     float sum = 0.0f;
@@ -567,7 +718,7 @@ __device__ float so2n_weight(const float* __restrict__ W, const float* __restric
 }
 
 __global__ __launch_bounds__(256) void so2n_weights_kernel(const float* __restrict__ W, const float* __restrict__ W_e, So2nW s,
-                                                           int lmax, int E, int n_rbf, bool transposed,
+                                                           int lmax, int E, int n_rbf, int form, bool transposed,
                                                            float* __restrict__ out, unsigned* __restrict__ w_max) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   float v = 0.0f;
@@ -575,7 +726,7 @@ __global__ __launch_bounds__(256) void so2n_weights_kernel(const float* __restri
     const int row = (int)(i / E), col = (int)(i - (long)row * E);
     int a = 0;
     while (row >= s.k_first[a + 1]) ++a;
-    v = so2n_weight(W, W_e, s, lmax, E, a, row - s.k_first[a], col, n_rbf, transposed);
+    v = so2n_weight(W, W_e, s, lmax, E, a, row - s.k_first[a], col, n_rbf, form, transposed);
     out[i] = v;
   }
   float mx = fabsf(v);
@@ -866,7 +1017,7 @@ __global__ __launch_bounds__(256) void so2n_unpack_wgrad_kernel(const float* __r
 // ---------------------------------------------------------------------------------------------- host side
 static size_t so2n_a256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-static void so2n_w_layout(int lmax, int E, bool aux, So2nW* s, So2nSteps* st) {
+static void so2n_w_layout(int lmax, int E, int form, So2nW* s, So2nSteps* st) {
   size_t off = 0;
   s->k_first[0] = st->first[0] = 0;
   for (int m = 0; m < 5; ++m) { s->off[m] = 0; s->K[m] = 0; }
@@ -877,7 +1028,7 @@ static void so2n_w_layout(int lmax, int E, bool aux, So2nW* s, So2nSteps* st) {
   }
   s->off[5] = off;
   for (int lo = 0; lo <= lmax; ++lo) {
-    s->K[lo] = so2n_ld(lmax, E, lo, aux);
+    s->K[lo] = so2n_ld(lmax, E, lo, form);
     s->k_first[lo + 1] = s->k_first[lo] + s->K[lo];
     st->first[lo + 1] = st->first[lo] + (s->K[lo] + 15) / 16;
   }
@@ -891,20 +1042,20 @@ static size_t so2n_packed_bytes(const egnn_ctx* ctx, long n_rows) {   // (a last
   return (size_t)n_rows * (ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels * 4 + 128;
 }
 
-size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t n_t, bool aux, char* base, So2nCall* out) {
+size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t n_t, int form, char* base, So2nCall* out) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   size_t used = 0;
   auto take = [&](size_t bytes) { char* q = base ? base + used : nullptr; used += so2n_a256(bytes); return q; };
   So2nW s;
   So2nSteps st;
-  so2n_w_layout(lmax, E, aux, &s, &st);
+  so2n_w_layout(lmax, E, form, &s, &st);
   So2nCall c;
   c.maxima = (unsigned*)take(256);
   c.packed = (uint32_t*)take(so2n_packed_bytes(ctx, n_rows));
   c.g = (float*)take((size_t)n_owned * so2n_nlm(lmax) * 4);
   c.wpath = (float*)take((size_t)s.k_first[lmax + 1] * E * 4);
   c.wpack = (uint4*)take((size_t)st.first[lmax + 1] * ((E + 31) / 32) * 128 * 16);
-  c.T = (float*)take((size_t)n_t * so2n_node_off(lmax, E, lmax + 1, aux) * 4);
+  c.T = (float*)take((size_t)n_t * so2n_node_off(lmax, E, lmax + 1, form) * 4);
   c.partial = nullptr;
   if (out) *out = c;
   return used;
@@ -920,15 +1071,15 @@ int so2n_pack_features(egnn_ctx* ctx, const float* x, long n_rows, const So2nCal
   return EGNN_OK;
 }
 
-int so2n_pack_weights(egnn_ctx* ctx, const float* W, const float* W_e, bool aux, bool transposed, const So2nCall& c,
+int so2n_pack_weights(egnn_ctx* ctx, const float* W, const float* W_e, int form, bool transposed, const So2nCall& c,
                       hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   So2nW s;
   So2nSteps steps;
-  so2n_w_layout(lmax, E, aux, &s, &steps);
+  so2n_w_layout(lmax, E, form, &s, &steps);
   const long n = (long)s.k_first[lmax + 1] * E;
   hipLaunchKernelGGL(so2n_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, W, W_e, s, lmax, E,
-                     ctx->desc.n_rbf, transposed, c.wpath, c.maxima + 1);
+                     ctx->desc.n_rbf, form, transposed, c.wpath, c.maxima + 1);
   EGNN_LAUNCH_CHECK(ctx, "so2n_weights_kernel");
   const int n_cb = (E + 31) / 32;
   const long m = (long)steps.first[lmax + 1] * n_cb * 64;
@@ -938,19 +1089,20 @@ int so2n_pack_weights(egnn_ctx* ctx, const float* W, const float* W_e, bool aux,
   return EGNN_OK;
 }
 
-template <int LMAX, int CS>
+template <int LMAX, int CS, bool OWN>
 static int so2n_launch_gather_t(egnn_ctx* ctx, const So2nArgs& a, hipStream_t st) {
   constexpr size_t lds = so2n_lds_bytes(LMAX, CS);
   if (lds > 64 * 1024) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(so2n_gather_kernel<LMAX, CS>),
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(so2n_gather_kernel<LMAX, CS, OWN>),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
     if (e != hipSuccess) return egnn_check_hip(ctx, e, "hipFuncSetAttribute(so2n_gather_kernel)");
   }
-  hipLaunchKernelGGL((so2n_gather_kernel<LMAX, CS>), dim3(8u * a.per_xcd * a.n_slices), dim3(SO2N_THREADS), lds, st, a);
+  hipLaunchKernelGGL((so2n_gather_kernel<LMAX, CS, OWN>), dim3(8u * a.per_xcd * a.n_slices), dim3(SO2N_THREADS), lds, st, a);
   EGNN_LAUNCH_CHECK(ctx, "so2n_gather_kernel");
   return EGNN_OK;
 }
 
+template <bool OWN>
 static int so2n_launch_gather(egnn_ctx* ctx, So2nArgs a, hipStream_t st) {
   const int n = a.j_end - a.j_begin;
   if (n <= 0) return EGNN_OK;
@@ -958,7 +1110,12 @@ static int so2n_launch_gather(egnn_ctx* ctx, So2nArgs a, hipStream_t st) {
   a.r_cut = ctx->desc.r_cut;
   a.n_slices = (a.E + 31) / 32;
   a.per_xcd = (n + 7) / 8;
-#define SO2N_L(L)                                                switch (so2n_cs(a.E)) {                                          case 8: return so2n_launch_gather_t<L, 8>(ctx, a, st);         case 16: return so2n_launch_gather_t<L, 16>(ctx, a, st);       default: return so2n_launch_gather_t<L, 32>(ctx, a, st);     }
+#define SO2N_L(L)                                                     \
+  switch (so2n_cs(a.E)) {                                             \
+    case 8: return so2n_launch_gather_t<L, 8, OWN>(ctx, a, st);       \
+    case 16: return so2n_launch_gather_t<L, 16, OWN>(ctx, a, st);     \
+    default: return so2n_launch_gather_t<L, 32, OWN>(ctx, a, st);     \
+  }
   switch (ctx->desc.lmax) {
     case 0: SO2N_L(0)
     case 1: SO2N_L(1)
@@ -969,21 +1126,21 @@ static int so2n_launch_gather(egnn_ctx* ctx, So2nArgs a, hipStream_t st) {
 #undef SO2N_L
 }
 
-static int so2n_launch_mix(egnn_ctx* ctx, const So2nCall& c, bool aux, int n_nodes, float scale, float* out, hipStream_t st) {
+static int so2n_launch_mix(egnn_ctx* ctx, const So2nCall& c, int form, int n_nodes, float scale, float* out, hipStream_t st) {
   if (n_nodes <= 0) return EGNN_OK;
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   So2nMix p;
   So2nW s;
-  so2n_w_layout(lmax, E, aux, &s, &p.st);
+  so2n_w_layout(lmax, E, form, &s, &p.st);
   p.T = c.T;
-  p.node_floats = so2n_node_off(lmax, E, lmax + 1, aux);
+  p.node_floats = so2n_node_off(lmax, E, lmax + 1, form);
   p.w = c.wpack;
   p.n_nodes = n_nodes; p.lmax = lmax; p.E = E; p.scale = scale; p.out = out; p.maxima = c.maxima;
   p.blocks[0] = 0;
   for (int lo = 0; lo < 5; ++lo) {
     p.K[lo] = s.K[lo];
-    p.ld[lo] = so2n_ld(lmax, E, lo, aux);
-    p.off[lo] = so2n_node_off(lmax, E, lo, aux);
+    p.ld[lo] = so2n_ld(lmax, E, lo, form);
+    p.off[lo] = so2n_node_off(lmax, E, lo, form);
     p.blocks[lo + 1] = p.blocks[lo] + (lo <= lmax ? (int)(((long)n_nodes * (2 * lo + 1) + 31) / 32) : 0);
   }
   const dim3 grid((unsigned)p.blocks[lmax + 1]), block(256);
@@ -994,20 +1151,20 @@ static int so2n_launch_mix(egnn_ctx* ctx, const So2nCall& c, bool aux, int n_nod
   return EGNN_OK;
 }
 
-static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, bool aux, So2nWgrad* p) {
+static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, int form, So2nWgrad* p) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
-  p->node_floats = so2n_node_off(lmax, E, lmax + 1, aux);
+  p->node_floats = so2n_node_off(lmax, E, lmax + 1, form);
   p->n_nodes = n_nodes; p->E = E; p->n_ct = (E + 31) / 32; p->D = (lmax + 1) * (lmax + 1);
   int tiles = 0;
-  for (int lo = 0; lo <= lmax; ++lo) tiles += (2 * lo + 1) * ((so2n_ld(lmax, E, lo, aux) + 127) / 128) * p->n_ct;
+  for (int lo = 0; lo <= lmax; ++lo) tiles += (2 * lo + 1) * ((so2n_ld(lmax, E, lo, form) + 127) / 128) * p->n_ct;
   // about 2,048 waves (two per SIMD): rows (node, mo) per wave, in steps of 16 nodes
   const long rows = std::max<long>(16, ((long)n_nodes * tiles + 2047) / 2048);
   p->unit0[0] = 0;
   p->part0[0] = 0;
   for (int lo = 0; lo < 5; ++lo) {
     const bool there = lo <= lmax;
-    p->K[lo] = p->ld[lo] = there ? so2n_ld(lmax, E, lo, aux) : 0;
-    p->off[lo] = there ? so2n_node_off(lmax, E, lo, aux) : 0;
+    p->K[lo] = p->ld[lo] = there ? so2n_ld(lmax, E, lo, form) : 0;
+    p->off[lo] = there ? so2n_node_off(lmax, E, lo, form) : 0;
     p->k_tiles[lo] = there ? (p->K[lo] + 127) / 128 : 1;
     p->per_chunk[lo] = (int)((rows / (2 * lo + 1) + 15) / 16 * 16);
     if (p->per_chunk[lo] < 16) p->per_chunk[lo] = 16;
@@ -1020,11 +1177,12 @@ static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, bool aux, So2nWgra
 size_t so2n_backward_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_total, char* base, So2nCall* out) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   // T of the owned nodes (with the Gaussian columns) and then of all nodes share one buffer
-  const size_t with = (size_t)n_owned * so2n_node_off(lmax, E, lmax + 1, true), without = (size_t)n_total * so2n_node_off(lmax, E, lmax + 1, false);
-  size_t used = so2n_carve(ctx, n_owned, n_total, 0, true, base, out);
+  const size_t with = (size_t)n_owned * so2n_node_off(lmax, E, lmax + 1, SO2N_GAUSS),
+               without = (size_t)n_total * so2n_node_off(lmax, E, lmax + 1, SO2N_PLAIN);
+  size_t used = so2n_carve(ctx, n_owned, n_total, 0, SO2N_GAUSS, base, out);
   auto take = [&](size_t bytes) { char* q = base ? base + used : nullptr; used += so2n_a256(bytes); return q; };
   So2nWgrad p;
-  so2n_wgrad_plan(ctx, n_owned, true, &p);
+  so2n_wgrad_plan(ctx, n_owned, SO2N_GAUSS, &p);
   float* partial = (float*)take(p.part0[lmax + 1] * 4);
   float* T = (float*)take(std::max(with, without) * 4);
   if (out) { out->T = T; out->partial = partial; }
@@ -1045,16 +1203,16 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.maxima = c.maxima; p.g_out = c.g;
-  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.n_rbf = ctx->desc.n_rbf;
-  if ((rc = so2n_launch_gather(ctx, p, st))) return rc;
+  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.n_rbf = ctx->desc.n_rbf; p.form = SO2N_GAUSS;
+  if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   So2nCall c2 = c;
   c2.maxima = c.maxima + 16;
   if ((rc = so2n_pack_features(ctx, da, g->n_owned, c2, st))) return rc;
   So2nW s;
   So2nSteps steps;
-  so2n_w_layout(lmax, E, true, &s, &steps);
+  so2n_w_layout(lmax, E, SO2N_GAUSS, &s, &steps);
   So2nWgrad w;
-  so2n_wgrad_plan(ctx, g->n_owned, true, &w);
+  so2n_wgrad_plan(ctx, g->n_owned, SO2N_GAUSS, &w);
   w.T = c.T; w.da = da; w.partial = c.partial; w.t_max = c.maxima + 2; w.da_max = c2.maxima;
   hipLaunchKernelGGL(so2n_wgrad_kernel, dim3((w.unit0[5] + 3) / 4), dim3(256), 0, st, w);
   EGNN_LAUNCH_CHECK(ctx, "so2n_wgrad_kernel");
@@ -1067,10 +1225,10 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   EGNN_LAUNCH_CHECK(ctx, "so2n_unpack_wgrad_kernel");
   p.ptr = col_ptr; p.perm = perm; p.index = g->dst;
   p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_owned); p.x_self = da; p.maxima = c2.maxima; p.g_out = nullptr; p.g_in = c.g;
-  p.j_end = g->n_total; p.n_rbf = 0;
-  if ((rc = so2n_launch_gather(ctx, p, st))) return rc;
-  if ((rc = so2n_pack_weights(ctx, W, nullptr, false, true, c2, st))) return rc;
-  return so2n_launch_mix(ctx, c2, false, g->n_total, scale, dx, st);
+  p.j_end = g->n_total; p.n_rbf = 0; p.form = SO2N_PLAIN;
+  if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_PLAIN, true, c2, st))) return rc;
+  return so2n_launch_mix(ctx, c2, SO2N_PLAIN, g->n_total, scale, dx, st);
 }
 
 // a[j] for the owned nodes; rhat_d and c carved by the caller, c.maxima zero on entry
@@ -1078,12 +1236,55 @@ int so2n_message_sum(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, co
                      float scale, float* a, const So2nCall& c, hipStream_t st) {
   int rc;
   if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
-  if ((rc = so2n_pack_weights(ctx, W, W_e, true, false, c, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, W_e, SO2N_GAUSS, false, c, st))) return rc;
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.maxima = c.maxima;
-  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.n_rbf = ctx->desc.n_rbf;
-  if ((rc = so2n_launch_gather(ctx, p, st))) return rc;
-  return so2n_launch_mix(ctx, c, true, g->n_owned, scale, a, st);
+  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.n_rbf = ctx->desc.n_rbf; p.form = SO2N_GAUSS;
+  if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
+  return so2n_launch_mix(ctx, c, SO2N_GAUSS, g->n_owned, scale, a, st);
+}
+
+// Node block: scores, their softmax, then the sums over the incoming edges weighted with it: source and destination as in the
+// message sum, the edges' own rows by a second gathering launch into the third group.
+int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* x, const float* T_edge, const float* W,
+                    const float* w_att, float* alpha, float* a, const So2nCall& c, hipStream_t st) {
+  const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
+  int rc;
+  if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_EDGES, false, c, st))) return rc;
+  const size_t lds = std::max<size_t>(32 * (size_t)((lmax + 1) * E + 4) * 4, 16384);
+  const dim3 grid((unsigned)((g->n_edges + 31) / 32));
+  const unsigned x_bytes = (unsigned)((size_t)g->n_total * (lmax + 1) * (lmax + 1) * E * 4);   // (32 bits: the caller's rule)
+#define SO2N_SCORE(L)                                                                                                         \
+  do {                                                                                                                        \
+    if (lds > 48 * 1024) {                                                                                                    \
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(so2n_score_kernel<L>),                                 \
+                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);                               \
+      if (e != hipSuccess) return egnn_check_hip(ctx, e, "hipFuncSetAttribute(so2n_score_kernel)");                           \
+    }                                                                                                                         \
+    hipLaunchKernelGGL(so2n_score_kernel<L>, grid, dim3(256), lds, st, g->src, g->dst, reinterpret_cast<const float4*>(rhat_d), \
+                       x, x_bytes, T_edge, W, w_att, alpha, (long)g->n_edges, ctx->log2_channels, c.maxima + 3);              \
+  } while (0)
+  switch (lmax) {
+    case 0: SO2N_SCORE(0); break;
+    case 1: SO2N_SCORE(1); break;
+    case 2: SO2N_SCORE(2); break;
+    case 3: SO2N_SCORE(3); break;
+    default: SO2N_SCORE(4); break;
+  }
+#undef SO2N_SCORE
+  EGNN_LAUNCH_CHECK(ctx, "so2n_score_kernel");
+  hipLaunchKernelGGL(so2n_softmax_kernel, dim3((g->n_owned + 3) / 4), dim3(256), 0, st, g->row_ptr, alpha, g->n_owned);
+  EGNN_LAUNCH_CHECK(ctx, "so2n_softmax_kernel");
+  So2nArgs p = {};
+  p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d); p.alpha = alpha;
+  p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
+  p.T = c.T; p.maxima = c.maxima; p.form = SO2N_EDGES;
+  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned;
+  if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
+  p.rows = T_edge; p.x_self = nullptr;
+  if ((rc = so2n_launch_gather<true>(ctx, p, st))) return rc;
+  return so2n_launch_mix(ctx, c, SO2N_EDGES, g->n_owned, 1.0f, a, st);
 }

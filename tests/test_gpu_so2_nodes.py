@@ -11,6 +11,9 @@ pytestmark = pytest.mark.gpu
 # Operands are cut to 22 bits twice (harmonics x features, coupled sums x weights), relative error 2^-22 per operand and
 # product at most, four operands: 4 * 2.4e-7; as much again for the 32-bit sums over up to 300 edges and 3,300 products.
 TOL = 2e-6
+# The attention weights: __expf of a score difference of up to ~10, whose 32-bit rounding (a sum of up to 3,000 products)
+# enters as an absolute error, 10 * 6e-8 times a few.
+TOL_ATT = 5e-6
 
 
 @pytest.fixture(scope="module")
@@ -56,6 +59,31 @@ def test_message_sum_per_node(B, lmax, E, n, n_owned, n_rbf):
     print(f"  {graph.n_edges} edges, rel err {e:.2e}", flush=True)
     assert e < TOL
     assert np.array_equal(a, m.egnn_so2_message_sum(*args, ws).cpu().numpy())
+
+
+@pytest.mark.parametrize("lmax,E,n,n_owned", [
+    # around the smallest degree of this route (31 is below it), ragged tiles of 32 edges, a batch of 256
+    (4, 32, 32, 9), (4, 32, 33, 1), (4, 32, 33, 31), (4, 32, 34, 5), (4, 32, 257, 2), (4, 32, 258, 3), (2, 32, 300, 4),
+    (0, 8, 40, 33), (0, 16, 40, 8), (0, 32, 36, 7), (1, 8, 40, 9), (1, 64, 40, 9), (2, 8, 37, 17), (2, 16, 41, 16), (3, 8, 39, 10),
+    (3, 16, 65, 10), (3, 32, 49, 10), (3, 64, 34, 10), (4, 8, 40, 13), (4, 16, 47, 12), (4, 64, 48, 11),
+    (3, 128, 35, 9)])                                                  # (more channels than this route takes)
+def test_node_block_per_node(B, lmax, E, n, n_owned):
+    import torch
+    print("case", lmax, E, n, n_owned, flush=True)
+    w, g, x, W_e, W0, Wr, Wi = case(lmax, E, n, n_owned, 8)
+    rng = np.random.default_rng(n)
+    T = rng.standard_normal((len(g[0]), (lmax + 1) ** 2, E)).astype(np.float32)
+    w_att = synth.normal(rng, (E,)).astype(np.float32)
+    ref = S.so2_node_block(g, w.pos, w.box, x, T, W0, Wr, Wi, w_att, lmax, E, w.r_cut)
+    m = B.Egnn(lmax, E, 8, w.r_cut, 7.0)
+    graph = m.egnn_nlist(B.to_device(w.pos), n_owned, w.box, w.pbc)
+    args = (graph, B.to_device(w.pos), w.box, B.to_device(x), B.to_device(T), B.to_device(S.so2_pack(W0, Wr, Wi)), B.to_device(w_att))
+    ws = torch.full((m.egnn_so2_blocks_workspace_bytes(graph.n_edges),), 0xFF, dtype=torch.uint8, device="cuda")
+    a = m.egnn_so2_node_block(*args, ws).cpu().numpy()
+    e = U.rel_err(a, ref)
+    print(f"  {graph.n_edges} edges, rel err {e:.2e}", flush=True)
+    assert e < TOL_ATT
+    assert np.array_equal(a, m.egnn_so2_node_block(*args, ws).cpu().numpy())
 
 
 # Weight gradients are differences of sums over all edges: the fp32 rounding of the terms enters with the ratio of their
