@@ -18,12 +18,13 @@
 //   4. so2_scatter_kernel  one workgroup per destination node, lane = (edge slot, channel): m-major rows of Y back to
 //                          (l, m) order, rotated back, times f_c, summed; slots added in fixed order (no atomics).
 // The sums of messages (plain and attention-weighted) mix their channels per node instead where nodes have enough edges
-// (so2_node.hip); this per-edge form serves sparse graphs, the edge block, whose messages are not summed, and the adjoints
-// of the two blocks.
+// (so2_node.hip), and the edge block keeps its operands in LDS (so2_edge.hip); this per-edge form serves sparse graphs, the
+// channel counts those do not take and the adjoints of the two blocks.
 #include <type_traits>
 #include "egnn_internal.h"
 #include "bond_frame.h"
 #include "stream_gemm.h"
+#include "so2_edge.h"
 #include "so2_node.h"
 
 struct So2Bufs {
@@ -630,6 +631,20 @@ static bool so2_block_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
              so2_ws(ctx, g->n_edges, true, false, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
+// Whether the edge block runs as one kernel over tiles of edges (so2_edge.hip).  us per call, per-edge kernels -> tiles: lmax 4,
+// 32 channels, 3,000 nodes with 209 / 37.8 / 1.6 edges each 5,000 -> 3,615 / 985 -> 713 / 216 -> 98; lmax 4, 64 channels,
+// 37.8 2,528 -> 2,085; lmax 2, 16 channels 225 -> 128; 100 nodes 61 -> 30 to 346 -> 154.  With 128 channels every tile of
+// edges would be rotated four times (lmax 2, 37.8 edges 1,907 -> 2,957), and 8 are half a matrix instruction: both stay
+// per edge.  So does an update in place with 64 channels, because its two blocks of output channels are two workgroups.
+static bool so2_block_use_tiles(const egnn_ctx* ctx, const egnn_graph* g, const float* T_in, const float* T_out) {
+  const int E = ctx->desc.channels;
+  const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * E * 4, all = (size_t)g->n_edges * row;
+  const uintptr_t in = (uintptr_t)T_in, out = (uintptr_t)T_out;
+  return E >= 16 && E <= 64 && (E <= 32 || in + all <= out || out + all <= in) && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
+         so2_a256((size_t)g->n_edges * 16) + 256 + so2e_weight_bytes(ctx) <=
+             so2_ws(ctx, g->n_edges, true, false, nullptr, nullptr, nullptr, nullptr, nullptr);
+}
+
 static int so2_scatter(egnn_ctx* ctx, const egnn_graph* g, const So2Call& call, const float* alpha, float scale, float* a,
                        hipStream_t st) {
   if (g->n_owned == 0) return EGNN_OK;
@@ -731,6 +746,13 @@ extern "C" int egnn_so2_edge_block(egnn_ctx* ctx, const egnn_graph* g, const flo
   if (n == 0) return EGNN_OK;
   if (!T_edge_in || !T_edge_out) return egnn_fail(ctx, EGNN_EINVAL, "so2_edge_block: null edge embeddings");
   hipStream_t st = (hipStream_t)stream;
+  if (so2_block_use_tiles(ctx, g, T_edge_in, T_edge_out)) {
+    float* rhat_d = (float*)ws;
+    unsigned* w_max = (unsigned*)((char*)ws + so2_a256((size_t)n * 16));
+    if ((rc = egnn_launch_fill_int(ctx, (int*)w_max, 64, 0, st))) return rc;
+    if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st))) return rc;
+    return so2e_edge_block(ctx, g, rhat_d, x, T_edge_in, W_so2, T_edge_out, w_max, (uint4*)(w_max + 64), st);
+  }
   So2Call call;
   if ((rc = so2_transform(ctx, g, pos, box, x, T_edge_in, true, W_so2, ws, &call, st))) return rc;
   const float4* rd = reinterpret_cast<const float4*>(call.rhat_d);

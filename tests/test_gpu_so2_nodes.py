@@ -86,6 +86,46 @@ def test_node_block_per_node(B, lmax, E, n, n_owned):
     assert np.array_equal(a, m.egnn_so2_node_block(*args, ws).cpu().numpy())
 
 
+@pytest.mark.parametrize("lmax,E,n,n_owned", [
+    # tiles of 64 edges: one edge, 63, 64, 65, several; units of one and of two slots; one and two blocks of output channels
+    (4, 32, 2, 1), (4, 32, 64, 1), (4, 32, 65, 1), (4, 32, 66, 1), (4, 16, 30, 9), (4, 64, 41, 3), (3, 16, 23, 5), (3, 32, 40, 7),
+    (3, 64, 33, 2), (2, 16, 66, 1), (2, 64, 20, 7), (1, 32, 25, 8), (0, 16, 30, 7), (0, 64, 30, 5),
+    (3, 128, 20, 4), (4, 8, 20, 4)])                                   # (outside this route)
+def test_edge_block_tiles(B, lmax, E, n, n_owned):
+    import torch
+    print("case", lmax, E, n, n_owned, flush=True)
+    w, g, x, W_e, W0, Wr, Wi = case(lmax, E, n, n_owned, 8)
+    rng = np.random.default_rng(n)
+    # rows of very different size: every edge has a scale of its own; one row is zero
+    size = 10.0 ** rng.uniform(-6, 6, size=(len(g[0]), 1, 1))
+    T = (size * rng.standard_normal((len(g[0]), (lmax + 1) ** 2, E))).astype(np.float32)
+    T[len(g[0]) // 2] = 0
+    ref = S.so2_edge_block(g, w.pos, w.box, x, T, W0, Wr, Wi, lmax, E, w.r_cut)
+    m = B.Egnn(lmax, E, 8, w.r_cut, 7.0)
+    graph = m.egnn_nlist(B.to_device(w.pos), n_owned, w.box, w.pbc)
+    Td = B.to_device(T)
+    args = (graph, B.to_device(w.pos), w.box, B.to_device(x))
+    Wd = B.to_device(S.so2_pack(W0, Wr, Wi))
+    ws = torch.full((m.egnn_so2_blocks_workspace_bytes(graph.n_edges),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = m.egnn_so2_edge_block(*args, Td, Wd, ws)
+    got = out.cpu().numpy().astype(np.float64)
+    # update of each edge against the largest of that edge (the per-edge kernels scale all edges alike, so only by 1e-2 of all)
+    upd, want = got - T, ref - T
+    tiles = 16 <= E <= 64
+    rows = np.abs(want).max(axis=(1, 2)) if tiles else np.full(len(T), np.abs(want).max())
+    rounding = 2.0 ** -23 * np.abs(ref).max(axis=(1, 2))                # of T + update
+    err = np.abs(upd - want).max(axis=(1, 2))
+    print(f"  {len(T)} edges, worst {np.max(err / (rows + rounding)):.2e}", flush=True)
+    assert np.all(err <= TOL * rows + rounding)
+    # in place
+    T2 = Td.clone()
+    m.egnn_so2_edge_block(*args, T2, Wd, ws, out=T2)
+    if E != 64:
+        assert torch.equal(T2, out)
+    else:
+        assert np.all(np.abs(T2.cpu().numpy() - ref).max(axis=(1, 2)) <= 2 * TOL * np.abs(want).max() + rounding)
+
+
 # Weight gradients are differences of sums over all edges: the fp32 rounding of the terms enters with the ratio of their
 # size to the result's, a few times at these shapes.
 TOL_BWD = 5e-6
