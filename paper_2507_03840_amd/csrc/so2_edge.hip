@@ -8,10 +8,11 @@
 // rotate a row, scale it by a power of two of the edge's own and cut it into half-precision pieces in LDS; the 8 waves
 // contract it with the weights, which come from L2 (1 MB for 64 edges: smaller tiles would be bound by that, larger ones
 // do not fit LDS), into accumulators of [output channel][edge], 25 x 64 x 32 floats at lmax 4 = 100 registers a thread.
-// 628,000 edges, lmax 4, 32 channels: 3.6 ms, of which vector ALU 1.0 (rotations and pieces), matrix cores 0.7; the rest are
+// 628,000 edges, lmax 4, 32 channels: 3.45 ms, of which vector ALU 1.1 (rotations and pieces), matrix cores 0.7; the rest are
 // loads and barriers that one workgroup of 8 waves x 256 registers per compute unit cannot hide.  Separate kernels: 5.0
 // (gather 1.5, products 2.4, update 1.1).  Both blocks of 32 edges at a time in the inner loop: 4.1 ms (32 registers
-// spilled); 16 waves of 128 registers: 8.4 (47 spilled).
+// spilled); 16 waves of 128 registers: 8.4 (47 spilled); rows of the next stage requested before the products: 3.8 to 4.2
+// (spills, or no registers left for the weights ahead).
 #include "bond_frame.h"
 #include "egnn_internal.h"
 #include "so2_edge.h"
@@ -198,6 +199,17 @@ __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[u][t][i] = 0.0f;
   const char* frag = s_a + hh * SO2E_HALF + l32 * 16;
+  // weights of the next input degree, unit or stage, requested one step ahead, so the first of a stage arrive while the rows are
+  // rotated (requested within the unit only: 3.65 instead of 3.45 ms)
+  auto weights = [&](int st, int u) SO2E_INLINE {
+    return p.w + (((size_t)cb * n_stages + st) * units.total_l + units.l0[units.slot[wave][u]]) * 256 + lane;
+  };
+  uint4 wn[4];
+  if (units.slot[wave][0] >= 0) {
+    const uint4* w = weights(0, 0);
+#pragma unroll
+    for (int q = 0; q < 4; ++q) wn[q] = w[q * 64];
+  }
 
   for (int st = 0; st < n_stages; ++st) {
     // rotated, scaled by the edge's own power of two (that of the largest value met so far) and cut into pieces
@@ -243,21 +255,17 @@ __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p)
           for (int i = 0; i < 16; ++i) acc[u][t][i] *= (t & 1) ? r1 : r0;
       }
       const int m = units.m[unit];
-      const uint4* w = p.w + (((size_t)cb * n_stages + st) * units.total_l + units.l0[unit]) * 256 + lane;
-      uint4 wn[4];
-#pragma unroll
-      for (int q = 0; q < 4; ++q) wn[q] = w[q * 64];
+      const uint4* w = weights(st, u);
+      const uint4* after = u + 1 < NS && units.slot[wave][NS - 1] >= 0 ? weights(st, NS - 1) : weights(st + 1 < n_stages ? st + 1 : st, 0);
 #define SO2E_F(comp, piece, eb) (*reinterpret_cast<const uint4*>(frag + (comp) * SO2E_COMP + (piece) * SO2E_PIECE + (eb) * 512))
 #define SO2E_MMA(W, A, C) C = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(W), sgh_as_h8(A), C, 0, 0, 0)
       for (int l = m; l <= LMAX; ++l) {
         uint4 wc[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) wc[q] = wn[q];
-        if (l < LMAX) {
-          w += 256;
+        w = l < LMAX ? w + 256 : after;
 #pragma unroll
-          for (int q = 0; q < 4; ++q) wn[q] = w[q * 64];
-        }
+        for (int q = 0; q < 4; ++q) wn[q] = w[q * 64];
         const int cp = l * l + l + m, cm = l * l + l - m;
 #pragma unroll
         for (int eb = 0; eb < 2; ++eb) {

@@ -632,7 +632,7 @@ static bool so2_block_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
 }
 
 // Whether the edge block runs as one kernel over tiles of edges (so2_edge.hip).  us per call, per-edge kernels -> tiles: lmax 4,
-// 32 channels, 3,000 nodes with 209 / 37.8 / 1.6 edges each 5,000 -> 3,615 / 985 -> 713 / 216 -> 98; lmax 4, 64 channels,
+// 32 channels, 3,000 nodes with 209 / 37.8 / 1.6 edges each 5,000 -> 3,450 / 985 -> 713 / 216 -> 98; lmax 4, 64 channels,
 // 37.8 2,528 -> 2,085; lmax 2, 16 channels 225 -> 128; 100 nodes 61 -> 30 to 346 -> 154.  With 128 channels every tile of
 // edges would be rotated four times (lmax 2, 37.8 edges 1,907 -> 2,957), and 8 are half a matrix instruction: both stay
 // per edge.  So does an update in place with 64 channels, because its two blocks of output channels are two workgroups.
