@@ -2,7 +2,7 @@
 #pragma once
 #include "egnn_internal.h"
 
-#define SO2N_AUX 32   // contraction columns of the Gaussian basis (message sum), padded
+#define SO2N_AUX 32   // columns of the Gaussian basis, padded
 
 // Coupling paths into degree lo: (li, L) with |lo - li| <= L <= lo + li, li-major, all parities.
 __host__ __device__ constexpr int so2n_path_base(int lo, int li) {
@@ -13,11 +13,12 @@ __host__ __device__ constexpr int so2n_path_base(int lo, int li) {
 __host__ __device__ constexpr int so2n_paths(int lmax, int lo) { return so2n_path_base(lo, lmax + 1); }
 
 // The coupled sums T: per node (lmax+1)^2 rows (lo, mo) of so2n_ld(lo) floats, columns (group, path, channel) with group
-// 0 = neighbours, 1 = the node itself, 2 = the edges' own rows; then, if asked for, SO2N_AUX columns of the Gaussian basis.
-enum So2nForm { SO2N_PLAIN = 0, SO2N_GAUSS = 1, SO2N_EDGES = 2 };   // two groups; with the basis; three groups
+// 0 = neighbours, 1 = the node itself, 2 = the edges' own rows; then, in the message sum, a column per channel of the initial
+// edge embedding.  The gradient of the path weights has rows of the same order, with those of the Gaussian basis itself instead.
+enum So2nForm { SO2N_PLAIN = 0, SO2N_GAUSS = 1, SO2N_EDGES = 2, SO2N_GRAD = 3 };   // two groups; message sum; three groups; gradient
 __host__ __device__ constexpr int so2n_groups(int form) { return form == SO2N_EDGES ? 3 : 2; }
 __host__ __device__ constexpr int so2n_ld(int lmax, int E, int lo, int form) {
-  return so2n_groups(form) * so2n_paths(lmax, lo) * E + (form == SO2N_GAUSS ? SO2N_AUX : 0);
+  return so2n_groups(form) * so2n_paths(lmax, lo) * E + (form == SO2N_GAUSS ? E : form == SO2N_GRAD ? SO2N_AUX : 0);
 }
 // first float of degree lo within a node; lo = lmax + 1: floats of a node
 __host__ __device__ constexpr int so2n_node_off(int lmax, int E, int lo, int form) {
@@ -29,11 +30,13 @@ __host__ __device__ constexpr int so2n_node_off(int lmax, int E, int lo, int for
 struct So2nCall {
   float* T;              // [n_t] nodes
   float* partial;        // reverse pass: partial gradients of the path weights
+  float* dwpath;         // and their sum
+  float* G;              // and [n_owned][(lmax + 1)^2][SO2N_AUX] sums of harmonics times Gaussian basis
   uint32_t* packed;      // feature rows as half-precision pieces (low piece in the high half)
   float* g;              // [n_owned][(2 lmax + 1)^2] weighted sums of the harmonics over the incoming edges
   float* wpath;          // path weights, fp32
   uint4* wpack;          // the same cut into pieces in operand order
-  unsigned* maxima;      // bit patterns: 0 features, 1 path weights, 2 T, 3 edge rows
+  unsigned* maxima;      // bit patterns: 0 features, 1 path weights, 2 T, 3 edge rows, 4 G
 };
 
 // base = NULL: bytes only.  n_rows feature rows, T for n_t nodes.

@@ -9,9 +9,10 @@
 //     T[lo][mo][(li, L)][c] = sum_{M, mi} C^(lo li L)[mo][mi][M] S[LM][(li, mi)][c]  (same kernel, constants in code)
 //     a[(lo, mo)][c_out]    = sum_{li, L, c} (sum_m beta_L^m W_m)[c_out][c] T        (so2n_mix_kernel, matrix cores)
 // The destination's own embedding is the same for all of the edges: its S is the outer product of x_j with
-// g_j[LM] = sum_k f_k Yhat_LM(r_k).  The L = 0 plane of the initial edge embedding, W_e B(d), enters through
-// sum_k f_k Yhat_LM(r_k) B_b(d_k), L <= lmax; persistent edge embeddings (node block) are gathered like the sources', each
-// edge its own row.
+// g_j[LM] = sum_k f_k Yhat_LM(r_k) (so2n_sums_kernel).  The L = 0 plane of the initial edge embedding, W_e B(d), enters through
+// G_j[LM][b] = sum_k f_k Yhat_LM(r_k) B_b(d_k), L <= lmax (same kernel), as columns W_e G of T beside the features' (it has
+// their size there, and the weights of both are plain W); persistent edge embeddings (node block) are gathered like the
+// sources', each edge its own row.
 #include "so2_node.h"
 #include "stream_gemm.h"
 #include "so2_node_gen.inc"
@@ -44,7 +45,7 @@ __host__ __device__ constexpr size_t so2n_lds_main(int lmax, int cs) {
   return s > y ? s : y;
 }
 __host__ __device__ constexpr size_t so2n_lds_bytes(int lmax, int E) {
-  return so2n_lds_main(lmax, so2n_cs(E)) + SO2N_BATCH * 8 + 96 * 4 + 64 + (size_t)(lmax + 1) * (lmax + 1) * so2n_cs(E) * 4;
+  return so2n_lds_main(lmax, so2n_cs(E)) + SO2N_BATCH * 4 + 96 * 4 + 64 + (size_t)(lmax + 1) * (lmax + 1) * so2n_cs(E) * 4;
 }
 
 typedef _Float16 so2n_h2 __attribute__((ext_vector_type(2)));
@@ -130,6 +131,13 @@ __device__ __forceinline__ void so2n_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
+// LDS written and read by one wave alone
+__device__ __forceinline__ void so2n_wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 struct So2nArgs {
   const int* ptr;            // segments: edges (or positions in perm) of node j
   const int* perm;           // NULL: the edges of node j are ptr[j] .. ptr[j + 1] themselves
@@ -140,13 +148,12 @@ struct So2nArgs {
   unsigned packed_bytes;
   const float* rows;         // OWN: the edges' own rows (fp32)
   const float* x_self;       // rows of the nodes themselves (fp32); NULL: that group is zero
-  const float* g_in;         // sums of the harmonics for the self group; NULL: those of this list
-  float* g_out;              // NULL: not kept
+  const float* g;            // [n_self] sums of the harmonics over their incoming edges
   float* T;
   unsigned* maxima;
   int j_begin, j_end;        // nodes of this launch; T starts at j_begin
   int n_self;                // nodes that have a self group
-  int per_xcd, E, n_slices, n_rbf, form;
+  int per_xcd, E, n_slices, form;
   float r_cut;
 };
 
@@ -154,8 +161,8 @@ struct So2nArgs {
 // (v_mfma_f32_32x32x16_f16, two half-precision pieces per operand, three products): operand A = harmonics of 32 (L, M) from
 // LDS, operand B = 32 columns (l, m, c) of the gathered rows, which a lane reads as one word per edge, both pieces, and
 // only has to permute.  Degree li couples to L <= lmax + li: at lmax 4 the 9 column tiles of li = 4 need 3 row tiles and go
-// to waves 0-2, the other 16 need 2 and go to waves 3-6, wave 7 sums the harmonics themselves and does the Gaussian
-// columns; 174 + 3 matrix instructions per 16 edges, 51 on the busiest SIMD.
+// to waves 0-2, the other 16 need 2 and go to waves 3-6, wave 7 only stages harmonics; 177 matrix instructions per 16 edges,
+// 51 on the busiest SIMD.
 // S of the node then goes through LDS to be coupled by straight runs of multiply-adds with constants in the code, every
 // wave its own blocks (li, L), lanes = (group, channel).
 // lmax 4, 32 channels, 3,000 nodes, 628,000 edges: 445 us (the per-edge form: gather, five products and scatter, 3.2 ms).  With
@@ -180,8 +187,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   char* s_y = reinterpret_cast<char*>(so2n_smem);
   float* s_s = reinterpret_cast<float*>(so2n_smem);
   unsigned* s_off = reinterpret_cast<unsigned*>(s_y + so2n_lds_main(LMAX, CS));
-  float* s_d = reinterpret_cast<float*>(s_off + SO2N_BATCH);
-  float* s_g = s_d + SO2N_BATCH;
+  float* s_g = reinterpret_cast<float*>(s_off + SO2N_BATCH);
   float* s_red = s_g + 96;
   float* s_x = s_red + 16;                         // the node's own row
 
@@ -200,6 +206,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   const bool has_self = p.x_self != nullptr && j < p.n_self;
   for (int i = tid; i < D * CS; i += SO2N_THREADS)
     s_x[i] = has_self ? p.x_self[((size_t)j * D + i / CS) * E + slice * CS + i % CS] : 0.0f;
+  for (int i = tid; i < NLM; i += SO2N_THREADS) s_g[i] = has_self ? p.g[(size_t)j * NLM + i] : 0.0f;
   const int e_own = tid & (SO2N_BATCH - 1);
   float4 g_own = make_float4(0.0f, 0.0f, 1.0f, 1.0f);
   float f_own = 0.0f;
@@ -211,10 +218,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
       const int k = p.perm ? p.perm[at] : at;
       g_own = p.rhat_d[k];
       f_own = e_own < nb ? egnn_envelope(g_own.w, p.r_cut) * (p.alpha ? p.alpha[k] : 1.0f) : 0.0f;
-      if (tid < SO2N_BATCH) {
-        s_off[e_own] = (unsigned)(OWN ? at - k0 - b0 : p.index[k]) * (unsigned)(D * E * 4);
-        s_d[e_own] = g_own.w;
-      }
+      if (tid < SO2N_BATCH) s_off[e_own] = (unsigned)(OWN ? at - k0 - b0 : p.index[k]) * (unsigned)(D * E * 4);
     }
   };
   load_edge(0);
@@ -410,80 +414,17 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
       }
     }
   };
-  // sums of the harmonics themselves, and (message sum) the columns of the Gaussian basis
-  auto sums = [&]() SO2N_INLINE {
-    const bool aux = p.n_rbf > 0 && slice == 0;
-    const float rbf_step = p.n_rbf > 1 ? p.r_cut / (float)(p.n_rbf - 1) : 1.0f;
-    const float rbf_inv = 0.5f / (rbf_step * rbf_step);
-    float gsum[MT];
-    float16v acc;
-#pragma unroll
-    for (int t = 0; t < MT; ++t) gsum[t] = 0.0f;
-#pragma unroll
-    for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
-    const so2n_h2 one = {(_Float16)1.0f, (_Float16)1.0f};
+  // the wave without tiles
+  auto stage_only = [&]() SO2N_INLINE {
     for (int b0 = 0; b0 < deg; b0 += SO2N_BATCH) {
       const int nb = deg - b0 < SO2N_BATCH ? deg - b0 : SO2N_BATCH;
-      const int n_steps = (nb + 15) >> 4;
       if (b0) {
         so2n_barrier();
         load_edge(b0);
         so2n_barrier();
       }
-      stage(std::integral_constant<int, 1>{}, n_steps);
+      stage(std::integral_constant<int, 1>{}, (nb + 15) >> 4);
       so2n_barrier();
-      for (int s = 0; s < n_steps; ++s) {
-#pragma unroll
-        for (int t = 0; t < MT; ++t) {
-          const uint4 h = SO2N_A(t, 0), l = SO2N_A(t, 1);
-          float a = gsum[t];
-          a = __builtin_amdgcn_fdot2(__builtin_bit_cast(so2n_h2, l.x), one, a, false);
-          a = __builtin_amdgcn_fdot2(__builtin_bit_cast(so2n_h2, l.y), one, a, false);
-          a = __builtin_amdgcn_fdot2(__builtin_bit_cast(so2n_h2, l.z), one, a, false);
-          a = __builtin_amdgcn_fdot2(__builtin_bit_cast(so2n_h2, l.w), one, a, false);
-          a = __builtin_amdgcn_fdot2(__builtin_bit_cast(so2n_h2, h.x), one, a, false);
-          a = __builtin_amdgcn_fdot2(__builtin_bit_cast(so2n_h2, h.y), one, a, false);
-          a = __builtin_amdgcn_fdot2(__builtin_bit_cast(so2n_h2, h.z), one, a, false);
-          gsum[t] = __builtin_amdgcn_fdot2(__builtin_bit_cast(so2n_h2, h.w), one, a, false);
-        }
-        if (aux) {
-          float bv[8];
-#pragma unroll
-          for (int q = 0; q < 8; ++q) {
-            const float u = s_d[s * 16 + 8 * hh + q] - (float)l32 * rbf_step;
-            bv[q] = l32 < p.n_rbf ? __expf(-u * u * rbf_inv) : 0.0f;
-          }
-          uint4 bh, bl;
-          sgh_split8(bv, 4096.0f, bh, bl);
-          const uint4 h = SO2N_A(0, 0), l = SO2N_A(0, 1);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(l), sgh_as_h8(bh), acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(h), sgh_as_h8(bl), acc, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(h), sgh_as_h8(bh), acc, 0, 0, 0);
-        }
-      }
-    }
-#pragma unroll
-    for (int t = 0; t < MT; ++t) {
-      const int lm = t * 32 + l32;
-      const float v = (gsum[t] + __shfl_xor(gsum[t], 32)) * ldexpf(1.0f, -ey);
-      if (hh == 0 && lm < NLM) {
-        if (p.g_out && slice == 0) p.g_out[(size_t)j * NLM + lm] = v;
-        s_g[lm] = !p.g_in ? v : j < p.n_self ? p.g_in[(size_t)j * NLM + lm] : 0.0f;
-      }
-    }
-    if (aux) {
-      // rows LM < D are the rows (lo, mo) of T
-      const float u = ldexpf(1.0f, -12 - ey);
-#pragma unroll
-      for (int i = 0; i < 16; ++i) {
-        const int lm = 8 * (i >> 2) + 4 * hh + (i & 3);
-        if (lm < D) {
-          const int lo = lm < 1 ? 0 : lm < 4 ? 1 : lm < 9 ? 2 : lm < 16 ? 3 : 4, ld = so2n_ld(LMAX, E, lo, SO2N_GAUSS);
-          const float v = u * acc[i];
-          amax = fmaxf(amax, fabsf(v));
-          T[so2n_node_off(LMAX, E, lo, SO2N_GAUSS) + (lm - lo * lo + 1) * ld - SO2N_AUX + l32] = v;
-        }
-      }
     }
   };
   // Two rounds at lmax 4, because S of all degrees exceeds the LDS: waves 0-2 hold degree 4 in registers during the first,
@@ -500,7 +441,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
     }
   } else {
     if (wave == 7) {
-      sums();
+      stage_only();
       so2n_barrier();                               // the staged harmonics are consumed
     } else {
       const int t0 = (wave - WB0) * NB;
@@ -526,6 +467,130 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   so2n_barrier();
   if (tid == 0) atomicMax(p.maxima + 2, __float_as_uint(s_red[8]));   // (no result is waited for)
 }
+
+// ---------------------------------------------------------------------------------------------- sums of the harmonics
+#define SO2N_SUM_WAVES 4
+struct So2nSums {
+  const int* ptr;
+  const float4* rhat_d;
+  const float* alpha;        // optional further weight per edge
+  const float* W_e;          // the edge embedding's columns of T (form SO2N_GAUSS); NULL: none
+  float* g;                  // [n_owned][(2 lmax + 1)^2]
+  float* G;                  // [n_owned][(lmax + 1)^2][SO2N_AUX] sums with the Gaussian basis; NULL: not kept
+  float* T;
+  unsigned* maxima;
+  int n_rbf, log2E;          // n_rbf = 0: g alone
+  float r_cut;
+};
+
+// One workgroup per node, a quarter of its edges per wave, a lane an edge: the harmonics go from the lane's registers to LDS,
+// half a wavefront's edges at a time (all 64 of two waves would leave room for six waves per compute unit), where they are
+// summed, lane = (L, M), and contracted with the Gaussian basis on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), all in 32
+// bits.  3,000 nodes, 628,000 edges, lmax 4, 32 channels: 57 us, without the basis 22; latency of the node's few edges.
+template <int LMAX>
+__global__ __launch_bounds__(64 * SO2N_SUM_WAVES) void so2n_sums_kernel(So2nSums p) {
+  constexpr int D = (LMAX + 1) * (LMAX + 1), NL = 2 * LMAX + 1, NLM = NL * NL;     // (NLM odd: lanes write different banks)
+  constexpr int NY = 32 * NLM + (NLM < 32 ? 32 : 0);      // (rows 25 .. 31 of the contraction read on; nobody uses them)
+  constexpr int THREADS = 64 * SO2N_SUM_WAVES;
+  __shared__ float s_y[SO2N_SUM_WAVES][NY > 32 * 33 ? NY : 32 * 33];
+  __shared__ float s_d[SO2N_SUM_WAVES][64];
+  __shared__ float s_sum[SO2N_SUM_WAVES][NLM];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int hh = lane >> 5, l32 = lane & 31, j = blockIdx.x;
+  const int k0 = p.ptr[j], deg = p.ptr[j + 1] - k0;
+  const int share = (deg + SO2N_SUM_WAVES - 1) / SO2N_SUM_WAVES, b_end = min((wave + 1) * share, deg);
+  const float rbf_step = p.n_rbf > 1 ? p.r_cut / (float)(p.n_rbf - 1) : 1.0f;
+  const float rbf_inv = 0.5f / (rbf_step * rbf_step);
+  float* y = s_y[wave];
+  constexpr int R = (NLM + 63) / 64;
+  float sum[R][4];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum[r][q] = 0.0f;
+  float16v acc;
+#pragma unroll
+  for (int i = 0; i < 16; ++i) acc[i] = 0.0f;
+  for (int b0 = wave * share; b0 < b_end; b0 += 64) {
+    float4 e = make_float4(0.0f, 0.0f, 1.0f, 1.0f);
+    float f = 0.0f;                                    // (edges past the last are zero)
+    if (b0 + lane < b_end) {
+      const int k = k0 + b0 + lane;
+      e = p.rhat_d[k];
+      f = egnn_envelope(e.w, p.r_cut) * (p.alpha ? p.alpha[k] : 1.0f);
+    }
+    float v[NLM];
+    so2n_harmonics<NL, 0, 2 * LMAX>(e.x, e.y, e.z, f, [&](int lm, float h) SO2N_INLINE { v[lm] = h; });
+    s_d[wave][lane] = e.w;
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      const int nb = min(b_end - b0 - 32 * half, 32);
+      if (nb <= 0) break;
+      if (hh == half)
+#pragma unroll
+        for (int i = 0; i < NLM; ++i) y[l32 * NLM + i] = v[i];
+      so2n_wave_sync();
+#pragma unroll
+      for (int r = 0; r < R; ++r) {
+        const int lm = r * 64 + lane;
+        if (lm < NLM)
+          for (int q = 0; q < nb; q += 8)
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum[r][u & 3] += y[(q + u) * NLM + lm];
+      }
+      if (p.n_rbf > 0)
+        for (int q0 = 0; q0 < nb; q0 += 8) {
+#pragma unroll
+          for (int t = 0; t < 8; t += 2) {
+            const int q = q0 + t + hh;
+            const float u = s_d[wave][32 * half + q] - (float)l32 * rbf_step;
+            const float basis = l32 < p.n_rbf ? __expf(-u * u * rbf_inv) : 0.0f;
+            acc = __builtin_amdgcn_mfma_f32_32x32x2f32(y[q * NLM + l32], basis, acc, 0, 0, 0);
+          }
+        }
+      so2n_wave_sync();
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (r * 64 + lane < NLM) s_sum[wave][r * 64 + lane] = (sum[r][0] + sum[r][1]) + (sum[r][2] + sum[r][3]);
+#pragma unroll
+  for (int i = 0; i < 16; ++i) y[(8 * (i >> 2) + 4 * hh + (i & 3)) * 33 + l32] = acc[i];
+  __syncthreads();
+  for (int i = tid; i < NLM; i += THREADS) p.g[(size_t)j * NLM + i] = (s_sum[0][i] + s_sum[1][i]) + (s_sum[2][i] + s_sum[3][i]);
+  if (p.n_rbf == 0) return;
+  float mx = 0.0f;
+  for (int i = tid; i < D * SO2N_AUX; i += THREADS) {
+    const int at = (i >> 5) * 33 + (i & 31);
+    const float v = (s_y[0][at] + s_y[1][at]) + (s_y[2][at] + s_y[3][at]);
+    s_y[0][at] = v;
+    mx = fmaxf(mx, fabsf(v));
+    if (p.G) p.G[(size_t)j * (D * SO2N_AUX) + i] = v;
+  }
+  if (p.W_e) {
+    __syncthreads();
+    mx = 0.0f;
+    const int E = 1 << p.log2E, c = tid & (E - 1);
+    float w[SO2N_AUX];
+#pragma unroll
+    for (int b = 0; b < SO2N_AUX; ++b) w[b] = p.W_e[c * p.n_rbf + min(b, p.n_rbf - 1)];   // (sums past the basis are zero)
+    float* T = p.T + (size_t)j * so2n_node_off(LMAX, E, LMAX + 1, SO2N_GAUSS) + c - E;
+    for (int i = tid >> p.log2E; i < D; i += THREADS >> p.log2E) {
+      float v = 0.0f;
+#pragma unroll
+      for (int b = 0; b < SO2N_AUX; ++b) v += s_y[0][i * 33 + b] * w[b];
+      const int lo = i < 1 ? 0 : i < 4 ? 1 : i < 9 ? 2 : i < 16 ? 3 : 4;
+      T[so2n_node_off(LMAX, E, lo, SO2N_GAUSS) + (i - lo * lo + 1) * so2n_ld(LMAX, E, lo, SO2N_GAUSS)] = v;
+      mx = fmaxf(mx, fabsf(v));
+    }
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+  if (lane == 0) s_d[0][wave] = mx;
+  __syncthreads();
+  if (tid == 0) egnn_raise_max(p.maxima + (p.W_e ? 2 : 4), fmaxf(fmaxf(s_d[0][0], s_d[0][1]), fmaxf(s_d[0][2], s_d[0][3])));
+}
+static_assert(SO2N_SUM_WAVES == 4 && SO2N_AUX == 32, "so2n_sums_kernel adds four waves' sums of 32 columns");
 
 // ---------------------------------------------------------------------------------------------- attention scores
 // score[k] = sum_c w_att[c] leaky(y0[k][c]) with y0 = the L = 0 plane of edge k's message: that plane needs only the m = 0
@@ -688,17 +753,11 @@ struct So2nW {
 // Weight of contraction row (group, path, channel) of output degree a into channel col.  Transposed (reverse pass): a is the
 // input degree of the forward pass, the paths run over its output degrees; swapping the two degrees of a coupling tensor
 // changes its sign with the parity of the degrees.
-__device__ float so2n_weight(const float* __restrict__ W, const float* __restrict__ W_e, const So2nW& s, int lmax, int E, int a,
-                             int k, int col, int n_rbf, int form, bool transposed) {
+__device__ float so2n_weight(const float* __restrict__ W, const So2nW& s, int lmax, int E, int a, int k, int col, int form,
+                             bool transposed) {
   const int np = so2n_paths(lmax, a);
-  if (k >= so2n_groups(form) * np * E) {
-    const int b = k - so2n_groups(form) * np * E;
-    if (b >= n_rbf) return 0.0f;
-    const float* row = W + (size_t)(a * E + col) * ((lmax + 1) * 3 * E) + 2 * E;   // W_0, edge columns of degree 0
-    float sum = 0.0f;
-    for (int c = 0; c < E; ++c) sum += row[c] * W_e[c * n_rbf + b];
-    return sum / sqrtf((float)(2 * a + 1));
-  }
+  if (k >= so2n_groups(form) * np * E)   // W_0, edge columns of degree 0
+    return W[(size_t)(a * E + col) * ((lmax + 1) * 3 * E) + 2 * E + (k - so2n_groups(form) * np * E)] / sqrtf((float)(2 * a + 1));
   const int g = k / (np * E), r = k - g * np * E;
   const int path = r / E, kc = r - path * E;
   int b = 0;
@@ -717,16 +776,15 @@ __device__ float so2n_weight(const float* __restrict__ W, const float* __restric
   return transposed && odd ? -sum : sum;
 }
 
-__global__ __launch_bounds__(256) void so2n_weights_kernel(const float* __restrict__ W, const float* __restrict__ W_e, So2nW s,
-                                                           int lmax, int E, int n_rbf, int form, bool transposed,
-                                                           float* __restrict__ out, unsigned* __restrict__ w_max) {
+__global__ __launch_bounds__(256) void so2n_weights_kernel(const float* __restrict__ W, So2nW s, int lmax, int E, int form,
+                                                           bool transposed, float* __restrict__ out, unsigned* __restrict__ w_max) {
   const long i = (long)blockIdx.x * 256 + threadIdx.x;
   float v = 0.0f;
   if (i < (long)s.k_first[lmax + 1] * E) {
     const int row = (int)(i / E), col = (int)(i - (long)row * E);
     int a = 0;
     while (row >= s.k_first[a + 1]) ++a;
-    v = so2n_weight(W, W_e, s, lmax, E, a, row - s.k_first[a], col, n_rbf, form, transposed);
+    v = so2n_weight(W, s, lmax, E, a, row - s.k_first[a], col, form, transposed);
     out[i] = v;
   }
   float mx = fabsf(v);
@@ -858,14 +916,16 @@ __global__ __launch_bounds__(256) void so2n_mix_kernel(So2nMix p) {
 
 // ---------------------------------------------------------------------------------------------- weight gradient
 struct So2nWgrad {
-  const float* T;
+  const float* T;        // form SO2N_PLAIN
+  const float* G;
   const float* da;       // [n_nodes][(lmax+1)^2][E]
   float* partial;
-  int node_floats, off[5], ld[5], K[5];
+  int node_floats, off[5], ld[5], K[5];   // K: rows of the result, those of T and then SO2N_AUX of G
   int k_tiles[5], chunks[5], per_chunk[5], unit0[6];
   size_t part0[6];       // first float of every degree's partial results
   int n_nodes, E, n_ct, D;
   const unsigned* t_max;
+  const unsigned* g_max;
   const unsigned* da_max;
 };
 
@@ -873,7 +933,9 @@ struct So2nWgrad {
 // owns 128 rows x 32 columns of the result; both operands are read in memory order, the contraction index being the row
 // index of both: lane (i, h) fetches 16 bytes of T and 4 of da for the eight nodes of its half-wave and finds in one
 // component of them the eight consecutive nodes one operand register wants, so accumulator a holds the rows
-// k0 + 4 r + a.  Degrees with more rows per node get fewer nodes per chunk, so that all waves take about equally long.
+// k0 + 4 r + a.  Degrees with more rows per node get fewer nodes per chunk, so that all waves take about equally long.  The
+// last wave of every column of tiles takes G in the place of T, with G's own scale: whichever of the two is the smaller keeps
+// its accuracy.
 // Bound: T read once (413 MB at 3,000 nodes, lmax 4, 32 channels: 94 us = 4.4 TB/s; per edge it was 2.26 ms).
 __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   const int lane = threadIdx.x & 63, i32 = lane & 31, hh = lane >> 5;
@@ -885,13 +947,16 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   const int kt = u % p.k_tiles[lo];
   u /= p.k_tiles[lo];
   const int ct = u % p.n_ct, chunk = u / p.n_ct;
-  const int K = p.K[lo], n_mo = 2 * lo + 1;
+  const bool basis = kt == p.k_tiles[lo] - 1;
+  const int k_first = basis ? p.K[lo] - SO2N_AUX : kt * 128, n_mo = 2 * lo + 1;
+  const int K = basis ? SO2N_AUX : p.K[lo] - SO2N_AUX - k_first;           // rows this wave can have
   const int n0 = chunk * p.per_chunk[lo], n1 = n0 + p.per_chunk[lo] < p.n_nodes ? n0 + p.per_chunk[lo] : p.n_nodes;
-  const int ca = kt * 128 + 4 * i32, cy = ct * 32 + i32;
+  const int ca = 4 * i32, cy = ct * 32 + i32;
   const bool a_ok = ca < K, y_ok = cy < p.E;
-  const int ea = sgh_scale_exp(*p.t_max), ey = sgh_scale_exp(*p.da_max);
+  const int ea = sgh_scale_exp(basis ? *p.g_max : *p.t_max), ey = sgh_scale_exp(*p.da_max);
   const float a_scale = ldexpf(1.0f, ea), y_scale = ldexpf(1.0f, ey), unscale = ldexpf(1.0f, -ea) * ldexpf(1.0f, -ey);
-  const float* T = p.T + p.off[lo] + (a_ok ? ca : K - 4);
+  const float* T = (basis ? p.G + lo * lo * SO2N_AUX : p.T + p.off[lo] + k_first) + (a_ok ? ca : K - 4);
+  const int ld = basis ? SO2N_AUX : p.ld[lo], node_floats = basis ? p.D * SO2N_AUX : p.node_floats;
   const float* Y = p.da + (size_t)(lo * lo) * p.E + (y_ok ? cy : 0);
   const size_t ys = (size_t)p.D * p.E;
   float16v acc[4];
@@ -904,13 +969,13 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   const int n_blocks = (n1 - n0 + 15) / 16, total = n_blocks * n_mo;
   auto fetch = [&](int q) SO2N_INLINE {
     const int mo = q / n_blocks, n = n0 + (q - mo * n_blocks) * 16 + 8 * hh;
-    const float* tm = T + (size_t)mo * p.ld[lo];
+    const float* tm = T + (size_t)mo * ld;
     const float* ym = Y + (size_t)mo * p.E;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
       // (past the chunk's last node: that node again, with zeros for da)
       const int nr = n + r < n1 ? n + r : n1 - 1;
-      ra[r] = *reinterpret_cast<const sg_f4*>(tm + (size_t)nr * p.node_floats);
+      ra[r] = *reinterpret_cast<const sg_f4*>(tm + (size_t)nr * node_floats);
       ry[r] = ym[(size_t)nr * ys];
     }
   };
@@ -936,12 +1001,12 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
     for (int a = 0; a < 4; ++a) acc[a] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah[a]), sgh_as_h8(yh), acc[a], 0, 0, 0);
   }
   if (y_ok) {
-    float* out = p.partial + p.part0[lo] + (size_t)chunk * K * p.E + cy;
+    float* out = p.partial + p.part0[lo] + ((size_t)chunk * p.K[lo] + k_first) * p.E + cy;
 #pragma unroll
     for (int a = 0; a < 4; ++a)
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
-        const int k = kt * 128 + 4 * (8 * (i >> 2) + 4 * hh + (i & 3)) + a;
+        const int k = 4 * (8 * (i >> 2) + 4 * hh + (i & 3)) + a;
         if (k < K) out[(size_t)k * p.E] = unscale * acc[a][i];
       }
   }
@@ -1056,7 +1121,7 @@ size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t 
   c.wpath = (float*)take((size_t)s.k_first[lmax + 1] * E * 4);
   c.wpack = (uint4*)take((size_t)st.first[lmax + 1] * ((E + 31) / 32) * 128 * 16);
   c.T = (float*)take((size_t)n_t * so2n_node_off(lmax, E, lmax + 1, form) * 4);
-  c.partial = nullptr;
+  c.partial = c.dwpath = c.G = nullptr;
   if (out) *out = c;
   return used;
 }
@@ -1071,15 +1136,14 @@ int so2n_pack_features(egnn_ctx* ctx, const float* x, long n_rows, const So2nCal
   return EGNN_OK;
 }
 
-int so2n_pack_weights(egnn_ctx* ctx, const float* W, const float* W_e, int form, bool transposed, const So2nCall& c,
-                      hipStream_t st) {
+int so2n_pack_weights(egnn_ctx* ctx, const float* W, int form, bool transposed, const So2nCall& c, hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   So2nW s;
   So2nSteps steps;
   so2n_w_layout(lmax, E, form, &s, &steps);
   const long n = (long)s.k_first[lmax + 1] * E;
-  hipLaunchKernelGGL(so2n_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, W, W_e, s, lmax, E,
-                     ctx->desc.n_rbf, form, transposed, c.wpath, c.maxima + 1);
+  hipLaunchKernelGGL(so2n_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, W, s, lmax, E, form,
+                     transposed, c.wpath, c.maxima + 1);
   EGNN_LAUNCH_CHECK(ctx, "so2n_weights_kernel");
   const int n_cb = (E + 31) / 32;
   const long m = (long)steps.first[lmax + 1] * n_cb * 64;
@@ -1126,6 +1190,25 @@ static int so2n_launch_gather(egnn_ctx* ctx, So2nArgs a, hipStream_t st) {
 #undef SO2N_L
 }
 
+// g of the owned nodes and, with n_rbf, the edge embedding's columns of T (W_e given) or G
+static int so2n_launch_sums(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* alpha, int n_rbf,
+                            const float* W_e, const So2nCall& c, hipStream_t st) {
+  if (g->n_owned <= 0) return EGNN_OK;
+  So2nSums p;
+  p.ptr = g->row_ptr; p.rhat_d = reinterpret_cast<const float4*>(rhat_d); p.alpha = alpha; p.W_e = W_e; p.g = c.g;
+  p.G = W_e ? nullptr : c.G; p.T = c.T; p.maxima = c.maxima; p.n_rbf = n_rbf; p.log2E = ctx->log2_channels; p.r_cut = ctx->desc.r_cut;
+  const dim3 grid((unsigned)g->n_owned), block(64 * SO2N_SUM_WAVES);
+  switch (ctx->desc.lmax) {
+    case 0: hipLaunchKernelGGL(so2n_sums_kernel<0>, grid, block, 0, st, p); break;
+    case 1: hipLaunchKernelGGL(so2n_sums_kernel<1>, grid, block, 0, st, p); break;
+    case 2: hipLaunchKernelGGL(so2n_sums_kernel<2>, grid, block, 0, st, p); break;
+    case 3: hipLaunchKernelGGL(so2n_sums_kernel<3>, grid, block, 0, st, p); break;
+    default: hipLaunchKernelGGL(so2n_sums_kernel<4>, grid, block, 0, st, p); break;
+  }
+  EGNN_LAUNCH_CHECK(ctx, "so2n_sums_kernel");
+  return EGNN_OK;
+}
+
 static int so2n_launch_mix(egnn_ctx* ctx, const So2nCall& c, int form, int n_nodes, float scale, float* out, hipStream_t st) {
   if (n_nodes <= 0) return EGNN_OK;
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
@@ -1151,21 +1234,23 @@ static int so2n_launch_mix(egnn_ctx* ctx, const So2nCall& c, int form, int n_nod
   return EGNN_OK;
 }
 
-static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, int form, So2nWgrad* p) {
+static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, So2nWgrad* p) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
-  p->node_floats = so2n_node_off(lmax, E, lmax + 1, form);
+  p->node_floats = so2n_node_off(lmax, E, lmax + 1, SO2N_PLAIN);
   p->n_nodes = n_nodes; p->E = E; p->n_ct = (E + 31) / 32; p->D = (lmax + 1) * (lmax + 1);
   int tiles = 0;
-  for (int lo = 0; lo <= lmax; ++lo) tiles += (2 * lo + 1) * ((so2n_ld(lmax, E, lo, form) + 127) / 128) * p->n_ct;
+  auto k_tiles = [&](int lo) { return (so2n_ld(lmax, E, lo, SO2N_PLAIN) + 127) / 128 + 1; };
+  for (int lo = 0; lo <= lmax; ++lo) tiles += (2 * lo + 1) * k_tiles(lo) * p->n_ct;
   // about 2,048 waves (two per SIMD): rows (node, mo) per wave, in steps of 16 nodes
   const long rows = std::max<long>(16, ((long)n_nodes * tiles + 2047) / 2048);
   p->unit0[0] = 0;
   p->part0[0] = 0;
   for (int lo = 0; lo < 5; ++lo) {
     const bool there = lo <= lmax;
-    p->K[lo] = p->ld[lo] = there ? so2n_ld(lmax, E, lo, form) : 0;
-    p->off[lo] = there ? so2n_node_off(lmax, E, lo, form) : 0;
-    p->k_tiles[lo] = there ? (p->K[lo] + 127) / 128 : 1;
+    p->K[lo] = there ? so2n_ld(lmax, E, lo, SO2N_GRAD) : 0;
+    p->ld[lo] = there ? so2n_ld(lmax, E, lo, SO2N_PLAIN) : 0;
+    p->off[lo] = there ? so2n_node_off(lmax, E, lo, SO2N_PLAIN) : 0;
+    p->k_tiles[lo] = there ? k_tiles(lo) : 1;
     p->per_chunk[lo] = (int)((rows / (2 * lo + 1) + 15) / 16 * 16);
     if (p->per_chunk[lo] < 16) p->per_chunk[lo] = 16;
     p->chunks[lo] = there ? (n_nodes + p->per_chunk[lo] - 1) / p->per_chunk[lo] : 0;
@@ -1176,16 +1261,18 @@ static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, int form, So2nWgra
 
 size_t so2n_backward_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_total, char* base, So2nCall* out) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
-  // T of the owned nodes (with the Gaussian columns) and then of all nodes share one buffer
-  const size_t with = (size_t)n_owned * so2n_node_off(lmax, E, lmax + 1, SO2N_GAUSS),
-               without = (size_t)n_total * so2n_node_off(lmax, E, lmax + 1, SO2N_PLAIN);
-  size_t used = so2n_carve(ctx, n_owned, n_total, 0, SO2N_GAUSS, base, out);
+  // (T of the owned nodes and then of all nodes share one buffer)
+  size_t used = so2n_carve(ctx, n_owned, n_total, n_total, SO2N_PLAIN, base, out);
   auto take = [&](size_t bytes) { char* q = base ? base + used : nullptr; used += so2n_a256(bytes); return q; };
+  So2nW s;
+  So2nSteps st;
+  so2n_w_layout(lmax, E, SO2N_GRAD, &s, &st);
   So2nWgrad p;
-  so2n_wgrad_plan(ctx, n_owned, SO2N_GAUSS, &p);
+  so2n_wgrad_plan(ctx, n_owned, &p);
   float* partial = (float*)take(p.part0[lmax + 1] * 4);
-  float* T = (float*)take(std::max(with, without) * 4);
-  if (out) { out->T = T; out->partial = partial; }
+  float* dwpath = (float*)take((size_t)s.k_first[lmax + 1] * E * 4);
+  float* G = (float*)take((size_t)n_owned * (lmax + 1) * (lmax + 1) * SO2N_AUX * 4);
+  if (out) { out->partial = partial; out->dwpath = dwpath; out->G = G; }
   return used;
 }
 
@@ -1202,32 +1289,33 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
-  p.T = c.T; p.maxima = c.maxima; p.g_out = c.g;
-  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.n_rbf = ctx->desc.n_rbf; p.form = SO2N_GAUSS;
+  p.T = c.T; p.maxima = c.maxima; p.g = c.g;
+  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.form = SO2N_PLAIN;
+  if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, nullptr, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   So2nCall c2 = c;
   c2.maxima = c.maxima + 16;
   if ((rc = so2n_pack_features(ctx, da, g->n_owned, c2, st))) return rc;
   So2nW s;
   So2nSteps steps;
-  so2n_w_layout(lmax, E, SO2N_GAUSS, &s, &steps);
+  so2n_w_layout(lmax, E, SO2N_GRAD, &s, &steps);
   So2nWgrad w;
-  so2n_wgrad_plan(ctx, g->n_owned, SO2N_GAUSS, &w);
-  w.T = c.T; w.da = da; w.partial = c.partial; w.t_max = c.maxima + 2; w.da_max = c2.maxima;
+  so2n_wgrad_plan(ctx, g->n_owned, &w);
+  w.T = c.T; w.G = c.G; w.da = da; w.partial = c.partial; w.t_max = c.maxima + 2; w.g_max = c.maxima + 4; w.da_max = c2.maxima;
   hipLaunchKernelGGL(so2n_wgrad_kernel, dim3((w.unit0[5] + 3) / 4), dim3(256), 0, st, w);
   EGNN_LAUNCH_CHECK(ctx, "so2n_wgrad_kernel");
   const long n_wp = (long)s.k_first[lmax + 1] * E;
-  hipLaunchKernelGGL(so2n_wgrad_sum_kernel, dim3((unsigned)((n_wp + 255) / 256)), dim3(256), 0, st, w, s, lmax, scale, c.wpath);
+  hipLaunchKernelGGL(so2n_wgrad_sum_kernel, dim3((unsigned)((n_wp + 255) / 256)), dim3(256), 0, st, w, s, lmax, scale, c.dwpath);
   EGNN_LAUNCH_CHECK(ctx, "so2n_wgrad_sum_kernel");
   const long n_un = (long)s.off[5] + (long)E * ctx->desc.n_rbf;
-  hipLaunchKernelGGL(so2n_unpack_wgrad_kernel, dim3((unsigned)((n_un + 255) / 256)), dim3(256), 0, st, c.wpath, s, lmax, E,
+  hipLaunchKernelGGL(so2n_unpack_wgrad_kernel, dim3((unsigned)((n_un + 255) / 256)), dim3(256), 0, st, c.dwpath, s, lmax, E,
                      ctx->desc.n_rbf, W, W_e, dW, dW_e);
   EGNN_LAUNCH_CHECK(ctx, "so2n_unpack_wgrad_kernel");
   p.ptr = col_ptr; p.perm = perm; p.index = g->dst;
-  p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_owned); p.x_self = da; p.maxima = c2.maxima; p.g_out = nullptr; p.g_in = c.g;
-  p.j_end = g->n_total; p.n_rbf = 0; p.form = SO2N_PLAIN;
+  p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_owned); p.x_self = da; p.maxima = c2.maxima;
+  p.j_end = g->n_total;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
-  if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_PLAIN, true, c2, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, SO2N_PLAIN, true, c2, st))) return rc;
   return so2n_launch_mix(ctx, c2, SO2N_PLAIN, g->n_total, scale, dx, st);
 }
 
@@ -1236,12 +1324,13 @@ int so2n_message_sum(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, co
                      float scale, float* a, const So2nCall& c, hipStream_t st) {
   int rc;
   if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
-  if ((rc = so2n_pack_weights(ctx, W, W_e, SO2N_GAUSS, false, c, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, SO2N_GAUSS, false, c, st))) return rc;
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
-  p.T = c.T; p.maxima = c.maxima;
-  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.n_rbf = ctx->desc.n_rbf; p.form = SO2N_GAUSS;
+  p.T = c.T; p.maxima = c.maxima; p.g = c.g;
+  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.form = SO2N_GAUSS;
+  if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, W_e, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   return so2n_launch_mix(ctx, c, SO2N_GAUSS, g->n_owned, scale, a, st);
 }
@@ -1253,7 +1342,7 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   int rc;
   if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
-  if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_EDGES, false, c, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, SO2N_EDGES, false, c, st))) return rc;
   const size_t lds = std::max<size_t>(32 * (size_t)((lmax + 1) * E + 4) * 4, 16384);
   const dim3 grid((unsigned)((g->n_edges + 31) / 32));
   const unsigned x_bytes = (unsigned)((size_t)g->n_total * (lmax + 1) * (lmax + 1) * E * 4);   // (32 bits: the caller's rule)
@@ -1281,8 +1370,9 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d); p.alpha = alpha;
   p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
-  p.T = c.T; p.maxima = c.maxima; p.form = SO2N_EDGES;
+  p.T = c.T; p.maxima = c.maxima; p.g = c.g; p.form = SO2N_EDGES;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned;
+  if ((rc = so2n_launch_sums(ctx, g, rhat_d, alpha, 0, nullptr, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   p.rows = T_edge; p.x_self = nullptr;
   if ((rc = so2n_launch_gather<true>(ctx, p, st))) return rc;
