@@ -33,10 +33,12 @@ struct So2nCall {
   float* dwpath;         // and their sum
   float* G;              // and [n_owned][(lmax + 1)^2][SO2N_AUX] sums of harmonics times Gaussian basis
   uint32_t* packed;      // feature rows as half-precision pieces (low piece in the high half)
+  int* row_exp;          // and the exponent each was scaled with
+  int* node_exp;         // reverse pass: which owned nodes have edges (so2n_pack_kernel)
   float* g;              // [n_owned][(2 lmax + 1)^2] weighted sums of the harmonics over the incoming edges
   float* wpath;          // path weights, fp32
   uint4* wpack;          // the same cut into pieces in operand order
-  unsigned* maxima;      // bit patterns: 0 features, 1 path weights, 2 T, 3 edge rows, 4 G
+  unsigned* maxima;      // bit patterns: 0 gradients da, 1 path weights, 2 T, 3 edge rows, 4 G
 };
 
 // base = NULL: bytes only.  n_rows feature rows, T for n_t nodes.

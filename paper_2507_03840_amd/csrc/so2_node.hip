@@ -58,6 +58,13 @@ __device__ __forceinline__ uint32_t so2n_split(float x) {   // high piece in the
   return (uint32_t)__builtin_bit_cast(unsigned short, h) | ((uint32_t)__builtin_bit_cast(unsigned short, l) << 16);
 }
 
+// exponent of the power of two that brings a largest magnitude into [2^13, 2^14); 0 for zero, infinite or NaN
+__device__ __forceinline__ int so2n_exp(float m) {
+  if (!(m > 0.0f && m < 3.0e38f)) return 0;
+  const int e = 13 - ilogbf(m);
+  return e < -120 ? -120 : (e > 120 ? 120 : e);
+}
+
 // eight words (piece pairs) -> the two operand registers
 __device__ __forceinline__ void so2n_pieces(const uint32_t (&w)[8], uint4& hi, uint4& lo) {
   hi.x = __builtin_amdgcn_perm(w[1], w[0], 0x05040100); lo.x = __builtin_amdgcn_perm(w[1], w[0], 0x07060302);
@@ -144,7 +151,8 @@ struct So2nArgs {
   const int* index;          // feature row of edge k
   const float4* rhat_d;
   const float* alpha;        // optional further weight per edge
-  const uint32_t* packed;    // feature rows in pieces
+  const uint32_t* packed;    // feature rows in pieces, every row scaled by
+  const int* row_exp;        // this power of two, which its edges' weights take back
   unsigned packed_bytes;
   const float* rows;         // OWN: the edges' own rows (fp32)
   const float* x_self;       // rows of the nodes themselves (fp32); NULL: that group is zero
@@ -210,22 +218,27 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   const int e_own = tid & (SO2N_BATCH - 1);
   float4 g_own = make_float4(0.0f, 0.0f, 1.0f, 1.0f);
   float f_own = 0.0f;
+  auto weight = [&](int k, int row, float d) SO2N_INLINE {
+    const float f = egnn_envelope(d, p.r_cut) * (p.alpha ? p.alpha[k] : 1.0f);
+    return OWN ? f : ldexpf(f, -p.row_exp[row]);
+  };
   auto load_edge = [&](int b0) SO2N_INLINE {
     const int nb = deg - b0 < SO2N_BATCH ? deg - b0 : SO2N_BATCH;
     if (e_own < ((nb + 15) & ~15)) {
       // (the last step of 16 is filled up with copies of the last edge, of weight zero)
       const int at = k0 + b0 + (e_own < nb ? e_own : nb - 1);
       const int k = p.perm ? p.perm[at] : at;
+      const int row = OWN ? at - k0 - b0 : p.index[k];
       g_own = p.rhat_d[k];
-      f_own = e_own < nb ? egnn_envelope(g_own.w, p.r_cut) * (p.alpha ? p.alpha[k] : 1.0f) : 0.0f;
-      if (tid < SO2N_BATCH) s_off[e_own] = (unsigned)(OWN ? at - k0 - b0 : p.index[k]) * (unsigned)(D * E * 4);
+      f_own = e_own < nb ? weight(k, row, g_own.w) : 0.0f;
+      if (tid < SO2N_BATCH) s_off[e_own] = (unsigned)row * (unsigned)(D * E * 4);
     }
   };
   load_edge(0);
   float wmax = f_own;
   for (int e = SO2N_BATCH + e_own; e < deg; e += SO2N_BATCH) {
     const int k = p.perm ? p.perm[k0 + e] : k0 + e;
-    wmax = fmaxf(wmax, egnn_envelope(p.rhat_d[k].w, p.r_cut) * (p.alpha ? p.alpha[k] : 1.0f));
+    wmax = fmaxf(wmax, weight(k, OWN ? 0 : p.index[k], p.rhat_d[k].w));
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) wmax = fmaxf(wmax, __shfl_xor(wmax, off));
@@ -235,8 +248,8 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
 #pragma unroll
   for (int q = 0; q < 8; ++q) wmax = fmaxf(wmax, s_red[q]);
   // |Yhat_LM| <= sqrt(17): three bits below the range the scaling of a maximum aims at
-  const int ey = sgh_scale_exp(__float_as_uint(wmax)) - 3;
-  const int ex = sgh_scale_exp(p.maxima[OWN ? 3 : 0]);
+  const int ey = so2n_exp(wmax) - 3;
+  const int ex = OWN ? sgh_scale_exp(p.maxima[3]) : 0;
   const float y_scale = ldexpf(1.0f, ey), unscale = ldexpf(1.0f, -ex) * ldexpf(1.0f, -ey);
   // (rows of the edges themselves lie together: those of a batch are addressed from its first)
   auto rows_of = [&](int b0) SO2N_INLINE {
@@ -725,22 +738,41 @@ __global__ __launch_bounds__(256) void so2n_softmax_kernel(const int* __restrict
 }
 
 // ---------------------------------------------------------------------------------------------- features in pieces
-// (one atomic per workgroup: from every wavefront at once they cost 80 us on 2.4 million values)
-__global__ __launch_bounds__(256) void so2n_max_kernel(const float* __restrict__ x, long n, unsigned* __restrict__ out) {
+// One wavefront per row: its largest magnitude, the power of two from that and the row in pieces.  A power of two for all rows
+// would have to leave out those that no edge reads, and lose the small ones beside the large (and take two kernels: 19 instead
+// of 10 us on 2.4 million values).  With `ptr` (gradients of the
+// owned nodes, which the weight gradient contracts with one scale) the largest of the nodes with edges goes to *used_max and
+// node_exp tells them from the others, up to a multiple of 16 nodes.
+#define SO2N_UNUSED (-1000000)
+__global__ __launch_bounds__(256) void so2n_pack_kernel(const float* __restrict__ x, int n_rows, int row_floats,
+                                                        uint32_t* __restrict__ out, int* __restrict__ row_exp,
+                                                        const int* __restrict__ ptr, int* __restrict__ node_exp,
+                                                        unsigned* __restrict__ used_max) {
   __shared__ float s_mx[4];
-  float mx = 0.0f;
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) mx = fmaxf(mx, fabsf(x[i]));
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  float used = 0.0f;
+  const int n_all = ptr ? (n_rows + 15) & ~15 : n_rows;
+  for (int i = blockIdx.x * 4 + wave; i < n_all; i += gridDim.x * 4) {
+    const bool there = i < n_rows, has_edges = there && ptr && ptr[i + 1] > ptr[i];
+    if (ptr && lane == 0) node_exp[i] = has_edges ? 0 : SO2N_UNUSED;
+    if (!there) continue;
+    const float* row = x + (size_t)i * row_floats;
+    float mx = 0.0f;
+#pragma unroll 4
+    for (int q = lane; q < row_floats; q += 64) mx = fmaxf(mx, fabsf(row[q]));
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  if ((threadIdx.x & 63) == 0) s_mx[threadIdx.x >> 6] = mx;
+    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+    const int e = so2n_exp(mx);
+    if (lane == 0) row_exp[i] = e;
+    if (has_edges) used = fmaxf(used, mx);
+    const float sc = ldexpf(1.0f, e);
+#pragma unroll 4
+    for (int q = lane; q < row_floats; q += 64) out[(size_t)i * row_floats + q] = so2n_split(row[q] * sc);
+  }
+  if (!ptr) return;
+  if (lane == 0) s_mx[wave] = used;
   __syncthreads();
-  if (threadIdx.x == 0) egnn_raise_max(out, fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3])));
-}
-
-__global__ __launch_bounds__(256) void so2n_pack_kernel(const float* __restrict__ x, long n, const unsigned* __restrict__ mx,
-                                                        uint32_t* __restrict__ out) {
-  const float sc = ldexpf(1.0f, sgh_scale_exp(*mx));
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) out[i] = so2n_split(x[i] * sc);
+  if (threadIdx.x == 0) egnn_raise_max(used_max, fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3])));
 }
 
 // ---------------------------------------------------------------------------------------------- path weights
@@ -924,6 +956,7 @@ struct So2nWgrad {
   int k_tiles[5], chunks[5], per_chunk[5], unit0[6];
   size_t part0[6];       // first float of every degree's partial results
   int n_nodes, E, n_ct, D;
+  const int* node_exp;   // SO2N_UNUSED: a node without edges, whose da counts as zero; up to a multiple of 16 nodes
   const unsigned* t_max;
   const unsigned* g_max;
   const unsigned* da_max;
@@ -966,14 +999,17 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
     for (int i = 0; i < 16; ++i) acc[a][i] = 0.0f;
   sg_f4 ra[8];
   float ry[8];
+  int re[8];
   const int n_blocks = (n1 - n0 + 15) / 16, total = n_blocks * n_mo;
   auto fetch = [&](int q) SO2N_INLINE {
     const int mo = q / n_blocks, n = n0 + (q - mo * n_blocks) * 16 + 8 * hh;
+    const int4 e0 = *reinterpret_cast<const int4*>(p.node_exp + n), e1 = *reinterpret_cast<const int4*>(p.node_exp + n + 4);
+    re[0] = e0.x; re[1] = e0.y; re[2] = e0.z; re[3] = e0.w; re[4] = e1.x; re[5] = e1.y; re[6] = e1.z; re[7] = e1.w;
     const float* tm = T + (size_t)mo * ld;
     const float* ym = Y + (size_t)mo * p.E;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-      // (past the chunk's last node: that node again, with zeros for da)
+      // (past the last node: that node again, with zeros for da)
       const int nr = n + r < n1 ? n + r : n1 - 1;
       ra[r] = *reinterpret_cast<const sg_f4*>(tm + (size_t)nr * node_floats);
       ry[r] = ym[(size_t)nr * ys];
@@ -982,10 +1018,9 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   fetch(0);
   for (int q = 0; q < total; ++q) {
     uint4 ah[4], al[4], yh, yl;
-    const int n = n0 + (q % n_blocks) * 16 + 8 * hh;
     float y[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) y[r] = n + r < n1 ? ry[r] : 0.0f;
+    for (int r = 0; r < 8; ++r) y[r] = re[r] != SO2N_UNUSED ? ry[r] : 0.0f;
     sgh_split8(y, y_scale, yh, yl);
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
@@ -1117,6 +1152,8 @@ size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t 
   So2nCall c;
   c.maxima = (unsigned*)take(256);
   c.packed = (uint32_t*)take(so2n_packed_bytes(ctx, n_rows));
+  c.row_exp = (int*)take((size_t)n_rows * 4);
+  c.node_exp = (int*)take(((size_t)n_owned + 16) * 4);
   c.g = (float*)take((size_t)n_owned * so2n_nlm(lmax) * 4);
   c.wpath = (float*)take((size_t)s.k_first[lmax + 1] * E * 4);
   c.wpack = (uint4*)take((size_t)st.first[lmax + 1] * ((E + 31) / 32) * 128 * 16);
@@ -1126,12 +1163,12 @@ size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t 
   return used;
 }
 
-int so2n_pack_features(egnn_ctx* ctx, const float* x, long n_rows, const So2nCall& c, hipStream_t st) {
-  const long n = n_rows * (ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels;
-  const unsigned wg = (unsigned)std::min<long>((n + 1023) / 1024, 2048);
-  hipLaunchKernelGGL(so2n_max_kernel, dim3(std::min(wg, 512u)), dim3(256), 0, st, x, n, c.maxima);
-  EGNN_LAUNCH_CHECK(ctx, "so2n_max_kernel");
-  hipLaunchKernelGGL(so2n_pack_kernel, dim3(wg), dim3(256), 0, st, x, n, c.maxima, c.packed);
+// ptr: edges of every row's node (see so2n_pack_kernel) or NULL
+static int so2n_pack_features(egnn_ctx* ctx, const float* x, int n_rows, const int32_t* ptr, const So2nCall& c, hipStream_t st) {
+  if (n_rows <= 0) return EGNN_OK;
+  const int row_floats = (ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels;
+  hipLaunchKernelGGL(so2n_pack_kernel, dim3((unsigned)std::min((n_rows + 3) / 4, 2048)), dim3(256), 0, st, x, n_rows, row_floats, c.packed,
+                     c.row_exp, ptr, c.node_exp, c.maxima);
   EGNN_LAUNCH_CHECK(ctx, "so2n_pack_kernel");
   return EGNN_OK;
 }
@@ -1285,23 +1322,24 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
                               float* dW_e, float* dW, const So2nCall& c, hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   int rc;
-  if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
+  if ((rc = so2n_pack_features(ctx, x, g->n_total, nullptr, c, st))) return rc;
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
-  p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
+  p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.maxima = c.maxima; p.g = c.g;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.form = SO2N_PLAIN;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, nullptr, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   So2nCall c2 = c;
   c2.maxima = c.maxima + 16;
-  if ((rc = so2n_pack_features(ctx, da, g->n_owned, c2, st))) return rc;
+  if ((rc = so2n_pack_features(ctx, da, g->n_owned, g->row_ptr, c2, st))) return rc;
   So2nW s;
   So2nSteps steps;
   so2n_w_layout(lmax, E, SO2N_GRAD, &s, &steps);
   So2nWgrad w;
   so2n_wgrad_plan(ctx, g->n_owned, &w);
-  w.T = c.T; w.G = c.G; w.da = da; w.partial = c.partial; w.t_max = c.maxima + 2; w.g_max = c.maxima + 4; w.da_max = c2.maxima;
+  w.T = c.T; w.G = c.G; w.da = da; w.partial = c.partial; w.t_max = c.maxima + 2; w.g_max = c.maxima + 4;
+  w.da_max = c2.maxima; w.node_exp = c.node_exp;
   hipLaunchKernelGGL(so2n_wgrad_kernel, dim3((w.unit0[5] + 3) / 4), dim3(256), 0, st, w);
   EGNN_LAUNCH_CHECK(ctx, "so2n_wgrad_kernel");
   const long n_wp = (long)s.k_first[lmax + 1] * E;
@@ -1323,11 +1361,11 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
 int so2n_message_sum(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* x, const float* W_e, const float* W,
                      float scale, float* a, const So2nCall& c, hipStream_t st) {
   int rc;
-  if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
+  if ((rc = so2n_pack_features(ctx, x, g->n_total, nullptr, c, st))) return rc;
   if ((rc = so2n_pack_weights(ctx, W, SO2N_GAUSS, false, c, st))) return rc;
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
-  p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
+  p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.maxima = c.maxima; p.g = c.g;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.form = SO2N_GAUSS;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, W_e, c, st))) return rc;
@@ -1341,7 +1379,7 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
                     const float* w_att, float* alpha, float* a, const So2nCall& c, hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   int rc;
-  if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
+  if ((rc = so2n_pack_features(ctx, x, g->n_total, nullptr, c, st))) return rc;
   if ((rc = so2n_pack_weights(ctx, W, SO2N_EDGES, false, c, st))) return rc;
   const size_t lds = std::max<size_t>(32 * (size_t)((lmax + 1) * E + 4) * 4, 16384);
   const dim3 grid((unsigned)((g->n_edges + 31) / 32));
@@ -1369,7 +1407,7 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
   EGNN_LAUNCH_CHECK(ctx, "so2n_softmax_kernel");
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d); p.alpha = alpha;
-  p.packed = c.packed; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
+  p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.maxima = c.maxima; p.g = c.g; p.form = SO2N_EDGES;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, alpha, 0, nullptr, c, st))) return rc;

@@ -1,5 +1,5 @@
 """SO(2) calls on operands of very different size: what is small beside something else that does not enter it keeps its
-accuracy.  Every case has enough edges a node to mix its channels per node."""
+accuracy, and what no edge reads has no influence.  Every case has enough edges a node to mix its channels per node."""
 import numpy as np
 import pytest
 
@@ -95,3 +95,34 @@ def test_operand_scales(B, lmax, E, n, n_rbf, x_scale, we_scale, w_scale, da_sca
     print(f"  forward {e:.2e}, adjoint " + " ".join(f"{k} {v:.1e}" for k, v in eb.items()), flush=True)
     assert e < 1e-5
     check(got, want, 1e-5)
+
+
+def with_loose_atoms(lmax, E, n, n_owned, n_rbf):
+    """The dense structure with an owned atom and a halo atom beyond every cutoff."""
+    w, x, da, weights = dense(lmax, E, n, n_owned, n_rbf, 12)
+    far = np.array([[400.0, 0.0, 0.0]], np.float32)
+    w.pos = np.concatenate([w.pos[:n_owned], far, w.pos[n_owned:], -far]).astype(np.float32)
+    w.n_owned, w.n_total = n_owned + 1, n + 2
+    row = np.zeros((1,) + x.shape[1:], np.float32)
+    return w, np.concatenate([x[:n_owned], row, x[n_owned:], row]), np.concatenate([da, row]), weights, [n_owned, n + 1]
+
+
+@pytest.mark.parametrize("lmax,E,n,n_owned", [(2, 16, 60, 50), (4, 32, 64, 60), (1, 64, 50, 45)])
+@pytest.mark.parametrize("value", [1e30])
+def test_rows_that_no_edge_reads(B, lmax, E, n, n_owned, value):
+    """Features and gradients of atoms without neighbours: the results are those with zeros there, bit for bit."""
+    print("case", lmax, E, n, n_owned, value, flush=True)
+    w, x, da, weights, loose = with_loose_atoms(lmax, E, n, n_owned, 8)
+    c = Call(B, w)
+    n_edges = c.graph.n_edges
+    assert n_edges == n_owned * (n - 1)
+    T = np.random.default_rng(3).standard_normal((n_edges, (lmax + 1) ** 2, E)).astype(np.float32)
+    w_att = synth.normal(np.random.default_rng(4), (E,)).astype(np.float32)
+    x2, da2 = x.copy(), da.copy()
+    x2[loose], da2[loose[0]] = value, value
+    a, a2 = c.forward(x, weights), c.forward(x2, weights)
+    b, b2 = c.node_block(x, T, weights, w_att), c.node_block(x2, T, weights, w_att)
+    d, d2 = c.backward(x, weights, da), c.backward(x2, weights, da2)
+    assert np.abs(a[:n_owned]).max() > 0 and not np.any(a[n_owned]) and not np.any(b[n_owned])
+    for name, p, q in [("a", a, a2), ("node block", b, b2), ("dx", d[0], d2[0]), ("dW_e", d[1], d2[1]), ("dW", d[2], d2[2])]:
+        assert np.array_equal(p, q), name
