@@ -156,7 +156,8 @@ struct So2nArgs {
   unsigned packed_bytes;
   const float* rows;         // OWN: the edges' own rows (fp32)
   const float* x_self;       // rows of the nodes themselves (fp32); NULL: that group is zero
-  const float* g;            // [n_self] sums of the harmonics over their incoming edges
+  const int* self_ptr;       // incoming edges of the nodes that have a self group
+  const float* g;            // [n_self] sums of the harmonics over them
   float* T;
   unsigned* maxima;
   int j_begin, j_end;        // nodes of this launch; T starts at j_begin
@@ -211,7 +212,8 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
 
   // The node's own row, the first batch of edges (their rows' offsets and lengths to LDS; direction and weight stay in
   // registers until the scaling is known) and the largest edge weight, whose power of two scales the harmonics.
-  const bool has_self = p.x_self != nullptr && j < p.n_self;
+  // (without incoming edges there is no message that the node's own row could enter, whatever it holds)
+  const bool has_self = p.x_self != nullptr && j < p.n_self && p.self_ptr[j + 1] > p.self_ptr[j];
   for (int i = tid; i < D * CS; i += SO2N_THREADS)
     s_x[i] = has_self ? p.x_self[((size_t)j * D + i / CS) * E + slice * CS + i % CS] : 0.0f;
   for (int i = tid; i < NLM; i += SO2N_THREADS) s_g[i] = has_self ? p.g[(size_t)j * NLM + i] : 0.0f;
@@ -283,7 +285,9 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
 
   // coupling of the blocks this wave owns: lane = (group, channel), group 0 reads S, group 1 forms g x on the spot
   const int c = lane % CS, grp = lane / CS;
-  const float from_s = grp == 0 ? 1.0f : 0.0f, from_x = grp == 1 ? 1.0f : 0.0f;
+  // (masks: as factors of 0 and 1 they would let one group's infinities reach the other, and take 12 us more; compares 78)
+  const uint32_t from_s = grp == 0 ? ~0u : 0u, from_x = grp == 1 ? ~0u : 0u;
+  auto only = [](float v, uint32_t mask) SO2N_INLINE { return __uint_as_float(__float_as_uint(v) & mask); };
   const int form = p.form;
   const int node_floats = so2n_node_off(LMAX, E, LMAX + 1, form);
   float* T = p.T + (size_t)node * node_floats;
@@ -294,7 +298,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
     if (wave != owners.w[li][L]) return;
     float xv[2 * li + 1];
 #pragma unroll
-    for (int q = 0; q < 2 * li + 1; ++q) xv[q] = from_x * s_x[(li * li + q) * CS + c];
+    for (int q = 0; q < 2 * li + 1; ++q) xv[q] = only(s_x[(li * li + q) * CS + c], from_x);
     float o[D];
 #pragma unroll
     for (int i = 0; i < D; ++i) o[i] = 0.0f;
@@ -306,7 +310,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
 #pragma unroll
           for (int mi = 0; mi < 2 * li + 1; ++mi) {
             const float sv = rows[(mi * nl + lm) * CS];
-            v[mi] = gl * xv[mi] + from_s * sv;
+            v[mi] = gl * xv[mi] + only(sv, from_s);
           }
         },
         o);
@@ -740,9 +744,9 @@ __global__ __launch_bounds__(256) void so2n_softmax_kernel(const int* __restrict
 // ---------------------------------------------------------------------------------------------- features in pieces
 // One wavefront per row: its largest magnitude, the power of two from that and the row in pieces.  A power of two for all rows
 // would have to leave out those that no edge reads, and lose the small ones beside the large (and take two kernels: 19 instead
-// of 10 us on 2.4 million values).  With `ptr` (gradients of the
-// owned nodes, which the weight gradient contracts with one scale) the largest of the nodes with edges goes to *used_max and
-// node_exp tells them from the others, up to a multiple of 16 nodes.
+// of 10 us on 2.4 million values).  With `ptr` (gradients of the owned nodes, which the weight gradient contracts with one
+// scale) the largest of the nodes with edges goes to *used_max and node_exp tells them from the others, up to a multiple of 16
+// nodes.
 #define SO2N_UNUSED (-1000000)
 __global__ __launch_bounds__(256) void so2n_pack_kernel(const float* __restrict__ x, int n_rows, int row_floats,
                                                         uint32_t* __restrict__ out, int* __restrict__ row_exp,
@@ -1327,7 +1331,7 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.maxima = c.maxima; p.g = c.g;
-  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.form = SO2N_PLAIN;
+  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_PLAIN;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, nullptr, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   So2nCall c2 = c;
@@ -1367,7 +1371,7 @@ int so2n_message_sum(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, co
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.maxima = c.maxima; p.g = c.g;
-  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.form = SO2N_GAUSS;
+  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_GAUSS;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, W_e, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   return so2n_launch_mix(ctx, c, SO2N_GAUSS, g->n_owned, scale, a, st);
@@ -1409,7 +1413,7 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d); p.alpha = alpha;
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.maxima = c.maxima; p.g = c.g; p.form = SO2N_EDGES;
-  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned;
+  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, alpha, 0, nullptr, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   p.rows = T_edge; p.x_self = nullptr;

@@ -108,7 +108,7 @@ def with_loose_atoms(lmax, E, n, n_owned, n_rbf):
 
 
 @pytest.mark.parametrize("lmax,E,n,n_owned", [(2, 16, 60, 50), (4, 32, 64, 60), (1, 64, 50, 45)])
-@pytest.mark.parametrize("value", [1e30])
+@pytest.mark.parametrize("value", [1e30, float("inf"), float("nan")])
 def test_rows_that_no_edge_reads(B, lmax, E, n, n_owned, value):
     """Features and gradients of atoms without neighbours: the results are those with zeros there, bit for bit."""
     print("case", lmax, E, n, n_owned, value, flush=True)
