@@ -159,8 +159,9 @@ struct So2nArgs {
   const int* self_ptr;       // incoming edges of the nodes that have a self group
   const float* g;            // [n_self] sums of the harmonics over them
   float* T;
-  unsigned* maxima;
-  int j_begin, j_end;        // nodes of this launch; T starts at j_begin
+  unsigned* t_max;           // per node: largest |T| as bits, raised here
+  const unsigned* rows_max;  // OWN: largest |rows|
+  int j_begin, j_end;        // nodes of this launch; T and t_max start at j_begin
   int n_self;                // nodes that have a self group
   int per_xcd, E, n_slices, form;
   float r_cut;
@@ -251,7 +252,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   for (int q = 0; q < 8; ++q) wmax = fmaxf(wmax, s_red[q]);
   // |Yhat_LM| <= sqrt(17): three bits below the range the scaling of a maximum aims at
   const int ey = so2n_exp(wmax) - 3;
-  const int ex = OWN ? sgh_scale_exp(p.maxima[3]) : 0;
+  const int ex = OWN ? sgh_scale_exp(*p.rows_max) : 0;
   const float y_scale = ldexpf(1.0f, ey), unscale = ldexpf(1.0f, -ex) * ldexpf(1.0f, -ey);
   // (rows of the edges themselves lie together: those of a batch are addressed from its first)
   auto rows_of = [&](int b0) SO2N_INLINE {
@@ -482,7 +483,7 @@ __global__ __launch_bounds__(SO2N_THREADS, 2) void so2n_gather_kernel(So2nArgs p
   for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
   if (lane == 0) atomicMax(reinterpret_cast<unsigned*>(s_red + 8), __float_as_uint(amax));
   so2n_barrier();
-  if (tid == 0) atomicMax(p.maxima + 2, __float_as_uint(s_red[8]));   // (no result is waited for)
+  if (tid == 0) atomicMax(p.t_max + node, __float_as_uint(s_red[8]));   // (no result is waited for)
 }
 
 // ---------------------------------------------------------------------------------------------- sums of the harmonics
@@ -495,7 +496,8 @@ struct So2nSums {
   float* g;                  // [n_owned][(2 lmax + 1)^2]
   float* G;                  // [n_owned][(lmax + 1)^2][SO2N_AUX] sums with the Gaussian basis; NULL: not kept
   float* T;
-  unsigned* maxima;
+  unsigned* t_max;           // per node: largest |T| (raised here) or |G| (set here) as bits
+  unsigned* G_max;
   int n_rbf, log2E;          // n_rbf = 0: g alone
   float r_cut;
 };
@@ -605,7 +607,11 @@ __global__ __launch_bounds__(64 * SO2N_SUM_WAVES) void so2n_sums_kernel(So2nSums
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
   if (lane == 0) s_d[0][wave] = mx;
   __syncthreads();
-  if (tid == 0) egnn_raise_max(p.maxima + (p.W_e ? 2 : 4), fmaxf(fmaxf(s_d[0][0], s_d[0][1]), fmaxf(s_d[0][2], s_d[0][3])));
+  if (tid == 0) {
+    const unsigned bits = __float_as_uint(fmaxf(fmaxf(s_d[0][0], s_d[0][1]), fmaxf(s_d[0][2], s_d[0][3])));
+    if (p.W_e) atomicMax(p.t_max + j, bits);
+    else p.G_max[j] = bits;
+  }
 }
 static_assert(SO2N_SUM_WAVES == 4 && SO2N_AUX == 32, "so2n_sums_kernel adds four waves' sums of 32 columns");
 
@@ -744,39 +750,69 @@ __global__ __launch_bounds__(256) void so2n_softmax_kernel(const int* __restrict
 // ---------------------------------------------------------------------------------------------- features in pieces
 // One wavefront per row: its largest magnitude, the power of two from that and the row in pieces.  A power of two for all rows
 // would have to leave out those that no edge reads, and lose the small ones beside the large (and take two kernels: 19 instead
-// of 10 us on 2.4 million values).  With `ptr` (gradients of the owned nodes, which the weight gradient contracts with one
-// scale) the largest of the nodes with edges goes to *used_max and node_exp tells them from the others, up to a multiple of 16
-// nodes.
+// of 10 us on 2.4 million values).
+//
+// With `ptr` the rows are the gradients da of the owned nodes, and the weight gradient's scales come from here too: sums over
+// the nodes n of X_n da_n, X = T and X = G, with X_n scaled by 2^node_exp[n] from its own largest value and da_n by the inverse
+// of that and 2^C for all.  C brings the largest da_n 2^-node_exp[n] to 2^13; its exponent (plus SO2N_EXP0) goes to *used[0] for
+// T, *used[1] for G.  Nodes whose X is zero, those without edges among them, and those that fill up a multiple of 16 are marked.
 #define SO2N_UNUSED (-1000000)
-__global__ __launch_bounds__(256) void so2n_pack_kernel(const float* __restrict__ x, int n_rows, int row_floats,
-                                                        uint32_t* __restrict__ out, int* __restrict__ row_exp,
-                                                        const int* __restrict__ ptr, int* __restrict__ node_exp,
-                                                        unsigned* __restrict__ used_max) {
-  __shared__ float s_mx[4];
+#define SO2N_EXP0 4096
+struct So2nPack {
+  const float* x;
+  int n_rows, row_floats;
+  uint32_t* out;
+  int* row_exp;
+  const int* ptr;                // NULL: rows only
+  const unsigned* X_max[2];      // largest |T|, |G| of every node
+  int* node_exp[2];
+  unsigned* used;
+};
+__global__ __launch_bounds__(256) void so2n_pack_kernel(So2nPack p) {
+  __shared__ unsigned s_used[2][4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float used = 0.0f;
-  const int n_all = ptr ? (n_rows + 15) & ~15 : n_rows;
+  unsigned used[2] = {0u, 0u};
+  const int n_all = p.ptr ? (p.n_rows + 15) & ~15 : p.n_rows;
   for (int i = blockIdx.x * 4 + wave; i < n_all; i += gridDim.x * 4) {
-    const bool there = i < n_rows, has_edges = there && ptr && ptr[i + 1] > ptr[i];
-    if (ptr && lane == 0) node_exp[i] = has_edges ? 0 : SO2N_UNUSED;
-    if (!there) continue;
-    const float* row = x + (size_t)i * row_floats;
+    const bool there = i < p.n_rows;
     float mx = 0.0f;
+    bool finite = true;
+    if (there) {
+      const float* row = p.x + (size_t)i * p.row_floats;
 #pragma unroll 4
-    for (int q = lane; q < row_floats; q += 64) mx = fmaxf(mx, fabsf(row[q]));
+      for (int q = lane; q < p.row_floats; q += 64) {
+        const float v = fabsf(row[q]);
+        mx = fmaxf(mx, v);
+        finite = finite && v < __builtin_inff();
+      }
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-    const int e = so2n_exp(mx);
-    if (lane == 0) row_exp[i] = e;
-    if (has_edges) used = fmaxf(used, mx);
-    const float sc = ldexpf(1.0f, e);
+      for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
+      const int e = so2n_exp(mx);
+      if (lane == 0) p.row_exp[i] = e;
+      const float sc = ldexpf(1.0f, e);
 #pragma unroll 4
-    for (int q = lane; q < row_floats; q += 64) out[(size_t)i * row_floats + q] = so2n_split(row[q] * sc);
+      for (int q = lane; q < p.row_floats; q += 64) p.out[(size_t)i * p.row_floats + q] = so2n_split(row[q] * sc);
+    }
+    if (!p.ptr) continue;
+    finite = __all(finite);
+    const bool edges = there && p.ptr[i + 1] > p.ptr[i];
+#pragma unroll
+    for (int z = 0; z < 2; ++z) {
+      const float X = edges ? __uint_as_float(p.X_max[z][i]) : 0.0f;
+      const int e = so2n_exp(X);
+      // (an infinite or NaN gradient shows in the result unless its node has no edges)
+      const bool unused = !edges || (X == 0.0f && finite);
+      if (lane == 0) p.node_exp[z][i] = unused ? SO2N_UNUSED : e;
+      if (!unused && finite && mx > 0.0f && X > 0.0f) used[z] = max(used[z], (unsigned)(ilogbf(mx) - e + SO2N_EXP0));
+    }
   }
-  if (!ptr) return;
-  if (lane == 0) s_mx[wave] = used;
+  if (!p.ptr) return;
+  if (lane == 0) { s_used[0][wave] = used[0]; s_used[1][wave] = used[1]; }
   __syncthreads();
-  if (threadIdx.x == 0) egnn_raise_max(used_max, fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3])));
+  if (threadIdx.x < 2) {
+    const unsigned* u = s_used[threadIdx.x];
+    atomicMax(p.used + threadIdx.x, max(max(u[0], u[1]), max(u[2], u[3])));
+  }
 }
 
 // ---------------------------------------------------------------------------------------------- path weights
@@ -860,7 +896,8 @@ struct So2nMix {
   int n_nodes, lmax, E;
   float scale;
   float* out;           // [n_nodes][(lmax+1)^2][E]
-  const unsigned* maxima;
+  const unsigned* t_max;
+  const unsigned* w_max;
 };
 
 // out[(n, (lo, mo))][col] = scale sum_k T[lo][n (2 lo + 1) + mo][k] w[lo][k][col].  A workgroup takes 32 rows, its four
@@ -881,7 +918,8 @@ __global__ __launch_bounds__(256) void so2n_mix_kernel(So2nMix p) {
   const long node = row / (2 * lo + 1);
   const float* a = p.T + (size_t)node * p.node_floats + p.off[lo] + (size_t)(row - node * (2 * lo + 1)) * p.ld[lo] + 8 * hh;
   const uint4* w = p.w + ((size_t)p.st.first[lo] * NCB) * 128 + lane;
-  const int ea = sgh_scale_exp(p.maxima[2]), eb = sgh_scale_exp(p.maxima[1]);
+  // (a scale per node: beside others' large sums, small ones, of features or edges near the cutoff, keep their accuracy)
+  const int ea = so2n_exp(__uint_as_float(p.t_max[node])), eb = sgh_scale_exp(*p.w_max);
   const float a_scale = ldexpf(1.0f, ea);
   float16v acc[NCB];
 #pragma unroll
@@ -932,7 +970,6 @@ __global__ __launch_bounds__(256) void so2n_mix_kernel(So2nMix p) {
   }
   __syncthreads();
   if (wave > 0) return;
-  const float f = p.scale * (ldexpf(1.0f, -ea) * ldexpf(1.0f, -eb));
   const int D = (p.lmax + 1) * (p.lmax + 1);
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
@@ -941,10 +978,12 @@ __global__ __launch_bounds__(256) void so2n_mix_kernel(So2nMix p) {
     for (int i = 0; i < 16; ++i) {
       const float sum = acc[cb][i] + s_part[0][(cb * 16 + i) * 64 + lane] + s_part[1][(cb * 16 + i) * 64 + lane] +
                         s_part[2][(cb * 16 + i) * 64 + lane];
-      const long r = r0 + 8 * (i >> 2) + 4 * hh + (i & 3);
+      const int r32 = 8 * (i >> 2) + 4 * hh + (i & 3);
+      const long r = r0 + r32;
+      const int e_row = __shfl(ea, r32);
       if (r < rows && col < p.E) {
         const long n = r / (2 * lo + 1);
-        p.out[((size_t)n * D + lo * lo + (r - n * (2 * lo + 1))) * p.E + col] = f * sum;
+        p.out[((size_t)n * D + lo * lo + (r - n * (2 * lo + 1))) * p.E + col] = p.scale * ldexpf(sum, -e_row - eb);
       }
     }
   }
@@ -960,10 +999,8 @@ struct So2nWgrad {
   int k_tiles[5], chunks[5], per_chunk[5], unit0[6];
   size_t part0[6];       // first float of every degree's partial results
   int n_nodes, E, n_ct, D;
-  const int* node_exp;   // SO2N_UNUSED: a node without edges, whose da counts as zero; up to a multiple of 16 nodes
-  const unsigned* t_max;
-  const unsigned* g_max;
-  const unsigned* da_max;
+  const int* node_exp[2];   // scales of T and G (so2n_pack_kernel)
+  const unsigned* used;
 };
 
 // partial[lo][chunk][k][col] = sum over the nodes n of the chunk and mo of T[n][(lo, mo)][k] da[n][(lo, mo)][col].  A wave
@@ -971,7 +1008,7 @@ struct So2nWgrad {
 // index of both: lane (i, h) fetches 16 bytes of T and 4 of da for the eight nodes of its half-wave and finds in one
 // component of them the eight consecutive nodes one operand register wants, so accumulator a holds the rows
 // k0 + 4 r + a.  Degrees with more rows per node get fewer nodes per chunk, so that all waves take about equally long.  The
-// last wave of every column of tiles takes G in the place of T, with G's own scale: whichever of the two is the smaller keeps
+// last wave of every column of tiles takes G in the place of T, with G's own scales: whichever of the two is the smaller keeps
 // its accuracy.
 // Bound: T read once (413 MB at 3,000 nodes, lmax 4, 32 channels: 94 us = 4.4 TB/s; per edge it was 2.26 ms).
 __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
@@ -990,8 +1027,9 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   const int n0 = chunk * p.per_chunk[lo], n1 = n0 + p.per_chunk[lo] < p.n_nodes ? n0 + p.per_chunk[lo] : p.n_nodes;
   const int ca = 4 * i32, cy = ct * 32 + i32;
   const bool a_ok = ca < K, y_ok = cy < p.E;
-  const int ea = sgh_scale_exp(basis ? *p.g_max : *p.t_max), ey = sgh_scale_exp(*p.da_max);
-  const float a_scale = ldexpf(1.0f, ea), y_scale = ldexpf(1.0f, ey), unscale = ldexpf(1.0f, -ea) * ldexpf(1.0f, -ey);
+  const unsigned largest = p.used[basis ? 1 : 0];
+  const int ey = largest ? 13 + SO2N_EXP0 - (int)largest : 0;
+  const int* node_exp = p.node_exp[basis ? 1 : 0];
   const float* T = (basis ? p.G + lo * lo * SO2N_AUX : p.T + p.off[lo] + k_first) + (a_ok ? ca : K - 4);
   const int ld = basis ? SO2N_AUX : p.ld[lo], node_floats = basis ? p.D * SO2N_AUX : p.node_floats;
   const float* Y = p.da + (size_t)(lo * lo) * p.E + (y_ok ? cy : 0);
@@ -1007,7 +1045,7 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   const int n_blocks = (n1 - n0 + 15) / 16, total = n_blocks * n_mo;
   auto fetch = [&](int q) SO2N_INLINE {
     const int mo = q / n_blocks, n = n0 + (q - mo * n_blocks) * 16 + 8 * hh;
-    const int4 e0 = *reinterpret_cast<const int4*>(p.node_exp + n), e1 = *reinterpret_cast<const int4*>(p.node_exp + n + 4);
+    const int4 e0 = *reinterpret_cast<const int4*>(node_exp + n), e1 = *reinterpret_cast<const int4*>(node_exp + n + 4);
     re[0] = e0.x; re[1] = e0.y; re[2] = e0.z; re[3] = e0.w; re[4] = e1.x; re[5] = e1.y; re[6] = e1.z; re[7] = e1.w;
     const float* tm = T + (size_t)mo * ld;
     const float* ym = Y + (size_t)mo * p.E;
@@ -1024,12 +1062,14 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
     uint4 ah[4], al[4], yh, yl;
     float y[8];
 #pragma unroll
-    for (int r = 0; r < 8; ++r) y[r] = re[r] != SO2N_UNUSED ? ry[r] : 0.0f;
-    sgh_split8(y, y_scale, yh, yl);
+    for (int r = 0; r < 8; ++r) y[r] = re[r] != SO2N_UNUSED ? ldexpf(ry[r], ey - re[r]) : 0.0f;
+    sgh_split8(y, 1.0f, yh, yl);
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
-      const float x[8] = {ra[0][a], ra[1][a], ra[2][a], ra[3][a], ra[4][a], ra[5][a], ra[6][a], ra[7][a]};
-      sgh_split8(x, a_scale, ah[a], al[a]);
+      float x[8];
+#pragma unroll
+      for (int r = 0; r < 8; ++r) x[r] = ldexpf(ra[r][a], re[r]);
+      sgh_split8(x, 1.0f, ah[a], al[a]);
     }
     fetch(q + 1 < total ? q + 1 : q);
 #pragma unroll
@@ -1046,7 +1086,7 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const int k = 4 * (8 * (i >> 2) + 4 * hh + (i & 3)) + a;
-        if (k < K) out[(size_t)k * p.E] = unscale * acc[a][i];
+        if (k < K) out[(size_t)k * p.E] = ldexpf(acc[a][i], -ey);
       }
   }
 }
@@ -1154,25 +1194,29 @@ size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t 
   So2nSteps st;
   so2n_w_layout(lmax, E, form, &s, &st);
   So2nCall c;
-  c.maxima = (unsigned*)take(256);
+  c.maxima = (unsigned*)take(256 + ((size_t)n_owned + n_t) * 4);
+  c.t_max = c.maxima ? c.maxima + 64 : nullptr;
   c.packed = (uint32_t*)take(so2n_packed_bytes(ctx, n_rows));
   c.row_exp = (int*)take((size_t)n_rows * 4);
-  c.node_exp = (int*)take(((size_t)n_owned + 16) * 4);
   c.g = (float*)take((size_t)n_owned * so2n_nlm(lmax) * 4);
   c.wpath = (float*)take((size_t)s.k_first[lmax + 1] * E * 4);
   c.wpack = (uint4*)take((size_t)st.first[lmax + 1] * ((E + 31) / 32) * 128 * 16);
   c.T = (float*)take((size_t)n_t * so2n_node_off(lmax, E, lmax + 1, form) * 4);
   c.partial = c.dwpath = c.G = nullptr;
+  c.G_max = nullptr;
+  c.node_exp[0] = c.node_exp[1] = nullptr;
   if (out) *out = c;
   return used;
 }
 
-// ptr: edges of every row's node (see so2n_pack_kernel) or NULL
+// ptr: edges of the nodes whose gradients the rows are (see so2n_pack_kernel), or NULL
 static int so2n_pack_features(egnn_ctx* ctx, const float* x, int n_rows, const int32_t* ptr, const So2nCall& c, hipStream_t st) {
   if (n_rows <= 0) return EGNN_OK;
-  const int row_floats = (ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels;
-  hipLaunchKernelGGL(so2n_pack_kernel, dim3((unsigned)std::min((n_rows + 3) / 4, 2048)), dim3(256), 0, st, x, n_rows, row_floats, c.packed,
-                     c.row_exp, ptr, c.node_exp, c.maxima);
+  So2nPack p;
+  p.x = x; p.n_rows = n_rows; p.row_floats = (ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels;
+  p.out = c.packed; p.row_exp = c.row_exp; p.ptr = ptr; p.X_max[0] = c.t_max; p.X_max[1] = c.G_max;
+  p.node_exp[0] = c.node_exp[0]; p.node_exp[1] = c.node_exp[1]; p.used = c.maxima + 4;
+  hipLaunchKernelGGL(so2n_pack_kernel, dim3((unsigned)std::min((n_rows + 3) / 4, 2048)), dim3(256), 0, st, p);
   EGNN_LAUNCH_CHECK(ctx, "so2n_pack_kernel");
   return EGNN_OK;
 }
@@ -1237,7 +1281,7 @@ static int so2n_launch_sums(egnn_ctx* ctx, const egnn_graph* g, const float* rha
   if (g->n_owned <= 0) return EGNN_OK;
   So2nSums p;
   p.ptr = g->row_ptr; p.rhat_d = reinterpret_cast<const float4*>(rhat_d); p.alpha = alpha; p.W_e = W_e; p.g = c.g;
-  p.G = W_e ? nullptr : c.G; p.T = c.T; p.maxima = c.maxima; p.n_rbf = n_rbf; p.log2E = ctx->log2_channels; p.r_cut = ctx->desc.r_cut;
+  p.G = W_e ? nullptr : c.G; p.T = c.T; p.t_max = c.t_max; p.G_max = c.G_max; p.n_rbf = n_rbf; p.log2E = ctx->log2_channels; p.r_cut = ctx->desc.r_cut;
   const dim3 grid((unsigned)g->n_owned), block(64 * SO2N_SUM_WAVES);
   switch (ctx->desc.lmax) {
     case 0: hipLaunchKernelGGL(so2n_sums_kernel<0>, grid, block, 0, st, p); break;
@@ -1259,7 +1303,8 @@ static int so2n_launch_mix(egnn_ctx* ctx, const So2nCall& c, int form, int n_nod
   p.T = c.T;
   p.node_floats = so2n_node_off(lmax, E, lmax + 1, form);
   p.w = c.wpack;
-  p.n_nodes = n_nodes; p.lmax = lmax; p.E = E; p.scale = scale; p.out = out; p.maxima = c.maxima;
+  p.n_nodes = n_nodes; p.lmax = lmax; p.E = E; p.scale = scale; p.out = out; p.t_max = c.t_max;
+  p.w_max = c.maxima + 1;
   p.blocks[0] = 0;
   for (int lo = 0; lo < 5; ++lo) {
     p.K[lo] = s.K[lo];
@@ -1313,14 +1358,20 @@ size_t so2n_backward_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_total
   float* partial = (float*)take(p.part0[lmax + 1] * 4);
   float* dwpath = (float*)take((size_t)s.k_first[lmax + 1] * E * 4);
   float* G = (float*)take((size_t)n_owned * (lmax + 1) * (lmax + 1) * SO2N_AUX * 4);
-  if (out) { out->partial = partial; out->dwpath = dwpath; out->G = G; }
+  unsigned* G_max = (unsigned*)take((size_t)n_owned * 4);
+  int* exps[2];
+  for (int z = 0; z < 2; ++z) exps[z] = (int*)take(((size_t)n_owned + 16) * 4);
+  if (out) {
+    out->partial = partial; out->dwpath = dwpath; out->G = G; out->G_max = G_max;
+    out->node_exp[0] = exps[0]; out->node_exp[1] = exps[1];
+  }
   return used;
 }
 
 // Reverse pass of the message sum.  T of the forward pass again -> gradient of the path weights and, from that, of W and W_e;
 // then the same sums over the outgoing edges with da in the place of the features (a message is linear in its source, and
 // the transpose of D_lo^T P D_li is D_li^T P^T D_lo) and the transposed weights -> dx; the destinations' part uses the
-// forward pass's sums of harmonics.  c from so2n_backward_carve, its maxima zero on entry.
+// forward pass's sums of harmonics.  c from so2n_backward_carve, its maxima and t_max zero on entry.
 int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t* col_ptr, const int32_t* perm, const float* rhat_d,
                               const float* x, const float* W_e, const float* W, const float* da, float scale, float* dx,
                               float* dW_e, float* dW, const So2nCall& c, hipStream_t st) {
@@ -1330,20 +1381,18 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
-  p.T = c.T; p.maxima = c.maxima; p.g = c.g;
+  p.T = c.T; p.t_max = c.t_max; p.g = c.g;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_PLAIN;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, nullptr, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
-  So2nCall c2 = c;
-  c2.maxima = c.maxima + 16;
-  if ((rc = so2n_pack_features(ctx, da, g->n_owned, g->row_ptr, c2, st))) return rc;
+  if ((rc = so2n_pack_features(ctx, da, g->n_owned, g->row_ptr, c, st))) return rc;
   So2nW s;
   So2nSteps steps;
   so2n_w_layout(lmax, E, SO2N_GRAD, &s, &steps);
   So2nWgrad w;
   so2n_wgrad_plan(ctx, g->n_owned, &w);
-  w.T = c.T; w.G = c.G; w.da = da; w.partial = c.partial; w.t_max = c.maxima + 2; w.g_max = c.maxima + 4;
-  w.da_max = c2.maxima; w.node_exp = c.node_exp;
+  w.T = c.T; w.G = c.G; w.da = da; w.partial = c.partial; w.used = c.maxima + 4;
+  w.node_exp[0] = c.node_exp[0]; w.node_exp[1] = c.node_exp[1];
   hipLaunchKernelGGL(so2n_wgrad_kernel, dim3((w.unit0[5] + 3) / 4), dim3(256), 0, st, w);
   EGNN_LAUNCH_CHECK(ctx, "so2n_wgrad_kernel");
   const long n_wp = (long)s.k_first[lmax + 1] * E;
@@ -1354,14 +1403,16 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
                      ctx->desc.n_rbf, W, W_e, dW, dW_e);
   EGNN_LAUNCH_CHECK(ctx, "so2n_unpack_wgrad_kernel");
   p.ptr = col_ptr; p.perm = perm; p.index = g->dst;
-  p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_owned); p.x_self = da; p.maxima = c2.maxima;
+  p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_owned); p.x_self = da;
+  So2nCall c2 = c;
+  c2.t_max = p.t_max = c.t_max + g->n_owned;
   p.j_end = g->n_total;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   if ((rc = so2n_pack_weights(ctx, W, SO2N_PLAIN, true, c2, st))) return rc;
   return so2n_launch_mix(ctx, c2, SO2N_PLAIN, g->n_total, scale, dx, st);
 }
 
-// a[j] for the owned nodes; rhat_d and c carved by the caller, c.maxima zero on entry
+// a[j] for the owned nodes; rhat_d and c carved by the caller, c.maxima and c.t_max zero on entry
 int so2n_message_sum(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* x, const float* W_e, const float* W,
                      float scale, float* a, const So2nCall& c, hipStream_t st) {
   int rc;
@@ -1370,7 +1421,7 @@ int so2n_message_sum(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, co
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
-  p.T = c.T; p.maxima = c.maxima; p.g = c.g;
+  p.T = c.T; p.t_max = c.t_max; p.g = c.g;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_GAUSS;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, W_e, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
@@ -1412,11 +1463,11 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d); p.alpha = alpha;
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
-  p.T = c.T; p.maxima = c.maxima; p.g = c.g; p.form = SO2N_EDGES;
+  p.T = c.T; p.t_max = c.t_max; p.g = c.g; p.form = SO2N_EDGES;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, alpha, 0, nullptr, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
-  p.rows = T_edge; p.x_self = nullptr;
+  p.rows = T_edge; p.rows_max = c.maxima + 3; p.x_self = nullptr;
   if ((rc = so2n_launch_gather<true>(ctx, p, st))) return rc;
   return so2n_launch_mix(ctx, c, SO2N_EDGES, g->n_owned, 1.0f, a, st);
 }

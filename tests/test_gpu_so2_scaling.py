@@ -126,3 +126,30 @@ def test_rows_that_no_edge_reads(B, lmax, E, n, n_owned, value):
     assert np.abs(a[:n_owned]).max() > 0 and not np.any(a[n_owned]) and not np.any(b[n_owned])
     for name, p, q in [("a", a, a2), ("node block", b, b2), ("dx", d[0], d2[0]), ("dW_e", d[1], d2[1]), ("dW", d[2], d2[2])]:
         assert np.array_equal(p, q), name
+
+
+@pytest.mark.parametrize("lmax,E", [(4, 32), (2, 64)])
+def test_rows_of_nodes_at_the_cutoff(B, lmax, E):
+    """A node whose single neighbour lies just inside the cutoff (on an axis, so that its distance is a 32-bit number and the
+    envelope exact to its last bits): a sum 1e-9 of the others' keeps its accuracy, a few roundings of 32 bits, and with a
+    gradient as much larger it counts as much as the others in the weight gradients."""
+    print("case", lmax, E, flush=True)
+    w, x, da, weights = dense(lmax, E, 60, 50, 8, 13)
+    w.pos -= w.pos[0]
+    w.pos[1:] *= np.float32(0.25)
+    w.pos[:, 0] = -np.abs(w.pos[:, 0])
+    w.pos[1:, 0] -= np.float32(1.0)                                     # atom 0 is the one with the largest x
+    w.pos = np.concatenate([[[w.r_cut - 3e-3, 0.0, 0.0]], w.pos]).astype(np.float32)    # the node at the cutoff comes first
+    w.n_owned, w.n_total = w.n_owned + 1, w.n_total + 1
+    x, da = np.concatenate([x[:1], x]), np.concatenate([da[:1] * np.float32(2e9), da])
+    g = U.oracle_graph(w)
+    assert np.sum(g[1] == 0) == 1
+    c = Call(B, w)
+    got, ref = c.forward(x, weights), S.so2_message_sum(g, w.pos, w.box, x, *weights, lmax, E, 8, w.r_cut, 7.0)
+    size, e, rest = np.abs(ref[0]).max() / np.abs(ref).max(), U.rel_err(got[0], ref[0]), U.rel_err(got[1:], ref[1:])
+    back, want = c.backward(x, weights, da), S.so2_message_sum_backward(g, w.pos, w.box, x, *weights, lmax, E, 8, w.r_cut, 7.0, da)
+    want = dict(dx=want[0], dW_e=want[1], dW0=want[2], **{f"dWr{i + 1}": v for i, v in enumerate(want[3])},
+                **{f"dWi{i + 1}": v for i, v in enumerate(want[4])})
+    print(f"  row {size:.1e} of the largest: error {e:.1e}, other rows {rest:.1e}", flush=True)
+    assert 1e-10 < size < 1e-8 and e < 2e-6 and rest < 2e-6
+    print(f"  adjoint {check(named(back, lmax, E), want, 5e-6):.1e}", flush=True)
