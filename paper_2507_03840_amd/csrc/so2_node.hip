@@ -492,7 +492,7 @@ struct So2nSums {
   const int* ptr;
   const float4* rhat_d;
   const float* alpha;        // optional further weight per edge
-  const float* W_e;          // the edge embedding's columns of T (form SO2N_GAUSS); NULL: none
+  const float* W_e;          // transposed, [SO2N_AUX][E]: the edge embedding's columns of T (form SO2N_GAUSS); NULL: none
   float* g;                  // [n_owned][(2 lmax + 1)^2]
   float* G;                  // [n_owned][(lmax + 1)^2][SO2N_AUX] sums with the Gaussian basis; NULL: not kept
   float* T;
@@ -592,7 +592,7 @@ __global__ __launch_bounds__(64 * SO2N_SUM_WAVES) void so2n_sums_kernel(So2nSums
     const int E = 1 << p.log2E, c = tid & (E - 1);
     float w[SO2N_AUX];
 #pragma unroll
-    for (int b = 0; b < SO2N_AUX; ++b) w[b] = p.W_e[c * p.n_rbf + min(b, p.n_rbf - 1)];   // (sums past the basis are zero)
+    for (int b = 0; b < SO2N_AUX; ++b) w[b] = p.W_e[(b << p.log2E) + c];
     float* T = p.T + (size_t)j * so2n_node_off(LMAX, E, LMAX + 1, SO2N_GAUSS) + c - E;
     for (int i = tid >> p.log2E; i < D; i += THREADS >> p.log2E) {
       float v = 0.0f;
@@ -848,11 +848,17 @@ __device__ float so2n_weight(const float* __restrict__ W, const So2nW& s, int lm
   return transposed && odd ? -sum : sum;
 }
 
-__global__ __launch_bounds__(256) void so2n_weights_kernel(const float* __restrict__ W, So2nW s, int lmax, int E, int form,
-                                                           bool transposed, float* __restrict__ out, unsigned* __restrict__ w_max) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+// out: the path weights and then, with W_e, its transpose padded to SO2N_AUX rows
+__global__ __launch_bounds__(256) void so2n_weights_kernel(const float* __restrict__ W, const float* __restrict__ W_e, So2nW s,
+                                                           int lmax, int E, int n_rbf, int form, bool transposed,
+                                                           float* __restrict__ out, unsigned* __restrict__ w_max) {
+  const long i = (long)blockIdx.x * 256 + threadIdx.x, n = (long)s.k_first[lmax + 1] * E;
   float v = 0.0f;
-  if (i < (long)s.k_first[lmax + 1] * E) {
+  if (W_e && i >= n && i < n + SO2N_AUX * E) {
+    const int b = (int)(i - n) / E, c = (int)(i - n) % E;
+    out[i] = b < n_rbf ? W_e[c * n_rbf + b] : 0.0f;
+  }
+  if (i < n) {
     const int row = (int)(i / E), col = (int)(i - (long)row * E);
     int a = 0;
     while (row >= s.k_first[a + 1]) ++a;
@@ -1199,7 +1205,7 @@ size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t 
   c.packed = (uint32_t*)take(so2n_packed_bytes(ctx, n_rows));
   c.row_exp = (int*)take((size_t)n_rows * 4);
   c.g = (float*)take((size_t)n_owned * so2n_nlm(lmax) * 4);
-  c.wpath = (float*)take((size_t)s.k_first[lmax + 1] * E * 4);
+  c.wpath = (float*)take(((size_t)s.k_first[lmax + 1] + SO2N_AUX) * E * 4);
   c.wpack = (uint4*)take((size_t)st.first[lmax + 1] * ((E + 31) / 32) * 128 * 16);
   c.T = (float*)take((size_t)n_t * so2n_node_off(lmax, E, lmax + 1, form) * 4);
   c.partial = c.dwpath = c.G = nullptr;
@@ -1221,14 +1227,15 @@ static int so2n_pack_features(egnn_ctx* ctx, const float* x, int n_rows, const i
   return EGNN_OK;
 }
 
-int so2n_pack_weights(egnn_ctx* ctx, const float* W, int form, bool transposed, const So2nCall& c, hipStream_t st) {
+static int so2n_pack_weights(egnn_ctx* ctx, const float* W, const float* W_e, int form, bool transposed, const So2nCall& c,
+                             hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   So2nW s;
   So2nSteps steps;
   so2n_w_layout(lmax, E, form, &s, &steps);
-  const long n = (long)s.k_first[lmax + 1] * E;
-  hipLaunchKernelGGL(so2n_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, W, s, lmax, E, form,
-                     transposed, c.wpath, c.maxima + 1);
+  const long n = (long)s.k_first[lmax + 1] * E + (W_e ? SO2N_AUX * E : 0);
+  hipLaunchKernelGGL(so2n_weights_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, W, W_e, s, lmax, E,
+                     ctx->desc.n_rbf, form, transposed, c.wpath, c.maxima + 1);
   EGNN_LAUNCH_CHECK(ctx, "so2n_weights_kernel");
   const int n_cb = (E + 31) / 32;
   const long m = (long)steps.first[lmax + 1] * n_cb * 64;
@@ -1275,10 +1282,14 @@ static int so2n_launch_gather(egnn_ctx* ctx, So2nArgs a, hipStream_t st) {
 #undef SO2N_L
 }
 
-// g of the owned nodes and, with n_rbf, the edge embedding's columns of T (W_e given) or G
-static int so2n_launch_sums(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* alpha, int n_rbf,
-                            const float* W_e, const So2nCall& c, hipStream_t st) {
+// g of the owned nodes and, with n_rbf, the edge embedding's columns of T (after so2n_pack_weights with W_e) or G
+static int so2n_launch_sums(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* alpha, int n_rbf, bool embed,
+                            const So2nCall& c, hipStream_t st) {
   if (g->n_owned <= 0) return EGNN_OK;
+  So2nW s;
+  So2nSteps steps;
+  so2n_w_layout(ctx->desc.lmax, ctx->desc.channels, SO2N_GAUSS, &s, &steps);
+  const float* W_e = embed ? c.wpath + (size_t)s.k_first[ctx->desc.lmax + 1] * ctx->desc.channels : nullptr;
   So2nSums p;
   p.ptr = g->row_ptr; p.rhat_d = reinterpret_cast<const float4*>(rhat_d); p.alpha = alpha; p.W_e = W_e; p.g = c.g;
   p.G = W_e ? nullptr : c.G; p.T = c.T; p.t_max = c.t_max; p.G_max = c.G_max; p.n_rbf = n_rbf; p.log2E = ctx->log2_channels; p.r_cut = ctx->desc.r_cut;
@@ -1383,7 +1394,7 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.t_max = c.t_max; p.g = c.g;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_PLAIN;
-  if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, nullptr, c, st))) return rc;
+  if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, false, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   if ((rc = so2n_pack_features(ctx, da, g->n_owned, g->row_ptr, c, st))) return rc;
   So2nW s;
@@ -1408,7 +1419,7 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   c2.t_max = p.t_max = c.t_max + g->n_owned;
   p.j_end = g->n_total;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
-  if ((rc = so2n_pack_weights(ctx, W, SO2N_PLAIN, true, c2, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_PLAIN, true, c2, st))) return rc;
   return so2n_launch_mix(ctx, c2, SO2N_PLAIN, g->n_total, scale, dx, st);
 }
 
@@ -1417,13 +1428,13 @@ int so2n_message_sum(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, co
                      float scale, float* a, const So2nCall& c, hipStream_t st) {
   int rc;
   if ((rc = so2n_pack_features(ctx, x, g->n_total, nullptr, c, st))) return rc;
-  if ((rc = so2n_pack_weights(ctx, W, SO2N_GAUSS, false, c, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, W_e, SO2N_GAUSS, false, c, st))) return rc;
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.t_max = c.t_max; p.g = c.g;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_GAUSS;
-  if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, W_e, c, st))) return rc;
+  if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, true, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   return so2n_launch_mix(ctx, c, SO2N_GAUSS, g->n_owned, scale, a, st);
 }
@@ -1435,7 +1446,7 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   int rc;
   if ((rc = so2n_pack_features(ctx, x, g->n_total, nullptr, c, st))) return rc;
-  if ((rc = so2n_pack_weights(ctx, W, SO2N_EDGES, false, c, st))) return rc;
+  if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_EDGES, false, c, st))) return rc;
   const size_t lds = std::max<size_t>(32 * (size_t)((lmax + 1) * E + 4) * 4, 16384);
   const dim3 grid((unsigned)((g->n_edges + 31) / 32));
   const unsigned x_bytes = (unsigned)((size_t)g->n_total * (lmax + 1) * (lmax + 1) * E * 4);   // (32 bits: the caller's rule)
@@ -1465,7 +1476,7 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
   p.T = c.T; p.t_max = c.t_max; p.g = c.g; p.form = SO2N_EDGES;
   p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr;
-  if ((rc = so2n_launch_sums(ctx, g, rhat_d, alpha, 0, nullptr, c, st))) return rc;
+  if ((rc = so2n_launch_sums(ctx, g, rhat_d, alpha, 0, false, c, st))) return rc;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   p.rows = T_edge; p.rows_max = c.maxima + 3; p.x_self = nullptr;
   if ((rc = so2n_launch_gather<true>(ctx, p, st))) return rc;
