@@ -153,3 +153,18 @@ def test_rows_of_nodes_at_the_cutoff(B, lmax, E):
     print(f"  row {size:.1e} of the largest: error {e:.1e}, other rows {rest:.1e}", flush=True)
     assert 1e-10 < size < 1e-8 and e < 2e-6 and rest < 2e-6
     print(f"  adjoint {check(named(back, lmax, E), want, 5e-6):.1e}", flush=True)
+
+
+@pytest.mark.parametrize("lmax,E,n,n_owned,bound", [(4, 32, 210, 24, 2.2e-7), (4, 64, 48, 40, 2.5e-7)])
+def test_running_sums(B, lmax, E, n, n_owned, bound):
+    """The channel mixing adds a quarter of 1,696 (64 channels: 3,392) columns in a row, four columns to a rounding.  A sum that
+    grows from zero and is rounded to 24 bits r times is off by about 2^-24 sqrt(r / 24) of its end value.  Correction products
+    in the same sum would make that 2.1e-7 (3.0e-7); in a sum of their own, and the rest in two, it is 0.9e-7 (1.2e-7).  The
+    sums over the edges add 1.5e-7 (0.7e-7), and everything else about 1e-7: 2.0e-7 (1.8e-7) against 2.8e-7 (3.3e-7)."""
+    print("case", lmax, E, n, flush=True)
+    w, x, da, weights = dense(lmax, E, n, n_owned, 8, 14)
+    g = U.oracle_graph(w)
+    ref = S.so2_message_sum(g, w.pos, w.box, x, *weights, lmax, E, 8, w.r_cut, 7.0)
+    e = np.linalg.norm(Call(B, w).forward(x, weights) - ref) / np.linalg.norm(ref)
+    print(f"  2-norm error {e:.2e}", flush=True)
+    assert e < bound
