@@ -126,6 +126,26 @@ def test_edge_block_tiles(B, lmax, E, n, n_owned):
         assert np.all(np.abs(T2.cpu().numpy() - ref).max(axis=(1, 2)) <= 2 * TOL * np.abs(want).max() + rounding)
 
 
+@pytest.mark.parametrize("lmax,E,n,n_owned", [(4, 64, 41, 3), (0, 64, 30, 5), (2, 64, 20, 7), (3, 32, 40, 7), (3, 128, 20, 4), (4, 8, 20, 4)])
+def test_edge_block_in_place(B, lmax, E, n, n_owned):
+    """The result does not depend on whether the output is the input, on any route."""
+    import torch
+    print("case", lmax, E, n, n_owned, flush=True)
+    w, g, x, W_e, W0, Wr, Wi = case(lmax, E, n, n_owned, 8)
+    rng = np.random.default_rng(n)
+    T = (10.0 ** rng.uniform(-6, 6, size=(len(g[0]), 1, 1)) * rng.standard_normal((len(g[0]), (lmax + 1) ** 2, E))).astype(np.float32)
+    m = B.Egnn(lmax, E, 8, w.r_cut, 7.0)
+    graph = m.egnn_nlist(B.to_device(w.pos), n_owned, w.box, w.pbc)
+    args = (graph, B.to_device(w.pos), w.box, B.to_device(x))
+    Td, Wd = B.to_device(T), B.to_device(S.so2_pack(W0, Wr, Wi))
+    ws = torch.full((m.egnn_so2_blocks_workspace_bytes(graph.n_edges),), 0xFF, dtype=torch.uint8, device="cuda")
+    out = m.egnn_so2_edge_block(*args, Td, Wd, ws)
+    ws.fill_(0xFF)
+    T2 = Td.clone()
+    assert m.egnn_so2_edge_block(*args, T2, Wd, ws, out=T2) is T2
+    assert torch.equal(T2, out)
+
+
 # Weight gradients are differences of sums over all edges: the fp32 rounding of the terms enters with the ratio of their
 # size to the result's, a few times at these shapes.
 TOL_BWD = 5e-6

@@ -157,7 +157,7 @@ def test_rows_of_nodes_at_the_cutoff(B, lmax, E):
 
 @pytest.mark.parametrize("lmax,E,n,n_owned,bound", [(4, 32, 210, 24, 2.2e-7), (4, 64, 48, 40, 2.5e-7)])
 def test_running_sums(B, lmax, E, n, n_owned, bound):
-    """The channel mixing adds a quarter of 1,696 (64 channels: 3,392) columns in a row, four columns to a rounding.  A sum that
+    """The channel mixing adds a quarter of 1,632 (64 channels: 3,264) columns in a row, four columns to a rounding.  A sum that
     grows from zero and is rounded to 24 bits r times is off by about 2^-24 sqrt(r / 24) of its end value.  Correction products
     in the same sum would make that 2.1e-7 (3.0e-7); in a sum of their own, and the rest in two, it is 0.9e-7 (1.2e-7).  The
     sums over the edges add 1.5e-7 (0.7e-7), and everything else about 1e-7: 2.0e-7 (1.8e-7) against 2.8e-7 (3.3e-7)."""
