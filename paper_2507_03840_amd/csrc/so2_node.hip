@@ -911,7 +911,7 @@ struct So2nMix {
 // node: without the split a few thousand waves would each walk a hundred dependent steps); partial sums meet in LDS in a
 // fixed order.  Bound: T, written by the gathering kernel and read here; 413 MB at 3,000 nodes, lmax 4, 32 channels: 112 us.
 template <int NCB>
-__global__ __launch_bounds__(256) void so2n_mix_kernel(So2nMix p) {
+__global__ __launch_bounds__(256, 2) void so2n_mix_kernel(So2nMix p) {
   __shared__ float s_part[3][NCB * 16 * 64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, l32 = lane & 31, hh = lane >> 5;
   int lo = 0;
@@ -930,16 +930,16 @@ __global__ __launch_bounds__(256) void so2n_mix_kernel(So2nMix p) {
   // The rounding of the running sums is the largest part of the error, so the products of a high and a low piece, 2^-11 of the
   // others, have a sum of their own, and odd steps too (all in one: error of the
   // message sum at lmax 4, 32 channels and 209 edges a node 2.75e-7 of the result instead of 2.0e-7; no slower).
-  constexpr int P = NCB == 4 ? 1 : 2;
-  float16v accs[P][NCB], rest[NCB];
+  // (128 channels: two sums, and two waves per SIMD asked for: with the one that the compiler chose, 10 to 30 % of the whole call
+  // were lost.)
+  constexpr int P = NCB == 4 ? 2 : 3, REST = P - 1;
+  float16v sums[P][NCB];
 #pragma unroll
-  for (int cb = 0; cb < NCB; ++cb)
+  for (int q = 0; q < P; ++q)
 #pragma unroll
-    for (int i = 0; i < 16; ++i) {
-      rest[cb][i] = 0.0f;
+    for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
-      for (int q = 0; q < P; ++q) accs[q][cb][i] = 0.0f;
-    }
+      for (int i = 0; i < 16; ++i) sums[q][cb][i] = 0.0f;
   constexpr int U = NCB == 4 ? 2 : 4;
   for (int s = s0; s < s1; s += U) {
     sg_f4 x0[U], x1[U];
@@ -966,19 +966,20 @@ __global__ __launch_bounds__(256) void so2n_mix_kernel(So2nMix p) {
         sgh_split8(v, a_scale, ah, al);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-          rest[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(al), sgh_as_h8(b[u][cb][0]), rest[cb], 0, 0, 0);
+          sums[REST][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(al), sgh_as_h8(b[u][cb][0]), sums[REST][cb], 0, 0, 0);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-          rest[cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah), sgh_as_h8(b[u][cb][1]), rest[cb], 0, 0, 0);
+          sums[REST][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah), sgh_as_h8(b[u][cb][1]), sums[REST][cb], 0, 0, 0);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-          accs[u % P][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah), sgh_as_h8(b[u][cb][0]), accs[u % P][cb], 0, 0, 0);
+          sums[P == 3 ? u % 2 : 0][cb] =
+              __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah), sgh_as_h8(b[u][cb][0]), sums[P == 3 ? u % 2 : 0][cb], 0, 0, 0);
       }
     }
   }
   float16v acc[NCB];
 #pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) acc[cb] = P == 2 ? accs[0][cb] + (accs[P - 1][cb] + rest[cb]) : accs[0][cb] + rest[cb];
+  for (int cb = 0; cb < NCB; ++cb) acc[cb] = sums[0][cb] + (P == 3 ? sums[1][cb] + sums[REST][cb] : sums[REST][cb]);
   if (wave > 0) {
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
