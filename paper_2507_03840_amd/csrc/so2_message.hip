@@ -596,23 +596,39 @@ static int so2_transform(egnn_ctx* ctx, const egnn_graph* g, const float* pos, c
   return EGNN_OK;
 }
 
-// Whether the message sum mixes channels per node (so2_node.hip): what that costs per node has to be worth the edges' part
-// of the per-edge products.  3,000 nodes, us per call per edge -> per node: lmax 4, 32 channels, 14.9 edges a node 350 -> 427,
-// 22.6 536 -> 416, 37.8 694 -> 433; lmax 3, 64 channels, 14.9 521 -> 464; lmax 2, 16 channels, 9.5 82 -> 88, 14.9 121 -> 87.
-// Its buffers must fit the workspace the caller was asked for (about 15 edges a node; many halo rows may not), and byte
-// offsets of feature rows 32 bits.
-#define SO2N_MIN_DEGREE 20
+// Whether the message sum mixes channels per node (so2_node.hip): what that costs per node, which depends on lmax and on
+// channels below a full tile of 32, has to be worth the edges' part of the per-edge products.  us per call, per edge -> per
+// node, at the degrees where it turns: 4,000 nodes, lmax 4: 8 channels, 30.5 edges a node 260 -> 296, 43.6 367 -> 305; 16
+// channels, 25.5 367 -> 372, 30.5 395 -> 376; 32 channels (10,000 nodes), 24.3 1,265 -> 1,332, 31.2 1,535 -> 1,345; 64
+// channels, 20.7 1,159 -> 1,189, 23.8 1,292 -> 1,188; 128 channels, 20.7 3,566 -> 2,670.  Lower lmax gains from 20 on (lmax 3:
+// 16 channels 214 -> 206, 64 714 -> 591; lmax 2: 32 channels 277 -> 123).  On few nodes the per-edge kernels, two per order,
+// are bound by their launches: 1,000 nodes, lmax 4, 20.6 edges: 16 channels 158 -> 120, 32 224 -> 154, 64 439 -> 350, but 8 100
+// -> 104 (25.3: 110 -> 105; 16 nodes 68 -> 42).  At lmax 0 there is only one order, and small calls gain nothing: 8 channels x
+// 7,000 edges 31 -> 33, x 13,600 44 -> 33; 32 x 1,200 31 -> 32, x 2,300 34 -> 33; 64 x 725 37 -> 34. Its buffers must fit the
+// workspace the caller was asked for (about 15 edges a node; many halo rows may not), and byte offsets of feature rows 32 bits.
+#define SO2N_FEW_NODES 1500
 static bool so2_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
-  const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels * 4;
-  return g->n_owned > 0 && g->n_edges >= (int64_t)SO2N_MIN_DEGREE * g->n_owned && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
+  const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
+  const size_t row = (size_t)(lmax + 1) * (lmax + 1) * E * 4;
+  int degree = 20;
+  if (lmax == 4 && g->n_owned > SO2N_FEW_NODES) degree = E == 8 ? 36 : E <= 32 ? 28 : E == 64 ? 23 : 20;
+  else if (lmax == 4 && E == 8 && g->n_owned > 500) degree = 26;
+  if (lmax == 0 && g->n_edges * E < (E <= 16 ? 100000 : 45000)) return false;
+  return g->n_owned > 0 && g->n_edges >= (int64_t)degree * g->n_owned && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
          so2_a256((size_t)g->n_edges * 16) + so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, SO2N_GAUSS, nullptr, nullptr) <=
              so2_ws(ctx, g->n_edges, false, false, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
-// The node block by the same means, with a pass over all edges for the attention scores first and a second gathering launch
-// for the edges' own rows.  3,000 nodes, us per call per edge -> per node: lmax 4, 32 channels, 22.6 edges a node 674 -> 797,
-// 37.8 910 -> 867, 209 4,500 -> 1,900; lmax 3, 64 channels, 22.6 916 -> 926, 37.8 1,319 -> 1,061; lmax 2, 16 channels, 13.7
-// 117 -> 153, 22.6 171 -> 163.  128 channels stay per edge (the score kernel's sums are laid out for two blocks of 32).
+// The node block by the same means, with a pass over all edges for the attention scores first and a second gathering launch for
+// the edges' own rows, so it turns later.  us per call, per edge -> per node: from 32 edges a node: lmax 4, 64 channels, 4,000
+// nodes, 37.7 2,947 -> 2,585; lmax 3, 32 channels, 37.7 690 -> 651; lmax 2, 8 channels, 33.5 193 -> 168.  At lmax 4 with fewer
+// channels later: 32 channels, 37.7 1,144 -> 1,159, 50 1,528 -> 1,226 (1,000 nodes, 37.3 379 -> 343); 16, 43.6 750 -> 812, 64
+// 1,054 -> 922 (1,000 nodes, 43.2 245 -> 234); 8, 43.6 497 -> 622, 62 677 -> 661 (100 nodes, 36.2 88 -> 74); so too lmax 1 with
+// 8: 33.5 112 -> 133, 61 76 -> 69.  Small calls of lmax 0 and 1 are bound by launches, of which this has three more: 8
+// channels, lmax 1, 4,700 edges 45 -> 48, 13,600 56 -> 53; lmax 0, 16 channels, 4,700 39 -> 44, 13,600 67 -> 52; 32 channels,
+// 4,700 54 -> 50; 64 channels, 1,200 50 -> 57, 2,400 76 -> 58.  And lmax 0 with up to 16 channels is bound by the edges'
+// offsets from 300,000 edges on (134,000 131 -> 105, 387,000 163 -> 168, 632,000 223 -> 258).  128 channels stay per edge (the
+// score kernel's sums are laid out for two blocks of 32).
 static size_t so2_block_nodes_ws(const egnn_ctx* ctx, const egnn_graph* g, char* base, float** rhat_d, float** alpha, So2nCall* c) {
   size_t used = 0;
   auto take = [&](size_t bytes) { char* q = base ? base + used : nullptr; used += so2_a256(bytes); return q; };
@@ -622,27 +638,40 @@ static size_t so2_block_nodes_ws(const egnn_ctx* ctx, const egnn_graph* g, char*
   if (alpha) *alpha = al;
   return used + so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, SO2N_EDGES, base ? base + used : nullptr, c);
 }
-#define SO2N_MIN_DEGREE_BLOCK 32
 static bool so2_block_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
-  const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels * 4;
-  return g->n_owned > 0 && ctx->desc.channels <= 64 && g->n_edges >= (int64_t)SO2N_MIN_DEGREE_BLOCK * g->n_owned &&
-         ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
+  const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
+  const size_t row = (size_t)(lmax + 1) * (lmax + 1) * E * 4;
+  int degree = 32;
+  if (lmax == 4 && E == 8) degree = g->n_owned <= 500 ? 32 : 60;
+  else if (lmax == 4 && E <= 32) degree = g->n_owned <= SO2N_FEW_NODES ? (E == 16 ? 40 : 32) : (E == 16 ? 54 : 40);
+  else if (lmax == 1 && E == 8) degree = 56;
+  if (lmax <= 1 && (size_t)g->n_edges * row < (E <= 16 ? 800000u : 400000u)) return false;
+  if (lmax == 0 && E <= 16 && g->n_edges > 300000) return false;
+  return g->n_owned > 0 && E <= 64 && g->n_edges >= (int64_t)degree * g->n_owned && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
          so2_block_nodes_ws(ctx, g, nullptr, nullptr, nullptr, nullptr) <=
              so2_ws(ctx, g->n_edges, true, false, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
-// Whether the edge block runs as one kernel over tiles of edges (so2_edge.hip).  us per call, per-edge kernels -> tiles: lmax 4,
-// 32 channels, 3,000 nodes with 209 / 37.8 / 1.6 edges each 5,000 -> 3,450 / 985 -> 713 / 216 -> 98; lmax 4, 64 channels,
-// 37.8 2,528 -> 2,085; lmax 2, 16 channels 225 -> 128; 100 nodes 61 -> 30 to 346 -> 154.  With 128 channels every tile of
-// edges would be rotated four times (lmax 2, 37.8 edges 1,907 -> 2,957), and 8 are half a matrix instruction: both stay
-// per edge.  With 64 channels the two blocks of output channels are two workgroups that both read the whole row, so an update in
-// place is written to the workspace first (*in_place; the copy of 729 MB takes 0.24 of 2.22 ms at 37.8 edges, per edge 2.32).
+// Whether the edge block runs as one kernel over tiles of edges (so2_edge.hip).  us per call, per-edge kernels -> tiles: lmax
+// 4, 32 channels, 3,000 nodes with 209 / 37.8 / 1.6 edges each 5,000 -> 3,450 / 985 -> 713 / 216 -> 98; lmax 4, 64 channels,
+// 37.8 2,528 -> 2,085; lmax 2, 16 channels 225 -> 128; 100 nodes 61 -> 30 to 346 -> 154.  With 128 channels every tile of edges
+// would be rotated four times (lmax 2, 37.8 edges 1,907 -> 2,957), and 8 are half a matrix instruction: both stay per edge. 
+// Few degrees have few units of work for a tile's eight waves (lmax 0 a single one), so there only calls that the per-edge
+// kernels spend on launches gain: lmax 0, 16 and 32 channels, 140,000 edges 137 -> 65 and 154 -> 110, 235,000 132 -> 109 and
+// 167 -> 184, 390,000 153 -> 172 and 218 -> 282; with 64 channels, whose rows are rotated twice, lmax 0, 13,600 136 -> 49,
+// 36,000 99 -> 104, 630,000 577 -> 1,609; lmax 1, 30,000 165 -> 140, 43,000 182 -> 195, 256,000 676 -> 978; lmax 2, 43,000 332
+// -> 319, 64,000 401 -> 430, 256,000 1,523 -> 1,707. With 64 channels the two blocks of output channels are two workgroups that
+// both read the whole row, so an update in place is written to the workspace first (*in_place; the copy of 729 MB takes 0.24 of
+// 2.22 ms at 37.8 edges, per edge 2.32).
 static bool so2_block_use_tiles(const egnn_ctx* ctx, const egnn_graph* g, const float* T_in, const float* T_out, bool* in_place) {
-  const int E = ctx->desc.channels;
-  const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * E * 4, all = (size_t)g->n_edges * row;
+  const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
+  const size_t row = (size_t)(lmax + 1) * (lmax + 1) * E * 4, all = (size_t)g->n_edges * row;
   const uintptr_t in = (uintptr_t)T_in, out = (uintptr_t)T_out;
   *in_place = E > 32 && in < out + all && out < in + all;
-  return E >= 16 && E <= 64 && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
+  int64_t most = INT64_MAX;
+  if (E == 64 && lmax <= 2) most = lmax == 2 ? 50000 : 32000;
+  else if (lmax == 0) most = E == 16 ? 300000 : 200000;
+  return E >= 16 && E <= 64 && g->n_edges <= most && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
          so2_a256((size_t)g->n_edges * 16) + 256 + so2_a256(so2e_weight_bytes(ctx)) + (*in_place ? all : 0) <=
              so2_ws(ctx, g->n_edges, true, false, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
@@ -1457,13 +1486,20 @@ static int so2_backward_check(egnn_ctx* ctx, const egnn_graph* g, const void* ws
   return EGNN_OK;
 }
 
-// As so2_use_nodes, per node of any kind: the sums over outgoing edges are taken for the halo nodes as well.  Per edge -> per
-// node, lmax 4, 32 channels: 7.4 edges a node 896 -> 895 us, 12.4 1247 -> 1227, 21.1 1807 -> 1269; lmax 3, 64 channels: 7.4
-// 1200 -> 1278, 12.4 1714 -> 1319.
-#define SO2N_MIN_DEGREE_BACKWARD 12
+// As so2_use_nodes, per node of any kind: the sums over outgoing edges are taken for the halo nodes as well.  us per call, per
+// edge -> per node: 4,000 nodes, lmax 4, 32 channels, 16.1 edges a node 1,010 -> 1,104, 20.7 1,225 -> 1,135; 64 channels, 16.1
+// 2,150 -> 2,457, 20.7 2,721 -> 2,514; 16 channels, 16.1 670 -> 744, 20.7 807 -> 757; 8 channels, 20.7 554 -> 576, 25.5 601 ->
+// 577.  Lower lmax: lmax 3, 64 channels, 10,000 nodes, 13.4 2,542 -> 2,654, 16.5 3,072 -> 2,739; 32 channels, 13 704 -> 553;
+// lmax 2, 128 channels, 13 1,628 -> 1,270.  Few nodes, lmax 4: 32 channels, 12.8 451 -> 332; 64 channels, 12.8 735 -> 778, 13.7
+// 491 -> 369, 16 811 -> 782.
 static bool so2_use_nodes_backward(const egnn_ctx* ctx, const egnn_graph* g) {
-  const size_t row = (size_t)(ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels * 4;
-  return g->n_owned > 0 && g->n_edges >= (int64_t)SO2N_MIN_DEGREE_BACKWARD * g->n_total && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
+  const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
+  const size_t row = (size_t)(lmax + 1) * (lmax + 1) * E * 4;
+  const bool few = g->n_total <= SO2N_FEW_NODES;
+  int degree = 12;
+  if (lmax == 4) degree = few ? (E <= 32 ? 12 : 13) : (E == 8 ? 24 : 19);
+  else if (lmax == 3 && E >= 64 && !few) degree = 14;
+  return g->n_owned > 0 && g->n_edges >= (int64_t)degree * g->n_total && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
          so2_a256((size_t)g->n_edges * 16) + so2n_backward_carve(ctx, g->n_owned, g->n_total, nullptr, nullptr) <=
              so2_bwd_ws(ctx, g->n_edges, g->n_owned, false, false, nullptr, nullptr);
 }

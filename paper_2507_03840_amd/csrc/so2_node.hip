@@ -907,9 +907,11 @@ struct So2nMix {
 };
 
 // out[(n, (lo, mo))][col] = scale sum_k T[lo][n (2 lo + 1) + mo][k] w[lo][k][col].  A workgroup takes 32 rows, its four
-// waves a quarter of the contraction each (rows are up to 3,300 values long while there are only (lmax+1)^2 of them per
-// node: without the split a few thousand waves would each walk a hundred dependent steps); partial sums meet in LDS in a
-// fixed order.  Bound: T, written by the gathering kernel and read here; 413 MB at 3,000 nodes, lmax 4, 32 channels: 112 us.
+// waves a quarter of the contraction each (rows are 1,632 values long at lmax 4 and 32 channels, up to 6,528 in all, while there
+// are only (lmax+1)^2 of them per node: without the split a few thousand waves would each walk a hundred dependent steps);
+// partial sums meet in LDS in a fixed order.  Bound: T, written by the gathering kernel and read here; 413 MB at 3,000 nodes,
+// lmax 4, 32 channels: 117 us.  128 channels are two workgroups of two column blocks each: one of four has no registers for
+// three sums, and even with two the whole call took 1,000 instead of 866 us on 1,000 nodes.
 template <int NCB>
 __global__ __launch_bounds__(256, 2) void so2n_mix_kernel(So2nMix p) {
   __shared__ float s_part[3][NCB * 16 * 64];
@@ -923,24 +925,22 @@ __global__ __launch_bounds__(256, 2) void so2n_mix_kernel(So2nMix p) {
   const long row = r0 + l32 < rows ? r0 + l32 : rows - 1;
   const long node = row / (2 * lo + 1);
   const float* a = p.T + (size_t)node * p.node_floats + p.off[lo] + (size_t)(row - node * (2 * lo + 1)) * p.ld[lo] + 8 * hh;
-  const uint4* w = p.w + ((size_t)p.st.first[lo] * NCB) * 128 + lane;
+  const int n_cb = gridDim.y * NCB, cb0 = blockIdx.y * NCB;
+  const uint4* w = p.w + ((size_t)p.st.first[lo] * n_cb + cb0) * 128 + lane;
   // (a scale per node: beside others' large sums, small ones, of features or edges near the cutoff, keep their accuracy)
   const int ea = so2n_exp(__uint_as_float(p.t_max[node])), eb = sgh_scale_exp(*p.w_max);
   const float a_scale = ldexpf(1.0f, ea);
-  // The rounding of the running sums is the largest part of the error, so the products of a high and a low piece, 2^-11 of the
-  // others, have a sum of their own, and odd steps too (all in one: error of the
-  // message sum at lmax 4, 32 channels and 209 edges a node 2.75e-7 of the result instead of 2.0e-7; no slower).
-  // (128 channels: two sums, and two waves per SIMD asked for: with the one that the compiler chose, 10 to 30 % of the whole call
-  // were lost.)
-  constexpr int P = NCB == 4 ? 2 : 3, REST = P - 1;
-  float16v sums[P][NCB];
+  // Even steps, odd steps, and the products of a high and a low piece, 2^-11 of the others: the rounding of the running sums is the
+  // largest part of the error (with one sum for all 2.75e-7 of the message sum at lmax 4, 32 channels and 209 edges a node, so
+  // 2.0e-7; no slower).
+  float16v sums[3][NCB];
 #pragma unroll
-  for (int q = 0; q < P; ++q)
+  for (int q = 0; q < 3; ++q)
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
 #pragma unroll
       for (int i = 0; i < 16; ++i) sums[q][cb][i] = 0.0f;
-  constexpr int U = NCB == 4 ? 2 : 4;
+  constexpr int U = 4;
   for (int s = s0; s < s1; s += U) {
     sg_f4 x0[U], x1[U];
     uint4 b[U][NCB][2];
@@ -954,8 +954,8 @@ __global__ __launch_bounds__(256, 2) void so2n_mix_kernel(So2nMix p) {
       x1[u] = *reinterpret_cast<const sg_f4*>(a + k + 4);
 #pragma unroll
       for (int cb = 0; cb < NCB; ++cb) {
-        b[u][cb][0] = w[((size_t)su * NCB + cb) * 128];
-        b[u][cb][1] = w[((size_t)su * NCB + cb) * 128 + 64];
+        b[u][cb][0] = w[((size_t)su * n_cb + cb) * 128];
+        b[u][cb][1] = w[((size_t)su * n_cb + cb) * 128 + 64];
       }
     }
 #pragma unroll
@@ -966,20 +966,19 @@ __global__ __launch_bounds__(256, 2) void so2n_mix_kernel(So2nMix p) {
         sgh_split8(v, a_scale, ah, al);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-          sums[REST][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(al), sgh_as_h8(b[u][cb][0]), sums[REST][cb], 0, 0, 0);
+          sums[2][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(al), sgh_as_h8(b[u][cb][0]), sums[2][cb], 0, 0, 0);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-          sums[REST][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah), sgh_as_h8(b[u][cb][1]), sums[REST][cb], 0, 0, 0);
+          sums[2][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah), sgh_as_h8(b[u][cb][1]), sums[2][cb], 0, 0, 0);
 #pragma unroll
         for (int cb = 0; cb < NCB; ++cb)
-          sums[P == 3 ? u % 2 : 0][cb] =
-              __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah), sgh_as_h8(b[u][cb][0]), sums[P == 3 ? u % 2 : 0][cb], 0, 0, 0);
+          sums[u % 2][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(ah), sgh_as_h8(b[u][cb][0]), sums[u % 2][cb], 0, 0, 0);
       }
     }
   }
   float16v acc[NCB];
 #pragma unroll
-  for (int cb = 0; cb < NCB; ++cb) acc[cb] = sums[0][cb] + (P == 3 ? sums[1][cb] + sums[REST][cb] : sums[REST][cb]);
+  for (int cb = 0; cb < NCB; ++cb) acc[cb] = sums[0][cb] + (sums[1][cb] + sums[2][cb]);
   if (wave > 0) {
 #pragma unroll
     for (int cb = 0; cb < NCB; ++cb)
@@ -991,7 +990,7 @@ __global__ __launch_bounds__(256, 2) void so2n_mix_kernel(So2nMix p) {
   const int D = (p.lmax + 1) * (p.lmax + 1);
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
-    const int col = cb * 32 + l32;
+    const int col = (cb0 + cb) * 32 + l32;
 #pragma unroll
     for (int i = 0; i < 16; ++i) {
       const float sum = acc[cb][i] + s_part[0][(cb * 16 + i) * 64 + lane] + s_part[1][(cb * 16 + i) * 64 + lane] +
@@ -1338,7 +1337,7 @@ static int so2n_launch_mix(egnn_ctx* ctx, const So2nCall& c, int form, int n_nod
   const dim3 grid((unsigned)p.blocks[lmax + 1]), block(256);
   if (E <= 32) hipLaunchKernelGGL(so2n_mix_kernel<1>, grid, block, 0, st, p);
   else if (E == 64) hipLaunchKernelGGL(so2n_mix_kernel<2>, grid, block, 0, st, p);
-  else hipLaunchKernelGGL(so2n_mix_kernel<4>, grid, block, 0, st, p);
+  else hipLaunchKernelGGL(so2n_mix_kernel<2>, dim3(grid.x, 2), block, 0, st, p);
   EGNN_LAUNCH_CHECK(ctx, "so2n_mix_kernel");
   return EGNN_OK;
 }

@@ -42,7 +42,9 @@ def case(lmax, E, n, n_owned, n_rbf):
     # every degree and slice width (a partial tile of columns at 0/8, 0/16, 2/8, 2/16, 4/8, 4/16), several slices
     (0, 8, 40, 33, 5), (0, 16, 40, 8, 6), (0, 32, 30, 7, 6), (1, 8, 40, 9, 6), (1, 16, 33, 11, 6), (1, 64, 40, 9, 6),
     (2, 8, 30, 17, 6), (2, 16, 41, 16, 6), (3, 8, 29, 10, 6), (3, 16, 65, 10, 6), (3, 32, 49, 10, 6), (4, 8, 40, 13, 6),
-    (4, 16, 47, 12, 6), (4, 64, 48, 11, 16), (3, 128, 31, 9, 8), (4, 128, 30, 5, 16)])
+    (4, 16, 47, 12, 6), (4, 64, 48, 11, 16), (3, 128, 31, 9, 8), (4, 128, 30, 5, 16),
+    # lmax 0 takes this route only with many edges
+    (0, 8, 130, 110, 5), (0, 16, 100, 80, 6), (0, 32, 60, 30, 6), (0, 128, 40, 21, 8)])
 def test_message_sum_per_node(B, lmax, E, n, n_owned, n_rbf):
     import torch
     print("case", lmax, E, n, n_owned, n_rbf, flush=True)
@@ -66,6 +68,8 @@ def test_message_sum_per_node(B, lmax, E, n, n_owned, n_rbf):
     (4, 32, 32, 9), (4, 32, 33, 1), (4, 32, 33, 31), (4, 32, 34, 5), (4, 32, 257, 2), (4, 32, 258, 3), (2, 32, 300, 4),
     (0, 8, 40, 33), (0, 16, 40, 8), (0, 32, 36, 7), (1, 8, 40, 9), (1, 64, 40, 9), (2, 8, 37, 17), (2, 16, 41, 16), (3, 8, 39, 10),
     (3, 16, 65, 10), (3, 32, 49, 10), (3, 64, 34, 10), (4, 8, 40, 13), (4, 16, 47, 12), (4, 64, 48, 11),
+    # where fewer channels or degrees need more edges a node or more edges in all for this route
+    (4, 8, 62, 5), (4, 16, 58, 7), (1, 8, 90, 80), (0, 8, 180, 150), (0, 16, 130, 110), (0, 64, 60, 58),
     (3, 128, 35, 9)])                                                  # (more channels than this route takes)
 def test_node_block_per_node(B, lmax, E, n, n_owned):
     import torch
