@@ -6,8 +6,8 @@
 //
 // A workgroup takes 64 edges through stages of 16 channels of one group (edge, source, destination): threads (edge, channel)
 // rotate a row, scale it by a power of two of the edge's own and cut it into half-precision pieces in LDS; the 8 waves
-// contract it with the weights, which come from L2 (1 MB for 64 edges: smaller tiles would be bound by that, larger ones
-// do not fit LDS), into accumulators of [output channel][edge], 25 x 64 x 32 floats at lmax 4 = 100 registers a thread.
+// contract it with the weights, which come from L2 (1 MB for 64 edges, 10 GB at 628,000, about 0.3 ms of L2's rate; larger
+// tiles do not fit LDS), into accumulators of [output channel][edge], 25 x 64 x 32 floats at lmax 4 = 100 registers a thread.
 // 628,000 edges, lmax 4, 32 channels: 3.45 ms, of which vector ALU 1.1 (rotations and pieces), matrix cores 0.7; the rest are
 // loads and barriers that one workgroup of 8 waves x 256 registers per compute unit cannot hide.  Separate kernels: 5.0
 // (gather 1.5, products 2.4, update 1.1).  Both blocks of 32 edges at a time in the inner loop: 4.1 ms (32 registers
@@ -70,14 +70,6 @@ template <int LMAX>
 constexpr int so2e_slots() { return So2eUnits<LMAX>().n > 8 ? 2 : 1; }
 
 // ---------------------------------------------------------------------------------------------- weights
-__global__ __launch_bounds__(256) void so2e_wmax_kernel(const float* __restrict__ W, long n, unsigned* __restrict__ w_max) {
-  float mx = 0.0f;
-  for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long)gridDim.x * 256) mx = fmaxf(mx, fabsf(W[i]));
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  if ((threadIdx.x & 63) == 0) egnn_raise_max(w_max, mx);
-}
-
 // out[block of 32 output channels][stage][unit, input degree][weight 0 / 1][piece][lane]; a lane holds eight input channels of
 // one output channel
 template <int LMAX>
@@ -370,11 +362,8 @@ static int so2e_launch(egnn_ctx* ctx, const So2eArgs& a, const float* W, uint4* 
 int so2e_edge_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* x, const float* T_in, const float* W,
                     float* T_out, unsigned* w_max, uint4* wpack, hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
-  long n_w = 0;
-  for (int m = 0; m <= lmax; ++m) n_w += (long)(m ? 2 : 1) * (lmax + 1 - m) * (lmax + 1 - m) * 3 * E * E;
-  const unsigned wg = (unsigned)((n_w + 255) / 256 < 256 ? (n_w + 255) / 256 : 256);
-  hipLaunchKernelGGL(so2e_wmax_kernel, dim3(wg), dim3(256), 0, st, W, n_w, w_max);
-  EGNN_LAUNCH_CHECK(ctx, "so2e_wmax_kernel");
+  int rc;
+  if ((rc = so2_launch_wmax(ctx, W, w_max, st))) return rc;
   So2eArgs a;
   a.src = g->src; a.dst = g->dst; a.rhat_d = reinterpret_cast<const float4*>(rhat_d); a.x = x;
   a.x_bytes = (unsigned)((size_t)g->n_total * (lmax + 1) * (lmax + 1) * E * 4);

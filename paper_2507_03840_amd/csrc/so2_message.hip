@@ -56,11 +56,6 @@ static size_t so2_w_offset(int lmax, int E, int m) {
   return off;
 }
 
-__device__ __forceinline__ void so2_raise_max(unsigned* target, float v) {
-  const unsigned bits = __float_as_uint(v);
-  if (bits > __atomic_load_n(target, __ATOMIC_RELAXED)) atomicMax(target, bits);
-}
-
 // ---------------------------------------------------------------------------------------------- 1. gather
 // FULL: edge_in is the edge embedding tensor [n_edges][(LMAX+1)^2][E]; otherwise it is W_e [E][n_rbf]
 template <int LMAX, bool FULL>
@@ -162,16 +157,26 @@ __global__ __launch_bounds__(256) void so2_gather_kernel(const int* __restrict__
   // it almost never is: atomics on one address run one after the other
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
-  if ((threadIdx.x & 63) == 0) so2_raise_max(a_max, amax);
+  if ((threadIdx.x & 63) == 0) egnn_raise_max(a_max, amax);
 }
 
-// largest magnitude of the weights of all orders (they share one scaling), by integer atomics as above
+// largest magnitude of the weights of all orders (they share one scaling); one atomic per workgroup, as those on one address run
+// one after the other
 __global__ __launch_bounds__(256) void so2_wmax_kernel(const float* __restrict__ W, long n_w, unsigned* __restrict__ w_max) {
+  __shared__ float s_mx[4];
   float mx = 0.0f;
   for (long i = (long)blockIdx.x * 256 + threadIdx.x; i < n_w; i += (long)gridDim.x * 256) mx = fmaxf(mx, fabsf(W[i]));
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-  if ((threadIdx.x & 63) == 0) so2_raise_max(w_max, mx);
+  if ((threadIdx.x & 63) == 0) s_mx[threadIdx.x >> 6] = mx;
+  __syncthreads();
+  if (threadIdx.x == 0) egnn_raise_max(w_max, fmaxf(fmaxf(s_mx[0], s_mx[1]), fmaxf(s_mx[2], s_mx[3])));
+}
+int so2_launch_wmax(egnn_ctx* ctx, const float* W, unsigned* w_max, hipStream_t st) {
+  const long n_w = (long)so2_w_offset(ctx->desc.lmax, ctx->desc.channels, ctx->desc.lmax + 1);
+  hipLaunchKernelGGL(so2_wmax_kernel, dim3((unsigned)std::min<long>((n_w + 255) / 256, 256)), dim3(256), 0, st, W, n_w, w_max);
+  EGNN_LAUNCH_CHECK(ctx, "so2_wmax_kernel");
+  return EGNN_OK;
 }
 
 // The initial edge embedding (Sec. 3 "Initialization"): L = 0 plane = W_e B(d_k), zeros elsewhere.
@@ -576,12 +581,7 @@ static int so2_transform(egnn_ctx* ctx, const egnn_graph* g, const float* pos, c
   }
 #undef GATHER
   EGNN_LAUNCH_CHECK(ctx, "so2_gather_kernel");
-  {
-    const long n_w = (long)so2_w_offset(lmax, E, lmax + 1);
-    const unsigned wg = (unsigned)((n_w + 255) / 256 < 256 ? (n_w + 255) / 256 : 256);
-    hipLaunchKernelGGL(so2_wmax_kernel, dim3(wg), dim3(256), 0, st, W_so2, n_w, call->maxima + 1);
-    EGNN_LAUNCH_CHECK(ctx, "so2_wmax_kernel");
-  }
+  if ((rc = so2_launch_wmax(ctx, W_so2, call->maxima + 1, st))) return rc;
   for (int m = 0; gemms && m <= lmax; ++m) {
     const int K = call->b.K[m], N = call->b.N[m], n_steps = so2_steps(K), n_ct = so2_tiles(N);
     const long total = (long)n_ct * n_steps * 64 * 32;
@@ -896,7 +896,7 @@ __global__ __launch_bounds__(256) void so2_dy_kernel(const int* __restrict__ dst
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off));
-  if ((threadIdx.x & 63) == 0) so2_raise_max(y_max, amax);
+  if ((threadIdx.x & 63) == 0) egnn_raise_max(y_max, amax);
 }
 
 // Adjoint of the attention weights of the node block, one workgroup per destination node j (lane = (edge slot,
@@ -1396,7 +1396,6 @@ static int so2_backward_tail(egnn_ctx* ctx, const egnn_graph* g, const int32_t* 
                              float* dW_so2, float* dT, const float* dT_add, hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels, D = (lmax + 1) * (lmax + 1);
   const long n = g->n_edges;
-  const long n_w = (long)so2_w_offset(lmax, E, lmax + 1);
   int rc;
   const float4* rd = reinterpret_cast<const float4*>(call.rhat_d);
   const int per_wg = 256 / E;
@@ -1408,11 +1407,7 @@ static int so2_backward_tail(egnn_ctx* ctx, const egnn_graph* g, const int32_t* 
   SO2_BY_LMAX(lmax, DY)
 #undef DY
   EGNN_LAUNCH_CHECK(ctx, "so2_dy_kernel");
-  {
-    const unsigned wg = (unsigned)((n_w + 255) / 256 < 256 ? (n_w + 255) / 256 : 256);
-    hipLaunchKernelGGL(so2_wmax_kernel, dim3(wg), dim3(256), 0, st, W_so2, n_w, bmax + 1);
-    EGNN_LAUNCH_CHECK(ctx, "so2_wmax_kernel");
-  }
+  if ((rc = so2_launch_wmax(ctx, W_so2, bmax + 1, st))) return rc;
   for (int m = 0; m <= lmax; ++m) {
     const int K = call.b.K[m], N = call.b.N[m];
     int chunks;

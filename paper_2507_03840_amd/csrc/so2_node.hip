@@ -175,9 +175,9 @@ struct So2nArgs {
 // 51 on the busiest SIMD.
 // S of the node then goes through LDS to be coupled by straight runs of multiply-adds with constants in the code, every
 // wave its own blocks (li, L), lanes = (group, channel).
-// lmax 4, 32 channels, 3,000 nodes, 628,000 edges: 445 us (the per-edge form: gather, five products and scatter, 3.2 ms).  With
-// one part left out: contraction 124 us, coupling 127, harmonics 61; the rest is what one workgroup of 8 waves x 251 registers
-// per compute unit cannot overlap (loads of the node's edges, barriers, starting the next workgroup).  Matrix cores at the
+// lmax 4, 32 channels, 3,000 nodes, 628,000 edges: 430 us (the per-edge form: gather, five products and scatter, 3.2 ms).  With
+// one part left out (of 445, when wave 7 summed the harmonics): contraction 124 us, coupling 127, harmonics 61; the rest is what
+// one workgroup of 8 waves x 250 registers per compute unit cannot overlap (loads of the node's edges, barriers, starting the next workgroup).  Matrix cores at the
 // contraction alone: 92 us.  Coupling on the matrix cores as well, with tables in memory: 630 us (chains of dependent loads);
 // persistent workgroups that request the next node's edges early: 532 us (67 registers spilled).
 // OWN: the rows are the edges' own, fp32 and read once from memory (2 GB: 560 us), cut into pieces on the way to the matrix
@@ -505,7 +505,7 @@ struct So2nSums {
 // One workgroup per node, a quarter of its edges per wave, a lane an edge: the harmonics go from the lane's registers to LDS,
 // half a wavefront's edges at a time (all 64 of two waves would leave room for six waves per compute unit), where they are
 // summed, lane = (L, M), and contracted with the Gaussian basis on the fp32 matrix cores (v_mfma_f32_32x32x2_f32), all in 32
-// bits.  3,000 nodes, 628,000 edges, lmax 4, 32 channels: 57 us, without the basis 22; latency of the node's few edges.
+// bits.  3,000 nodes, 628,000 edges, lmax 4, 32 channels: 46 us, without the basis 22; latency of the node's few edges.
 template <int LMAX>
 __global__ __launch_bounds__(64 * SO2N_SUM_WAVES) void so2n_sums_kernel(So2nSums p) {
   constexpr int D = (LMAX + 1) * (LMAX + 1), NL = 2 * LMAX + 1, NLM = NL * NL;     // (NLM odd: lanes write different banks)
@@ -1027,7 +1027,8 @@ struct So2nWgrad {
 // k0 + 4 r + a.  Degrees with more rows per node get fewer nodes per chunk, so that all waves take about equally long.  The
 // last wave of every column of tiles takes G in the place of T, with G's own scales: whichever of the two is the smaller keeps
 // its accuracy.
-// Bound: T read once (413 MB at 3,000 nodes, lmax 4, 32 channels: 94 us = 4.4 TB/s; per edge it was 2.26 ms).
+// Bound: T read once (403 MB at 3,000 nodes, lmax 4, 32 channels: 105 us = 3.8 TB/s, of which the scales per node and G take 10;
+// per edge it was 2.26 ms).
 __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   const int lane = threadIdx.x & 63, i32 = lane & 31, hh = lane >> 5;
   const int unit = __builtin_amdgcn_readfirstlane((int)(blockIdx.x * 4 + (threadIdx.x >> 6)));
