@@ -15,7 +15,9 @@ def B():
 # edges: fewer than one chunk of 2,048, around two chunks, ragged last chunk, more than 1,024 chunks' worth; nodes: one, more
 # than one round of the scan (8,192); outgoing edges of a node: none, below and above the 1,024 that are sorted in LDS
 @pytest.mark.parametrize("n_edges,n_owned,n_total", [(1, 1, 2), (63, 1, 64), (2047, 30, 40), (2048, 30, 40), (4095, 3, 3), (4097, 50, 50),
-                                                     (70001, 9000, 20000), (2100000, 8193, 16385), (9001, 5, 9)])
+                                                     (70001, 9000, 20000), (2100000, 8193, 16385), (9001, 5, 9),
+                                                     # the parts that a chunk's four waves take: one edge, one short of four parts, ragged
+                                                     (65, 3, 4), (255, 9, 9), (257, 9, 9), (2113, 20, 30), (8450, 300, 300)])
 def test_length_bins_and_transpose(B, n_edges, n_owned, n_total):
     import torch
     rng = np.random.default_rng(n_edges)
