@@ -1,0 +1,568 @@
+// S3 + S4 in one kernel: the radial weights of an (edge, channel) come off the matrix cores into the registers of the lane that
+// uses them; no weight tensor in memory.
+//
+//   a[j] = nbar^-1/2 sum_{k: dst(k)=j} sum_p w_k[p][c] (C_p . h_src(k) . Yhat(rhat_k)),
+//   w_k[p][c] = fc(d_k) alpha_p (W_r2 SiLU(W_r1 B(d_k)))[p*E + c]
+// (Sec. 3 "Message passing"; coupling of Sec. 2.2 / Eq. 1 in the bond frame of Sec. 2.1 / Fig. 2(d)).
+//
+// Through memory, w is the largest object of a layer: at 3,000 atoms, 32 channels and lmax 4 it took 1.7 GB of writes (353 us)
+// and 3.4 GB of reads (640 us).  Here, same case: 520-575 us for the kernel below and 50 us of preparation; 12,000 + 8,000
+// atoms at 64 channels 7.4 -> 4.3 ms.
+//
+// Work: a wavefront takes a destination node and 4 channels and walks the node's edges 16 at a time.  The 16x16x32 tiles have the
+// rows of W_r2 as rows (4 paths x 4 channels) and the 16 edges as columns, so result register r of lane (n, q) is path 4 t + r
+// of edge n and channel 4 group + q: 11 tiles of 6 products give a lane the 42 weights of its (edge, channel), which then runs the
+// bond-frame product as S4 does.  (A tile of 32 edges x 2 channels, 32x32x16, takes fewer LDS reads but leaves more lanes idle
+// at a node's end and more lines per gathered row: 1,180 against 1,058 ns for the arithmetic of 64 lanes.)  The lane keeps
+// its 25 sums until the node ends; then the 16 edges are added.  No atomics, a fixed order.
+//
+// What bounds it: power and issue.  The products (66 x 16 cycles a tile) and the vector work (555 instructions) of the two
+// wavefronts of a SIMD overlap in part; together, without any memory access, they take 347 us at the clock that the chip holds
+// under them (2.3 GHz on zeros, 1.7-1.9 on data).  What the layout is for:
+//   * W_r2 of 4 channels (45 KB at lmax 4) stays on the compute unit: high pieces in registers, low pieces in LDS.  With all of it
+//     in LDS (44 reads of 1 KB a tile and wavefront) LDS and the products took turns.
+//   * Both gathered streams go from memory straight to LDS one tile ahead, four neighbouring lanes per 64 bytes.  As loads to
+//     registers in the products' lane order, neighbouring lanes were different edges, every 16 bytes an access of its own:
+//     728 accesses a tile, and the vector cache, one a cycle, was the limit (1.0 of 1.1 M cycles).
+//   * The hidden activations (256 bytes a row of weights) are read once per group of channels: two groups share an XCD, so
+//     that its L2 serves one of them (misses halve; no difference beyond two).
+#include "egnn_internal.h"
+#include "bond_frame.h"
+#include "half_scales.h"
+#include "edge_fused.h"
+
+typedef _Float16 ef_h8 __attribute__((ext_vector_type(8)));
+typedef float ef_f4 __attribute__((ext_vector_type(4)));
+
+__device__ __forceinline__ uint4 ef_pack8(const float (&x)[8], uint4& lo) {
+  uint32_t h[8], l[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const _Float16 a = (_Float16)x[i];
+    const _Float16 b = (_Float16)(x[i] - (float)a);
+    h[i] = __builtin_bit_cast(unsigned short, a);
+    l[i] = __builtin_bit_cast(unsigned short, b);
+  }
+  lo = make_uint4(l[0] | (l[1] << 16), l[2] | (l[3] << 16), l[4] | (l[5] << 16), l[6] | (l[7] << 16));
+  return make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
+}
+
+// First preparation.  Per edge the rotation into its frame (cos p, sin p, cos t, sin t of the azimuth and polar angle), per row
+// of radial weights the length; the last HS_BLOCKS workgroups take the parts of the operands' scalings.
+struct EfFirst {
+  const int* src;
+  const int* dst;
+  const int8_t* shift;
+  const float* pos;
+  const int* w_row;
+  const float* W_r1;
+  const float* W_r2;
+  float4* frame;
+  float* length;
+  float* scales;
+  double bx, by, bz;
+  long n_edges;
+  int n_rbf, PE, log2E;
+  PathAlpha alpha;
+};
+__global__ __launch_bounds__(256) void ef_first_kernel(EfFirst g) {
+  const int part = (int)blockIdx.x - ((int)gridDim.x - HS_BLOCKS);
+  if (part >= 0) {
+    half_scales_part(part, g.W_r1, g.W_r2, g.n_rbf, g.PE, g.log2E, g.alpha, g.scales);
+    return;
+  }
+  const long k = (long)blockIdx.x * 256 + threadIdx.x;
+  if (k >= g.n_edges) return;
+  const int i = g.src[k], j = g.dst[k];
+  double dx = (double)g.pos[3 * i + 0] - (double)g.pos[3 * j + 0];
+  double dy = (double)g.pos[3 * i + 1] - (double)g.pos[3 * j + 1];
+  double dz = (double)g.pos[3 * i + 2] - (double)g.pos[3 * j + 2];
+  if (g.shift) {
+    dx += (double)g.shift[3 * k + 0] * g.bx;
+    dy += (double)g.shift[3 * k + 1] * g.by;
+    dz += (double)g.shift[3 * k + 2] * g.bz;
+  }
+  const double rho2 = dx * dx + dy * dy, d = sqrt(rho2 + dz * dz);
+  const double inv = 1.0 / d, rho = sqrt(rho2);
+  const bool polar = rho <= 1e-15 * d;                  // (the azimuth is free there)
+  const double irho = polar ? 0.0 : 1.0 / rho;
+  g.frame[k] = make_float4(polar ? 1.0f : (float)(dx * irho), (float)(dy * irho), (float)(dz * inv), (float)(rho * inv));
+  const int r = g.w_row ? g.w_row[k] : (int)k;
+  if (r >= 0) g.length[r] = (float)d;
+}
+
+// Second preparation: both operands of the radial contraction, scaled and cut into two half-precision pieces.  The contraction
+// runs over the 64 hidden units in two steps of 32; slot (step, q, i) of it, i = 0 .. 7, is unit 32 step + 16 (i / 4) + 4 q + i % 4:
+// the order in which the lanes (row n, q) of the fp32 products with W_r1 hold their results.
+//   rec  [row][step][piece][q] of 16 bytes: hidden activations of a row times the cutoff envelope
+//   A    [group of 4 channels][tile of 4 paths][step][piece][lane] of 16 bytes: alpha W_r2; lane (m, q) holds path
+//        4 tile + m % 4, channel 4 group + m / 4
+// A wavefront takes 16 rows at a time: four Gaussians a lane and step of four, 16 units a lane from 16x16x4 fp32 products (one
+// thread per octet of units with all Gaussians each took 42 us for 313,500 rows).  The last workgroups write A.
+struct EfSecond {
+  const float* length;
+  const float* W_r1;
+  const float* W_r2;
+  const float* scales;
+  uint4* rec;
+  uint4* A;
+  long n_rows;
+  int n_rbf, P, NT, log2E, row_blocks;
+  float r_cut;
+  PathAlpha alpha;
+};
+__device__ __forceinline__ int ef_unit(int step, int q, int i) { return 32 * step + 16 * (i >> 2) + 4 * q + (i & 3); }
+
+__global__ __launch_bounds__(256) void ef_second_kernel(EfSecond g) {
+  float s_w, s_g, inv;
+  half_scales_of(g.scales, s_w, s_g, inv);
+  const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
+  const int ab = (int)blockIdx.x - g.row_blocks;
+  if (ab >= 0) {
+    const int idx = ab * 256 + threadIdx.x;      // [group][tile][step][lane]
+    const int ks = (idx >> 6) & 1, tile = (idx >> 7) % g.NT, cg = (idx >> 7) / g.NT;
+    if (cg >= (1 << g.log2E) / 4) return;
+    const int p = 4 * tile + (n & 3), c = 4 * cg + (n >> 2);
+    const float f = p < g.P ? g.alpha.a[p] * s_w : 0.0f;
+    const float* W = g.W_r2 + ((size_t)((p < g.P ? p : 0) << g.log2E) + c) * EGNN_HIDDEN;
+    float x[8];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) x[i] = p < g.P ? f * W[ef_unit(ks, q, i)] : 0.0f;
+    uint4 lo;
+    const uint4 hi = ef_pack8(x, lo);
+    uint4* out = g.A + ((size_t)(cg * g.NT + tile) * 2 + ks) * 128 + lane;
+    out[0] = hi;
+    out[64] = lo;
+    return;
+  }
+  const int steps = (g.n_rbf + 3) >> 2;                  // 1 .. 8 products of four Gaussians
+  float W[4][8];
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) W[t][s] = s < steps && 4 * s + q < g.n_rbf ? g.W_r1[(16 * t + n) * g.n_rbf + 4 * s + q] : 0.0f;
+  const float step_r = g.r_cut / (float)(g.n_rbf - 1);
+  const float inv2s2 = 0.5f / (step_r * step_r);
+  const long wave = (long)blockIdx.x * 4 + (threadIdx.x >> 6), n_waves = (long)g.row_blocks * 4;
+  for (long r0 = wave * 16; r0 < g.n_rows; r0 += n_waves * 16) {
+    const long row = r0 + n < g.n_rows ? r0 + n : g.n_rows - 1;
+    const float d = g.length[row];
+    ef_f4 pre[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) pre[t] = ef_f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      if (s < steps) {
+        const float u = d - (float)(4 * s + q) * step_r;
+        const float B = __expf(-u * u * inv2s2);         // (past the last Gaussian: its weights are zero)
+#pragma unroll
+        for (int t = 0; t < 4; ++t) pre[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[t][s], B, pre[t], 0, 0, 0);
+      }
+    const float fc = s_g * egnn_envelope(d, g.r_cut);
+    uint4* out = g.rec + row * 16 + q;
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      float x[8];
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const float y = pre[2 * ks + (i >> 2)][i & 3];
+        x[i] = fc * y / (1.0f + __expf(-y));
+      }
+      uint4 lo;
+      const uint4 hi = ef_pack8(x, lo);
+      if (r0 + n < g.n_rows) {
+        out[ks * 8] = hi;
+        out[ks * 8 + 4] = lo;
+      }
+    }
+  }
+}
+
+template <int CTRL>
+__device__ __forceinline__ float ef_dpp(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
+}
+
+// The compiler does not know which LDS words a load from memory to LDS writes, nor when: both waits are spelled out, and the
+// fences (no instructions at this scope) keep the LDS reads on their side of them.
+__device__ __forceinline__ void ef_wait_arrived() {         // the loads to LDS issued so far have arrived
+  __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0)
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+}
+__device__ __forceinline__ void ef_wait_read() {            // the LDS reads issued so far have returned
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_s_waitcnt(0xC07F);                       // lgkmcnt(0)
+}
+
+
+// Sums of N values over the 16 lanes of a row, shared out among them: each of the four steps adds a lane's partner's part and
+// keeps one half of the values (3 instructions for each that is kept, against one per value and step of a full sum, and the
+// results lie in the lanes that store them).  Lane n ends with values ef_slot(n) .. of x[0 ..].
+template <int N> struct EfHalves {
+  static constexpr int H1 = (N + 1) / 2, H2 = (H1 + 1) / 2, H3 = (H2 + 1) / 2, H4 = (H3 + 1) / 2;
+};
+template <int N, int H, int CTRL>
+__device__ __forceinline__ void ef_halve(float* x, bool upper) {
+#pragma unroll
+  for (int i = 0; i < H; ++i) {
+    const float lo = x[i], hi = i + H < N ? x[i + H] : 0.0f;
+    const float keep = upper ? hi : lo, give = upper ? lo : hi;
+    x[i] = keep + ef_dpp<CTRL>(give);
+  }
+}
+template <int N>
+__device__ __forceinline__ void ef_sum16(float* x, int n) {
+  using S = EfHalves<N>;
+  ef_halve<N, S::H1, 0x140>(x, n & 8);          // lane 15 - n
+  ef_halve<S::H1, S::H2, 0x141>(x, n & 4);      // lane 7 - n of the eight
+  ef_halve<S::H2, S::H3, 0x4E>(x, n & 2);       // lane ^ 2
+  ef_halve<S::H3, S::H4, 0xB1>(x, n & 1);       // lane ^ 1
+}
+// index of value r of lane n, or -1
+template <int N>
+__device__ __forceinline__ int ef_slot(int n, int r) {
+  using S = EfHalves<N>;
+  const int i4 = r + ((n & 1) ? S::H4 : 0), i3 = i4 + ((n & 2) ? S::H3 : 0), i2 = i3 + ((n & 4) ? S::H2 : 0),
+            i1 = i2 + ((n & 8) ? S::H1 : 0);
+  return i4 < S::H3 && i3 < S::H2 && i2 < S::H1 && i1 < N ? i1 : -1;
+}
+
+template <int LMAX, bool HALF, bool SHARED>
+__global__ __launch_bounds__(256, EF_WG_PER_CU) void ef_layer_kernel(
+    const int* __restrict__ row_ptr, const int* __restrict__ src, const int* __restrict__ w_row,
+    const float4* __restrict__ frame, const uint4* __restrict__ rec, const uint4* __restrict__ A,
+    const float4* __restrict__ h4, const float* __restrict__ scales, float* __restrict__ a, int n_owned, int n_edges,
+    int log2E, int parts, float scale) {
+  using Mid = typename LayerMid<LMAX>::T;
+  constexpr int D = (LMAX + 1) * (LMAX + 1), P = Mid::P, NT = (P + 3) / 4, NQ = (D + 3) / 4;
+  __shared__ uint4 sLo[NT * 2 * 64];         // low pieces of W_r2
+  __shared__ uint4 sRec[4][4 * 64];          // per wavefront: the operand of its next tile
+  __shared__ uint4 sH[4][NQ * 64];           //                and the features
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int G = 1 << (log2E - 2);
+  // channel group and part of the nodes, see the launch
+  const int xcd = blockIdx.x & 7, i_x = blockIdx.x >> 3;
+  const int per = min(G, EF_CGX), sets = G / per;         // groups that share an XCD, sets of them
+  int cg, part;
+  if (sets >= 8) {
+    const int turns = sets >> 3;
+    cg = (xcd + 8 * ((i_x / per) % turns)) * per + i_x % per;
+    part = i_x / (per * turns);
+  } else {
+    cg = (xcd % sets) * per + i_x % per;
+    part = (i_x / per) * (8 / sets) + xcd / sets;
+  }
+  const uint4* Ag = A + (size_t)cg * NT * 256;
+  for (int i = tid; i < NT * 2 * 64; i += 256) sLo[i] = Ag[(i >> 6) * 128 + 64 + (i & 63)];
+  uint4 ah[NT][2];                           // high pieces
+#pragma unroll
+  for (int t = 0; t < NT; ++t)
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) ah[t][ks] = Ag[(t * 2 + ks) * 128 + lane];
+  float s_w, s_g, unscale;
+  half_scales_of(scales, s_w, s_g, unscale);
+  // the scalings of the operands are undone half before and half after the product (a whole power of two each)
+  const int ex = ilogbf(unscale), exh = ex / 2;
+  const float f = HALF ? 1.0f : ldexpf(1.0f, exh);
+  const float fin = HALF ? scale : scale * ldexpf(1.0f, ex - 2 * exh);
+  __syncthreads();
+
+  const int n = lane & 15, q = lane >> 4;
+  const int stride = parts * 4;
+  int j = part * 4 + wave;
+  if (j >= n_owned) return;
+  const int last = n_edges - 1;
+  float acc[D];
+#pragma unroll
+  for (int i = 0; i < D; ++i) acc[i] = 0.0f;
+
+  // Tiles of 16 edges, three of them under way: tile 0 is worked on, the operand and the features of tile 1 are being
+  // loaded, so are the indices of tile 2.  (k, k1): first edge of a tile and end of its node's edges; (kb, kb1): edges of the
+  // node that follows tile 2's node.
+  int k0 = row_ptr[j], k0_1 = row_ptr[j + 1], k1, k1_1, k2, k2_1, jn = j, kb, kb1;
+  auto fetch_node = [&]() {
+    jn += stride;
+    const int jj = min(jn, n_owned - 1);
+    kb = row_ptr[jj];
+    kb1 = row_ptr[jj + 1];
+  };
+  auto advance = [&](int k, int k_1, int& kn, int& kn_1) {
+    if (k + 16 >= k_1) {
+      kn = kb;
+      kn_1 = kb1;
+      fetch_node();
+    } else {
+      kn = k + 16;
+      kn_1 = k_1;
+    }
+  };
+  fetch_node();
+  advance(k0, k0_1, k1, k1_1);
+  advance(k1, k1_1, k2, k2_1);
+
+  // Memory to LDS: four neighbouring lanes bring the 64 bytes that the four channels (octets of units) of one edge need, so that
+  // a request is a whole one; lane (q, n) then reads piece q of edge n.  The order of the four inside an edge is turned by
+  // the edge's quad, which spreads the reads over the banks.
+  const int e4 = lane >> 2, p4 = (lane & 3) ^ (lane >> 4), at4 = 4 * n + (q ^ (n >> 2));
+  uint4* const myRec = sRec[wave];
+  uint4* const myH = sH[wave];
+  auto load_rec = [&](int raw) {
+    const uint4* p = rec + (size_t)(SHARED && raw < 0 ? ~raw : raw) * 16 + p4;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p + 4 * i),
+                                       (__attribute__((address_space(3))) void*)(myRec + 64 * i), 16, 0, 0);
+  };
+  auto load_h = [&](int s) {
+    const float4* p = h4 + ((size_t)s * G + cg) * (NQ * 4) + p4;
+#pragma unroll
+    for (int i = 0; i < NQ; ++i)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(p + 4 * i),
+                                       (__attribute__((address_space(3))) void*)(myH + 64 * i), 16, 0, 0);
+  };
+  float4 fr;
+  int s1, r1;
+  {
+    const int kk = min(k0 + e4, last);
+    const int kk1 = min(k1 + e4, last);
+    const int s = src[kk], r = SHARED ? w_row[kk] : kk;
+    s1 = src[kk1];
+    r1 = SHARED ? w_row[kk1] : kk1;
+    fr = frame[min(k0 + n, last)];
+    load_rec(r);
+    load_h(s);
+  }
+  // The sums of a finished node are stored early in the next tile: a store in flight would hold up that tile's wait for its
+  // operands.
+  constexpr int H4 = EfHalves<D>::H4;
+  float done[H4];
+  int j_done = -1;
+  auto store_node = [&]() {
+    float* out = a + (((size_t)j_done * D) << log2E) + 4 * cg + q;
+#pragma unroll
+    for (int i = 0; i < H4; ++i) {
+      const int at = ef_slot<D>(n, i);
+      if (at >= 0) out[(size_t)at << log2E] = done[i];
+    }
+    j_done = -1;
+  };
+  while (true) {
+    const bool node_done = k0 + 16 >= k0_1;
+    ef_wait_arrived();
+    uint4 b[2][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) b[i >> 1][i & 1] = myRec[64 * i + at4];
+    float v[NQ * 4], o[D];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+      const uint4 x = myH[64 * i + at4];
+      v[4 * i] = __uint_as_float(x.x); v[4 * i + 1] = __uint_as_float(x.y);
+      v[4 * i + 2] = __uint_as_float(x.z); v[4 * i + 3] = __uint_as_float(x.w);
+    }
+    const int kk2 = min(k2 + e4, last);
+    const int s2 = src[kk2];
+    const int r2 = SHARED ? w_row[kk2] : kk2;
+    const float4 frn = frame[min(k1 + n, last)];
+    ef_wait_read();                  // (before the next ones may arrive)
+    if (j_done >= 0) store_node();
+    load_rec(r1);
+    load_h(s1);
+    __builtin_amdgcn_sched_barrier(0);
+
+    int at = lane;
+    asm volatile("" : "+v"(at));     // (the operand stays in LDS: read ahead of the loop it would not fit the registers)
+    ef_f4 c[NT];
+#pragma unroll
+    for (int t = 0; t < NT; ++t) c[t] = ef_f4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) {
+      const ef_h8 bh = __builtin_bit_cast(ef_h8, b[ks][0]), bl = __builtin_bit_cast(ef_h8, b[ks][1]);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, ah[t][ks]), bl, c[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, sLo[(t * 2 + ks) * 64 + at]), bh, c[t], 0, 0, 0);
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, ah[t][ks]), bh, c[t], 0, 0, 0);
+    }
+    float w[NT * 4];
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) w[4 * t + r] = HALF ? (float)(_Float16)(c[t][r] * unscale) : c[t][r];
+    __builtin_amdgcn_sched_barrier(0);
+
+    BondTrig t;
+    t.cp[0] = 1.0f; t.sp[0] = 0.0f; t.ct[0] = 1.0f; t.st[0] = 0.0f;
+    t.cp[1] = fr.x; t.sp[1] = fr.y; t.ct[1] = fr.z; t.st[1] = fr.w;
+#pragma unroll
+    for (int m = 2; m <= LMAX; ++m) {
+      t.cp[m] = t.cp[m - 1] * fr.x - t.sp[m - 1] * fr.y;
+      t.sp[m] = t.sp[m - 1] * fr.x + t.cp[m - 1] * fr.y;
+      t.ct[m] = t.ct[m - 1] * fr.z - t.st[m - 1] * fr.w;
+      t.st[m] = t.st[m - 1] * fr.z + t.ct[m - 1] * fr.w;
+    }
+    if (!HALF) {
+#pragma unroll
+      for (int m = 1; m <= LMAX; ++m) { t.cp[m] *= f; t.sp[m] *= f; }
+#pragma unroll
+      for (int l = 0; l <= LMAX; ++l) v[l * l + l] *= f;
+    }
+    egnn_to_bond_frame<LMAX>(v, t);
+    Mid::run(v, w, o);
+    egnn_from_bond_frame<LMAX>(o, t);
+    if (!HALF) {
+#pragma unroll
+      for (int l = 0; l <= LMAX; ++l) o[l * l + l] *= f;
+    }
+    if (node_done) {      // (lanes past the node's last edge hold other edges: left out)
+      const bool valid = k0 + n < k0_1;
+#pragma unroll
+      for (int i = 0; i < D; ++i) acc[i] += valid ? o[i] : 0.0f;
+      ef_sum16<D>(acc, n);
+#pragma unroll
+      for (int i = 0; i < H4; ++i) done[i] = fin * acc[i];
+      j_done = j;
+#pragma unroll
+      for (int i = 0; i < D; ++i) acc[i] = 0.0f;
+      j += stride;
+      if (j >= n_owned) break;
+    } else {
+#pragma unroll
+      for (int i = 0; i < D; ++i) acc[i] += o[i];
+    }
+    k0 = k1; k0_1 = k1_1; k1 = k2; k1_1 = k2_1;
+    advance(k1, k1_1, k2, k2_1);
+    fr = frn;
+    s1 = s2;
+    r1 = r2;
+  }
+  ef_wait_arrived();                 // (nothing is on its way to LDS when the workgroup gives it back)
+  store_node();
+}
+
+static size_t ef_align(size_t b) { return (b + 255) & ~(size_t)255; }
+
+// scratch: scales and their parts (256 bytes), A, frames, lengths, records, h in groups of four channels
+struct EfScratch {
+  float* scales;
+  uint4* A;
+  float4* frame;
+  float* length;
+  uint4* rec;
+  float* h4;
+  size_t bytes;
+};
+static int ef_tiles(const egnn_ctx* ctx) { return (ctx->n_paths[0] + 3) / 4; }
+static int ef_quads(const egnn_ctx* ctx) { return ((ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) + 3) / 4; }
+static EfScratch ef_carve(const egnn_ctx* ctx, const egnn_graph* g, void* base) {
+  const size_t G = ctx->desc.channels / 4, n_rows = g->n_edges;
+  const size_t a = 256, f = a + ef_align(G * ef_tiles(ctx) * 256 * sizeof(uint4)), l = f + ef_align((size_t)g->n_edges * 16),
+               r = l + ef_align(n_rows * 4), h = r + ef_align(n_rows * 256),
+               end = h + ef_align((size_t)g->n_total * G * ef_quads(ctx) * 64);
+  char* p = (char*)base;
+  return {reinterpret_cast<float*>(p), reinterpret_cast<uint4*>(p + a), reinterpret_cast<float4*>(p + f),
+          reinterpret_cast<float*>(p + l), reinterpret_cast<uint4*>(p + r), reinterpret_cast<float*>(p + h), end};
+}
+
+// Where this kernel is the faster one, measured on 48 .. 3,000 atoms of 21 .. 209 edges, whole layers against the two kernels: 1.1 to
+// 2.5 times from lmax 2 on; at lmax 1 0.99 to 1.7 times at 32 and 64 channels, 0.89 to 1.7 at 128; at lmax 0, where one path takes a
+// tile of four, 0.58 to 1.0 for 37,000 edges and more.
+// The scratch is the room of a weight tensor in memory, which is not needed then; whether it is large enough is asked for one row
+// per edge, so that a graph with shared rows goes the same way as one without (lmax 1: from 32 channels on).
+bool egnn_edge_fused_fits(const egnn_ctx* ctx, const egnn_graph* g) {
+  const int lmax = ctx->desc.lmax;
+  return (lmax >= 2 || (lmax == 1 && ctx->desc.channels <= 64)) && g->n_edges > 0 && g->n_owned > 0 &&
+         ef_carve(ctx, g, nullptr).bytes <= (size_t)g->n_edges * ctx->n_paths[0] * ctx->desc.channels * sizeof(float);
+}
+
+static PathAlpha ef_alpha(const egnn_ctx* ctx) {
+  PathAlpha al;
+  for (int p = 0; p < EGNN_MAX_PATHS; ++p) al.a[p] = p < ctx->n_paths[0] ? ctx->alpha[0][p] : 0.0f;
+  return al;
+}
+
+int egnn_launch_edge_fused_first(egnn_ctx* ctx, const egnn_graph* g, const float* pos, const float box[3], const float* W_r1,
+                                 const float* W_r2, void* scratch, hipStream_t stream) {
+  const EfScratch s = ef_carve(ctx, g, scratch);
+  const EfFirst x = {g->src, g->dst, g->shift, pos, g->w_row, W_r1, W_r2, s.frame, s.length, s.scales,
+                     (double)box[0], (double)box[1], (double)box[2], (long)g->n_edges, ctx->desc.n_rbf,
+                     ctx->n_paths[0] * ctx->desc.channels, ctx->log2_channels, ef_alpha(ctx)};
+  hipLaunchKernelGGL(ef_first_kernel, dim3((unsigned)((g->n_edges + 255) / 256 + HS_BLOCKS)), dim3(256), 0, stream, x);
+  EGNN_LAUNCH_CHECK(ctx, "ef_first_kernel");
+  return EGNN_OK;
+}
+
+int egnn_launch_edge_fused_second(egnn_ctx* ctx, const egnn_graph* g, const float* W_r1, const float* W_r2, void* scratch,
+                                  hipStream_t stream) {
+  const EfScratch s = ef_carve(ctx, g, scratch);
+  const long n_rows = g->w_row ? g->n_w_rows : g->n_edges;
+  const int NT = ef_tiles(ctx), a_blocks = (ctx->desc.channels / 4 * NT * 128 + 255) / 256;
+  const long groups = (n_rows + 63) / 64;                // of four wavefronts
+  const int row_blocks = (int)(groups < 4 * EGNN_CUS ? groups : 4 * EGNN_CUS);
+  const EfSecond x = {s.length, W_r1, W_r2, s.scales, s.rec, s.A, n_rows, ctx->desc.n_rbf, ctx->n_paths[0], NT,
+                      ctx->log2_channels, row_blocks, ctx->desc.r_cut, ef_alpha(ctx)};
+  hipLaunchKernelGGL(ef_second_kernel, dim3((unsigned)(row_blocks + a_blocks)), dim3(256), 0, stream, x);
+  EGNN_LAUNCH_CHECK(ctx, "ef_second_kernel");
+  return EGNN_OK;
+}
+
+int egnn_launch_edge_fused_features(egnn_ctx* ctx, const egnn_graph* g, const float* x_in, const float* W_pre, void* scratch,
+                                    hipStream_t stream) {
+  return egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, ef_carve(ctx, g, scratch).h4, g->n_total, stream, 0,
+                              ef_quads(ctx));
+}
+
+int egnn_launch_edge_fused_sum(egnn_ctx* ctx, const egnn_graph* g, void* scratch, float* a, bool half, hipStream_t stream) {
+  const EfScratch s = ef_carve(ctx, g, scratch);
+  const int G = ctx->desc.channels / 4;
+  const float4* h4 = reinterpret_cast<const float4*>(s.h4);
+  const float* scales = s.scales;
+  const float scale = 1.0f / sqrtf(ctx->desc.agg_norm);
+  // Workgroups: EF_WG_PER_CU on every compute unit, fewer where there are not that many nodes for their wavefronts.  EF_CGX channel
+  // groups share an XCD; the sets of them are dealt to the XCDs, and where there are fewer than eight sets, so are the nodes.
+  const int per = G < EF_CGX ? G : EF_CGX, sets = G / per;
+  const int turns = sets >= 8 ? sets / 8 : 1;
+  const int mult = per * turns;                              // workgroups of an XCD that make up one part
+  const int parts_per = sets >= 8 ? 1 : 8 / sets;            // parts that the eight XCDs bring at a time
+  int i_max = (EGNN_CUS / 8) * EF_WG_PER_CU / mult;
+  const int need = (g->n_owned + 3) / 4;                     // parts that still have a node for every wavefront
+  const int i_need = (need + parts_per - 1) / parts_per;
+  if (i_max < 1) i_max = 1;
+  if (i_max > i_need) i_max = i_need;
+  const int parts = i_max * parts_per;
+  const dim3 grid(8 * i_max * mult), block(256);
+#define KERNEL(L, H, S)                                                                                                   \
+  hipLaunchKernelGGL((ef_layer_kernel<L, H, S>), grid, block, 0, stream, g->row_ptr, g->src, g->w_row,                      \
+                     s.frame, s.rec, s.A, h4, scales, a, \
+                     g->n_owned, (int)g->n_edges, ctx->log2_channels,     \
+                     parts, scale)
+#define LAUNCH(L)                                       \
+  case L:                                               \
+    if (half && g->w_row) KERNEL(L, true, true);        \
+    else if (half) KERNEL(L, true, false);              \
+    else if (g->w_row) KERNEL(L, false, true);          \
+    else KERNEL(L, false, false);                       \
+    break;
+  switch (ctx->desc.lmax) {
+    LAUNCH(1) LAUNCH(2) LAUNCH(3) LAUNCH(4)
+    default: return egnn_fail(ctx, EGNN_EINVAL, "edge_fused: lmax out of range");
+  }
+#undef LAUNCH
+#undef KERNEL
+  EGNN_LAUNCH_CHECK(ctx, "ef_layer_kernel");
+  return EGNN_OK;
+}
+
+int egnn_launch_edge_fused(egnn_ctx* ctx, const egnn_graph* g, const float* pos, const float box[3], const float* x_in,
+                           const float* W_pre, const float* W_r1, const float* W_r2, void* scratch, float* a,
+                           hipStream_t stream) {
+  int rc = egnn_launch_edge_fused_first(ctx, g, pos, box, W_r1, W_r2, scratch, stream);
+  if (!rc) rc = egnn_launch_edge_fused_second(ctx, g, W_r1, W_r2, scratch, stream);
+  if (!rc) rc = egnn_launch_edge_fused_features(ctx, g, x_in, W_pre, scratch, stream);
+  return rc ? rc : egnn_launch_edge_fused_sum(ctx, g, scratch, a, false, stream);
+}

@@ -3,6 +3,7 @@
 #include <string.h>
 #include "egnn_internal.h"
 #include "w_half.h"
+#include "edge_fused.h"
 #define EGNN_GEN_HOST_TABLES
 #include "egnn_gen.inc"
 
@@ -380,6 +381,7 @@ static int layer_forward_impl(egnn_ctx* ctx, const egnn_graph* g, const float* p
   const size_t w_bytes = with_w ? layer_w_bytes(ctx, g->n_edges, g->n_total) : 0;
   float* w = with_w ? (float*)c.take(w_bytes) : nullptr;
   const bool saving = w_save || a_save;
+  float* const scratch = w;
   if (w_save && with_w) w = w_save;
   if (a_save) a = a_save;
   void* w2s = with_w ? c.take(egnn_radial_ws_bytes(ctx, 0)) : nullptr;
@@ -387,9 +389,24 @@ static int layer_forward_impl(egnn_ctx* ctx, const egnn_graph* g, const float* p
   const bool shared = with_w && g->w_row != nullptr;
   float* rd_rows = shared ? (float*)c.take((size_t)g->n_edges * 16) : nullptr;
   StageTimer tm(ctx, st, 0);
+  // Default: S3 and S4 in one kernel, where that is the faster way
+  const bool in_one = with_w && (saving || ctx->use_fused == 0) && egnn_edge_fused_fits(ctx, g);
+  if (in_one && !saving) {
+    if ((rc = egnn_launch_edge_fused_first(ctx, g, pos, box, W_r1, W_r2, w, st))) return rc;
+    tm.mark(0);
+    if ((rc = egnn_launch_edge_fused_second(ctx, g, W_r1, W_r2, w, st))) return rc;
+    tm.mark(1);
+    if ((rc = egnn_launch_edge_fused_features(ctx, g, x_in, W_pre, w, st))) return rc;
+    tm.mark(2);
+    if ((rc = egnn_launch_edge_fused_sum(ctx, g, w, a, ctx->w_half, st))) return rc;
+    tm.mark(3);
+    rc = egnn_launch_node_mix(ctx, a, W_post, x_in, W_self, x_out, g->n_owned, st);
+    tm.mark(4);
+    return rc;
+  }
   if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st, rd_rows))) return rc;
   tm.mark(0);
-  // Default: S3 writes the weight tensor, S4 reads it.  Opt-in (EGNN_OPT_FUSED): the weights are produced and
+  // Else S3 writes the weight tensor, S4 reads it.  Opt-in (EGNN_OPT_FUSED): the weights are produced and
   // consumed inside one kernel and never leave the chip.
   // (the scratch of the fused route lives where the weight tensor would be)
   const bool fused_lane = with_w && !saving && ctx->use_fused == 2 && egnn_fused_lane_supported(ctx);
@@ -403,9 +420,13 @@ static int layer_forward_impl(egnn_ctx* ctx, const egnn_graph* g, const float* p
       return rc;
   }
   tm.mark(1);
-  if ((rc = egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, h, g->n_total, st))) return rc;
+  if (!in_one && (rc = egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, h, g->n_total, st))) return rc;
   tm.mark(2);
-  if (fused_lane) {
+  if (in_one) {
+    // (saving: the sums are those of the call that does not save, to the bit; the weight tensor is for the reverse pass.  Measured at
+    // 3,000 atoms: no slower than S4 with its reads of that tensor)
+    if ((rc = egnn_launch_edge_fused(ctx, g, pos, box, x_in, W_pre, W_r1, W_r2, scratch, a, st))) return rc;
+  } else if (fused_lane) {
     if ((rc = egnn_launch_layer_fused_lane(ctx, g, rhat_d, h, W_r1, W_r2, w, w_bytes, a, st))) return rc;
   } else if (fused) {
     if ((rc = egnn_launch_layer_fused(ctx, g, rhat_d, h, W_r1, w2s, w, w_bytes, a, st))) return rc;

@@ -3,6 +3,7 @@
 // 3.4 GB per layer at 3,000 atoms; Sec. 3 "Implementation" quotes 115 GB of saved activations for that size).
 #include <math.h>
 #include "egnn_internal.h"
+#include "edge_fused.h"
 
 static size_t a256(size_t n) { return (n + 255) & ~(size_t)255; }
 
@@ -145,7 +146,11 @@ static int layer_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32_t
                                            W_r2, b.w, b.w2s, st)))
     return rc;
   if ((rc = egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, b.h, n_t, st))) return rc;
-  if (!a_saved && (rc = egnn_launch_tp_segsum(ctx, g, b.rhat_d, b.h, w, b.a, st, false, shared))) return rc;
+  // (the sums as the forward call takes them, to the bit; the room of dw is free until then)
+  if (!a_saved && (rc = egnn_edge_fused_fits(ctx, g)
+                            ? egnn_launch_edge_fused(ctx, g, pos, box, x_in, W_pre, W_r1, W_r2, b.dw, b.a, st)
+                            : egnn_launch_tp_segsum(ctx, g, b.rhat_d, b.h, w, b.a, st, false, shared)))
+    return rc;
   tm.mark(0);
   // x_out = W_post a + W_self x_in[:n_owned]
   if ((rc = egnn_launch_node_mix(ctx, dx_out, W_post, nullptr, nullptr, b.da, n_o, st, 1))) return rc;

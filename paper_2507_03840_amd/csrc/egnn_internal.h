@@ -101,8 +101,9 @@ __device__ __forceinline__ void egnn_raise_max(unsigned* target, float v) {
   } while (0)
 
 // stage launchers (one per translation unit)
+// group_quads > 0: y in the layout of groups of four channels (node_mix.hip) instead of [node][(l,m)][channel]
 int egnn_launch_node_mix(egnn_ctx*, const float* x1, const float* W1, const float* x2, const float* W2,
-                         float* y, int n_nodes, hipStream_t, int transpose = 0);
+                         float* y, int n_nodes, hipStream_t, int transpose = 0, int group_quads = 0);
 int egnn_launch_mix_wgrad(egnn_ctx*, const float* dy, const float* x, float* dW, float* partial, int n_nodes,
                           hipStream_t);
 size_t egnn_mix_wgrad_ws_bytes(const egnn_ctx*);

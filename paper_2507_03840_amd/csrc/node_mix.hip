@@ -10,10 +10,17 @@
 #define MIX_RPT 4      // rows per thread
 #define MIX_TILES 8    // row tiles per workgroup at most (fewer on small inputs, to have enough workgroups in flight)
 
+// Where the mix puts (node, row (l,m), channel): [node][row][channel], or, for a kernel that works on four channels of a node
+// at a time, [node][group of 4 channels][quad of rows (group_quads of them)][channel][row of the quad].
+__device__ __forceinline__ size_t mix_out(long node, int row, int c, int D, int log2E, int group_quads) {
+  if (!group_quads) return (((size_t)node * D + row) << log2E) + c;
+  return ((((size_t)node << (log2E - 2)) + (c >> 2)) * group_quads + (row >> 2)) * 16 + (c & 3) * 4 + (row & 3);
+}
+
 __global__ __launch_bounds__(256) void node_mix_kernel(const float* __restrict__ x1, const float* __restrict__ W1,
                                                        const float* __restrict__ x2, const float* __restrict__ W2,
                                                        float* __restrict__ y, int n_nodes, int lmax, int log2E,
-                                                       int transpose, int tiles) {
+                                                       int transpose, int tiles, int group_quads) {
   extern __shared__ float smem[];
   const int E = 1 << log2E;
   const int l = blockIdx.y;
@@ -73,7 +80,7 @@ __global__ __launch_bounds__(256) void node_mix_kernel(const float* __restrict__
       if (r < n_rows) {
         const long node = r / nm;
         const int mm = (int)(r - node * nm);
-        y[(((size_t)node * D + l * l + mm) << log2E) + c] = acc[q];
+        y[mix_out(node, l * l + mm, c, D, log2E, group_quads)] = acc[q];
       }
     }
   }
@@ -90,7 +97,7 @@ template <int LOG2E>
 __global__ __launch_bounds__(256) void node_mix_mfma_kernel(const float* __restrict__ x1, const float* __restrict__ W1,
                                                             const float* __restrict__ x2, const float* __restrict__ W2,
                                                             float* __restrict__ y, int n_nodes, int lmax, int transpose,
-                                                            int tiles) {
+                                                            int tiles, int group_quads) {
   constexpr int E = 1 << LOG2E, KH = E / 2, NCB = E / 32;
   extern __shared__ float smem[];   // [n_in][c'][c]
   const int l = blockIdx.y;
@@ -159,9 +166,10 @@ __global__ __launch_bounds__(256) void node_mix_mfma_kernel(const float* __restr
       const long ro = r0 + 8 * (i >> 2) + 4 * hh + (i & 3);
       if (ro < n_rows) {
         const long no = ro / nm;
-        float* out = y + (((size_t)no * D + l * l + (int)(ro - no * nm)) << LOG2E) + m;
+        float* out = y + mix_out(no, l * l + (int)(ro - no * nm), m, D, LOG2E, group_quads);
+        const int next = group_quads ? 8 * group_quads * 16 : 32;
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) out[32 * cb] = acc[cb][i];
+        for (int cb = 0; cb < NCB; ++cb) out[next * cb] = acc[cb][i];
       }
     }
     if (!valid_next) break;
@@ -171,7 +179,7 @@ __global__ __launch_bounds__(256) void node_mix_mfma_kernel(const float* __restr
 
 template <int LOG2E>
 static int launch_node_mix_mfma(egnn_ctx* ctx, const float* x1, const float* W1, const float* x2, const float* W2,
-                                float* y, int n_nodes, hipStream_t stream, int transpose) {
+                                float* y, int n_nodes, hipStream_t stream, int transpose, int group_quads) {
   constexpr int E = 1 << LOG2E;
   const int lmax = ctx->desc.lmax;
   const long max_rows = (long)n_nodes * (2 * lmax + 1);
@@ -183,16 +191,16 @@ static int launch_node_mix_mfma(egnn_ctx* ctx, const float* x1, const float* W1,
   dim3 grid((unsigned)((n_tiles + tiles - 1) / tiles), lmax + 1), block(256);
   const size_t shmem = (size_t)(W2 ? 2 : 1) * E * E * sizeof(float);
   hipLaunchKernelGGL(node_mix_mfma_kernel<LOG2E>, grid, block, shmem, stream, x1, W1, x2, W2, y, n_nodes, lmax, transpose,
-                     (int)tiles);
+                     (int)tiles, group_quads);
   EGNN_LAUNCH_CHECK(ctx, "node_mix_mfma_kernel");
   return EGNN_OK;
 }
 
 int egnn_launch_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, const float* x2, const float* W2,
-                         float* y, int n_nodes, hipStream_t stream, int transpose) {
+                         float* y, int n_nodes, hipStream_t stream, int transpose, int group_quads) {
   if (n_nodes == 0) return EGNN_OK;
-  if (ctx->desc.channels == 32) return launch_node_mix_mfma<5>(ctx, x1, W1, x2, W2, y, n_nodes, stream, transpose);
-  if (ctx->desc.channels == 64) return launch_node_mix_mfma<6>(ctx, x1, W1, x2, W2, y, n_nodes, stream, transpose);
+  if (ctx->desc.channels == 32) return launch_node_mix_mfma<5>(ctx, x1, W1, x2, W2, y, n_nodes, stream, transpose, group_quads);
+  if (ctx->desc.channels == 64) return launch_node_mix_mfma<6>(ctx, x1, W1, x2, W2, y, n_nodes, stream, transpose, group_quads);
   const int E = ctx->desc.channels, lmax = ctx->desc.lmax;
   const int rows_per_tile = MIX_RPT * (256 / E);
   const long max_rows = (long)n_nodes * (2 * lmax + 1);
@@ -210,7 +218,7 @@ int egnn_launch_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, const 
     if (e != hipSuccess) return egnn_check_hip(ctx, e, "hipFuncSetAttribute(node_mix_kernel)");
   }
   hipLaunchKernelGGL(node_mix_kernel, grid, block, shmem, stream, x1, W1, x2, W2, y, n_nodes, lmax,
-                     ctx->log2_channels, transpose, (int)tiles);
+                     ctx->log2_channels, transpose, (int)tiles, group_quads);
   EGNN_LAUNCH_CHECK(ctx, "node_mix_kernel");
   return EGNN_OK;
 }
