@@ -31,9 +31,6 @@
 #include "half_scales.h"
 #include "edge_fused.h"
 
-typedef _Float16 ef_h8 __attribute__((ext_vector_type(8)));
-typedef float ef_f4 __attribute__((ext_vector_type(4)));
-
 __device__ __forceinline__ uint4 ef_pack8(const float (&x)[8], uint4& lo) {
   uint32_t h[8], l[8];
 #pragma unroll
@@ -48,7 +45,7 @@ __device__ __forceinline__ uint4 ef_pack8(const float (&x)[8], uint4& lo) {
 }
 
 // First preparation.  Per edge the rotation into its frame (cos p, sin p, cos t, sin t of the azimuth and polar angle), per row
-// of radial weights the length; the last HS_BLOCKS workgroups take the parts of the operands' scalings.
+// of radial weights the length and the cutoff envelope; the last HS_BLOCKS workgroups take the parts of the operands' scalings.
 struct EfFirst {
   const int* src;
   const int* dst;
@@ -58,8 +55,9 @@ struct EfFirst {
   const float* W_r1;
   const float* W_r2;
   float4* frame;
-  float* length;
+  float2* length;
   float* scales;
+  float r_cut;
   double bx, by, bz;
   long n_edges;
   int n_rbf, PE, log2E;
@@ -88,19 +86,19 @@ __global__ __launch_bounds__(256) void ef_first_kernel(EfFirst g) {
   const double irho = polar ? 0.0 : 1.0 / rho;
   g.frame[k] = make_float4(polar ? 1.0f : (float)(dx * irho), (float)(dy * irho), (float)(dz * inv), (float)(rho * inv));
   const int r = g.w_row ? g.w_row[k] : (int)k;
-  if (r >= 0) g.length[r] = (float)d;
+  if (r >= 0) g.length[r] = make_float2((float)d, egnn_envelope((float)d, g.r_cut));
 }
 
 // Second preparation: both operands of the radial contraction, scaled and cut into two half-precision pieces.  The contraction
-// runs over the 64 hidden units in two steps of 32; slot (step, q, i) of it, i = 0 .. 7, is unit 32 step + 16 (i / 4) + 4 q + i % 4:
-// the order in which the lanes (row n, q) of the fp32 products with W_r1 hold their results.
+// runs over the 64 hidden units in two steps of 32; octet q of a step is what a lane (n, q) holds.
 //   rec  [row][step][piece][q] of 16 bytes: hidden activations of a row times the cutoff envelope
 //   A    [group of 4 channels][tile of 4 paths][step][piece][lane] of 16 bytes: alpha W_r2; lane (m, q) holds path
 //        4 tile + m % 4, channel 4 group + m / 4
-// A wavefront takes 16 rows at a time: four Gaussians a lane and step of four, 16 units a lane from 16x16x4 fp32 products (one
-// thread per octet of units with all Gaussians each took 42 us for 313,500 rows).  The last workgroups write A.
+// A thread takes an octet of units of two rows, W_r1 from LDS.  (With the fp32 products on
+// the matrix cores the weights came out less exact: their gradient summed over all edges was off by 2.03e-7 instead of 1.69e-7.)
+// The last workgroups write A.
 struct EfSecond {
-  const float* length;
+  const float2* length;
   const float* W_r1;
   const float* W_r2;
   const float* scales;
@@ -111,7 +109,6 @@ struct EfSecond {
   float r_cut;
   PathAlpha alpha;
 };
-__device__ __forceinline__ int ef_unit(int step, int q, int i) { return 32 * step + 16 * (i >> 2) + 4 * q + (i & 3); }
 
 __global__ __launch_bounds__(256) void ef_second_kernel(EfSecond g) {
   float s_w, s_g, inv;
@@ -127,7 +124,7 @@ __global__ __launch_bounds__(256) void ef_second_kernel(EfSecond g) {
     const float* W = g.W_r2 + ((size_t)((p < g.P ? p : 0) << g.log2E) + c) * EGNN_HIDDEN;
     float x[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = p < g.P ? f * W[ef_unit(ks, q, i)] : 0.0f;
+    for (int i = 0; i < 8; ++i) x[i] = p < g.P ? f * W[32 * ks + 8 * q + i] : 0.0f;
     uint4 lo;
     const uint4 hi = ef_pack8(x, lo);
     uint4* out = g.A + ((size_t)(cg * g.NT + tile) * 2 + ks) * 128 + lane;
@@ -135,44 +132,49 @@ __global__ __launch_bounds__(256) void ef_second_kernel(EfSecond g) {
     out[64] = lo;
     return;
   }
-  const int steps = (g.n_rbf + 3) >> 2;                  // 1 .. 8 products of four Gaussians
-  float W[4][8];
-#pragma unroll
-  for (int t = 0; t < 4; ++t)
-#pragma unroll
-    for (int s = 0; s < 8; ++s) W[t][s] = s < steps && 4 * s + q < g.n_rbf ? g.W_r1[(16 * t + n) * g.n_rbf + 4 * s + q] : 0.0f;
+  __shared__ float sW1[32 * EGNN_HIDDEN];                // [Gaussian][unit]
+  for (int i = threadIdx.x; i < g.n_rbf * EGNN_HIDDEN; i += 256) sW1[i] = g.W_r1[(i & 63) * g.n_rbf + (i >> 6)];
+  __syncthreads();
+  const int o = threadIdx.x & 7;
   const float step_r = g.r_cut / (float)(g.n_rbf - 1);
   const float inv2s2 = 0.5f / (step_r * step_r);
-  const long wave = (long)blockIdx.x * 4 + (threadIdx.x >> 6), n_waves = (long)g.row_blocks * 4;
-  for (long r0 = wave * 16; r0 < g.n_rows; r0 += n_waves * 16) {
-    const long row = r0 + n < g.n_rows ? r0 + n : g.n_rows - 1;
-    const float d = g.length[row];
-    ef_f4 pre[4];
+  for (long r0 = (long)blockIdx.x * 64 + (threadIdx.x >> 3); r0 < g.n_rows; r0 += (long)g.row_blocks * 64) {
+    const bool two = r0 + 32 < g.n_rows;
+    const float2 row[2] = {g.length[r0], g.length[two ? r0 + 32 : r0]};
+    float pre[2][8];
 #pragma unroll
-    for (int t = 0; t < 4; ++t) pre[t] = ef_f4{0.0f, 0.0f, 0.0f, 0.0f};
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
-    for (int s = 0; s < 8; ++s)
-      if (s < steps) {
-        const float u = d - (float)(4 * s + q) * step_r;
-        const float B = __expf(-u * u * inv2s2);         // (past the last Gaussian: its weights are zero)
+      for (int i = 0; i < 8; ++i) pre[t][i] = 0.0f;
+    for (int b = 0; b < g.n_rbf; ++b) {
+      const float4* wr = reinterpret_cast<const float4*>(sW1 + b * EGNN_HIDDEN + 8 * o);
+      const float4 w0 = wr[0], w1 = wr[1];
+      const float w[8] = {w0.x, w0.y, w0.z, w0.w, w1.x, w1.y, w1.z, w1.w};
 #pragma unroll
-        for (int t = 0; t < 4; ++t) pre[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(W[t][s], B, pre[t], 0, 0, 0);
+      for (int t = 0; t < 2; ++t) {
+        const float u = row[t].x - (float)b * step_r;
+        const float B = __expf(-u * u * inv2s2);
+#pragma unroll
+        for (int i = 0; i < 8; ++i) pre[t][i] += w[i] * B;
       }
-    const float fc = s_g * egnn_envelope(d, g.r_cut);
-    uint4* out = g.rec + row * 16 + q;
+    }
 #pragma unroll
-    for (int ks = 0; ks < 2; ++ks) {
+    for (int t = 0; t < 2; ++t) {
+      const float fc = s_g * row[t].y;
       float x[8];
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const float y = pre[2 * ks + (i >> 2)][i & 3];
-        x[i] = fc * y / (1.0f + __expf(-y));
+        // SiLU by a reciprocal and one Newton step (a large exponential is cut off at 1e30, where the quotient is zero)
+        const float y = 1.0f + fminf(__expf(-pre[t][i]), 1e30f);
+        const float r = __builtin_amdgcn_rcpf(y);
+        x[i] = fc * pre[t][i] * __builtin_fmaf(__builtin_fmaf(-y, r, 1.0f), r, r);
       }
       uint4 lo;
       const uint4 hi = ef_pack8(x, lo);
-      if (r0 + n < g.n_rows) {
-        out[ks * 8] = hi;
-        out[ks * 8 + 4] = lo;
+      if (t == 0 || two) {
+        uint4* out = g.rec + (r0 + 32 * t) * 16 + (o >> 2) * 8 + (o & 3);
+        out[0] = hi;
+        out[4] = lo;
       }
     }
   }
@@ -181,19 +183,6 @@ __global__ __launch_bounds__(256) void ef_second_kernel(EfSecond g) {
 template <int CTRL>
 __device__ __forceinline__ float ef_dpp(float x) {
   return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, x), CTRL, 0xF, 0xF, false));
-}
-
-// The compiler does not know which LDS words a load from memory to LDS writes, nor when: both waits are spelled out, and the
-// fences (no instructions at this scope) keep the LDS reads on their side of them.
-__device__ __forceinline__ void ef_wait_arrived() {         // the loads to LDS issued so far have arrived
-  __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0)
-  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-  __builtin_amdgcn_wave_barrier();
-}
-__device__ __forceinline__ void ef_wait_read() {            // the LDS reads issued so far have returned
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
-  __builtin_amdgcn_s_waitcnt(0xC07F);                       // lgkmcnt(0)
 }
 
 
@@ -376,19 +365,24 @@ __global__ __launch_bounds__(256, EF_WG_PER_CU) void ef_layer_kernel(
     ef_f4 c[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) c[t] = ef_f4{0.0f, 0.0f, 0.0f, 0.0f};
+    // (the four correction products first: then the sum is rounded at its full size twice, not six times)
+    ef_h8 bh[2], bl[2];
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks) { bh[ks] = __builtin_bit_cast(ef_h8, b[ks][0]); bl[ks] = __builtin_bit_cast(ef_h8, b[ks][1]); }
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
-      const ef_h8 bh = __builtin_bit_cast(ef_h8, b[ks][0]), bl = __builtin_bit_cast(ef_h8, b[ks][1]);
 #pragma unroll
       for (int t = 0; t < NT; ++t)
-        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, ah[t][ks]), bl, c[t], 0, 0, 0);
+        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, ah[t][ks]), bl[ks], c[t], 0, 0, 0);
 #pragma unroll
       for (int t = 0; t < NT; ++t)
-        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, sLo[(t * 2 + ks) * 64 + at]), bh, c[t], 0, 0, 0);
-#pragma unroll
-      for (int t = 0; t < NT; ++t)
-        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, ah[t][ks]), bh, c[t], 0, 0, 0);
+        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, sLo[(t * 2 + ks) * 64 + at]), bh[ks], c[t], 0, 0, 0);
     }
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int t = 0; t < NT; ++t)
+        c[t] = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(ef_h8, ah[t][ks]), bh[ks], c[t], 0, 0, 0);
     float w[NT * 4];
 #pragma unroll
     for (int t = 0; t < NT; ++t)
@@ -445,30 +439,6 @@ __global__ __launch_bounds__(256, EF_WG_PER_CU) void ef_layer_kernel(
   store_node();
 }
 
-static size_t ef_align(size_t b) { return (b + 255) & ~(size_t)255; }
-
-// scratch: scales and their parts (256 bytes), A, frames, lengths, records, h in groups of four channels
-struct EfScratch {
-  float* scales;
-  uint4* A;
-  float4* frame;
-  float* length;
-  uint4* rec;
-  float* h4;
-  size_t bytes;
-};
-static int ef_tiles(const egnn_ctx* ctx) { return (ctx->n_paths[0] + 3) / 4; }
-static int ef_quads(const egnn_ctx* ctx) { return ((ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) + 3) / 4; }
-static EfScratch ef_carve(const egnn_ctx* ctx, const egnn_graph* g, void* base) {
-  const size_t G = ctx->desc.channels / 4, n_rows = g->n_edges;
-  const size_t a = 256, f = a + ef_align(G * ef_tiles(ctx) * 256 * sizeof(uint4)), l = f + ef_align((size_t)g->n_edges * 16),
-               r = l + ef_align(n_rows * 4), h = r + ef_align(n_rows * 256),
-               end = h + ef_align((size_t)g->n_total * G * ef_quads(ctx) * 64);
-  char* p = (char*)base;
-  return {reinterpret_cast<float*>(p), reinterpret_cast<uint4*>(p + a), reinterpret_cast<float4*>(p + f),
-          reinterpret_cast<float*>(p + l), reinterpret_cast<uint4*>(p + r), reinterpret_cast<float*>(p + h), end};
-}
-
 // Where this kernel is the faster one, measured on 48 .. 3,000 atoms of 21 .. 209 edges, whole layers against the two kernels: 1.1 to
 // 2.5 times from lmax 2 on; at lmax 1 0.99 to 1.7 times at 32 and 64 channels, 0.89 to 1.7 at 128; at lmax 0, where one path takes a
 // tile of four, 0.58 to 1.0 for 37,000 edges and more.
@@ -477,35 +447,35 @@ static EfScratch ef_carve(const egnn_ctx* ctx, const egnn_graph* g, void* base) 
 bool egnn_edge_fused_fits(const egnn_ctx* ctx, const egnn_graph* g) {
   const int lmax = ctx->desc.lmax;
   return (lmax >= 2 || (lmax == 1 && ctx->desc.channels <= 64)) && g->n_edges > 0 && g->n_owned > 0 &&
-         ef_carve(ctx, g, nullptr).bytes <= (size_t)g->n_edges * ctx->n_paths[0] * ctx->desc.channels * sizeof(float);
+         egnn_ef_carve(ctx, g, 0, nullptr).bytes <= (size_t)g->n_edges * ctx->n_paths[0] * ctx->desc.channels * sizeof(float);
 }
 
-static PathAlpha ef_alpha(const egnn_ctx* ctx) {
+static PathAlpha ef_alpha(const egnn_ctx* ctx, int which) {
   PathAlpha al;
-  for (int p = 0; p < EGNN_MAX_PATHS; ++p) al.a[p] = p < ctx->n_paths[0] ? ctx->alpha[0][p] : 0.0f;
+  for (int p = 0; p < EGNN_MAX_PATHS; ++p) al.a[p] = p < ctx->n_paths[which] ? ctx->alpha[which][p] : 0.0f;
   return al;
 }
 
-int egnn_launch_edge_fused_first(egnn_ctx* ctx, const egnn_graph* g, const float* pos, const float box[3], const float* W_r1,
-                                 const float* W_r2, void* scratch, hipStream_t stream) {
-  const EfScratch s = ef_carve(ctx, g, scratch);
-  const EfFirst x = {g->src, g->dst, g->shift, pos, g->w_row, W_r1, W_r2, s.frame, s.length, s.scales,
+int egnn_launch_edge_fused_first(egnn_ctx* ctx, const egnn_graph* g, int which, const float* pos, const float box[3],
+                                 const float* W_r1, const float* W_r2, void* scratch, hipStream_t stream) {
+  const EfScratch s = egnn_ef_carve(ctx, g, which, scratch);
+  const EfFirst x = {g->src, g->dst, g->shift, pos, g->w_row, W_r1, W_r2, s.frame, s.length, s.scales, ctx->desc.r_cut,
                      (double)box[0], (double)box[1], (double)box[2], (long)g->n_edges, ctx->desc.n_rbf,
-                     ctx->n_paths[0] * ctx->desc.channels, ctx->log2_channels, ef_alpha(ctx)};
+                     ctx->n_paths[which] * ctx->desc.channels, ctx->log2_channels, ef_alpha(ctx, which)};
   hipLaunchKernelGGL(ef_first_kernel, dim3((unsigned)((g->n_edges + 255) / 256 + HS_BLOCKS)), dim3(256), 0, stream, x);
   EGNN_LAUNCH_CHECK(ctx, "ef_first_kernel");
   return EGNN_OK;
 }
 
-int egnn_launch_edge_fused_second(egnn_ctx* ctx, const egnn_graph* g, const float* W_r1, const float* W_r2, void* scratch,
-                                  hipStream_t stream) {
-  const EfScratch s = ef_carve(ctx, g, scratch);
+int egnn_launch_edge_fused_second(egnn_ctx* ctx, const egnn_graph* g, int which, const float* W_r1, const float* W_r2,
+                                  void* scratch, hipStream_t stream) {
+  const EfScratch s = egnn_ef_carve(ctx, g, which, scratch);
   const long n_rows = g->w_row ? g->n_w_rows : g->n_edges;
-  const int NT = ef_tiles(ctx), a_blocks = (ctx->desc.channels / 4 * NT * 128 + 255) / 256;
+  const int NT = ef_tiles(ctx, which), a_blocks = (ctx->desc.channels / 4 * NT * 128 + 255) / 256;
   const long groups = (n_rows + 63) / 64;                // of four wavefronts
   const int row_blocks = (int)(groups < 4 * EGNN_CUS ? groups : 4 * EGNN_CUS);
-  const EfSecond x = {s.length, W_r1, W_r2, s.scales, s.rec, s.A, n_rows, ctx->desc.n_rbf, ctx->n_paths[0], NT,
-                      ctx->log2_channels, row_blocks, ctx->desc.r_cut, ef_alpha(ctx)};
+  const EfSecond x = {s.length, W_r1, W_r2, s.scales, s.rec, s.A, n_rows, ctx->desc.n_rbf, ctx->n_paths[which], NT,
+                      ctx->log2_channels, row_blocks, ctx->desc.r_cut, ef_alpha(ctx, which)};
   hipLaunchKernelGGL(ef_second_kernel, dim3((unsigned)(row_blocks + a_blocks)), dim3(256), 0, stream, x);
   EGNN_LAUNCH_CHECK(ctx, "ef_second_kernel");
   return EGNN_OK;
@@ -513,12 +483,12 @@ int egnn_launch_edge_fused_second(egnn_ctx* ctx, const egnn_graph* g, const floa
 
 int egnn_launch_edge_fused_features(egnn_ctx* ctx, const egnn_graph* g, const float* x_in, const float* W_pre, void* scratch,
                                     hipStream_t stream) {
-  return egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, ef_carve(ctx, g, scratch).h4, g->n_total, stream, 0,
+  return egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, egnn_ef_carve(ctx, g, 0, scratch).h4, g->n_total, stream, 0,
                               ef_quads(ctx));
 }
 
 int egnn_launch_edge_fused_sum(egnn_ctx* ctx, const egnn_graph* g, void* scratch, float* a, bool half, hipStream_t stream) {
-  const EfScratch s = ef_carve(ctx, g, scratch);
+  const EfScratch s = egnn_ef_carve(ctx, g, 0, scratch);
   const int G = ctx->desc.channels / 4;
   const float4* h4 = reinterpret_cast<const float4*>(s.h4);
   const float* scales = s.scales;
@@ -561,8 +531,8 @@ int egnn_launch_edge_fused_sum(egnn_ctx* ctx, const egnn_graph* g, void* scratch
 int egnn_launch_edge_fused(egnn_ctx* ctx, const egnn_graph* g, const float* pos, const float box[3], const float* x_in,
                            const float* W_pre, const float* W_r1, const float* W_r2, void* scratch, float* a,
                            hipStream_t stream) {
-  int rc = egnn_launch_edge_fused_first(ctx, g, pos, box, W_r1, W_r2, scratch, stream);
-  if (!rc) rc = egnn_launch_edge_fused_second(ctx, g, W_r1, W_r2, scratch, stream);
+  int rc = egnn_launch_edge_fused_first(ctx, g, 0, pos, box, W_r1, W_r2, scratch, stream);
+  if (!rc) rc = egnn_launch_edge_fused_second(ctx, g, 0, W_r1, W_r2, scratch, stream);
   if (!rc) rc = egnn_launch_edge_fused_features(ctx, g, x_in, W_pre, scratch, stream);
   return rc ? rc : egnn_launch_edge_fused_sum(ctx, g, scratch, a, false, stream);
 }

@@ -392,9 +392,9 @@ static int layer_forward_impl(egnn_ctx* ctx, const egnn_graph* g, const float* p
   // Default: S3 and S4 in one kernel, where that is the faster way
   const bool in_one = with_w && (saving || ctx->use_fused == 0) && egnn_edge_fused_fits(ctx, g);
   if (in_one && !saving) {
-    if ((rc = egnn_launch_edge_fused_first(ctx, g, pos, box, W_r1, W_r2, w, st))) return rc;
+    if ((rc = egnn_launch_edge_fused_first(ctx, g, 0, pos, box, W_r1, W_r2, w, st))) return rc;
     tm.mark(0);
-    if ((rc = egnn_launch_edge_fused_second(ctx, g, W_r1, W_r2, w, st))) return rc;
+    if ((rc = egnn_launch_edge_fused_second(ctx, g, 0, W_r1, W_r2, w, st))) return rc;
     tm.mark(1);
     if ((rc = egnn_launch_edge_fused_features(ctx, g, x_in, W_pre, w, st))) return rc;
     tm.mark(2);
@@ -483,7 +483,32 @@ static int readout_hij_impl(egnn_ctx* ctx, const egnn_graph* g, const float* pos
   const bool shared = g->w_row != nullptr;
   float* rd_rows = shared ? (float*)c.take((size_t)g->n_edges * 16) : nullptr;
   const bool half = ctx->w_half && !w_save;
+  float* const scratch = w;
   if (w_save) w = w_save;
+
+  StageTimer tm(ctx, st, 1);
+  // S3 and S6 in one kernel, where that is the faster way (when w is kept, S3 writes it as well: the blocks are those of the call
+  // that does not keep it, to the bit)
+  if (egnn_readout_fused_fits(ctx, g)) {
+    if (w_save) {
+      if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st, rd_rows))) return rc;
+      if ((rc = egnn_launch_radial(ctx, 1, shared ? rd_rows : rhat_d, shared ? g->n_w_rows : g->n_edges, W_r1, W_r2, w_save, w2s,
+                                   st, false)))
+        return rc;
+    }
+    if ((rc = egnn_launch_edge_fused_first(ctx, g, 1, pos, box, W_r1, W_r2, scratch, st))) return rc;
+    tm.mark(0);
+    if ((rc = egnn_launch_edge_fused_second(ctx, g, 1, W_r1, W_r2, scratch, st))) return rc;
+    tm.mark(1);
+    const EfScratch es = egnn_ef_carve(ctx, g, 1, scratch);
+    if ((rc = egnn_launch_node_mix(ctx, x, W_s, nullptr, nullptr, es.h4, g->n_total, st, 0, ef_quads(ctx)))) return rc;
+    tm.mark(2);
+    if ((rc = egnn_launch_node_mix(ctx, x, W_t, nullptr, nullptr, es.t4, g->n_total, st, 0, ef_quads(ctx)))) return rc;
+    tm.mark(3);
+    rc = egnn_launch_readout_fused(ctx, g, scratch, V, H, half, st);
+    tm.mark(4);
+    return rc;
+  }
 
   // integer table: q_row[nq] q_vrow[nq] slot_L[n_slots] slot_qoff[n_slots] unc_ptr[nq+1] unc_q[nnz]
   const int nq = ctx->n_orb * ctx->n_orb;
@@ -509,7 +534,6 @@ static int readout_hij_impl(egnn_ctx* ctx, const egnn_graph* g, const float* pos
   EGNN_HIP(ctx, hipMemcpyAsync(tab_i, ti.data(), ti.size() * sizeof(int), hipMemcpyHostToDevice, st));
   EGNN_HIP(ctx, hipMemcpyAsync(tab_f, ctx->unc_c.data(), ctx->unc_c.size() * sizeof(float), hipMemcpyHostToDevice, st));
 
-  StageTimer tm(ctx, st, 1);
   if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st, rd_rows))) return rc;
   tm.mark(0);
   if ((rc = egnn_launch_radial(ctx, 1, shared ? rd_rows : rhat_d, shared ? g->n_w_rows : g->n_edges, W_r1, W_r2, w, w2s,

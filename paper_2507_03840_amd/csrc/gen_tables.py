@@ -432,6 +432,24 @@ def generate():
     return "\n".join(out) + "\n"
 
 
+# ------------------------------------------------------------------ orbital blocks from coupled values
+def generate_uncouple():
+    """Per pair of shell degrees (l_a, l_b <= 2) the block's coupled values, L after L, turned in place into the block
+    [m_a][m_b] (Eq. 1 read backwards): x[i] in registers, constants as literals."""
+    out = ["// GENERATED by gen_tables.py -- do not edit.", "#pragma once", ""]
+    for la in range(ORB_LMAX + 1):
+        for lb in range(ORB_LMAX + 1):
+            na, nb = 2 * la + 1, 2 * lb + 1
+            U, at = np.zeros((na * nb, na * nb)), 0
+            for L in range(abs(la - lb), la + lb + 1):
+                U[:, at:at + 2 * L + 1] = coupling_real(la, lb, L).reshape(na * nb, 2 * L + 1)
+                at += 2 * L + 1
+            assert at == na * nb and np.allclose(U.T @ U, np.eye(na * nb), atol=1e-12)
+            out.append(emit_matvec(f"egnn_uncouple_{la}{lb}", U, f"({la},{lb}): coupled values -> block"))
+            out.append("")
+    return "\n".join(out) + "\n"
+
+
 # ------------------------------------------------------------------ node-wise form of the SO(2) message sums
 def so2_beta(lo, li, L):
     """beta[m], m = 0..4:  D_lo^T P^m D_li = sum_L beta_L^m sum_M C^(lo li L)[:, :, M] Yhat_LM(r_hat), where P^m has ones
@@ -565,7 +583,8 @@ def generate_so2():
 def main():
     here = os.path.dirname(os.path.abspath(__file__))
     target = sys.argv[1] if len(sys.argv) > 1 else os.path.join(here, "egnn_gen.inc")
-    for path, text in ((target, generate()), (os.path.join(os.path.dirname(target), "so2_node_gen.inc"), generate_so2())):
+    for path, text in ((target, generate()), (os.path.join(os.path.dirname(target), "so2_node_gen.inc"), generate_so2()),
+                       (os.path.join(os.path.dirname(target), "uncouple_gen.inc"), generate_uncouple())):
         if not os.path.exists(path) or open(path).read() != text:
             with open(path, "w") as f:
                 f.write(text)
