@@ -752,27 +752,30 @@ __global__ __launch_bounds__(256) void so2n_softmax_kernel(const int* __restrict
 // would have to leave out those that no edge reads, and lose the small ones beside the large (and take two kernels: 19 instead
 // of 10 us on 2.4 million values).
 //
-// With `ptr` the rows are the gradients da of the owned nodes, and the weight gradient's scales come from here too: sums over
-// the nodes n of X_n da_n, X = T and X = G, with X_n scaled by 2^node_exp[n] from its own largest value and da_n by the inverse
-// of that and 2^C for all.  C brings the largest da_n 2^-node_exp[n] to 2^13; its exponent (plus SO2N_EXP0) goes to *used[0] for
-// T, *used[1] for G.  Nodes whose X is zero, those without edges among them, and those that fill up a multiple of 16 are marked.
+// With X_max the scales of a weight gradient come from here too: sums over the nodes n of X_n y_n with y the rows (X = the coupled
+// sums T and y = the features; X = G and y = da), X_n scaled by 2^node_exp[n] from its own largest value and y_n by the inverse
+// of that and 2^C for all.  C brings the largest y_n 2^-node_exp[n] to 2^13; its exponent (plus SO2N_EXP0) goes to *used.  Nodes
+// whose X is zero, those without edges (incoming ones of the first n_ptr nodes, outgoing ones with col_ptr) among them, and those
+// that fill up a multiple of 16 are marked.
 #define SO2N_UNUSED (-1000000)
 #define SO2N_EXP0 4096
 struct So2nPack {
   const float* x;
   int n_rows, row_floats;
-  uint32_t* out;
+  uint32_t* out;                 // NULL: scales only
   int* row_exp;
-  const int* ptr;                // NULL: rows only
-  const unsigned* X_max[2];      // largest |T|, |G| of every node
-  int* node_exp[2];
+  const unsigned* X_max;         // largest |X| of every node; NULL: rows only
+  const int* ptr;
+  int n_ptr;
+  const int* col_ptr;            // may be NULL
+  int* node_exp;
   unsigned* used;
 };
 __global__ __launch_bounds__(256) void so2n_pack_kernel(So2nPack p) {
-  __shared__ unsigned s_used[2][4];
+  __shared__ unsigned s_used[4];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  unsigned used[2] = {0u, 0u};
-  const int n_all = p.ptr ? (p.n_rows + 15) & ~15 : p.n_rows;
+  unsigned used = 0u;
+  const int n_all = p.X_max ? (p.n_rows + 15) & ~15 : p.n_rows;
   for (int i = blockIdx.x * 4 + wave; i < n_all; i += gridDim.x * 4) {
     const bool there = i < p.n_rows;
     float mx = 0.0f;
@@ -787,32 +790,28 @@ __global__ __launch_bounds__(256) void so2n_pack_kernel(So2nPack p) {
       }
 #pragma unroll
       for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
-      const int e = so2n_exp(mx);
-      if (lane == 0) p.row_exp[i] = e;
-      const float sc = ldexpf(1.0f, e);
+      if (p.out) {
+        const int e = so2n_exp(mx);
+        if (lane == 0) p.row_exp[i] = e;
+        const float sc = ldexpf(1.0f, e);
 #pragma unroll 4
-      for (int q = lane; q < p.row_floats; q += 64) p.out[(size_t)i * p.row_floats + q] = so2n_split(row[q] * sc);
+        for (int q = lane; q < p.row_floats; q += 64) p.out[(size_t)i * p.row_floats + q] = so2n_split(row[q] * sc);
+      }
     }
-    if (!p.ptr) continue;
+    if (!p.X_max) continue;
     finite = __all(finite);
-    const bool edges = there && p.ptr[i + 1] > p.ptr[i];
-#pragma unroll
-    for (int z = 0; z < 2; ++z) {
-      const float X = edges ? __uint_as_float(p.X_max[z][i]) : 0.0f;
-      const int e = so2n_exp(X);
-      // (an infinite or NaN gradient shows in the result unless its node has no edges)
-      const bool unused = !edges || (X == 0.0f && finite);
-      if (lane == 0) p.node_exp[z][i] = unused ? SO2N_UNUSED : e;
-      if (!unused && finite && mx > 0.0f && X > 0.0f) used[z] = max(used[z], (unsigned)(ilogbf(mx) - e + SO2N_EXP0));
-    }
+    const bool edges = there && ((i < p.n_ptr && p.ptr[i + 1] > p.ptr[i]) || (p.col_ptr && p.col_ptr[i + 1] > p.col_ptr[i]));
+    const float X = edges ? __uint_as_float(p.X_max[i]) : 0.0f;
+    const int e = so2n_exp(X);
+    // (an infinite or NaN row shows in the result unless its node has no edges)
+    const bool unused = !edges || (X == 0.0f && finite);
+    if (lane == 0) p.node_exp[i] = unused ? SO2N_UNUSED : e;
+    if (!unused && finite && mx > 0.0f && X > 0.0f) used = max(used, (unsigned)(ilogbf(mx) - e + SO2N_EXP0));
   }
-  if (!p.ptr) return;
-  if (lane == 0) { s_used[0][wave] = used[0]; s_used[1][wave] = used[1]; }
+  if (!p.X_max) return;
+  if (lane == 0) s_used[wave] = used;
   __syncthreads();
-  if (threadIdx.x < 2) {
-    const unsigned* u = s_used[threadIdx.x];
-    atomicMax(p.used + threadIdx.x, max(max(u[0], u[1]), max(u[2], u[3])));
-  }
+  if (threadIdx.x == 0) atomicMax(p.used, max(max(s_used[0], s_used[1]), max(s_used[2], s_used[3])));
 }
 
 // ---------------------------------------------------------------------------------------------- path weights
@@ -1008,24 +1007,28 @@ __global__ __launch_bounds__(256, 2) void so2n_mix_kernel(So2nMix p) {
 
 // ---------------------------------------------------------------------------------------------- weight gradient
 struct So2nWgrad {
-  const float* T;        // form SO2N_PLAIN
-  const float* G;
-  const float* da;       // [n_nodes][(lmax+1)^2][E]
+  const float* T;        // form SO2N_PLAIN, of n_nodes nodes
+  const float* x;        // [n_nodes][(lmax+1)^2][E]
+  const float* G;        // of n_G <= n_nodes nodes
+  const float* da;       // [n_G][(lmax+1)^2][E]
   float* partial;
   int node_floats, off[5], ld[5], K[5];   // K: rows of the result, those of T and then SO2N_AUX of G
   int k_tiles[5], chunks[5], per_chunk[5], unit0[6];
   size_t part0[6];       // first float of every degree's partial results
-  int n_nodes, E, n_ct, D;
+  int n_nodes, n_G, E, n_ct, D;
   const int* node_exp[2];   // scales of T and G (so2n_pack_kernel)
   const unsigned* used;
 };
 
-// partial[lo][chunk][k][col] = sum over the nodes n of the chunk and mo of T[n][(lo, mo)][k] da[n][(lo, mo)][col].  A wave
+// partial[l][chunk][k][col] = sum over the nodes n of the chunk and m of T[n][(l, m)][k] x[n][(l, m)][col].  T are the sums over
+// the outgoing edges that dx is made of (l an input degree of the message, k = (group, path to an output degree, its channel), col
+// an input channel): sum_edges Yhat x_src da_dst is the same number whether it is gathered at one end or at the other, so the sums
+// over the incoming edges need not be formed again (445 of 1,815 us of a call and its adjoint at 3,000 nodes).  A wave
 // owns 128 rows x 32 columns of the result; both operands are read in memory order, the contraction index being the row
 // index of both: lane (i, h) fetches 16 bytes of T and 4 of da for the eight nodes of its half-wave and finds in one
 // component of them the eight consecutive nodes one operand register wants, so accumulator a holds the rows
 // k0 + 4 r + a.  Degrees with more rows per node get fewer nodes per chunk, so that all waves take about equally long.  The
-// last wave of every column of tiles takes G in the place of T, with G's own scales: whichever of the two is the smaller keeps
+// last wave of every column of tiles takes G and da in the place of T and x, with G's own scales: whichever of the two is the smaller keeps
 // its accuracy.
 // Bound: T read once (403 MB at 3,000 nodes, lmax 4, 32 channels: 105 us = 3.8 TB/s, of which the scales per node and G take 10;
 // per edge it was 2.26 ms).
@@ -1042,7 +1045,8 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   const bool basis = kt == p.k_tiles[lo] - 1;
   const int k_first = basis ? p.K[lo] - SO2N_AUX : kt * 128, n_mo = 2 * lo + 1;
   const int K = basis ? SO2N_AUX : p.K[lo] - SO2N_AUX - k_first;           // rows this wave can have
-  const int n0 = chunk * p.per_chunk[lo], n1 = n0 + p.per_chunk[lo] < p.n_nodes ? n0 + p.per_chunk[lo] : p.n_nodes;
+  const int n_n = basis ? p.n_G : p.n_nodes;
+  const int n0 = chunk * p.per_chunk[lo], n1 = n0 + p.per_chunk[lo] < n_n ? n0 + p.per_chunk[lo] : n_n;
   const int ca = 4 * i32, cy = ct * 32 + i32;
   const bool a_ok = ca < K, y_ok = cy < p.E;
   const unsigned largest = p.used[basis ? 1 : 0];
@@ -1050,7 +1054,7 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   const int* node_exp = p.node_exp[basis ? 1 : 0];
   const float* T = (basis ? p.G + lo * lo * SO2N_AUX : p.T + p.off[lo] + k_first) + (a_ok ? ca : K - 4);
   const int ld = basis ? SO2N_AUX : p.ld[lo], node_floats = basis ? p.D * SO2N_AUX : p.node_floats;
-  const float* Y = p.da + (size_t)(lo * lo) * p.E + (y_ok ? cy : 0);
+  const float* Y = (basis ? p.da : p.x) + (size_t)(lo * lo) * p.E + (y_ok ? cy : 0);
   const size_t ys = (size_t)p.D * p.E;
   float16v acc[4], rest[4];      // (as in so2n_mix_kernel)
 #pragma unroll
@@ -1060,7 +1064,7 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
   sg_f4 ra[8];
   float ry[8];
   int re[8];
-  const int n_blocks = (n1 - n0 + 15) / 16, total = n_blocks * n_mo;
+  const int n_blocks = n1 > n0 ? (n1 - n0 + 15) / 16 : 0, total = n_blocks * n_mo;   // (a chunk past G's nodes: zeros)
   auto fetch = [&](int q) SO2N_INLINE {
     const int mo = q / n_blocks, n = n0 + (q - mo * n_blocks) * 16 + 8 * hh;
     const int4 e0 = *reinterpret_cast<const int4*>(node_exp + n), e1 = *reinterpret_cast<const int4*>(node_exp + n + 4);
@@ -1075,7 +1079,7 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
       ry[r] = ym[(size_t)nr * ys];
     }
   };
-  fetch(0);
+  if (total) fetch(0);
   for (int q = 0; q < total; ++q) {
     uint4 ah[4], al[4], yh, yl;
     float y[8];
@@ -1131,27 +1135,32 @@ __global__ __launch_bounds__(256) void so2n_wgrad_sum_kernel(So2nWgrad p, So2nW 
   out[i] = scale * sum;
 }
 
-// gradient of the path weights -> gradient of W_0 / (Wr_m, Wi_m) in their layout, and of W_e (the last E n_rbf threads)
+// gradient of the path weights (rows of an input degree, columns its channels: neighbouring threads read neighbouring words; and
+// rows of G of an output degree, columns that degree's channels) -> gradient of W_0 / (Wr_m, Wi_m) in their layout; and of W_e, a
+// wavefront per element in the last workgroups (a thread per element, 160 products one after the other: 66 us in all)
 __global__ __launch_bounds__(256) void so2n_unpack_wgrad_kernel(const float* __restrict__ dwp, So2nW s, int lmax, int E, int n_rbf,
                                                                 const float* __restrict__ W, const float* __restrict__ W_e,
                                                                 float* __restrict__ dW, float* __restrict__ dW_e) {
-  long i = (long)blockIdx.x * 256 + threadIdx.x;
-  const long n_w = (long)s.off[5];
-  if (i >= n_w) {
-    i -= n_w;
-    if (i >= (long)E * n_rbf) return;
-    const int ci = (int)(i / n_rbf), b = (int)(i - (long)ci * n_rbf);
+  const long n_w = (long)s.off[5], w_blocks = (n_w + 255) / 256;
+  if ((long)blockIdx.x >= w_blocks) {
+    const int e = (int)(blockIdx.x - w_blocks) * 4 + (int)(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (e >= E * n_rbf) return;
+    const int ci = e / n_rbf, b = e - ci * n_rbf;
     float sum = 0.0f;
     for (int lo = 0; lo <= lmax; ++lo) {
       const float* d = dwp + (size_t)(s.k_first[lo] + 2 * so2n_paths(lmax, lo) * E + b) * E;
       const float* row = W + (size_t)(lo * E) * ((lmax + 1) * 3 * E) + 2 * E + ci;
       float part = 0.0f;
-      for (int co = 0; co < E; ++co) part += row[(size_t)co * ((lmax + 1) * 3 * E)] * d[co];
+      for (int co = lane; co < E; co += 64) part += row[(size_t)co * ((lmax + 1) * 3 * E)] * d[co];
       sum += part / sqrtf((float)(2 * lo + 1));
     }
-    dW_e[i] = sum;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) sum += __shfl_xor(sum, off);
+    if (lane == 0) dW_e[e] = sum;
     return;
   }
+  const long i = (long)blockIdx.x * 256 + threadIdx.x;
+  if (i >= n_w) return;
   int m = 0;
   while (m < lmax && i >= (long)s.off[m + 1]) ++m;
   long r = i - (long)s.off[m];
@@ -1166,7 +1175,8 @@ __global__ __launch_bounds__(256) void so2n_unpack_wgrad_kernel(const float* __r
     for (int L = d; L <= lo + li; ++L)
       if (((lo + li + L) & 1) == odd)
         sum += SO2N_BETA[lo][li][L - d][m] *
-               dwp[(size_t)(s.k_first[lo] + (g * np + so2n_path_base(lo, li) + L - d) * E + ci) * E + co];
+               dwp[(size_t)(s.k_first[li] + (g * so2n_paths(lmax, li) + so2n_path_base(li, lo) + L - d) * E + co) * E + ci];
+    if (odd) sum = -sum;                 // (swapping the two degrees of a coupling tensor, see so2n_weight)
   } else if (m == 0 && li == 0) {
     // (the edge's other planes are zero on this path, and so are their weights' gradients)
     for (int b = 0; b < n_rbf; ++b)
@@ -1227,16 +1237,17 @@ size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t 
   return used;
 }
 
-// ptr: edges of the nodes whose gradients the rows are (see so2n_pack_kernel), or NULL
-static int so2n_pack_features(egnn_ctx* ctx, const float* x, int n_rows, const int32_t* ptr, const So2nCall& c, hipStream_t st) {
-  if (n_rows <= 0) return EGNN_OK;
-  So2nPack p;
-  p.x = x; p.n_rows = n_rows; p.row_floats = (ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels;
-  p.out = c.packed; p.row_exp = c.row_exp; p.ptr = ptr; p.X_max[0] = c.t_max; p.X_max[1] = c.G_max;
-  p.node_exp[0] = c.node_exp[0]; p.node_exp[1] = c.node_exp[1]; p.used = c.maxima + 4;
-  hipLaunchKernelGGL(so2n_pack_kernel, dim3((unsigned)std::min((n_rows + 3) / 4, 2048)), dim3(256), 0, st, p);
+static int so2n_launch_pack(egnn_ctx* ctx, So2nPack p, hipStream_t st) {
+  if (p.n_rows <= 0) return EGNN_OK;
+  p.row_floats = (ctx->desc.lmax + 1) * (ctx->desc.lmax + 1) * ctx->desc.channels;
+  hipLaunchKernelGGL(so2n_pack_kernel, dim3((unsigned)std::min((p.n_rows + 3) / 4, 2048)), dim3(256), 0, st, p);
   EGNN_LAUNCH_CHECK(ctx, "so2n_pack_kernel");
   return EGNN_OK;
+}
+static int so2n_pack_features(egnn_ctx* ctx, const float* x, int n_rows, const So2nCall& c, hipStream_t st) {
+  So2nPack p = {};
+  p.x = x; p.n_rows = n_rows; p.out = c.packed; p.row_exp = c.row_exp;
+  return so2n_launch_pack(ctx, p, st);
 }
 
 static int so2n_pack_weights(egnn_ctx* ctx, const float* W, const float* W_e, int form, bool transposed, const So2nCall& c,
@@ -1343,10 +1354,10 @@ static int so2n_launch_mix(egnn_ctx* ctx, const So2nCall& c, int form, int n_nod
   return EGNN_OK;
 }
 
-static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, So2nWgrad* p) {
+static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, int n_owned, So2nWgrad* p) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   p->node_floats = so2n_node_off(lmax, E, lmax + 1, SO2N_PLAIN);
-  p->n_nodes = n_nodes; p->E = E; p->n_ct = (E + 31) / 32; p->D = (lmax + 1) * (lmax + 1);
+  p->n_nodes = n_nodes; p->n_G = n_owned; p->E = E; p->n_ct = (E + 31) / 32; p->D = (lmax + 1) * (lmax + 1);
   int tiles = 0;
   auto k_tiles = [&](int lo) { return (so2n_ld(lmax, E, lo, SO2N_PLAIN) + 127) / 128 + 1; };
   for (int lo = 0; lo <= lmax; ++lo) tiles += (2 * lo + 1) * k_tiles(lo) * p->n_ct;
@@ -1370,20 +1381,19 @@ static void so2n_wgrad_plan(const egnn_ctx* ctx, int n_nodes, So2nWgrad* p) {
 
 size_t so2n_backward_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_total, char* base, So2nCall* out) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
-  // (T of the owned nodes and then of all nodes share one buffer)
   size_t used = so2n_carve(ctx, n_owned, n_total, n_total, SO2N_PLAIN, base, out);
   auto take = [&](size_t bytes) { char* q = base ? base + used : nullptr; used += so2n_a256(bytes); return q; };
   So2nW s;
   So2nSteps st;
   so2n_w_layout(lmax, E, SO2N_GRAD, &s, &st);
   So2nWgrad p;
-  so2n_wgrad_plan(ctx, n_owned, &p);
+  so2n_wgrad_plan(ctx, n_total, n_owned, &p);
   float* partial = (float*)take(p.part0[lmax + 1] * 4);
   float* dwpath = (float*)take((size_t)s.k_first[lmax + 1] * E * 4);
   float* G = (float*)take((size_t)n_owned * (lmax + 1) * (lmax + 1) * SO2N_AUX * 4);
   unsigned* G_max = (unsigned*)take((size_t)n_owned * 4);
   int* exps[2];
-  for (int z = 0; z < 2; ++z) exps[z] = (int*)take(((size_t)n_owned + 16) * 4);
+  for (int z = 0; z < 2; ++z) exps[z] = (int*)take(((size_t)(z ? n_owned : n_total) + 16) * 4);
   if (out) {
     out->partial = partial; out->dwpath = dwpath; out->G = G; out->G_max = G_max;
     out->node_exp[0] = exps[0]; out->node_exp[1] = exps[1];
@@ -1391,46 +1401,47 @@ size_t so2n_backward_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_total
   return used;
 }
 
-// Reverse pass of the message sum.  T of the forward pass again -> gradient of the path weights and, from that, of W and W_e;
-// then the same sums over the outgoing edges with da in the place of the features (a message is linear in its source, and
-// the transpose of D_lo^T P D_li is D_li^T P^T D_lo) and the transposed weights -> dx; the destinations' part uses the
-// forward pass's sums of harmonics.  c from so2n_backward_carve, its maxima and t_max zero on entry.
+// Reverse pass of the message sum.  The sums of the forward pass over the outgoing edges, with da in the place of the features (a
+// message is linear in its source, and the transpose of D_lo^T P D_li is D_li^T P^T D_lo), and the transposed weights -> dx;
+// the destinations' part uses the forward pass's sums of harmonics.  The same sums against the features -> gradient of the path
+// weights and, from that, of W and W_e.  c from so2n_backward_carve, its maxima and t_max zero on entry.
 int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t* col_ptr, const int32_t* perm, const float* rhat_d,
                               const float* x, const float* W_e, const float* W, const float* da, float scale, float* dx,
                               float* dW_e, float* dW, const So2nCall& c, hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   int rc;
-  if ((rc = so2n_pack_features(ctx, x, g->n_total, nullptr, c, st))) return rc;
-  So2nArgs p = {};
-  p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
-  p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_total); p.x_self = x;
-  p.T = c.T; p.t_max = c.t_max; p.g = c.g;
-  p.j_begin = 0; p.j_end = g->n_owned; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_PLAIN;
   if ((rc = so2n_launch_sums(ctx, g, rhat_d, nullptr, ctx->desc.n_rbf, false, c, st))) return rc;
+  So2nPack q = {};
+  q.x = da; q.n_rows = g->n_owned; q.out = c.packed; q.row_exp = c.row_exp;
+  q.X_max = c.G_max; q.ptr = g->row_ptr; q.n_ptr = g->n_owned; q.node_exp = c.node_exp[1]; q.used = c.maxima + 5;
+  if ((rc = so2n_launch_pack(ctx, q, st))) return rc;
+  So2nArgs p = {};
+  p.ptr = col_ptr; p.perm = perm; p.index = g->dst; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
+  p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_owned); p.x_self = da;
+  p.T = c.T; p.t_max = c.t_max + g->n_owned; p.g = c.g;
+  p.j_begin = 0; p.j_end = g->n_total; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_PLAIN;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
-  if ((rc = so2n_pack_features(ctx, da, g->n_owned, g->row_ptr, c, st))) return rc;
+  q.x = x; q.n_rows = g->n_total; q.out = nullptr; q.row_exp = nullptr;
+  q.X_max = p.t_max; q.col_ptr = col_ptr; q.node_exp = c.node_exp[0]; q.used = c.maxima + 4;
+  if ((rc = so2n_launch_pack(ctx, q, st))) return rc;
   So2nW s;
   So2nSteps steps;
   so2n_w_layout(lmax, E, SO2N_GRAD, &s, &steps);
   So2nWgrad w;
-  so2n_wgrad_plan(ctx, g->n_owned, &w);
-  w.T = c.T; w.G = c.G; w.da = da; w.partial = c.partial; w.used = c.maxima + 4;
+  so2n_wgrad_plan(ctx, g->n_total, g->n_owned, &w);
+  w.T = c.T; w.x = x; w.G = c.G; w.da = da; w.partial = c.partial; w.used = c.maxima + 4;
   w.node_exp[0] = c.node_exp[0]; w.node_exp[1] = c.node_exp[1];
   hipLaunchKernelGGL(so2n_wgrad_kernel, dim3((w.unit0[5] + 3) / 4), dim3(256), 0, st, w);
   EGNN_LAUNCH_CHECK(ctx, "so2n_wgrad_kernel");
   const long n_wp = (long)s.k_first[lmax + 1] * E;
   hipLaunchKernelGGL(so2n_wgrad_sum_kernel, dim3((unsigned)((n_wp + 255) / 256)), dim3(256), 0, st, w, s, lmax, scale, c.dwpath);
   EGNN_LAUNCH_CHECK(ctx, "so2n_wgrad_sum_kernel");
-  const long n_un = (long)s.off[5] + (long)E * ctx->desc.n_rbf;
-  hipLaunchKernelGGL(so2n_unpack_wgrad_kernel, dim3((unsigned)((n_un + 255) / 256)), dim3(256), 0, st, c.dwpath, s, lmax, E,
+  const long un_blocks = ((long)s.off[5] + 255) / 256 + ((long)E * ctx->desc.n_rbf + 3) / 4;
+  hipLaunchKernelGGL(so2n_unpack_wgrad_kernel, dim3((unsigned)un_blocks), dim3(256), 0, st, c.dwpath, s, lmax, E,
                      ctx->desc.n_rbf, W, W_e, dW, dW_e);
   EGNN_LAUNCH_CHECK(ctx, "so2n_unpack_wgrad_kernel");
-  p.ptr = col_ptr; p.perm = perm; p.index = g->dst;
-  p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_owned); p.x_self = da;
   So2nCall c2 = c;
-  c2.t_max = p.t_max = c.t_max + g->n_owned;
-  p.j_end = g->n_total;
-  if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
+  c2.t_max = p.t_max;
   if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_PLAIN, true, c2, st))) return rc;
   return so2n_launch_mix(ctx, c2, SO2N_PLAIN, g->n_total, scale, dx, st);
 }
@@ -1439,7 +1450,7 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
 int so2n_message_sum(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* x, const float* W_e, const float* W,
                      float scale, float* a, const So2nCall& c, hipStream_t st) {
   int rc;
-  if ((rc = so2n_pack_features(ctx, x, g->n_total, nullptr, c, st))) return rc;
+  if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
   if ((rc = so2n_pack_weights(ctx, W, W_e, SO2N_GAUSS, false, c, st))) return rc;
   So2nArgs p = {};
   p.ptr = g->row_ptr; p.index = g->src; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
@@ -1457,7 +1468,7 @@ int so2n_node_block(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, con
                     const float* w_att, float* alpha, float* a, const So2nCall& c, hipStream_t st) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   int rc;
-  if ((rc = so2n_pack_features(ctx, x, g->n_total, nullptr, c, st))) return rc;
+  if ((rc = so2n_pack_features(ctx, x, g->n_total, c, st))) return rc;
   if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_EDGES, false, c, st))) return rc;
   const size_t lds = std::max<size_t>(32 * (size_t)((lmax + 1) * E + 4) * 4, 16384);
   const dim3 grid((unsigned)((g->n_edges + 31) / 32));
