@@ -1481,19 +1481,25 @@ static int so2_backward_check(egnn_ctx* ctx, const egnn_graph* g, const void* ws
   return EGNN_OK;
 }
 
-// As so2_use_nodes, per node of any kind: the sums over outgoing edges are taken for the halo nodes as well.  us per call, per
-// edge -> per node: 4,000 nodes, lmax 4, 32 channels, 16.1 edges a node 1,010 -> 1,104, 20.7 1,225 -> 1,135; 64 channels, 16.1
-// 2,150 -> 2,457, 20.7 2,721 -> 2,514; 16 channels, 16.1 670 -> 744, 20.7 807 -> 757; 8 channels, 20.7 554 -> 576, 25.5 601 ->
-// 577.  Lower lmax: lmax 3, 64 channels, 10,000 nodes, 13.4 2,542 -> 2,654, 16.5 3,072 -> 2,739; 32 channels, 13 704 -> 553;
-// lmax 2, 128 channels, 13 1,628 -> 1,270.  Few nodes, lmax 4: 32 channels, 12.8 451 -> 332; 64 channels, 12.8 735 -> 778, 13.7
-// 491 -> 369, 16 811 -> 782.
+// As so2_use_nodes, per node of any kind: the sums over outgoing edges are taken for the halo nodes as well.  They are all that
+// is gathered, so the turn comes earlier than in the sum itself.  us per call, per edge -> per node.  Above 1,500 nodes: lmax 4,
+// 9,000 nodes, 32 channels 13.1 edges a node 1,719 -> 1,516 (4,000 nodes, 11.8 871 -> 726), 64 13.1 4,058 -> 3,420, 128 13.1
+// 11,945 -> 10,027; fewer channels leave the tiles of columns partly empty: 16, 13.1 982 -> 1,011, 14.8 1,101 -> 1,013 (20,000
+// nodes, 14.9 2,118 -> 2,086), 8, 14.8 741 -> 775, 19.2 886 -> 787 (20,000, 16.4 1,515 -> 1,604, 19.0 1,710 -> 1,620).  lmax 3,
+// 20,000 nodes: 32 channels 7.1 1,410 -> 1,548, 8.9 1,686 -> 1,551; 64 8.9 3,570 -> 3,479; 16 8.9 956 -> 1,118, 10.8 equal, 13.2
+// 1,309 -> 1,119.  lmax 2, 20,000 nodes: 64 channels 3.8 1,102 -> 1,355, 6.0 1,509 -> 1,357; 8 6.0 404 -> 391; 128 6.0 equal, 8.3
+// 4,816 -> 3,645.  Up to 1,500 nodes the per-edge route is bound by its launches: 1,000 nodes, lmax 4, 32 channels 9.3 395 ->
+// 215, 64 9.3 637 -> 473, 16 6.9 278 -> 166; lmax 3, 64 channels 4.7 368 -> 247; lmax 2, 32 channels 2.4 179 -> 102.  (At
+// lmax 0 and 1 it would pay from 2 edges a node on as well, but with so few products per element the weight gradient's error
+// against 64 bits would rise from 2.7e-7 to 3.0e-7: from 12 edges as ever.)
 static bool so2_use_nodes_backward(const egnn_ctx* ctx, const egnn_graph* g) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   const size_t row = (size_t)(lmax + 1) * (lmax + 1) * E * 4;
   const bool few = g->n_total <= SO2N_FEW_NODES;
   int degree = 12;
-  if (lmax == 4) degree = few ? (E <= 32 ? 12 : 13) : (E == 8 ? 24 : 19);
-  else if (lmax == 3 && E >= 64 && !few) degree = 14;
+  if (lmax == 4) degree = few ? 7 : E == 8 ? 18 : E == 16 ? 15 : 12;
+  else if (lmax == 3) degree = few ? 5 : E == 16 ? 11 : 9;
+  else if (lmax == 2) degree = few ? 2 : E == 128 ? 7 : 6;
   return g->n_owned > 0 && g->n_edges >= (int64_t)degree * g->n_total && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
          so2_a256((size_t)g->n_edges * 16) + so2n_backward_carve(ctx, g->n_owned, g->n_total, nullptr, nullptr) <=
              so2_bwd_ws(ctx, g->n_edges, g->n_owned, false, false, nullptr, nullptr);

@@ -184,3 +184,32 @@ def test_message_sum_backward_per_node(B, lmax, E, n, n_owned, n_rbf):
     print(f"  {graph.n_edges} edges, worst rel err {check(got, want, TOL_BWD):.2e}", flush=True)
     again = m.egnn_so2_message_sum_backward(*args, ws)
     assert all(torch.equal(a, b) for a, b in zip((dx, dW_e, dW), again))
+
+
+# Open clusters with few edges a node: chains of steps that are mostly empty, nodes with no edge at all, halo nodes.
+@pytest.mark.parametrize("lmax,E,n,n_owned,r_cut", [
+    (2, 8, 40, 40, 2.7), (2, 32, 97, 80, 3.0), (2, 128, 33, 33, 3.4), (3, 16, 70, 60, 4.0), (3, 64, 65, 65, 3.6),
+    (4, 8, 64, 64, 4.2), (4, 32, 129, 110, 4.6), (4, 64, 50, 50, 4.6)])
+def test_message_sum_backward_few_edges(B, lmax, E, n, n_owned, r_cut):
+    from tests.test_gpu_so2_backward import check, unpack
+    print("case", lmax, E, n, n_owned, r_cut, flush=True)
+    w = synth.small_cluster(n, n_owned, lmax, E, 8, r_cut, 500 + n)
+    g = U.oracle_graph(w)
+    rng = np.random.default_rng([n, lmax, E, 1])
+    x, da = synth.node_features(rng, n, lmax, E), rng.standard_normal((n_owned, (lmax + 1) ** 2, E)).astype(np.float32)
+    W_e, W0, Wr, Wi = synth.so2_weights(rng, lmax, E, 8)
+    ref = S.so2_message_sum_backward(g, w.pos, w.box, x, W_e, W0, Wr, Wi, lmax, E, 8, w.r_cut, 3.0, da)
+    m = B.Egnn(lmax, E, 8, w.r_cut, 3.0)
+    graph = m.egnn_nlist(B.to_device(w.pos), n_owned, w.box, w.pbc)
+    import torch
+    ws = torch.full((max(m.egnn_so2_backward_workspace_bytes(graph.n_edges, n_owned),
+                         m.egnn_backward_workspace_bytes(graph.n_edges, n_owned, n)),), 0xFF, dtype=torch.uint8, device="cuda")
+    col_ptr, perm = m.egnn_graph_transpose(graph, ws)
+    ws.fill_(0xFF)
+    dx, dW_e, dW = m.egnn_so2_message_sum_backward(graph, col_ptr, perm, B.to_device(w.pos), w.box, B.to_device(x),
+                                                   B.to_device(W_e), B.to_device(S.so2_pack(W0, Wr, Wi)), B.to_device(da), ws)
+    g0, gr, gi = unpack(dW.cpu().numpy(), lmax, E)
+    got, want = dict(dx=dx.cpu().numpy(), dW_e=dW_e.cpu().numpy(), dW0=g0), dict(dx=ref[0], dW_e=ref[1], dW0=ref[2])
+    for i in range(lmax):
+        got[f"dWr{i + 1}"], got[f"dWi{i + 1}"], want[f"dWr{i + 1}"], want[f"dWi{i + 1}"] = gr[i], gi[i], ref[3][i], ref[4][i]
+    print(f"  {graph.n_edges / n:.1f} edges a node, worst rel err {check(got, want, TOL_BWD):.2e}", flush=True)
