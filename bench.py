@@ -266,7 +266,7 @@ def run_config(args, index, extras):
     ms, n_calls = m.egnn_timing_read()
     m.egnn_timing_enable(0)
 
-    # ---- the same step with the radial weights stored in half precision between S3 and S4 / S6 (a reduced-precision
+    # ---- the same step with the radial weights rounded to half precision before S4 / S6 use them (a reduced-precision
     #      option; reported next to `value`, never as `value`) ----
     w_fp16 = None
     if not args.forward_only:
@@ -290,7 +290,7 @@ def run_config(args, index, extras):
                       note="EGNN_OPT_W_FP16: only the per-edge path weights w are rounded to half precision (once); node "
                            "features, gathered rows and H stay fp32, products and sums fp32; not the fp32 figure")
 
-    # ---- the same fp32 step with S3 and S4 as one kernel whose radial weights never leave the registers
+    # ---- the same fp32 step with the older of the two kernels whose radial weights never leave the registers
     #      (EGNN_OPT_FUSED = 2); reported next to the main figure unless --fused already selected a fused route ----
     fused_lane = None
     if args.fused == 0 and not args.forward_only:
@@ -315,9 +315,8 @@ def run_config(args, index, extras):
         fused_lane = dict(ms_per_step=1e3 * dtfl, steps=nfl, edge_layer_evaluations_per_s=n_edges * w.n_layers / dtfl,
                           s3_s4_kernel_ms=layer_fl, edges_per_s=n_edges / (layer_fl * 1e-3),
                           f16_mfma_TFLOPs=mfma_flop / (layer_fl * 1e-3) / 1e12, f16_mfma_peak_TFLOPs=2500.0,
-                          note="EGNN_OPT_FUSED = 2: radial weights produced on the matrix cores in the registers of the "
-                               "lane that consumes them, no weight tensor in memory; bound by matrix-core plus vector "
-                               "work of the same SIMD, not by HBM")
+                          note="EGNN_OPT_FUSED = 2, an older kernel than the default's: tiles of 32 edges, no weight tensor in "
+                               "memory either; bound by matrix-core plus vector work of the same SIMD, not by HBM")
 
     # ---- S7: training step on the same graph and model (config 5 when the workload is config 3) ----
     training = None
@@ -636,14 +635,39 @@ def run_config(args, index, extras):
         return d
 
     n_ro = 1 if w.readout else 0
-    s3_ms = (layer_ms["radial_weights"] * n_calls[0] + ro_ms["radial_weights"] * n_calls[1]) / max(1, sum(n_calls))
-    roofs = [hbm_roof("tp_segsum_kernel", s4_min, layer_ms["tp_segsum"], w.n_layers, table_bytes=s4_bytes),
-             hbm_roof("radial_weights_kernel", s3_bytes, s3_ms, w.n_layers + n_ro,
-                      mfma_TFLOPs=s3_flops / (s3_ms * 1e-3) / 1e12, mfma_peak_TFLOPs_f16=2500.0,
-                      note="fp32-equivalent rate; the contraction runs on the f16 matrix cores with both operands "
-                           "cut into two half-precision pieces (3 products per fp32 product, 3 x this rate in f16 work)")]
-    if w.readout:
-        roofs.append(hbm_roof("readout_kernel", s6_min, ro_ms["readout"], 1, table_bytes=s6_bytes))
+
+    def mfma_roof(kernel, n_paths, avg_ms, calls_per_step, nbytes):
+        """The kernels that make the radial weights in the registers of their consumer: the half-precision work of the
+        contraction (three piece products per fp32 product, every edge of its own) against the dense f16 rate, and the
+        bytes they have to move at least beside it."""
+        t = avg_ms * 1e-3
+        flops = 3.0 * 2.0 * 64 * n_paths * w.channels * n_edges
+        return dict(kernel=kernel, bound="f16 matrix cores + vector ALU of the same SIMD", achieved=flops / t / 1e12,
+                    peak=2500.0, unit="TFLOP/s", frac=flops / t / 1e12 / 2500.0, traffic=None, frac_traffic=None,
+                    avg_ms=avg_ms, flops_per_launch=flops, bytes_per_launch=nbytes, hbm_GBs=nbytes / t / 1e9,
+                    hbm_frac=nbytes / t / 1e9 / HBM_PEAK_GBS, launches_per_step=calls_per_step,
+                    ms_per_step=avg_ms * calls_per_step, edges_per_s=n_edges / t,
+                    bytes_counted="hidden activations (256 bytes a weight row), rotation, indices, every node row once, "
+                                  "outputs; no weight tensor")
+
+    # the default route of these configurations has no weight tensor (S3 + S4 and S3 + S6 in one kernel each)
+    if args.fused == 0 and w.lmax >= 2:
+        edge = n_rows * (256 + 8) + n_edges * 24
+        node = 4 * (w.lmax + 1) ** 2 * w.channels
+        roofs = [mfma_roof("ef_layer_kernel", m.n_paths, layer_ms["tp_segsum"], w.n_layers,
+                           edge + (w.n_total + w.n_owned) * node)]
+        if w.readout:
+            roofs.append(mfma_roof("rf_kernel", m.n_paths_readout, ro_ms["readout"], 1,
+                                   edge + 2 * w.n_total * node + n_edges * 4 * w.n_orb ** 2))
+    else:
+        s3_ms = (layer_ms["radial_weights"] * n_calls[0] + ro_ms["radial_weights"] * n_calls[1]) / max(1, sum(n_calls))
+        roofs = [hbm_roof("tp_segsum_kernel", s4_min, layer_ms["tp_segsum"], w.n_layers, table_bytes=s4_bytes),
+                 hbm_roof("radial_weights_kernel", s3_bytes, s3_ms, w.n_layers + n_ro,
+                          mfma_TFLOPs=s3_flops / (s3_ms * 1e-3) / 1e12, mfma_peak_TFLOPs_f16=2500.0,
+                          note="fp32-equivalent rate; the contraction runs on the f16 matrix cores with both operands "
+                               "cut into two half-precision pieces (3 products per fp32 product, 3 x this rate in f16 work)")]
+        if w.readout:
+            roofs.append(hbm_roof("readout_kernel", s6_min, ro_ms["readout"], 1, table_bytes=s6_bytes))
     roofs.sort(key=lambda r: -r["ms_per_step"])
     dominant, other = roofs[0], roofs[1:]
 

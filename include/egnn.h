@@ -205,22 +205,23 @@ int egnn_tp_segsum_f16h(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d,
 int egnn_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, const float* x2, const float* W2,
                   float* y, int32_t n_nodes, void* stream);
 
-/* Options.  EGNN_OPT_FUSED (default 0): when 1 or 2, egnn_layer_forward with its own radial MLP, a power of two >= 8
- * channels and at most 32 radial bases produces and consumes the radial weights inside one kernel (they are never
- * written to memory); when 0 it goes through the materialised weight tensor (S3 then S4), as it always does for
- * caller-supplied weights, for the _save calls and for shapes the chosen kernel does not support.  All routes compute
- * the same function.  1: producer and consumer waves hand the weights over through LDS (needs lmax >= 1).
- * 2: transposed matrix-core tiles put the weights of one (edge, channel) into the registers of the lane that consumes
- * them (needs its LDS tiles to fit: up to 128 channels at lmax 4); its contraction cuts the operands into two
- * half-precision pieces with scalings taken from W_r1 and W_r2 on the device, as accurate as the default route for
- * any finite weights.  At 32 channels route 2 takes about 8 % less time than the two kernels of the default route, at
- * 64 channels about 10-15 % less; route 1 is slower than both. */
+/* Options.  EGNN_OPT_FUSED (default 0): how egnn_layer_forward with its own radial MLP gets from the radial weights (S3)
+ * to the summed messages (S4).  0: one kernel that makes the weights of an (edge, channel) on the matrix cores in the
+ * registers of the lane that uses them, from lmax 2 on (lmax 1 up to 64 channels); elsewhere, and where the scratch of
+ * a small graph is too little for it, through a weight tensor in the workspace, as always for caller-supplied weights.
+ * 1 and 2 choose older kernels, for a power of two >= 8 channels and at most 32 radial bases; they never write the
+ * weights to memory either and are slower than the default (1: producer and consumer waves hand the weights over
+ * through LDS, needs lmax >= 1; 2: tiles of 32 edges, needs its LDS tiles to fit: up to 128 channels at lmax 4); for
+ * shapes that the chosen kernel does not support the weight tensor is used.  The _save calls take the default kernel for
+ * the sums, whatever the option.  All routes compute the same function and cut the operands of the contraction into two
+ * half-precision pieces with scalings taken from W_r1 and W_r2 on the device (1: three bfloat16 pieces). */
 #define EGNN_OPT_FUSED 1
-/* EGNN_OPT_W_FP16 (default 0): when 1, the radial weights that egnn_layer_forward (two-kernel route, own radial MLP)
- * and egnn_readout_hij pass from S3 to S4 / S6 inside their workspace are stored in half precision, as by
- * egnn_radial_weights_f16; all products and sums stay in fp32.  This halves the dominant memory traffic of both
- * calls at a relative rounding error of 2^-12 per weight: a reduced-precision mode, not covered by the fp32 accuracy
- * statement of the default.  Caller-supplied w_edge and the reverse pass always use fp32 weights. */
+/* EGNN_OPT_W_FP16 (default 0): when 1, egnn_layer_forward (option FUSED 0, own radial MLP) and egnn_readout_hij round the
+ * radial weights to half precision, as by egnn_radial_weights_f16, before S4 / S6 use them; all products and sums stay
+ * in fp32.  Where the weights pass through the workspace this halves the dominant memory traffic; where one kernel makes
+ * and uses them they are rounded in registers.  The relative rounding error is 2^-12 per weight: a reduced-precision
+ * mode, not covered by the fp32 accuracy statement of the default.  Caller-supplied w_edge and the reverse pass always
+ * use fp32 weights. */
 #define EGNN_OPT_W_FP16 2
 /* EGNN_OPT_RADIAL_BWD (default 0): how egnn_layer_backward / egnn_readout_backward (and their _saved forms) turn the
  * gradient dw of the radial weights into dW_r1 and dW_r2.  1: two contractions on the matrix cores, each streaming dw.
@@ -232,13 +233,14 @@ int egnn_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, const float* 
 #define EGNN_OPT_RADIAL_BWD 3
 int egnn_set_option(egnn_ctx* ctx, int32_t option, int32_t value);
 
-/* ---- one message-passing layer, forward: S2 -> S5(pre) -> S3+S4 fused (or S3 -> S4) -> S5(post) ----
+/* ---- one message-passing layer, forward: S2 -> S5(pre) -> S3+S4 in one kernel (or S3 -> S4) -> S5(post) ----
  * x_out[j] = W_post a_j + W_self x_in[j] for j < n_owned, with h = W_pre x_in.  x_in has n_total rows;
  * x_out has n_owned rows (may be NULL if n_owned is 0) and must not alias x_in.  If w_edge != NULL ([n_edges][P][channels]) it is used as
  * the radial weights (W_r1, W_r2 ignored).  ws: at least egnn_workspace_bytes(...) bytes, 256-byte aligned.
  * The call enqueues kernels only (no copies, no memsets, no host synchronisation; box is read on the host at call
- * time), so a stack of layers may be recorded into a graph by stream capture and replayed (tested); egnn_readout_hij
- * uploads its index tables with asynchronous copies from context memory and is not meant to be recorded. */
+ * time), so a stack of layers may be recorded into a graph by stream capture and replayed (tested); egnn_readout_hij,
+ * where it goes through a weight tensor, uploads its index tables with asynchronous copies from context memory and is
+ * not meant to be recorded. */
 int egnn_layer_forward(egnn_ctx* ctx, const egnn_graph* g, const float* pos, const float box[3],
                        const float* x_in, const float* W_pre, const float* W_post, const float* W_self,
                        const float* W_r1, const float* W_r2, const float* w_edge, float* x_out,
@@ -286,7 +288,7 @@ int egnn_layer_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t* col_p
 /* Keeping forward quantities instead of recomputing them (a trade of memory for time: at 3,000 atoms the weight
  * tensors of three layers and the readout are 13.5 GB, a few per cent of this GPU's memory; the paper reports 115 GB
  * of saved activations for its training runs at that size, Sec. 4).  egnn_layer_forward_save / egnn_readout_hij_save
- * compute exactly what egnn_layer_forward (own radial MLP, route through the materialised fp32 weight tensor) /
+ * compute exactly what egnn_layer_forward (own radial MLP, option FUSED 0, fp32 weights) /
  * egnn_readout_hij compute and leave the radial weights w_save [n_edges][P][channels] and, for the layer, the summed
  * messages a_save [n_owned][(lmax+1)^2][channels] in caller buffers; egnn_layer_backward_saved /
  * egnn_readout_backward_saved take them back (either may be NULL: then it is recomputed) and give bit-identical
@@ -492,6 +494,8 @@ int egnn_unpack_rows(egnn_ctx* ctx, const void* buf, int32_t n_rows, int32_t hal
  * the record:
  *   ms[0..4]    layer:           geometry, radial weights, pre mix, tensor-product + segmented sum, post mix
  *   ms[5..9]    readout:         geometry, radial weights, source mix, destination mix, product + collapse + uncoupling
+ *               where one kernel makes and uses the radial weights, "radial weights" holds what prepares its operands
+ *               (hidden activations, pieces of W_r2) and the kernel counts under the product
  *   ms[10..14]  layer adjoint:   forward quantities (what is not supplied), adjoint of the post mix + weight
  *                                gradients, adjoint of the messages, adjoint of the pre mix + weight gradient,
  *                                radial MLP
