@@ -213,3 +213,32 @@ def test_message_sum_backward_few_edges(B, lmax, E, n, n_owned, r_cut):
     for i in range(lmax):
         got[f"dWr{i + 1}"], got[f"dWi{i + 1}"], want[f"dWr{i + 1}"], want[f"dWi{i + 1}"] = gr[i], gi[i], ref[3][i], ref[4][i]
     print(f"  {graph.n_edges / n:.1f} edges a node, worst rel err {check(got, want, TOL_BWD):.2e}", flush=True)
+
+
+# The rows of the edges are added per source 16 bytes a lane, or 4 where the result does not begin at a multiple of 16: the same
+# sums in the same order.  Segments of 0, 1, 7, 8, 9 ... rows; 32 to 1152 words a row.
+@pytest.mark.parametrize("lmax,E,n,r_cut", [(1, 8, 60, 4.4), (0, 32, 40, 4.0), (1, 64, 33, 4.0), (2, 128, 21, 2.3), (1, 16, 11, 9.0)])
+def test_sums_over_outgoing_edges_alignment(B, lmax, E, n, r_cut):
+    import ctypes as C
+    import torch
+    print("case", lmax, E, n, r_cut, flush=True)
+    w = synth.small_cluster(n, n, lmax, E, 6, r_cut, 700 + n)
+    rng = np.random.default_rng([n, lmax, E, 2])
+    D = (lmax + 1) ** 2
+    x, da = (B.to_device(rng.standard_normal((n, D, E)).astype(np.float32)) for _ in range(2))
+    W_e, W0, Wr, Wi = synth.so2_weights(rng, lmax, E, 6)
+    W_e, W = B.to_device(W_e), B.to_device(S.so2_pack(W0, Wr, Wi))
+    m = B.Egnn(lmax, E, 6, w.r_cut, 3.0)
+    pos = B.to_device(w.pos)
+    graph = m.egnn_nlist(pos, n, w.box, w.pbc)
+    ws = torch.empty((max(m.egnn_so2_backward_workspace_bytes(graph.n_edges, n),
+                          m.egnn_backward_workspace_bytes(graph.n_edges, n, n)),), dtype=torch.uint8, device="cuda")
+    col_ptr, perm = m.egnn_graph_transpose(graph, ws)
+    dx = m.egnn_so2_message_sum_backward(graph, col_ptr, perm, pos, w.box, x, W_e, W, da, ws)[0]
+    room = torch.full((n * D * E + 2,), float("nan"), dtype=torch.float32, device="cuda")
+    dW_e, dW, g = torch.empty_like(W_e), torch.empty_like(W), graph.desc()
+    m._check(m.lib.egnn_so2_message_sum_backward(
+        m.ctx, C.byref(g), B._ptr(col_ptr), B._ptr(perm), B._ptr(pos), B._f3(w.box), B._ptr(x), B._ptr(W_e), B._ptr(W),
+        B._ptr(da), B._ptr(room[1:]), B._ptr(dW_e), B._ptr(dW), B._ptr(ws), C.c_size_t(ws.numel()), B._stream()))
+    assert torch.equal(room[1:-1].view_as(dx), dx)
+    assert torch.isnan(room[0]) and torch.isnan(room[-1])
