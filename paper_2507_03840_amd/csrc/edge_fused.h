@@ -47,17 +47,16 @@ static inline EfScratch egnn_ef_carve(const egnn_ctx* ctx, const egnn_graph* g, 
 }
 
 bool egnn_edge_fused_fits(const egnn_ctx*, const egnn_graph*);
-// the steps one by one (scratch: as large as a weight tensor in fp32, one row per edge) ...
+// the steps one by one (scratch: as large as a weight tensor in fp32, one row per edge).
+// For a call that needs a weight tensor as well, the steps leave what S3 and the reverse pass read, so that nothing is prepared twice:
+// rhat_d (as egnn_launch_geometry writes it), w2s (for egnn_launch_radial_prepared, with rec), h in rows; each may be NULL.
 int egnn_launch_edge_fused_first(egnn_ctx*, const egnn_graph*, int which, const float* pos, const float box[3],
-                                 const float* W_r1, const float* W_r2, void* scratch, hipStream_t);
+                                 const float* W_r1, const float* W_r2, void* scratch, hipStream_t, float* rhat_d = nullptr);
 int egnn_launch_edge_fused_second(egnn_ctx*, const egnn_graph*, int which, const float* W_r1, const float* W_r2, void* scratch,
-                                  hipStream_t);
+                                  hipStream_t, void* w2s = nullptr);
 int egnn_launch_edge_fused_features(egnn_ctx*, const egnn_graph*, const float* x_in, const float* W_pre, void* scratch,
-                                    hipStream_t);
+                                    hipStream_t, float* h = nullptr);
 int egnn_launch_edge_fused_sum(egnn_ctx*, const egnn_graph*, void* scratch, float* a, bool half, hipStream_t);
-// ... and all of them: a = the summed messages
-int egnn_launch_edge_fused(egnn_ctx*, const egnn_graph*, const float* pos, const float box[3], const float* x_in,
-                           const float* W_pre, const float* W_r1, const float* W_r2, void* scratch, float* a, hipStream_t);
 
 // S3 + S6 in one kernel (readout_fused.hip), from the same preparation with which = 1
 bool egnn_readout_fused_fits(const egnn_ctx*, const egnn_graph*);

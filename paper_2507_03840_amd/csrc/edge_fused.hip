@@ -29,6 +29,7 @@
 #include "egnn_internal.h"
 #include "bond_frame.h"
 #include "half_scales.h"
+#include "edge_vector.h"
 #include "edge_fused.h"
 
 __device__ __forceinline__ uint4 ef_pack8(const float (&x)[8], uint4& lo) {
@@ -57,6 +58,7 @@ struct EfFirst {
   float4* frame;
   float2* length;
   float* scales;
+  float4* rhat_d;                 // may be NULL (see edge_fused.h)
   float r_cut;
   double bx, by, bz;
   long n_edges;
@@ -71,22 +73,14 @@ __global__ __launch_bounds__(256) void ef_first_kernel(EfFirst g) {
   }
   const long k = (long)blockIdx.x * 256 + threadIdx.x;
   if (k >= g.n_edges) return;
-  const int i = g.src[k], j = g.dst[k];
-  double dx = (double)g.pos[3 * i + 0] - (double)g.pos[3 * j + 0];
-  double dy = (double)g.pos[3 * i + 1] - (double)g.pos[3 * j + 1];
-  double dz = (double)g.pos[3 * i + 2] - (double)g.pos[3 * j + 2];
-  if (g.shift) {
-    dx += (double)g.shift[3 * k + 0] * g.bx;
-    dy += (double)g.shift[3 * k + 1] * g.by;
-    dz += (double)g.shift[3 * k + 2] * g.bz;
-  }
-  const double rho2 = dx * dx + dy * dy, d = sqrt(rho2 + dz * dz);
-  const double inv = 1.0 / d, rho = sqrt(rho2);
-  const bool polar = rho <= 1e-15 * d;                  // (the azimuth is free there)
+  const EdgeVector v = egnn_edge_vector(g.pos, g.shift, k, g.src[k], g.dst[k], g.bx, g.by, g.bz);
+  const double inv = 1.0 / v.d, rho = sqrt(v.rho2);
+  const bool polar = rho <= 1e-15 * v.d;                // (the azimuth is free there)
   const double irho = polar ? 0.0 : 1.0 / rho;
-  g.frame[k] = make_float4(polar ? 1.0f : (float)(dx * irho), (float)(dy * irho), (float)(dz * inv), (float)(rho * inv));
+  g.frame[k] = make_float4(polar ? 1.0f : (float)(v.x * irho), (float)(v.y * irho), (float)(v.z * inv), (float)(rho * inv));
   const int r = g.w_row ? g.w_row[k] : (int)k;
-  if (r >= 0) g.length[r] = make_float2((float)d, egnn_envelope((float)d, g.r_cut));
+  if (r >= 0) g.length[r] = make_float2((float)v.d, egnn_envelope((float)v.d, g.r_cut));
+  if (g.rhat_d) g.rhat_d[k] = egnn_edge_record(v, inv);
 }
 
 // Second preparation: both operands of the radial contraction, scaled and cut into two half-precision pieces.  The contraction
@@ -96,7 +90,7 @@ __global__ __launch_bounds__(256) void ef_first_kernel(EfFirst g) {
 //        4 tile + m % 4, channel 4 group + m / 4
 // A thread takes an octet of units of two rows, W_r1 from LDS.  (With the fp32 products on
 // the matrix cores the weights came out less exact: their gradient summed over all edges was off by 2.03e-7 instead of 1.69e-7.)
-// The last workgroups write A.
+// The next workgroups write A, the last ones (if w2s) scalings and pieces as S3 takes them.
 struct EfSecond {
   const float2* length;
   const float* W_r1;
@@ -105,9 +99,10 @@ struct EfSecond {
   uint4* rec;
   uint4* A;
   long n_rows;
-  int n_rbf, P, NT, log2E, row_blocks;
+  int n_rbf, P, NT, log2E, row_blocks, a_blocks;
   float r_cut;
   PathAlpha alpha;
+  float* w2s;
 };
 
 __global__ __launch_bounds__(256) void ef_second_kernel(EfSecond g) {
@@ -115,6 +110,13 @@ __global__ __launch_bounds__(256) void ef_second_kernel(EfSecond g) {
   half_scales_of(g.scales, s_w, s_g, inv);
   const int lane = threadIdx.x & 63, n = lane & 15, q = lane >> 4;
   const int ab = (int)blockIdx.x - g.row_blocks;
+  if (ab >= g.a_blocks) {
+    const int i = (ab - g.a_blocks) * 256 + threadIdx.x;
+    if (i == 0) { g.w2s[0] = s_w; g.w2s[1] = s_g; g.w2s[2] = inv; }
+    if (i < (g.P << g.log2E) * EGNN_HIDDEN)
+      half_piece_of_w2(g.W_r2[i], i, s_w, reinterpret_cast<uint16_t*>(g.w2s + 64), g.log2E, g.alpha);
+    return;
+  }
   if (ab >= 0) {
     const int idx = ab * 256 + threadIdx.x;      // [group][tile][step][lane]
     const int ks = (idx >> 6) & 1, tile = (idx >> 7) % g.NT, cg = (idx >> 7) / g.NT;
@@ -457,9 +459,10 @@ static PathAlpha ef_alpha(const egnn_ctx* ctx, int which) {
 }
 
 int egnn_launch_edge_fused_first(egnn_ctx* ctx, const egnn_graph* g, int which, const float* pos, const float box[3],
-                                 const float* W_r1, const float* W_r2, void* scratch, hipStream_t stream) {
+                                 const float* W_r1, const float* W_r2, void* scratch, hipStream_t stream, float* rhat_d) {
   const EfScratch s = egnn_ef_carve(ctx, g, which, scratch);
-  const EfFirst x = {g->src, g->dst, g->shift, pos, g->w_row, W_r1, W_r2, s.frame, s.length, s.scales, ctx->desc.r_cut,
+  const EfFirst x = {g->src, g->dst, g->shift, pos, g->w_row, W_r1, W_r2, s.frame, s.length, s.scales,
+                     reinterpret_cast<float4*>(rhat_d), ctx->desc.r_cut,
                      (double)box[0], (double)box[1], (double)box[2], (long)g->n_edges, ctx->desc.n_rbf,
                      ctx->n_paths[which] * ctx->desc.channels, ctx->log2_channels, ef_alpha(ctx, which)};
   hipLaunchKernelGGL(ef_first_kernel, dim3((unsigned)((g->n_edges + 255) / 256 + HS_BLOCKS)), dim3(256), 0, stream, x);
@@ -468,23 +471,24 @@ int egnn_launch_edge_fused_first(egnn_ctx* ctx, const egnn_graph* g, int which, 
 }
 
 int egnn_launch_edge_fused_second(egnn_ctx* ctx, const egnn_graph* g, int which, const float* W_r1, const float* W_r2,
-                                  void* scratch, hipStream_t stream) {
+                                  void* scratch, hipStream_t stream, void* w2s) {
   const EfScratch s = egnn_ef_carve(ctx, g, which, scratch);
   const long n_rows = g->w_row ? g->n_w_rows : g->n_edges;
   const int NT = ef_tiles(ctx, which), a_blocks = (ctx->desc.channels / 4 * NT * 128 + 255) / 256;
   const long groups = (n_rows + 63) / 64;                // of four wavefronts
   const int row_blocks = (int)(groups < 4 * EGNN_CUS ? groups : 4 * EGNN_CUS);
+  const int w2_blocks = w2s ? (ctx->n_paths[which] * ctx->desc.channels * EGNN_HIDDEN + 255) / 256 : 0;
   const EfSecond x = {s.length, W_r1, W_r2, s.scales, s.rec, s.A, n_rows, ctx->desc.n_rbf, ctx->n_paths[which], NT,
-                      ctx->log2_channels, row_blocks, ctx->desc.r_cut, ef_alpha(ctx, which)};
-  hipLaunchKernelGGL(ef_second_kernel, dim3((unsigned)(row_blocks + a_blocks)), dim3(256), 0, stream, x);
+                      ctx->log2_channels, row_blocks, a_blocks, ctx->desc.r_cut, ef_alpha(ctx, which), (float*)w2s};
+  hipLaunchKernelGGL(ef_second_kernel, dim3((unsigned)(row_blocks + a_blocks + w2_blocks)), dim3(256), 0, stream, x);
   EGNN_LAUNCH_CHECK(ctx, "ef_second_kernel");
   return EGNN_OK;
 }
 
 int egnn_launch_edge_fused_features(egnn_ctx* ctx, const egnn_graph* g, const float* x_in, const float* W_pre, void* scratch,
-                                    hipStream_t stream) {
-  return egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, egnn_ef_carve(ctx, g, 0, scratch).h4, g->n_total, stream, 0,
-                              ef_quads(ctx));
+                                    hipStream_t stream, float* h) {
+  return egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, h, g->n_total, stream, 0,
+                              egnn_ef_carve(ctx, g, 0, scratch).h4, ef_quads(ctx));
 }
 
 int egnn_launch_edge_fused_sum(egnn_ctx* ctx, const egnn_graph* g, void* scratch, float* a, bool half, hipStream_t stream) {
@@ -526,13 +530,4 @@ int egnn_launch_edge_fused_sum(egnn_ctx* ctx, const egnn_graph* g, void* scratch
 #undef KERNEL
   EGNN_LAUNCH_CHECK(ctx, "ef_layer_kernel");
   return EGNN_OK;
-}
-
-int egnn_launch_edge_fused(egnn_ctx* ctx, const egnn_graph* g, const float* pos, const float box[3], const float* x_in,
-                           const float* W_pre, const float* W_r1, const float* W_r2, void* scratch, float* a,
-                           hipStream_t stream) {
-  int rc = egnn_launch_edge_fused_first(ctx, g, 0, pos, box, W_r1, W_r2, scratch, stream);
-  if (!rc) rc = egnn_launch_edge_fused_second(ctx, g, 0, W_r1, W_r2, scratch, stream);
-  if (!rc) rc = egnn_launch_edge_fused_features(ctx, g, x_in, W_pre, scratch, stream);
-  return rc ? rc : egnn_launch_edge_fused_sum(ctx, g, scratch, a, false, stream);
 }

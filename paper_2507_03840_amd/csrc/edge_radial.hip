@@ -8,6 +8,7 @@
 //     registers as the A operand for the whole row.
 #include <algorithm>
 #include "egnn_internal.h"
+#include "edge_vector.h"
 
 // ------------------------------------------------------------------------------------------------ S2
 template <int LSH>
@@ -60,24 +61,14 @@ __global__ __launch_bounds__(256) void edge_geometry_kernel(const int* __restric
                                                             float4* __restrict__ rd_rows) {
   const long k = (long)blockIdx.x * 256 + threadIdx.x;
   if (k >= n_edges) return;
-  const int i = src[k], j = dst[k];
-  double dx = (double)pos[3 * i + 0] - (double)pos[3 * j + 0];
-  double dy = (double)pos[3 * i + 1] - (double)pos[3 * j + 1];
-  double dz = (double)pos[3 * i + 2] - (double)pos[3 * j + 2];
-  if (shift) {
-    dx += (double)shift[3 * k + 0] * bx;
-    dy += (double)shift[3 * k + 1] * by;
-    dz += (double)shift[3 * k + 2] * bz;
-  }
-  const double d = sqrt(dx * dx + dy * dy + dz * dz);
-  const double inv = 1.0 / d;
-  const float x = (float)(dx * inv), y = (float)(dy * inv), z = (float)(dz * inv);
-  const float df = (float)d;
-  rhat_d[k] = make_float4(x, y, z, df);
+  const EdgeVector v = egnn_edge_vector(pos, shift, k, src[k], dst[k], bx, by, bz);
+  const float4 rec = egnn_edge_record(v, 1.0 / v.d);
+  const float x = rec.x, y = rec.y, z = rec.z, df = rec.w;
+  rhat_d[k] = rec;
   // shared rows of radial weights: the edge that owns a row leaves its record (of which only the length is used) there
   if (rd_rows) {
     const int r = w_row[k];
-    if (r >= 0) rd_rows[r] = make_float4(x, y, z, df);
+    if (r >= 0) rd_rows[r] = rec;
   }
   if (Y) {
     constexpr int NY = (LSH + 1) * (LSH + 1);
@@ -139,13 +130,6 @@ int egnn_launch_geometry(egnn_ctx* ctx, const egnn_graph* g, const float* pos, c
 
 typedef _Float16 rw_h8 __attribute__((ext_vector_type(8)));
 __device__ __forceinline__ rw_h8 rw_as_h8(uint4 v) { return __builtin_bit_cast(rw_h8, v); }
-// x -> (hi, lo) half-precision pieces, as raw bits
-__device__ __forceinline__ void rw_split(float x, uint32_t& hi, uint32_t& lo) {
-  const _Float16 h = (_Float16)x;
-  const _Float16 l = (_Float16)(x - (float)h);
-  hi = __builtin_bit_cast(unsigned short, h);
-  lo = __builtin_bit_cast(unsigned short, l);
-}
 
 // scales[0] = s_w, scales[1] = s_g (powers of two, see above), scales[2] = 1 / (s_w s_g).  In two steps: the largest
 // |alpha W_r2| of each of HS_BLOCKS parts and, by the first workgroup, the largest row sum of |W_r1| go to scales[HS_PART ..]
@@ -207,13 +191,7 @@ __global__ __launch_bounds__(256) void split_w2_half_kernel(const float* __restr
   float s_w, s_g, inv;
   half_scales_of(scales, s_w, s_g, inv);
   if (i == 0) { scales[0] = s_w; scales[1] = s_g; scales[2] = inv; }
-  if (i >= PE * EGNN_HIDDEN) return;
-  const int n = i >> 6, j = i & 63;
-  uint32_t hi, lo;
-  rw_split(x * alpha.a[n >> log2E] * s_w, hi, lo);
-  uint16_t* o = out + (size_t)n * 2 * EGNN_HIDDEN + j;
-  o[0] = (uint16_t)hi;
-  o[EGNN_HIDDEN] = (uint16_t)lo;
+  if (i < PE * EGNN_HIDDEN) half_piece_of_w2(x, i, s_w, out, log2E, alpha);
 }
 
 // Workgroup = 8 wavefronts (one per register-file slot of a CU at this kernel's register count).  Waves 0-6 each
@@ -306,21 +284,26 @@ __device__ __forceinline__ void rw_block(const uint4* __restrict__ sB_nb, const 
 }
 
 // HALF: w is stored in half precision (layout of w_half.h), two column blocks per 32-bit word.
-template <bool HALF>
-__global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(const float4* __restrict__ rhat_d, long n_edges,
+// HIDDEN: the operand's pieces come from memory (rec, as ef_second_kernel writes them for the sums as well), rhat_d and W_r1 are
+// not read: 260,000 rows of 352 columns 108 -> 78 us, 24,000 rows 22 -> 12.
+template <bool HALF, bool HIDDEN>
+__global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(const float4* __restrict__ rhat_d,
+                                                             const uint4* __restrict__ rec, long n_edges,
                                                              const float* __restrict__ W_r1,
                                                              const uint16_t* __restrict__ W2s,
                                                              const float* __restrict__ scales,
                                                              float* __restrict__ w, int n_rbf, int PE,
                                                              float r_cut, int rows_per_wave, int split_blocks) {
-  __shared__ float sW1[32 * EGNN_HIDDEN];  // [b][j], n_rbf <= 32
+  __shared__ float sW1[HIDDEN ? 1 : 32 * EGNN_HIDDEN];  // [b][j], n_rbf <= 32
   __shared__ uint4 sB[2][32 * RW_BROW4];
   const int tid = threadIdx.x;
-  for (int i = tid; i < n_rbf * EGNN_HIDDEN; i += RW_THREADS) {
-    const int jj = i & (EGNN_HIDDEN - 1), b = i >> 6;
-    sW1[i] = W_r1[jj * n_rbf + b];
+  if constexpr (!HIDDEN) {
+    for (int i = tid; i < n_rbf * EGNN_HIDDEN; i += RW_THREADS) {
+      const int jj = i & (EGNN_HIDDEN - 1), b = i >> 6;
+      sW1[i] = W_r1[jj * n_rbf + b];
+    }
+    __syncthreads();
   }
-  __syncthreads();
 
   const int lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   // this workgroup's column blocks (few rows: several workgroups share them out, see egnn_launch_radial; an even first one,
@@ -374,6 +357,11 @@ __global__ __launch_bounds__(RW_THREADS, RW_MIN_WG) void radial_weights_kernel(c
     }
     long e = e_base + mb * 32 + m;
     if (e >= n_edges) e = n_edges - 1;
+    if constexpr (HIDDEN) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) a_frag[mb][i >> 2][i & 3] = rec[e * 16 + hh * 8 + i];
+      continue;
+    }
     const float d = rhat_d[e].w;
     float pre[32];
 #pragma unroll
@@ -530,23 +518,13 @@ int egnn_launch_split_w2(egnn_ctx* ctx, int which, const float* W_r2, void* scra
   return EGNN_OK;
 }
 
-// `scratch` holds egnn_radial_ws_bytes: the three scalings (256 bytes), then the half-precision pieces of W_r2.
-int egnn_launch_radial(egnn_ctx* ctx, int which, const float* rhat_d, int64_t n_edges, const float* W_r1,
-                       const float* W_r2, float* w, void* scratch, hipStream_t stream, bool half) {
+// S3 with its preparation done (scratch: see egnn_launch_radial); rec (may be NULL): the hidden layer, too
+static int launch_radial_kernel(egnn_ctx* ctx, int which, const float* rhat_d, const uint4* rec, int64_t n_edges, const float* W_r1,
+                                float* w, const void* scratch, hipStream_t stream, bool half) {
   if (n_edges == 0) return EGNN_OK;
-  const int P = ctx->n_paths[which];
-  const int PE = P * ctx->desc.channels;
-  float* scales = (float*)scratch;
-  uint16_t* W2s = (uint16_t*)((char*)scratch + 256);
-  int rc = launch_half_scales_part(ctx, which, W_r1, W_r2, scales, stream);
-  if (rc) return rc;
-  {
-    PathAlpha al;
-    for (int p = 0; p < EGNN_MAX_PATHS; ++p) al.a[p] = p < P ? ctx->alpha[which][p] : 0.0f;
-    hipLaunchKernelGGL(split_w2_half_kernel, dim3((PE * EGNN_HIDDEN + 255) / 256), dim3(256), 0, stream, W_r2, W2s, PE,
-                       ctx->log2_channels, al, scales);
-    EGNN_LAUNCH_CHECK(ctx, "split_w2_half_kernel");
-  }
+  const int PE = ctx->n_paths[which] * ctx->desc.channels;
+  const float* scales = (const float*)scratch;
+  const uint16_t* W2s = (const uint16_t*)((const char*)scratch + 256);
   // Workgroups: enough for RW_ROWS rows per wave; beyond one round of the 256 CUs their number is rounded up to whole
   // rounds and the edges are spread evenly, so that the last round is as full as the others.
   const long per_wg = (long)RW_ROWS * RW_COMPUTE_WAVES;
@@ -567,15 +545,44 @@ int egnn_launch_radial(egnn_ctx* ctx, int which, const float* rhat_d, int64_t n_
   // there are compute units.  Every share repeats the hidden layer of its rows, and beyond that the stores of all together are
   // what takes the time: 1,387 rows x 176 columns, 4 -> 12 workgroups, 16.5 -> 13.1 us; 53,000 x 736, 119 -> 238: 44 -> 48 us.
   const int n_blocks = (PE + 31) / 32;
-  const long splits = std::max<long>(1, std::min<long>(EGNN_CUS / 2 / n_wg, (n_blocks + 1) / 2));
+  // With the hidden layer from memory nothing is repeated, and while w is small the shares go up to all compute units: 6,700 rows x
+  // 1,344, 15 -> 105 -> 210 workgroups, 18 -> 13 us; 24,000 x 352 (33 MB) 13.0 -> 11.9; but 47,000 x 704 (134 MB) 6 us slower.
+  const long most = rec && (size_t)n_edges * PE * sizeof(float) <= ((size_t)48 << 20) ? EGNN_CUS : EGNN_CUS / 2;
+  const long splits = std::max<long>(1, std::min<long>(most / n_wg, (n_blocks + 1) / 2));
   const int split_blocks = (int)(((n_blocks + splits - 1) / splits + 1) / 2 * 2);
   dim3 grid((unsigned)n_wg, (unsigned)((n_blocks + split_blocks - 1) / split_blocks)), block(RW_THREADS);
-  if (half)
-    hipLaunchKernelGGL(radial_weights_kernel<true>, grid, block, 0, stream, reinterpret_cast<const float4*>(rhat_d),
-                       (long)n_edges, W_r1, W2s, scales, w, ctx->desc.n_rbf, PE, ctx->desc.r_cut, rows_per_wave, split_blocks);
-  else
-    hipLaunchKernelGGL(radial_weights_kernel<false>, grid, block, 0, stream, reinterpret_cast<const float4*>(rhat_d),
-                       (long)n_edges, W_r1, W2s, scales, w, ctx->desc.n_rbf, PE, ctx->desc.r_cut, rows_per_wave, split_blocks);
+#define KERNEL(HALF, HIDDEN)                                                                                              \
+  hipLaunchKernelGGL((radial_weights_kernel<HALF, HIDDEN>), grid, block, 0, stream, reinterpret_cast<const float4*>(rhat_d), \
+                     rec, (long)n_edges, W_r1, W2s, scales, w, ctx->desc.n_rbf, PE, ctx->desc.r_cut,          \
+                     rows_per_wave, split_blocks)
+  if (half) KERNEL(true, false);
+  else if (rec) KERNEL(false, true);
+  else KERNEL(false, false);
+#undef KERNEL
   EGNN_LAUNCH_CHECK(ctx, "radial_weights_kernel");
   return EGNN_OK;
+}
+
+// `scratch` holds egnn_radial_ws_bytes: the three scalings (256 bytes), then the half-precision pieces of W_r2.
+int egnn_launch_radial(egnn_ctx* ctx, int which, const float* rhat_d, int64_t n_edges, const float* W_r1,
+                       const float* W_r2, float* w, void* scratch, hipStream_t stream, bool half) {
+  if (n_edges == 0) return EGNN_OK;
+  const int P = ctx->n_paths[which];
+  const int PE = P * ctx->desc.channels;
+  float* scales = (float*)scratch;
+  int rc = launch_half_scales_part(ctx, which, W_r1, W_r2, scales, stream);
+  if (rc) return rc;
+  {
+    PathAlpha al;
+    for (int p = 0; p < EGNN_MAX_PATHS; ++p) al.a[p] = p < P ? ctx->alpha[which][p] : 0.0f;
+    hipLaunchKernelGGL(split_w2_half_kernel, dim3((PE * EGNN_HIDDEN + 255) / 256), dim3(256), 0, stream, W_r2,
+                       (uint16_t*)((char*)scratch + 256), PE, ctx->log2_channels, al, scales);
+    EGNN_LAUNCH_CHECK(ctx, "split_w2_half_kernel");
+  }
+  return launch_radial_kernel(ctx, which, rhat_d, nullptr, n_edges, W_r1, w, scratch, stream, half);
+}
+
+int egnn_launch_radial_prepared(egnn_ctx* ctx, int which, int64_t n_rows, const void* rec, float* w, const void* scratch,
+                                hipStream_t stream) {
+  return launch_radial_kernel(ctx, which, nullptr, (const uint4*)rec, n_rows, nullptr, w, scratch, stream, false);
 }

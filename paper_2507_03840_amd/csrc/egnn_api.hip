@@ -354,8 +354,8 @@ extern "C" int egnn_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, co
 }
 
 // ---- composite entry points ----------------------------------------------------------------------
-// w_save / a_save (may be NULL): caller buffers that receive the weight tensor and the summed messages instead of the
-// workspace (then the route through the materialised fp32 weights is taken whatever the options say)
+// w_save / a_save (both or neither NULL): caller buffers that receive the fp32 weight tensor and the summed messages.  Then options
+// FUSED and W_FP16 are not looked at: the sums are those of a call that does not save with both options 0, to the bit.
 static int layer_forward_impl(egnn_ctx* ctx, const egnn_graph* g, const float* pos, const float box[3],
                               const float* x_in, const float* W_pre, const float* W_post, const float* W_self,
                               const float* W_r1, const float* W_r2, const float* w_edge, float* x_out, float* w_save,
@@ -391,14 +391,18 @@ static int layer_forward_impl(egnn_ctx* ctx, const egnn_graph* g, const float* p
   StageTimer tm(ctx, st, 0);
   // Default: S3 and S4 in one kernel, where that is the faster way
   const bool in_one = with_w && (saving || ctx->use_fused == 0) && egnn_edge_fused_fits(ctx, g);
-  if (in_one && !saving) {
-    if ((rc = egnn_launch_edge_fused_first(ctx, g, 0, pos, box, W_r1, W_r2, w, st))) return rc;
+  if (in_one) {
+    // (saving: S3 writes the weight tensor for the reverse pass from what was prepared for the sums)
+    if ((rc = egnn_launch_edge_fused_first(ctx, g, 0, pos, box, W_r1, W_r2, scratch, st))) return rc;
     tm.mark(0);
-    if ((rc = egnn_launch_edge_fused_second(ctx, g, 0, W_r1, W_r2, w, st))) return rc;
+    if ((rc = egnn_launch_edge_fused_second(ctx, g, 0, W_r1, W_r2, scratch, st, saving ? w2s : nullptr))) return rc;
+    if (saving && (rc = egnn_launch_radial_prepared(ctx, 0, shared ? g->n_w_rows : g->n_edges,
+                                                    egnn_ef_carve(ctx, g, 0, scratch).rec, w, w2s, st)))
+      return rc;
     tm.mark(1);
-    if ((rc = egnn_launch_edge_fused_features(ctx, g, x_in, W_pre, w, st))) return rc;
+    if ((rc = egnn_launch_edge_fused_features(ctx, g, x_in, W_pre, scratch, st))) return rc;
     tm.mark(2);
-    if ((rc = egnn_launch_edge_fused_sum(ctx, g, w, a, ctx->w_half, st))) return rc;
+    if ((rc = egnn_launch_edge_fused_sum(ctx, g, scratch, a, !saving && ctx->w_half, st))) return rc;
     tm.mark(3);
     rc = egnn_launch_node_mix(ctx, a, W_post, x_in, W_self, x_out, g->n_owned, st);
     tm.mark(4);
@@ -420,13 +424,9 @@ static int layer_forward_impl(egnn_ctx* ctx, const egnn_graph* g, const float* p
       return rc;
   }
   tm.mark(1);
-  if (!in_one && (rc = egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, h, g->n_total, st))) return rc;
+  if ((rc = egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, h, g->n_total, st))) return rc;
   tm.mark(2);
-  if (in_one) {
-    // (saving: the sums are those of the call that does not save, to the bit; the weight tensor is for the reverse pass.  Measured at
-    // 3,000 atoms: no slower than S4 with its reads of that tensor)
-    if ((rc = egnn_launch_edge_fused(ctx, g, pos, box, x_in, W_pre, W_r1, W_r2, scratch, a, st))) return rc;
-  } else if (fused_lane) {
+  if (fused_lane) {
     if ((rc = egnn_launch_layer_fused_lane(ctx, g, rhat_d, h, W_r1, W_r2, w, w_bytes, a, st))) return rc;
   } else if (fused) {
     if ((rc = egnn_launch_layer_fused(ctx, g, rhat_d, h, W_r1, w2s, w, w_bytes, a, st))) return rc;
@@ -487,23 +487,18 @@ static int readout_hij_impl(egnn_ctx* ctx, const egnn_graph* g, const float* pos
   if (w_save) w = w_save;
 
   StageTimer tm(ctx, st, 1);
-  // S3 and S6 in one kernel, where that is the faster way (when w is kept, S3 writes it as well: the blocks are those of the call
-  // that does not keep it, to the bit)
+  // S3 and S6 in one kernel, where that is the faster way.  When w is kept, S3 writes it as well, from the same preparation: the
+  // blocks are those of the call that does not keep it (with fp32 weights, option W_FP16 = 0), to the bit.
   if (egnn_readout_fused_fits(ctx, g)) {
-    if (w_save) {
-      if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st, rd_rows))) return rc;
-      if ((rc = egnn_launch_radial(ctx, 1, shared ? rd_rows : rhat_d, shared ? g->n_w_rows : g->n_edges, W_r1, W_r2, w_save, w2s,
-                                   st, false)))
-        return rc;
-    }
     if ((rc = egnn_launch_edge_fused_first(ctx, g, 1, pos, box, W_r1, W_r2, scratch, st))) return rc;
     tm.mark(0);
-    if ((rc = egnn_launch_edge_fused_second(ctx, g, 1, W_r1, W_r2, scratch, st))) return rc;
-    tm.mark(1);
+    if ((rc = egnn_launch_edge_fused_second(ctx, g, 1, W_r1, W_r2, scratch, st, w_save ? w2s : nullptr))) return rc;
     const EfScratch es = egnn_ef_carve(ctx, g, 1, scratch);
-    if ((rc = egnn_launch_node_mix(ctx, x, W_s, nullptr, nullptr, es.h4, g->n_total, st, 0, ef_quads(ctx)))) return rc;
+    if (w_save && (rc = egnn_launch_radial_prepared(ctx, 1, shared ? g->n_w_rows : g->n_edges, es.rec, w_save, w2s, st))) return rc;
+    tm.mark(1);
+    if ((rc = egnn_launch_node_mix(ctx, x, W_s, nullptr, nullptr, nullptr, g->n_total, st, 0, es.h4, ef_quads(ctx)))) return rc;
     tm.mark(2);
-    if ((rc = egnn_launch_node_mix(ctx, x, W_t, nullptr, nullptr, es.t4, g->n_total, st, 0, ef_quads(ctx)))) return rc;
+    if ((rc = egnn_launch_node_mix(ctx, x, W_t, nullptr, nullptr, nullptr, g->n_total, st, 0, es.t4, ef_quads(ctx)))) return rc;
     tm.mark(3);
     rc = egnn_launch_readout_fused(ctx, g, scratch, V, H, half, st);
     tm.mark(4);

@@ -138,19 +138,24 @@ static int layer_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32_t
   // (graphs with shared rows: the forward weights, recomputed or kept, have one row per row index; dw one per edge)
   const bool shared = g->w_row != nullptr;
   StageTimer tm(ctx, st, 2);
-  if ((rc = egnn_launch_geometry(ctx, g, pos, box, b.rhat_d, nullptr, nullptr, nullptr, st, shared ? b.rd_rows : nullptr)))
-    return rc;
   const float* w = w_saved ? w_saved : b.w;
   const float* a = a_saved ? a_saved : b.a;
-  if (!w_saved && (rc = egnn_launch_radial(ctx, 0, shared ? b.rd_rows : b.rhat_d, shared ? g->n_w_rows : g->n_edges, W_r1,
-                                           W_r2, b.w, b.w2s, st)))
-    return rc;
-  if ((rc = egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, b.h, n_t, st))) return rc;
-  // (the sums as the forward call takes them, to the bit; the room of dw is free until then)
-  if (!a_saved && (rc = egnn_edge_fused_fits(ctx, g)
-                            ? egnn_launch_edge_fused(ctx, g, pos, box, x_in, W_pre, W_r1, W_r2, b.dw, b.a, st)
-                            : egnn_launch_tp_segsum(ctx, g, b.rhat_d, b.h, w, b.a, st, false, shared)))
-    return rc;
+  const int64_t n_rows = shared ? g->n_w_rows : g->n_edges;
+  if ((!w_saved || !a_saved) && egnn_edge_fused_fits(ctx, g)) {
+    // weights and sums are those of egnn_layer_forward_save, to the bit (the room of dw is free until then)
+    if ((rc = egnn_launch_edge_fused_first(ctx, g, 0, pos, box, W_r1, W_r2, b.dw, st, b.rhat_d))) return rc;
+    if ((rc = egnn_launch_edge_fused_second(ctx, g, 0, W_r1, W_r2, b.dw, st, w_saved ? nullptr : b.w2s))) return rc;
+    if (!w_saved && (rc = egnn_launch_radial_prepared(ctx, 0, n_rows, egnn_ef_carve(ctx, g, 0, b.dw).rec, b.w, b.w2s, st)))
+      return rc;
+    if ((rc = egnn_launch_edge_fused_features(ctx, g, x_in, W_pre, b.dw, st, b.h))) return rc;
+    if (!a_saved && (rc = egnn_launch_edge_fused_sum(ctx, g, b.dw, b.a, false, st))) return rc;
+  } else {
+    if ((rc = egnn_launch_geometry(ctx, g, pos, box, b.rhat_d, nullptr, nullptr, nullptr, st, shared ? b.rd_rows : nullptr)))
+      return rc;
+    if (!w_saved && (rc = egnn_launch_radial(ctx, 0, shared ? b.rd_rows : b.rhat_d, n_rows, W_r1, W_r2, b.w, b.w2s, st))) return rc;
+    if ((rc = egnn_launch_node_mix(ctx, x_in, W_pre, nullptr, nullptr, b.h, n_t, st))) return rc;
+    if (!a_saved && (rc = egnn_launch_tp_segsum(ctx, g, b.rhat_d, b.h, w, b.a, st, false, shared))) return rc;
+  }
   tm.mark(0);
   // x_out = W_post a + W_self x_in[:n_owned]
   if ((rc = egnn_launch_node_mix(ctx, dx_out, W_post, nullptr, nullptr, b.da, n_o, st, 1))) return rc;
@@ -260,12 +265,18 @@ static int readout_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32
 
   const bool shared = g->w_row != nullptr;
   StageTimer tm(ctx, st, 3);
-  if ((rc = egnn_launch_geometry(ctx, g, pos, box, b.rhat_d, nullptr, nullptr, nullptr, st, shared ? b.rd_rows : nullptr)))
-    return rc;
   const float* w = w_saved ? w_saved : b.w;
-  if (!w_saved && (rc = egnn_launch_radial(ctx, 1, shared ? b.rd_rows : b.rhat_d, shared ? g->n_w_rows : g->n_edges, W_r1,
-                                           W_r2, b.w, b.w2s, st)))
-    return rc;
+  const int64_t n_rows = shared ? g->n_w_rows : g->n_edges;
+  if (!w_saved && egnn_readout_fused_fits(ctx, g)) {
+    // the weights are those of egnn_readout_hij_save, to the bit (the room of dw is free until then)
+    if ((rc = egnn_launch_edge_fused_first(ctx, g, 1, pos, box, W_r1, W_r2, b.dw, st, b.rhat_d))) return rc;
+    if ((rc = egnn_launch_edge_fused_second(ctx, g, 1, W_r1, W_r2, b.dw, st, b.w2s))) return rc;
+    if ((rc = egnn_launch_radial_prepared(ctx, 1, n_rows, egnn_ef_carve(ctx, g, 1, b.dw).rec, b.w, b.w2s, st))) return rc;
+  } else {
+    if ((rc = egnn_launch_geometry(ctx, g, pos, box, b.rhat_d, nullptr, nullptr, nullptr, st, shared ? b.rd_rows : nullptr)))
+      return rc;
+    if (!w_saved && (rc = egnn_launch_radial(ctx, 1, shared ? b.rd_rows : b.rhat_d, n_rows, W_r1, W_r2, b.w, b.w2s, st))) return rc;
+  }
   if ((rc = egnn_launch_node_mix(ctx, x, W_s, nullptr, nullptr, b.zs, n_t, st))) return rc;
   if ((rc = egnn_launch_node_mix(ctx, x, W_t, nullptr, nullptr, b.zt, n_t, st))) return rc;
   tm.mark(0);

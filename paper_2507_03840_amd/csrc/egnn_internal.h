@@ -101,9 +101,10 @@ __device__ __forceinline__ void egnn_raise_max(unsigned* target, float v) {
   } while (0)
 
 // stage launchers (one per translation unit)
-// group_quads > 0: y in the layout of groups of four channels (node_mix.hip) instead of [node][(l,m)][channel]
+// y_groups (may be NULL): the result also, or with y = NULL only, in the layout of groups of four channels, group_quads quads of
+// rows each (node_mix.hip)
 int egnn_launch_node_mix(egnn_ctx*, const float* x1, const float* W1, const float* x2, const float* W2,
-                         float* y, int n_nodes, hipStream_t, int transpose = 0, int group_quads = 0);
+                         float* y, int n_nodes, hipStream_t, int transpose = 0, float* y_groups = nullptr, int group_quads = 0);
 int egnn_launch_mix_wgrad(egnn_ctx*, const float* dy, const float* x, float* dW, float* partial, int n_nodes,
                           hipStream_t);
 size_t egnn_mix_wgrad_ws_bytes(const egnn_ctx*);
@@ -152,6 +153,9 @@ int egnn_launch_tp_segsum(egnn_ctx*, const egnn_graph*, const float* rhat_d, con
                           float* a, hipStream_t, bool half = false, bool shared_rows = false, bool h_half = false);
 int egnn_launch_radial(egnn_ctx*, int which, const float* rhat_d, int64_t n_edges, const float* W_r1,
                        const float* W_r2, float* w, void* scratch, hipStream_t, bool half = false);
+// the same from what egnn_launch_edge_fused_second leaves: scalings and pieces of W_r2 in `scratch` (its w2s), pieces of the hidden
+// activations of the rows in rec
+int egnn_launch_radial_prepared(egnn_ctx*, int which, int64_t n_rows, const void* rec, float* w, const void* scratch, hipStream_t);
 // looks up the address of the built-in scratch array of egnn_radial_weights_static on the current device, if there is one
 void egnn_static_scratch_prepare();
 size_t egnn_w_bytes(const egnn_ctx*, int which, int64_t n_edges);   // room for w in either precision

@@ -7,6 +7,25 @@
 #define HS_PART 8
 static_assert(HS_PART + HS_BLOCKS <= 32, "see above");
 
+// x -> (hi, lo) half-precision pieces, as raw bits
+__device__ __forceinline__ void rw_split(float x, uint32_t& hi, uint32_t& lo) {
+  const _Float16 h = (_Float16)x;
+  const _Float16 l = (_Float16)(x - (float)h);
+  hi = __builtin_bit_cast(unsigned short, h);
+  lo = __builtin_bit_cast(unsigned short, l);
+}
+
+// element i of W_r2 (x), times alpha and s_w, as S3 reads it: out[i / 64][piece][i % 64]
+__device__ __forceinline__ void half_piece_of_w2(float x, int i, float s_w, uint16_t* __restrict__ out, int log2E,
+                                                 const PathAlpha& alpha) {
+  const int n = i >> 6, j = i & 63;
+  uint32_t hi, lo;
+  rw_split(x * alpha.a[n >> log2E] * s_w, hi, lo);
+  uint16_t* o = out + (size_t)n * 2 * EGNN_HIDDEN + j;
+  o[0] = (uint16_t)hi;
+  o[EGNN_HIDDEN] = (uint16_t)lo;
+}
+
 // part `block` of HS_BLOCKS, by a workgroup of 256 threads
 __device__ __forceinline__ void half_scales_part(int block, const float* __restrict__ W_r1, const float* __restrict__ W_r2,
                                                  int n_rbf, int PE, int log2E, const PathAlpha& alpha,

@@ -10,20 +10,24 @@
 #define MIX_RPT 4      // rows per thread
 #define MIX_TILES 8    // row tiles per workgroup at most (fewer on small inputs, to have enough workgroups in flight)
 
-// Where the mix puts (node, row (l,m), channel): [node][row][channel], or, for a kernel that works on four channels of a node
-// at a time, [node][group of 4 channels][quad of rows (group_quads of them)][channel][row of the quad].  Which of the two is a
-// constant of the kernel: decided at run time, the calls that want rows took 0.3 to 0.7 of 4 to 9 us longer.
-template <bool GROUPS>
-__device__ __forceinline__ size_t mix_out(long node, int row, int c, int D, int log2E, int group_quads) {
-  if constexpr (!GROUPS) return (((size_t)node * D + row) << log2E) + c;
+// Where the mix puts (node, row (l,m), channel): [node][row][channel] in y and, for a kernel that works on four channels of a node
+// at a time, [node][group of 4 channels][quad of rows (group_quads of them)][channel][row of the quad] in y_groups.  Which of
+// them is a constant of the kernels (MIX_Y, MIX_GROUPS): the plain ones take 0.3 to 0.7 of 4 to 9 us less than with tests.
+#define MIX_Y 1
+#define MIX_GROUPS 2
+__device__ __forceinline__ size_t mix_at(long node, int row, int c, int D, int log2E) {
+  return (((size_t)node * D + row) << log2E) + c;
+}
+__device__ __forceinline__ size_t mix_groups_at(long node, int row, int c, int log2E, int group_quads) {
   return ((((size_t)node << (log2E - 2)) + (c >> 2)) * group_quads + (row >> 2)) * 16 + (c & 3) * 4 + (row & 3);
 }
 
-template <bool GROUPS>
+template <int OUT>
 __global__ __launch_bounds__(256) void node_mix_kernel(const float* __restrict__ x1, const float* __restrict__ W1,
                                                        const float* __restrict__ x2, const float* __restrict__ W2,
                                                        float* __restrict__ y, int n_nodes, int lmax, int log2E,
-                                                       int transpose, int tiles, int group_quads) {
+                                                       int transpose, int tiles, float* __restrict__ y_groups,
+                                                       int group_quads) {
   extern __shared__ float smem[];
   const int E = 1 << log2E;
   const int l = blockIdx.y;
@@ -83,7 +87,8 @@ __global__ __launch_bounds__(256) void node_mix_kernel(const float* __restrict__
       if (r < n_rows) {
         const long node = r / nm;
         const int mm = (int)(r - node * nm);
-        y[mix_out<GROUPS>(node, l * l + mm, c, D, log2E, group_quads)] = acc[q];
+        if constexpr (OUT & MIX_Y) y[mix_at(node, l * l + mm, c, D, log2E)] = acc[q];
+        if constexpr (OUT & MIX_GROUPS) y_groups[mix_groups_at(node, l * l + mm, c, log2E, group_quads)] = acc[q];
       }
     }
   }
@@ -96,11 +101,11 @@ __global__ __launch_bounds__(256) void node_mix_kernel(const float* __restrict__
 // both operands use it; this one lets a lane fetch its half row as contiguous 16-byte loads).
 typedef float mix_float16v __attribute__((ext_vector_type(16)));
 
-template <int LOG2E, bool GROUPS>
+template <int LOG2E, int OUT>
 __global__ __launch_bounds__(256) void node_mix_mfma_kernel(const float* __restrict__ x1, const float* __restrict__ W1,
                                                             const float* __restrict__ x2, const float* __restrict__ W2,
                                                             float* __restrict__ y, int n_nodes, int lmax, int transpose,
-                                                            int tiles, int group_quads) {
+                                                            int tiles, float* __restrict__ y_groups, int group_quads) {
   constexpr int E = 1 << LOG2E, KH = E / 2, NCB = E / 32;
   extern __shared__ float smem[];   // [n_in][c'][c]
   const int l = blockIdx.y;
@@ -169,10 +174,17 @@ __global__ __launch_bounds__(256) void node_mix_mfma_kernel(const float* __restr
       const long ro = r0 + 8 * (i >> 2) + 4 * hh + (i & 3);
       if (ro < n_rows) {
         const long no = ro / nm;
-        float* out = y + mix_out<GROUPS>(no, l * l + (int)(ro - no * nm), m, D, LOG2E, group_quads);
-        const int next = GROUPS ? 8 * group_quads * 16 : 32;
+        const int row = l * l + (int)(ro - no * nm);
+        if constexpr (OUT & MIX_Y) {
+          float* out = y + mix_at(no, row, m, D, LOG2E);
 #pragma unroll
-        for (int cb = 0; cb < NCB; ++cb) out[next * cb] = acc[cb][i];
+          for (int cb = 0; cb < NCB; ++cb) out[32 * cb] = acc[cb][i];
+        }
+        if constexpr (OUT & MIX_GROUPS) {
+          float* out = y_groups + mix_groups_at(no, row, m, LOG2E, group_quads);
+#pragma unroll
+          for (int cb = 0; cb < NCB; ++cb) out[8 * group_quads * 16 * cb] = acc[cb][i];
+        }
       }
     }
     if (!valid_next) break;
@@ -182,7 +194,7 @@ __global__ __launch_bounds__(256) void node_mix_mfma_kernel(const float* __restr
 
 template <int LOG2E>
 static int launch_node_mix_mfma(egnn_ctx* ctx, const float* x1, const float* W1, const float* x2, const float* W2,
-                                float* y, int n_nodes, hipStream_t stream, int transpose, int group_quads) {
+                                float* y, int n_nodes, hipStream_t stream, int transpose, float* y_groups, int group_quads) {
   constexpr int E = 1 << LOG2E;
   const int lmax = ctx->desc.lmax;
   const long max_rows = (long)n_nodes * (2 * lmax + 1);
@@ -193,18 +205,20 @@ static int launch_node_mix_mfma(egnn_ctx* ctx, const float* x1, const float* W1,
   tiles = tiles < 1 ? 1 : (tiles > 8 ? 8 : tiles);
   dim3 grid((unsigned)((n_tiles + tiles - 1) / tiles), lmax + 1), block(256);
   const size_t shmem = (size_t)(W2 ? 2 : 1) * E * E * sizeof(float);
-  const auto kern = group_quads ? node_mix_mfma_kernel<LOG2E, true> : node_mix_mfma_kernel<LOG2E, false>;
-  hipLaunchKernelGGL(kern, grid, block, shmem, stream, x1, W1, x2, W2, y, n_nodes, lmax, transpose,
-                     (int)tiles, group_quads);
+  const auto kern = !y_groups ? node_mix_mfma_kernel<LOG2E, MIX_Y>
+                    : y       ? node_mix_mfma_kernel<LOG2E, MIX_Y | MIX_GROUPS>
+                              : node_mix_mfma_kernel<LOG2E, MIX_GROUPS>;
+  hipLaunchKernelGGL(kern, grid, block, shmem, stream, x1, W1, x2, W2, y, n_nodes, lmax, transpose, (int)tiles, y_groups,
+                     group_quads);
   EGNN_LAUNCH_CHECK(ctx, "node_mix_mfma_kernel");
   return EGNN_OK;
 }
 
 int egnn_launch_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, const float* x2, const float* W2,
-                         float* y, int n_nodes, hipStream_t stream, int transpose, int group_quads) {
+                         float* y, int n_nodes, hipStream_t stream, int transpose, float* y_groups, int group_quads) {
   if (n_nodes == 0) return EGNN_OK;
-  if (ctx->desc.channels == 32) return launch_node_mix_mfma<5>(ctx, x1, W1, x2, W2, y, n_nodes, stream, transpose, group_quads);
-  if (ctx->desc.channels == 64) return launch_node_mix_mfma<6>(ctx, x1, W1, x2, W2, y, n_nodes, stream, transpose, group_quads);
+  if (ctx->desc.channels == 32) return launch_node_mix_mfma<5>(ctx, x1, W1, x2, W2, y, n_nodes, stream, transpose, y_groups, group_quads);
+  if (ctx->desc.channels == 64) return launch_node_mix_mfma<6>(ctx, x1, W1, x2, W2, y, n_nodes, stream, transpose, y_groups, group_quads);
   const int E = ctx->desc.channels, lmax = ctx->desc.lmax;
   const int rows_per_tile = MIX_RPT * (256 / E);
   const long max_rows = (long)n_nodes * (2 * lmax + 1);
@@ -216,14 +230,14 @@ int egnn_launch_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, const 
   dim3 grid((unsigned)((max_rows + per_wg - 1) / per_wg), lmax + 1), block(256);
   const int n_in = W2 ? 2 : 1;
   const size_t shmem = ((size_t)n_in * E * E + (size_t)n_in * rows_per_tile * (E + 1)) * sizeof(float);
-  const auto kern = group_quads ? node_mix_kernel<true> : node_mix_kernel<false>;
+  const auto kern = !y_groups ? node_mix_kernel<MIX_Y> : y ? node_mix_kernel<MIX_Y | MIX_GROUPS> : node_mix_kernel<MIX_GROUPS>;
   if (shmem > 64 * 1024) {
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
     if (e != hipSuccess) return egnn_check_hip(ctx, e, "hipFuncSetAttribute(node_mix_kernel)");
   }
   hipLaunchKernelGGL(kern, grid, block, shmem, stream, x1, W1, x2, W2, y, n_nodes, lmax,
-                     ctx->log2_channels, transpose, (int)tiles, group_quads);
+                     ctx->log2_channels, transpose, (int)tiles, y_groups, group_quads);
   EGNN_LAUNCH_CHECK(ctx, "node_mix_kernel");
   return EGNN_OK;
 }

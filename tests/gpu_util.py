@@ -216,3 +216,29 @@ def gpu_training_step(w, wt, agg, T, repeats=1, timing=None, keep=False, shared_
         out = dict(loss=float(loss.cpu()[0]), grads={k: v.cpu().numpy() for k, v in grads.items()},
                    n_edges=graph.n_edges)
     return out
+
+
+def fused_route(B, m, which, n_edges, n_owned, n_total):
+    """Whether a call on a graph of these sizes takes the kernel that keeps the radial weights in registers (which = "layer" or
+    "readout"): the library's own rule, asked without a GPU."""
+    import ctypes as C
+    names = dict(layer="_Z20egnn_edge_fused_fitsPK8egnn_ctxPK10egnn_graph",
+                 readout="_Z23egnn_readout_fused_fitsPK8egnn_ctxPK10egnn_graph")
+    f = getattr(m.lib, names[which])
+    f.restype = C.c_bool
+    g = B.GraphDesc(None, None, None, None, n_edges, n_owned, n_total, None, 0, None, None)
+    return bool(f(m.ctx, C.byref(g)))
+
+
+def recorded_nodes(lib, call):
+    """Number of nodes (kernels, here) that `call` leaves in a recorded graph."""
+    import ctypes as C
+    import torch
+    call()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph(keep_graph=True)
+    with torch.cuda.graph(graph):
+        call()
+    n = C.c_size_t()
+    assert lib.hipGraphGetNodes(C.c_void_p(graph.raw_cuda_graph()), None, C.byref(n)) == 0
+    return n.value
