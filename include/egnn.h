@@ -207,7 +207,7 @@ int egnn_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, const float* 
 
 /* Options.  EGNN_OPT_FUSED (default 0): how egnn_layer_forward with its own radial MLP gets from the radial weights (S3)
  * to the summed messages (S4).  0: one kernel that makes the weights of an (edge, channel) on the matrix cores in the
- * registers of the lane that uses them, from lmax 2 on (lmax 1 up to 64 channels); elsewhere, and where the scratch of
+ * registers of the lane that uses them, from lmax 2 on (at lmax 1 on small graphs); elsewhere, and where the scratch of
  * a small graph is too little for it, through a weight tensor in the workspace, as always for caller-supplied weights.
  * 1 and 2 choose older kernels, for a power of two >= 8 channels and at most 32 radial bases; they never write the
  * weights to memory either and are slower than the default (1: producer and consumer waves hand the weights over

@@ -441,15 +441,23 @@ __global__ __launch_bounds__(256, EF_WG_PER_CU) void ef_layer_kernel(
   store_node();
 }
 
-// Where this kernel is the faster one, measured on 48 .. 3,000 atoms of 21 .. 209 edges, whole layers against the two kernels: 1.1 to
-// 2.5 times from lmax 2 on; at lmax 1 0.99 to 1.7 times at 32 and 64 channels, 0.89 to 1.7 at 128; at lmax 0, where one path takes a
-// tile of four, 0.58 to 1.0 for 37,000 edges and more.
+// Where this kernel is the faster one, measured on 48 .. 3,000 atoms of 13 .. 209 edges, whole calls against the two kernels: the one
+// that makes the weights for itself, and the one that also writes them for the reverse pass.  Both give the same bits, so one
+// rule holds for both; the second runs S3 as well, on what was prepared for the sums.
+//   lmax 2 to 4, up to 64 channels: 1.06 to 2.9 times; keeping the weights 0.92 to 1.6, median 1.05 to 1.1, below 0.97 at lmax 2 on
+//     graphs without shared rows.  Where a node has about 19 edges, which leave every second tile of 16 nearly empty, keeping
+//     them 0.87 to 0.98 (2 to 20 us of the call, up to 3 % of a training step of the layer), not keeping them 1.06 to 1.4.
+//   lmax 2, 128 channels: 0.94 to 1.55, keeping them 0.85 to 1.4.
+//   lmax 1, where w is small: up to 800 nodes x 32 channels and 46,000 edges x 32 channels 1.11 to 1.45, keeping them 0.98 to 1.23;
+//     beyond, 0.95 to 1.27 and 0.78 to 0.98: not taken.  128 channels 0.89 to 1.7: not taken.
+//   lmax 0, where one path takes a tile of four, 0.58 to 1.0 for 37,000 edges and more: not taken.
 // The scratch is the room of a weight tensor in memory, which is not needed then; whether it is large enough is asked for one row
 // per edge, so that a graph with shared rows goes the same way as one without (lmax 1: from 32 channels on).
 bool egnn_edge_fused_fits(const egnn_ctx* ctx, const egnn_graph* g) {
-  const int lmax = ctx->desc.lmax;
-  return (lmax >= 2 || (lmax == 1 && ctx->desc.channels <= 64)) && g->n_edges > 0 && g->n_owned > 0 &&
-         egnn_ef_carve(ctx, g, 0, nullptr).bytes <= (size_t)g->n_edges * ctx->n_paths[0] * ctx->desc.channels * sizeof(float);
+  const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
+  const bool small = (int64_t)g->n_owned * E <= 800 * 32 && g->n_edges * E <= 46000 * 32;
+  return (lmax >= 2 || (lmax == 1 && E <= 64 && small)) && g->n_edges > 0 && g->n_owned > 0 &&
+         egnn_ef_carve(ctx, g, 0, nullptr).bytes <= (size_t)g->n_edges * ctx->n_paths[0] * E * sizeof(float);
 }
 
 static PathAlpha ef_alpha(const egnn_ctx* ctx, int which) {
