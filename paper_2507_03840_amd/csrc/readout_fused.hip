@@ -335,15 +335,33 @@ static size_t rf_lds_bytes(const egnn_ctx* ctx) {
   return (size_t)ef_tiles(ctx, 1) * 4096 + 4 * (RF_WAVES * rf_stage_words(ctx) + 3 * G * 64 + G * 32 + RF_POS + RF_MAX_Q + RF_MAX_BLOCKS);
 }
 
-// Where this kernel is the faster one, measured on 48 .. 1,500 atoms (1,000 .. 313,000 edges), whole calls against the two kernels.
-// 13 orbitals: 1.2 to 3.8 times up to 32 channels, 1.01 to 1.7 when the weights are kept (S3 then runs as well); at 64 channels,
-// where a wavefront goes through 16 groups one after the other, 0.75 to 1.0 below 20,000 edges, 0.94 to 1.2 at 68,000, 1.2 to
-// 2.0 at 313,000.  4 orbitals, where the collapse that the old kernel spends its time on is small: 1.04 to 2.3 times up to 16
-// channels, 0.93 to 1.5 at 32.  The same for calls that keep the weights and calls that do not: both give the same bits.
+// The fewest orbitals an atom from which this kernel is the faster one: the old kernel's collapse grows with them, this one's does not.
+// Measured as whole calls against the two kernels, 48 .. 2,600 atoms (1,000 .. 546,000 edges), 4 .. 13 orbitals, for the call that
+// keeps the weights (S3 runs as well, on the same preparation) and the one that does not; both give the same bits, so that one
+// rule holds for both, and the lines lie where the call that keeps them turns slower.  A round is the 32,768 edges that the
+// chip's wavefronts take at a time.  Times of the old kernels over the new ones, keeping / not keeping:
+//   64 channels, from 150,000 edges: 12 and 13 orbitals 1.00 .. 1.67 / 1.4 .. 1.9, 9 and 10 0.92 .. 1.05 / 1.16 .. 1.67 (lmax 1 1.13 ..
+//     1.25 / 1.3 .. 1.5), 8 0.80 .. 1.03.  Below, where a wavefront goes through 16 groups one after the other, 13 orbitals 0.75 .. 1.2.
+//   32 channels: one round 8 orbitals 1.00 .. 1.19 / 1.15 .. 1.7, 4 0.93 .. 1.5.  Up to half of a second one, which takes as long as a
+//     whole one, 13 1.00 .. 1.30 / 1.23 .. 1.46, 12 0.96 .. 1.06 (lmax 1 1.2), 8 .. 10 0.91 .. 1.02.  More: lmax 2 10 orbitals 0.99 ..
+//     1.05, 9 0.93 .. 0.98, 8 0.86 .. 0.93; lmax 3 9 1.00 .. 1.04, 8 0.95 .. 1.01; lmax 4 8 0.98 .. 1.07; lmax 1 9 1.0 .. 1.1, 8
+//     0.95 .. 0.98.
+//   16 channels: one round 4 orbitals 1.17 .. 1.3; more: lmax 2 9 1.1, 8 0.95 .. 0.98, 5 0.90 .. 1.1; lmax 1 8 1.0, 5 0.92 .. 0.96;
+//     lmax 3 and 4 4 orbitals 1.00 .. 1.1.
+//   8 channels: 4 orbitals 1.0 .. 2.
+static int rf_least_orbitals(int lmax, int E, int64_t n_edges) {
+  const int64_t round = 16 * RF_WAVES * EGNN_CUS;
+  const int never = 1000;
+  if (E == 64) return n_edges < 150000 ? never : lmax == 1 ? 9 : 12;
+  if (E == 32) return n_edges <= round ? 8 : n_edges <= round + round / 2 ? 13 : lmax == 4 ? 8 : lmax == 2 ? 10 : 9;
+  if (E == 16) return n_edges > round && lmax <= 2 ? (lmax == 2 ? 9 : 8) : 1;
+  return E == 8 ? 1 : never;
+}
+
 bool egnn_readout_fused_fits(const egnn_ctx* ctx, const egnn_graph* g) {
-  const int E = ctx->desc.channels;
-  if (!(E <= 16 || (ctx->n_orb >= 8 && (E <= 32 || (E == 64 && g->n_edges >= 150000))))) return false;
-  if (ctx->desc.lmax < 1 || g->n_edges <= 0 || rf_lds_bytes(ctx) > 160 * 1024) return false;
+  if (ctx->desc.lmax < 1 || g->n_edges <= 0 || ctx->n_orb < rf_least_orbitals(ctx->desc.lmax, ctx->desc.channels, g->n_edges) ||
+      rf_lds_bytes(ctx) > 160 * 1024)
+    return false;
   for (int L = 0; L <= EGNN_L_READOUT; ++L)
     if (ctx->n_out[L] > rf_room[L]) return false;
   return egnn_ef_carve(ctx, g, 1, nullptr).bytes <= (size_t)g->n_edges * ctx->n_paths[1] * ctx->desc.channels * sizeof(float);

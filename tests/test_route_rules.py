@@ -34,3 +34,30 @@ def test_layer_from_lmax_2(B, lmax, E):
     assert _layer(B, lmax, E, 524172, 2500) and _layer(B, lmax, E, 12560, 300) and _layer(B, lmax, E, 2000000, 12000, 20000)
     assert not _layer(B, lmax, E, 40, 30)                # (the scratch does not fit where w would lie)
     assert not _layer(B, lmax, E, 0, 30) and not _layer(B, lmax, E, 0, 0, 30)
+
+
+SETS = {4: (0, 1), 5: (0, 0, 1), 7: (0, 1, 1), 8: (0, 0, 1, 1), 9: (0, 1, 2), 10: (0, 0, 1, 2), 12: (0, 1, 1, 2), 13: (0, 0, 1, 1, 2)}
+
+
+def _readout(B, lmax, E, n_orb, n_edges):
+    m = B.Egnn(lmax, E, 16, 10.0, 20.0, orb_l=SETS[n_orb])
+    return U.fused_route(B, m, "readout", n_edges, 1200, 1200)
+
+
+# (lmax, channels, orbitals, last or first edge count, whether it is taken there, one edge on)
+@pytest.mark.parametrize("lmax,E,n_orb,n_edges,here,beyond", [
+    (2, 64, 13, 149999, False, True), (4, 64, 12, 149999, False, True), (3, 64, 10, 149999, False, False), (1, 64, 9, 149999, False, True),
+    (1, 64, 8, 149999, False, False), (2, 32, 8, 32768, True, False), (4, 32, 8, 32768, True, False), (4, 32, 8, 49152, False, True),
+    (3, 32, 9, 49152, False, True), (3, 32, 8, 49152, False, False), (2, 32, 10, 49152, False, True), (2, 32, 9, 49152, False, False),
+    (1, 32, 9, 49152, False, True), (4, 32, 12, 32768, True, False), (2, 32, 13, 32768, True, True), (4, 32, 13, 49152, True, True),
+    (2, 32, 7, 20000, False, False), (2, 16, 4, 32768, True, False), (2, 16, 8, 32768, True, False), (2, 16, 9, 32768, True, True),
+    (1, 16, 5, 32768, True, False), (1, 16, 8, 32768, True, True), (3, 16, 4, 32768, True, True), (4, 16, 4, 32768, True, True),
+    (2, 8, 4, 32768, True, True), (4, 128, 13, 300000, False, False), (0, 32, 13, 32768, False, False)])
+def test_readout(B, lmax, E, n_orb, n_edges, here, beyond):
+    assert _readout(B, lmax, E, n_orb, n_edges) == here and _readout(B, lmax, E, n_orb, n_edges + 1) == beyond
+
+
+@pytest.mark.parametrize("orb", [(0, 0, 0, 1, 1, 2), (0, 1, 2, 2), (0, 0, 1, 1, 1), (2, 2, 1)])
+def test_readout_rows_of_v(B, orb):
+    """Sets with more rows of V in a degree than the kernel has room for: the two kernels."""
+    assert not U.fused_route(B, B.Egnn(3, 32, 16, 10.0, 20.0, orb_l=orb), "readout", 300000, 1200, 1200)
