@@ -84,13 +84,19 @@ __global__ __launch_bounds__(64) void edge_rows_segsum_kernel(const T* __restric
 #pragma unroll
     for (int u = 0; u < 8; ++u) acc[u & 3] += v[u];
   }
-  // up to seven more: 64 consecutive lanes ask for one row each time, so the guarded loads are uniform
+  // up to seven more, all asked for at once: past the end the last row again, which is not added.  (Each behind a test of its own,
+  // they came one after the other: 6.6 instead of 4.6 us for 2,500 segments of 7 rows of 64 bytes.)
+  if (idx < p1) {
+    T v[7];
 #pragma unroll
-  for (int u = 0; u < 7; ++u) {
-    if (idx + u < p1) {
-      const long k = perm ? perm[idx + u] : idx + u;
-      acc[u & 3] += __builtin_nontemporal_load(rows + k * row_len + q);
+    for (int u = 0; u < 7; ++u) {
+      const int at = min(idx + u, p1 - 1);
+      const long k = perm ? perm[at] : at;
+      v[u] = __builtin_nontemporal_load(rows + k * row_len + q);
     }
+#pragma unroll
+    for (int u = 0; u < 7; ++u)
+      if (idx + u < p1) acc[u & 3] += v[u];
   }
   out[(long)i * row_len + q] = (acc[0] + acc[1]) + (acc[2] + acc[3]);
 }
