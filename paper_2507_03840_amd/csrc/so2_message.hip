@@ -714,7 +714,7 @@ extern "C" int egnn_so2_message_sum(egnn_ctx* ctx, const egnn_graph* g, const fl
     So2nCall c;
     float* rhat_d = (float*)ws;
     so2n_carve(ctx, g->n_owned, g->n_total, g->n_owned, SO2N_GAUSS, (char*)ws + so2_a256((size_t)g->n_edges * 16), &c);
-    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, so2n_zero_words(g->n_owned, 0), 0, st))) return rc;
+    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, so2n_zero_words(g->n_owned), 0, st))) return rc;
     if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st))) return rc;
     return so2n_message_sum(ctx, g, rhat_d, x, W_e, W_so2, scale, a, c, st);
   }
@@ -756,7 +756,7 @@ extern "C" int egnn_so2_node_block(egnn_ctx* ctx, const egnn_graph* g, const flo
     float *rhat_d, *alpha;
     So2nCall c;
     so2_block_nodes_ws(ctx, g, (char*)ws, &rhat_d, &alpha, &c);
-    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, so2n_zero_words(g->n_owned, 0), 0, st))) return rc;
+    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, so2n_zero_words(g->n_owned), 0, st))) return rc;
     if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st))) return rc;
     return so2n_node_block(ctx, g, rhat_d, x, T_edge, W_so2, w_att, alpha, a, c, st);
   }
@@ -1529,7 +1529,7 @@ extern "C" int egnn_so2_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g,
     So2nCall c;
     float* rhat_d = (float*)ws;
     so2n_backward_carve(ctx, g->n_owned, g->n_total, (char*)ws + so2_a256((size_t)n * 16), &c);
-    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, so2n_zero_words(g->n_owned, g->n_total), 0, st))) return rc;
+    if ((rc = egnn_launch_fill_int(ctx, (int*)c.maxima, so2n_zero_words(g->n_total), 0, st))) return rc;
     if ((rc = egnn_launch_geometry(ctx, g, pos, box, rhat_d, nullptr, nullptr, nullptr, st))) return rc;
     return so2n_message_sum_backward(ctx, g, col_ptr, perm, rhat_d, x, W_e, W_so2, da, 1.0f / sqrtf(ctx->desc.agg_norm), dx, dW_e,
                                      dW_so2, c, st);

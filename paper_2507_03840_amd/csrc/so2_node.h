@@ -38,12 +38,12 @@ struct So2nCall {
   float* wpath;          // path weights, fp32
   uint4* wpack;          // the same cut into pieces in operand order
   unsigned* maxima;      // bit patterns: 1 path weights, 3 edge rows; 4, 5 scales of the weight gradient
-  unsigned* t_max;       // largest |T| of every node: the owned ones; then n_t of them (reverse pass)
+  unsigned* t_max;       // largest |T| of every one of the n_t nodes
   unsigned* G_max;       // reverse pass: largest |G| of every owned node, and the exponents that T and G are scaled with
   int* node_exp[2];
 };
 // words from maxima on that start at zero
-inline long so2n_zero_words(int32_t n_owned, int32_t n_t) { return 64 + (long)n_owned + n_t; }
+inline long so2n_zero_words(int32_t n_t) { return 64 + (long)n_t; }
 
 // base = NULL: bytes only.  n_rows feature rows, T for n_t nodes.
 size_t so2n_carve(const egnn_ctx*, int32_t n_owned, int32_t n_rows, int32_t n_t, int form, char* base, So2nCall* out);

@@ -1025,7 +1025,7 @@ struct So2nWgrad {
 // an input channel): sum_edges Yhat x_src da_dst is the same number whether it is gathered at one end or at the other, so the sums
 // over the incoming edges need not be formed again (445 of 1,815 us of a call and its adjoint at 3,000 nodes).  A wave
 // owns 128 rows x 32 columns of the result; both operands are read in memory order, the contraction index being the row
-// index of both: lane (i, h) fetches 16 bytes of T and 4 of da for the eight nodes of its half-wave and finds in one
+// index of both: lane (i, h) fetches 16 bytes of T and 4 of x for the eight nodes of its half-wave and finds in one
 // component of them the eight consecutive nodes one operand register wants, so accumulator a holds the rows
 // k0 + 4 r + a.  Degrees with more rows per node get fewer nodes per chunk, so that all waves take about equally long.  The
 // last wave of every column of tiles takes G and da in the place of T and x, with G's own scales: whichever of the two is the smaller keeps
@@ -1073,7 +1073,7 @@ __global__ __launch_bounds__(256, 2) void so2n_wgrad_kernel(So2nWgrad p) {
     const float* ym = Y + (size_t)mo * p.E;
 #pragma unroll
     for (int r = 0; r < 8; ++r) {
-      // (past the last node: that node again, with zeros for da)
+      // (past the last node: that node again, with zeros for x or da)
       const int nr = n + r < n1 ? n + r : n1 - 1;
       ra[r] = *reinterpret_cast<const sg_f4*>(tm + (size_t)nr * node_floats);
       ry[r] = ym[(size_t)nr * ys];
@@ -1222,7 +1222,7 @@ size_t so2n_carve(const egnn_ctx* ctx, int32_t n_owned, int32_t n_rows, int32_t 
   So2nSteps st;
   so2n_w_layout(lmax, E, form, &s, &st);
   So2nCall c;
-  c.maxima = (unsigned*)take(256 + ((size_t)n_owned + n_t) * 4);
+  c.maxima = (unsigned*)take(256 + (size_t)n_t * 4);
   c.t_max = c.maxima ? c.maxima + 64 : nullptr;
   c.packed = (uint32_t*)take(so2n_packed_bytes(ctx, n_rows));
   c.row_exp = (int*)take((size_t)n_rows * 4);
@@ -1418,11 +1418,11 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   So2nArgs p = {};
   p.ptr = col_ptr; p.perm = perm; p.index = g->dst; p.rhat_d = reinterpret_cast<const float4*>(rhat_d);
   p.packed = c.packed; p.row_exp = c.row_exp; p.packed_bytes = (unsigned)so2n_packed_bytes(ctx, g->n_owned); p.x_self = da;
-  p.T = c.T; p.t_max = c.t_max + g->n_owned; p.g = c.g;
+  p.T = c.T; p.t_max = c.t_max; p.g = c.g;
   p.j_begin = 0; p.j_end = g->n_total; p.n_self = g->n_owned; p.self_ptr = g->row_ptr; p.form = SO2N_PLAIN;
   if ((rc = so2n_launch_gather<false>(ctx, p, st))) return rc;
   q.x = x; q.n_rows = g->n_total; q.out = nullptr; q.row_exp = nullptr;
-  q.X_max = p.t_max; q.col_ptr = col_ptr; q.node_exp = c.node_exp[0]; q.used = c.maxima + 4;
+  q.X_max = c.t_max; q.col_ptr = col_ptr; q.node_exp = c.node_exp[0]; q.used = c.maxima + 4;
   if ((rc = so2n_launch_pack(ctx, q, st))) return rc;
   So2nW s;
   So2nSteps steps;
@@ -1440,10 +1440,8 @@ int so2n_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g, const int32_t*
   hipLaunchKernelGGL(so2n_unpack_wgrad_kernel, dim3((unsigned)un_blocks), dim3(256), 0, st, c.dwpath, s, lmax, E,
                      ctx->desc.n_rbf, W, W_e, dW, dW_e);
   EGNN_LAUNCH_CHECK(ctx, "so2n_unpack_wgrad_kernel");
-  So2nCall c2 = c;
-  c2.t_max = p.t_max;
-  if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_PLAIN, true, c2, st))) return rc;
-  return so2n_launch_mix(ctx, c2, SO2N_PLAIN, g->n_total, scale, dx, st);
+  if ((rc = so2n_pack_weights(ctx, W, nullptr, SO2N_PLAIN, true, c, st))) return rc;
+  return so2n_launch_mix(ctx, c, SO2N_PLAIN, g->n_total, scale, dx, st);
 }
 
 // a[j] for the owned nodes; rhat_d and c carved by the caller, c.maxima and c.t_max zero on entry
