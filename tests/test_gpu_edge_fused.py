@@ -1,6 +1,7 @@
 """GPU tests of the layer kernel that keeps the radial weights in registers (edge_fused.hip), at the edges of its tiles: nodes
-of 0, 1, 15, 16, 17, 31, 32 and 33 edges, every channel count that it takes, with and without shared rows of weights, against the
-oracle on the same edge list."""
+of 0, 1, 15, 16, 17, 31, 32 and 33 edges, every channel count that it takes, with and without shared rows of weights, wavefronts that
+take one node and wavefronts that take several, against the oracle on the same edge list; and the graphs that go through a weight
+tensor instead."""
 import numpy as np
 import pytest
 
@@ -23,12 +24,12 @@ def B():
     return binding
 
 
-def _pruned(lmax, E, n, n_owned, seed):
-    """A cluster whose owned atoms keep as many edges as DEGREES says in turn (the cutoff gives each at least 33)."""
-    w = synth.small_cluster(n, n_owned, lmax, E, 11, 14.0, seed)
+def _pruned(lmax, E, n, n_owned, seed, want=None, r_cut=14.0):
+    """A cluster whose owned atoms keep as many edges as `want` or else DEGREES says in turn (the cutoff gives each at least 33)."""
+    w = synth.small_cluster(n, n_owned, lmax, E, 11, r_cut, seed)
     src, dst, shift, row_ptr = U.oracle_graph(w)
     rank = np.arange(len(src)) - row_ptr[:-1][dst]
-    want = np.array([DEGREES[j % len(DEGREES)] for j in range(n_owned)])
+    want = np.array([DEGREES[j % len(DEGREES)] for j in range(n_owned)] if want is None else want)
     keep = rank < want[dst]
     count = np.bincount(dst[keep], minlength=n_owned)
     assert np.array_equal(count, want)
@@ -83,3 +84,67 @@ def test_what_is_not_finite_stays_with_its_edges(B):
         assert hit.sum() < n // 2
         assert np.array_equal(got[~hit], clean[~hit])
         assert not np.isfinite(got[hit]).all(axis=(1, 2)).any()
+
+
+def _stride(E):
+    """Nodes between two that one wavefront takes, where there are enough of them: the workgroups that the chip holds, four wavefronts
+    each, shared out over the groups of four channels."""
+    return 4 * 2 * 256 // (E // 4)
+
+
+# Degrees of the nodes that a wavefront takes one after the other: runs of empty ones, one tile after several, the last of a tile.
+CHAINS = ((33, 0, 0, 16, 1), (0, 0, 0, 17, 0), (16, 16, 31, 0, 32), (1, 0, 33, 0, 15), (0, 32, 1, 0, 0), (17, 33, 0, 15, 16))
+
+
+def _chains(E, n_owned):
+    s = _stride(E)
+    return [CHAINS[j % s % len(CHAINS)][j // s % 5] for j in range(n_owned)]
+
+
+@pytest.mark.parametrize("lmax,E,n,n_owned,half", [(4, 128, 330, 300, False), (3, 64, 400, 390, False), (1, 64, 400, 400, False),
+                                                   (4, 32, 700, 650, True), (2, 16, 1200, 1100, False), (2, 8, 2200, 2200, False)])
+def test_several_nodes_a_wavefront(B, lmax, E, n, n_owned, half):
+    assert n_owned > 2 * _stride(E) or E < 64
+    w, g = _pruned(lmax, E, n, n_owned, 160 + lmax + E, _chains(E, n_owned), 14.0 if n < 1000 else 12.0)
+    m = B.Egnn(lmax, E, 11, w.r_cut, 7.0)
+    assert U.fused_route(B, m, "layer", len(g[0]), n_owned, n)
+    rng = np.random.default_rng(lmax * 100 + E)
+    W = synth.layer_weights(rng, lmax, E, w.n_rbf, 64, len(O.tp_paths(lmax, lmax, lmax)))
+    x = synth.node_features(rng, n, lmax, E)
+    print("case", lmax, E, n_owned, len(g[0]), flush=True)
+    ref = O.layer_forward(g, w.pos, w.box, x, W, lmax, lmax, E, w.n_rbf, w.r_cut, 7.0, w_dtype=np.float16 if half else None)
+    a = _run(B, w, g, W, x, False, half)
+    assert np.array_equal(a, _run(B, w, g, W, x, True, half))
+    e = U.rel_err(a, ref)
+    print(f"  rel err {e:.2e}", flush=True)
+    assert e < (1e-4 if half else TOL)
+    # a source that is not finite: neither the other lanes of its tiles nor the later nodes of their wavefronts see it
+    clean = _run(B, w, g, W, x, False, half)
+    for bad in (np.nan, np.inf):
+        x2 = x.copy()
+        sources = np.unique(g[0])[::23]
+        x2[sources] = bad
+        got = _run(B, w, g, W, x2, False, half)
+        hit = np.zeros(n_owned, bool)
+        hit[g[1][np.isin(g[0], sources)]] = True
+        hit[sources[sources < n_owned]] = True
+        assert 0 < hit.sum() < n_owned and not np.isfinite(got[hit]).all(axis=(1, 2)).any()
+        assert np.array_equal(got[~hit], clean[~hit])
+
+
+@pytest.mark.parametrize("shared", [False, True])
+@pytest.mark.parametrize("lmax,E,n,n_owned,r_cut", [(2, 16, 30, 30, 2.5), (2, 64, 60, 40, 1.9), (3, 8, 50, 50, 2.0), (3, 128, 40, 40, 2.2),
+                                                    (4, 32, 60, 50, 2.0), (0, 32, 60, 60, 5.0), (1, 64, 450, 450, 4.0)])
+def test_graphs_that_go_through_a_weight_tensor(B, lmax, E, n, n_owned, r_cut, shared):
+    """Sparse and tiny graphs, whose weight tensor is less than the scratch of the other route; lmax 0; many nodes at lmax 1."""
+    w = synth.small_cluster(n, n_owned, lmax, E, 9, r_cut, 260 + lmax + E)
+    g = U.oracle_graph(w)
+    m = B.Egnn(lmax, E, 9, w.r_cut, 7.0)
+    assert len(g[0]) > 5 and not U.fused_route(B, m, "layer", len(g[0]), n_owned, n)
+    rng = np.random.default_rng(lmax * 100 + E)
+    W = synth.layer_weights(rng, lmax, E, 9, 64, len(O.tp_paths(lmax, lmax, lmax)))
+    x = synth.node_features(rng, n, lmax, E)
+    ref = O.layer_forward(g, w.pos, w.box, x, W, lmax, lmax, E, 9, w.r_cut, 7.0)
+    e = U.rel_err(_run(B, w, g, W, x, shared), ref)
+    print(f"lmax {lmax} E {E}: {len(g[0])} edges, rel err {e:.2e}", flush=True)
+    assert e < TOL
