@@ -38,7 +38,7 @@ struct egnn_ctx {
   int nl_grid_atoms = -1;                //   and the atom count, workspace and positions it was built for
   const void* nl_grid_ws = nullptr;
   const void* nl_grid_pos = nullptr;
-  int use_fused = 0;                     // egnn_set_option(EGNN_OPT_FUSED): 0 two kernels, 1 / 2 the fused designs
+  int use_fused = 0;                     // egnn_set_option(EGNN_OPT_FUSED): 0 by the rules of edge_fused.hip, 1 / 2 older kernels
   bool w_half = false;                   // egnn_set_option(EGNN_OPT_W_FP16)
   int radial_bwd_route = 0;              // egnn_set_option(EGNN_OPT_RADIAL_BWD): 0 decided on the device, 1 exact, 2 grid
   // index tables of the readout / on-site kernels in the order the kernels read them, built on first use and kept:

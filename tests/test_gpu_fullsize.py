@@ -69,8 +69,8 @@ def test_fullsize_edge_set_bit_exact(index, cell_list):
 @pytest.mark.parametrize("index,fused", [(3, False), (4, False), (3, "shared"), (4, "shared"), (3, True), (4, True),
                                          (3, 2), (4, 2)])
 def test_fullsize_sampled_rows(index, fused):
-    """fused: False = S3 then S4 through the weight tensor, one row per edge; "shared" = the same with one row per
-    unordered pair of owned atoms (what bench.py times); True / 2 = the two fused designs."""
+    """fused: False = the default route (S3 and S4 in one kernel, S3 and S6 in one kernel), one row of weights per edge; "shared" = the
+    same with one row per unordered pair of owned atoms (what bench.py times); True / 2 = the two older fused designs."""
     import torch
     assert torch.cuda.is_available()
     path = os.path.join(GOLDEN, f"config{index}_samples.npz")

@@ -19,7 +19,8 @@ def B():
 
 @pytest.mark.parametrize("fused", [0, "shared", 1, 2])
 def test_layers_replay_from_a_graph(B, fused):
-    """fused: 0 = S3 then S4, "shared" = the same on a graph with shared rows of radial weights, 1 / 2 = fused designs."""
+    """fused: 0 = the default route, "shared" = the same on a graph with shared rows of radial weights, 1 / 2 = the older fused
+    designs."""
     import torch
     w = synth.small_cluster(150, 110, 3, 32, 6, 4.0, 41, False, 0.05)
     w.n_layers = 2

@@ -226,8 +226,8 @@ def test_tp_segsum_edge_along_polar_axis(B):
 @pytest.mark.parametrize("fused", [False, True, 2])
 @pytest.mark.parametrize("index", [1, 2])
 def test_model_forward_configs_full(B, index, fused):
-    """Configs 1 and 2 in full: species embedding, all layers, H_ij readout, every element; once through the materialised weight tensor
-    (default) and once with the fused radial-weights + message kernel."""
+    """Configs 1 and 2 in full: species embedding, all layers, H_ij readout, every element; by the default route (radial weights in the
+    registers of the kernels that use them) and by the two older kernels without a weight tensor."""
     w = synth.workload(index)
     wt = U.model_weights(w)
     g = U.oracle_graph(w)
@@ -282,8 +282,9 @@ def test_fused_sparse_graph(B, r_cut, fused):
 
 @pytest.mark.parametrize("s1,s2", [(1e-4, 1e-6), (30.0, 1e5), (1.0, 3e-9), (2e-3, 4e7)])
 def test_radial_weight_scales(B, s1, s2):
-    """The radial contraction (S3, and the second fused design) cuts its matrix-core operands into half-precision
-    pieces; their scalings come from the weights, so tiny and huge radial weights keep fp32-level accuracy."""
+    """The radial contraction cuts its matrix-core operands into half-precision pieces; their scalings come from the weights, so tiny
+    and huge radial weights keep fp32-level accuracy: in the layer and the readout with the weights in registers (the default
+    here), in the second fused design, and in S3 (test_radial_weight_scales_through_a_tensor)."""
     w = _cluster(120, 90, 3, 16, n_rbf=6, r_cut=4.0, seed=77)
     w.n_layers = 1
     wt = U.model_weights(w)
@@ -302,8 +303,39 @@ def test_radial_weight_scales(B, s1, s2):
         errs.append(U.rel_err(xs[0].cpu().numpy(), xs_ref[0]))
         if fused == 0:
             errs.append(U.rel_err(H.cpu().numpy(), H_ref))
-    print("rel err two-kernel %.2e (H_ij %.2e), fused %.2e" % tuple(errs), flush=True)
+    print("rel err default route %.2e (H_ij %.2e), fused lane %.2e" % tuple(errs), flush=True)
     assert max(errs) < 1e-5
+
+
+@pytest.mark.parametrize("s1,s2", [(1e-4, 1e-6), (30.0, 1e5), (1.0, 3e-9), (2e-3, 4e7)])
+def test_radial_weight_scales_through_a_tensor(B, s1, s2):
+    """The same scales where the weights go through memory: S3 with its own hidden layer (stage call, and the readout at 128 channels)
+    and with the hidden layer prepared for the sums as well (kept weights of a layer and a readout)."""
+    for lmax, E, n, n_owned, r_cut in ((3, 16, 120, 90, 4.0), (2, 128, 60, 40, 4.0)):
+        w = _cluster(n, n_owned, lmax, E, n_rbf=6, r_cut=r_cut, seed=78)
+        g = U.oracle_graph(w)
+        m = B.Egnn(lmax, E, 6, r_cut, 5.0)
+        graph = m.egnn_nlist(B.to_device(w.pos), n_owned, w.box, w.pbc)
+        rng = np.random.default_rng(E)
+        W = synth.layer_weights(rng, lmax, E, 6, 64, m.n_paths)
+        R = synth.readout_weights(rng, lmax, E, 6, 64, m.n_paths_readout, sum(m.n_out))
+        for mats in (W, R):
+            mats["W_r1"], mats["W_r2"] = mats["W_r1"] * np.float32(s1), mats["W_r2"] * np.float32(s2)
+        x = synth.node_features(rng, n, lmax, E)
+        d = np.linalg.norm(O.edge_vectors(w.pos, w.box, *g[:3]), axis=1)
+        rd = B.to_device(np.concatenate([np.zeros((len(d), 3)), d[:, None]], 1).astype(np.float32))
+        args = (graph, B.to_device(w.pos), w.box, B.to_device(x))
+        ws = m.workspace(graph)
+        routes = [U.fused_route(B, m, k, graph.n_edges, n_owned, n) for k in ("layer", "readout")]
+        assert routes == [True, E == 16]
+        H, wr = m.egnn_readout_hij_save(*args, B.to_device(R), ws)
+        got = [(m.egnn_radial_weights(0, rd, B.to_device(W["W_r1"]), B.to_device(W["W_r2"])), W, lmax),
+               (m.egnn_layer_forward_save(*args, B.to_device(W), ws)[1][0], W, lmax), (wr, R, O.L_READOUT)]
+        errs = [U.rel_err(a.cpu().numpy(), O.radial_weights(d, mats["W_r1"], mats["W_r2"], O.tp_paths(lmax, lmax, l_out), E, 6, r_cut))
+                for a, mats, l_out in got]
+        errs.append(U.rel_err(H.cpu().numpy(), O.readout_hij(g, w.pos, w.box, x, R, lmax, lmax, E, 6, r_cut, (0, 0, 1, 1, 2))))
+        print(f"E {E}: S3 {errs[0]:.2e}, kept {errs[1]:.2e} {errs[2]:.2e}, H_ij {errs[3]:.2e}", flush=True)
+        assert max(errs[:3]) < 3e-6 and errs[3] < 1e-5
 
 
 def _model_forward_small(B, lmax, E, periodic, n, n_owned, fused, r_cut=4.0):
