@@ -6,8 +6,8 @@
 // (Sec. 3 "Message passing"; coupling of Sec. 2.2 / Eq. 1 in the bond frame of Sec. 2.1 / Fig. 2(d)).
 //
 // Through memory, w is the largest object of a layer: at 3,000 atoms, 32 channels and lmax 4 it took 1.7 GB of writes (353 us)
-// and 3.4 GB of reads (640 us).  Here, same case: 520-575 us for the kernel below and 50 us of preparation; 12,000 + 8,000
-// atoms at 64 channels 7.4 -> 4.3 ms.
+// and 3.4 GB of reads (640 us).  Here, same case: 500 to 600 us for the kernel below (passes one after the other; 525 between
+// pauses) and 50 us of preparation; 12,000 + 8,000 atoms at 64 channels 7.4 -> 4.5 ms.
 //
 // Work: a wavefront takes a destination node and 4 channels and walks the node's edges 16 at a time.  The 16x16x32 tiles have the
 // rows of W_r2 as rows (4 paths x 4 channels) and the 16 edges as columns, so result register r of lane (n, q) is path 4 t + r
@@ -16,9 +16,10 @@
 // at a node's end and more lines per gathered row: 1,180 against 1,058 ns for the arithmetic of 64 lanes.)  The lane keeps
 // its 25 sums until the node ends; then the 16 edges are added.  No atomics, a fixed order.
 //
-// What bounds it: power and issue.  The products (66 x 16 cycles a tile) and the vector work (555 instructions) of the two
-// wavefronts of a SIMD overlap in part; together, without any memory access, they take 347 us at the clock that the chip holds
-// under them (2.3 GHz on zeros, 1.7-1.9 on data).  What the layout is for:
+// What bounds it: issue, at the clock that the chip holds under it.  Counters of that launch: 1.76 GHz (2.3 on zeros), vector
+// instructions, matrix ones among them, issue in 90 % of the SIMD-cycles, the matrix cores are busy in 36 %, the vector cache in 30 %, LDS in
+// 24 % of a CU's, 0.4 GB fetched.  The products (66 x 16 cycles a tile) and the vector work (555 instructions) of the two
+// wavefronts of a SIMD overlap in part; a copy of the loop without its memory accesses took 347 us.  What the layout is for:
 //   * W_r2 of 4 channels (45 KB at lmax 4) stays on the compute unit: high pieces in registers, low pieces in LDS.  With all of it
 //     in LDS (44 reads of 1 KB a tile and wavefront) LDS and the products took turns.
 //   * Both gathered streams go from memory straight to LDS one tile ahead, four neighbouring lanes per 64 bytes.  As loads to
@@ -88,7 +89,9 @@ __global__ __launch_bounds__(256) void ef_first_kernel(EfFirst g) {
 //   rec  [row][step][piece][q] of 16 bytes: hidden activations of a row times the cutoff envelope
 //   A    [group of 4 channels][tile of 4 paths][step][piece][lane] of 16 bytes: alpha W_r2; lane (m, q) holds path
 //        4 tile + m % 4, channel 4 group + m / 4
-// A thread takes an octet of units of two rows, W_r1 from LDS.  (With the fp32 products on
+// A thread takes an octet of units of two rows, W_r1 from LDS.  What bounds it: the vector ALU (busy throughout by the counters, 1.7 GHz;
+// 34 us for 313,000 rows of 16 Gaussians; sixteen lanes a row that share out its exponentials, rows asked for ahead and stores
+// without a test measured the same).  (With the fp32 products on
 // the matrix cores the weights came out less exact: their gradient summed over all edges was off by 2.03e-7 instead of 1.69e-7.)
 // The next workgroups write A, the last ones (if w2s) scalings and pieces as S3 takes them.
 struct EfSecond {
