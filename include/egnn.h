@@ -210,10 +210,10 @@ int egnn_node_mix(egnn_ctx* ctx, const float* x1, const float* W1, const float* 
  * registers of the lane that uses them, from lmax 2 on (at lmax 1 on small graphs); elsewhere, and where the scratch of
  * a small graph is too little for it, through a weight tensor in the workspace, as always for caller-supplied weights.
  * 1 and 2 choose older kernels, for a power of two >= 8 channels and at most 32 radial bases; they never write the
- * weights to memory either and are slower than the default (1: producer and consumer waves hand the weights over
+ * weights to memory either and are slower than that kernel (1: producer and consumer waves hand the weights over
  * through LDS, needs lmax >= 1; 2: tiles of 32 edges, needs its LDS tiles to fit: up to 128 channels at lmax 4); for
- * shapes that the chosen kernel does not support the weight tensor is used.  The _save calls take the default kernel for
- * the sums, whatever the option.  All routes compute the same function and cut the operands of the contraction into two
+ * shapes that the chosen kernel does not support the weight tensor is used.  The _save calls and the reverse pass take the
+ * route of option 0 for the sums, whatever the option.  All routes compute the same function and cut the operands of the contraction into two
  * half-precision pieces with scalings taken from W_r1 and W_r2 on the device (1: three bfloat16 pieces). */
 #define EGNN_OPT_FUSED 1
 /* EGNN_OPT_W_FP16 (default 0): when 1, egnn_layer_forward (option FUSED 0, own radial MLP) and egnn_readout_hij round the
