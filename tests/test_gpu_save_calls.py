@@ -105,3 +105,39 @@ def test_bits_of_saved_and_recomputed_quantities(B, lmax, E, n, n_owned, n_rbf, 
         ws.fill_(0xFF)
         dx2, grads2 = m.egnn_readout_backward_saved(g, col_ptr, perm, pos, w.box, x, R, kept, dH, ws)
         assert torch.equal(dx, dx2) and same(grads, grads2)
+
+
+@pytest.mark.parametrize("lmax,E,shared", [(2, 32, True), (3, 128, False), (4, 16, True)])
+def test_saving_and_recomputing_calls_replay_from_a_graph(B, lmax, E, shared):
+    """Recorded once (kernels only), replayed with new features and positions in the recorded buffers: the bits of eager calls."""
+    import torch
+    w, m, g, pos, _, _, W, R, ws, col_ptr, perm, x, dy, _ = _case(B, lmax, E, 120, 100, 11, 7.0, shared)
+    readout = U.fused_route(B, m, "readout", g.n_edges, 100, 120)         # (the other route copies tables: not meant to be recorded)
+
+    def calls():
+        y, kept = m.egnn_layer_forward_save(g, pos, w.box, x, W, ws)
+        out = [y, *kept]
+        if readout:
+            out += m.egnn_readout_hij_save(g, pos, w.box, x, R, ws)
+        dx, grads = m.egnn_layer_backward(g, col_ptr, perm, pos, w.box, x, W, dy, ws)
+        return out + [dx] + [grads[k] for k in sorted(grads)]
+
+    calls()
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        recorded = calls()
+    rng = np.random.default_rng(5)
+    for rep in range(4):
+        print("replay", rep, "readout", readout, flush=True)
+        if rep >= 2:
+            x.copy_(B.to_device(rng.standard_normal(tuple(x.shape)).astype(np.float32)))
+            pos.add_(B.to_device((1e-3 * rng.standard_normal(tuple(pos.shape))).astype(np.float32)))
+        want = [t.clone() for t in calls()]
+        torch.cuda.synchronize()
+        ws.fill_(0xFF)
+        for t in recorded:
+            t.fill_(float("nan"))
+        graph.replay()
+        torch.cuda.synchronize()
+        assert all(torch.equal(a, b) for a, b in zip(recorded, want))

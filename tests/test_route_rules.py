@@ -1,6 +1,8 @@
 """The rules that send a call to the kernels with the radial weights in registers or through a weight tensor, at the sizes where they
 turn, asked of the library without a GPU.  Each line is one that measurements on both sides set; what they measured stands beside
 the rules in edge_fused.hip and readout_fused.hip."""
+import os
+
 import pytest
 
 from tests import gpu_util as U
@@ -9,6 +11,9 @@ from tests import gpu_util as U
 @pytest.fixture(scope="module")
 def B():
     from paper_2507_03840_amd import binding
+    if not os.path.exists(binding.LIB_PATH):
+        import __graft_entry__
+        __graft_entry__.build()
     binding.load_library()
     return binding
 
