@@ -450,7 +450,9 @@ __global__ __launch_bounds__(256, EF_WG_PER_CU) void ef_layer_kernel(
 //   lmax 2 to 4, up to 64 channels: 1.06 to 2.9 times; keeping the weights 0.92 to 1.6, median 1.05 to 1.1, below 0.97 at lmax 2 on
 //     graphs without shared rows.  Where a node has about 19 edges, which leave every second tile of 16 nearly empty, keeping
 //     them 0.87 to 0.98 (2 to 20 us of the call, up to 3 % of a training step of the layer), not keeping them 1.06 to 1.4.
-//   lmax 2, 128 channels: 0.94 to 1.55, keeping them 0.85 to 1.4.
+//   lmax 2, 128 channels, whose 32 groups of channels read the hidden activations 32 times: up to 300 nodes 1.05 to 1.8, keeping them
+//     0.91 to 1.56; on more from 60 edges a node 1.06 to 1.46 and 0.96 to 1.2, from 800 nodes and 25 edges a node 1.06 to 1.46 and
+//     0.98 to 1.07.  Between them 0.94 to 1.14 and 0.85 to 1.04, from 800 nodes below 25 edges 1.02 to 1.06 and 0.96 to 1.0: not taken.
 //   lmax 1, where w is small: up to 800 nodes x 32 channels and 46,000 edges x 32 channels 1.11 to 1.45, keeping them 0.98 to 1.23;
 //     beyond, 0.95 to 1.27 and 0.78 to 0.98: not taken.  128 channels 0.89 to 1.7: not taken.
 //   lmax 0, where one path takes a tile of four, 0.58 to 1.0 for 37,000 edges and more: not taken.
@@ -459,7 +461,9 @@ __global__ __launch_bounds__(256, EF_WG_PER_CU) void ef_layer_kernel(
 bool egnn_edge_fused_fits(const egnn_ctx* ctx, const egnn_graph* g) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   const bool small = (int64_t)g->n_owned * E <= 800 * 32 && g->n_edges * E <= 46000 * 32;
-  return (lmax >= 2 || (lmax == 1 && E <= 64 && small)) && g->n_edges > 0 && g->n_owned > 0 &&
+  if (lmax == 0 || (lmax == 1 && (E > 64 || !small))) return false;
+  if (lmax == 2 && E == 128 && g->n_owned > 300 && g->n_edges < (int64_t)(g->n_owned < 800 ? 60 : 25) * g->n_owned) return false;
+  return g->n_edges > 0 && g->n_owned > 0 &&
          egnn_ef_carve(ctx, g, 0, nullptr).bytes <= (size_t)g->n_edges * ctx->n_paths[0] * E * sizeof(float);
 }
 

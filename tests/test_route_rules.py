@@ -36,7 +36,11 @@ def test_layer_lmax_1(B, E):
 @pytest.mark.parametrize("lmax", [2, 3, 4])
 @pytest.mark.parametrize("E", [8, 16, 32, 64, 128])
 def test_layer_from_lmax_2(B, lmax, E):
-    assert _layer(B, lmax, E, 524172, 2500) and _layer(B, lmax, E, 12560, 300) and _layer(B, lmax, E, 2000000, 12000, 20000)
+    assert _layer(B, lmax, E, 524172, 2500) and _layer(B, lmax, E, 9000, 300) and _layer(B, lmax, E, 2000000, 12000, 20000)
+    odd = lmax == 2 and E == 128                         # few edges on more than 300 nodes
+    assert _layer(B, lmax, E, 60 * 301, 301) and _layer(B, lmax, E, 60 * 301 - 1, 301) != odd
+    assert _layer(B, lmax, E, 60 * 799, 799) and _layer(B, lmax, E, 60 * 799 - 1, 799) != odd
+    assert _layer(B, lmax, E, 25 * 800, 800) and _layer(B, lmax, E, 25 * 800 - 1, 800) != odd
     assert not _layer(B, lmax, E, 40, 30)                # (the scratch does not fit where w would lie)
     assert not _layer(B, lmax, E, 0, 30) and not _layer(B, lmax, E, 0, 0, 30)
 
