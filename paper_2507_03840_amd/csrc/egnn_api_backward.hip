@@ -166,7 +166,12 @@ static int layer_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32_t
   // (the largest |dw|, kept by the kernel that writes dw, scales the contractions that read it)
   unsigned* dw_max = egnn_radial_backward_dw_max(b.radial);
   if ((rc = egnn_launch_fill_int(ctx, (int*)dw_max, 64, 0, st))) return rc;
-  if ((rc = egnn_launch_tp_backward(ctx, g, col_ptr, perm, b.rhat_d, b.h, w, b.da, b.dh, b.dw, dw_max, st, shared)))
+  // on the grid route the gradients of the weights are made where they are summed per length interval
+  const TpBinsArgs made = {g->src, g->dst, b.h, b.da};
+  const bool bins = egnn_tp_bins_fits(ctx, g->n_edges);
+  int* route = bins ? egnn_radial_backward_route(b.radial) : nullptr;
+  if (bins && (rc = egnn_launch_radial_route(ctx, W_r1, route, st))) return rc;
+  if ((rc = egnn_launch_tp_backward(ctx, g, col_ptr, perm, b.rhat_d, b.h, w, b.da, b.dh, b.dw, dw_max, st, shared, route)))
     return rc;
   tm.mark(2);
   // h = W_pre x_in ; owned rows also receive the self term
@@ -179,7 +184,7 @@ static int layer_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32_t
   tm.mark(3);
   // radial MLP
   rc = egnn_launch_radial_backward(ctx, 0, b.rhat_d, g->n_edges, W_r1, W_r2, b.dw, dW_r1, dW_r2, b.radial, true, st,
-                                   g->len_ptr, g->len_perm);
+                                   g->len_ptr, g->len_perm, bins ? &made : nullptr);
   tm.mark(4);
   return rc;
 }

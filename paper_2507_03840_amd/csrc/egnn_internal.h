@@ -120,25 +120,36 @@ size_t egnn_radial_grid_ws_bytes(const egnn_ctx*, int which, int64_t n_edges);
 int egnn_launch_radial_route(egnn_ctx*, const float* W_r1, int* route, hipStream_t);
 int egnn_launch_length_bins(egnn_ctx*, const float4* rd, int64_t n_edges, int* bin_ptr, int* perm, int* key, int* bucket,
                             int* cursor, const int* route, hipStream_t);
+// made (may be NULL): the binned gradients come from these rows (tp_bins.hip), not from dw
+struct TpBinsArgs {
+  const int *src, *dst;
+  const float *h, *da;      // features [n_total][D][E], gradients of the summed messages [n_owned][D][E]
+};
 int egnn_launch_radial_grid(egnn_ctx*, int which, const float* rhat_d, int64_t n_edges, const int* len_ptr,
                             const int* len_perm, const float* W_r1,
                             const float* W_r2, const float* dw, float* dW_r1, float* dW_r2, void* ws, const int* route,
                             int (*hidden_launch)(egnn_ctx*, const float*, long, const float*, float*, float*, hipStream_t),
-                            hipStream_t);
+                            hipStream_t, const TpBinsArgs* made = nullptr);
+bool egnn_tp_bins_fits(const egnn_ctx*, int64_t n_edges);
+int egnn_launch_tp_bins(egnn_ctx*, const TpBinsArgs&, const float* rhat_d, int64_t n_edges, const int* bin_ptr, const int* perm,
+                        float* Zp, const int* route, hipStream_t);
 size_t egnn_transpose_ws_bytes(int64_t n_edges, int32_t n_total);
-// dw_max (may be NULL): a word the caller has set to zero; raised to the bit pattern of the largest |dw| written
+// dw_max (may be NULL): a word the caller has set to zero; raised to the bit pattern of the largest |dw| written.
+// route (may be NULL): a device word; where it is 1, dw is left unwritten
 int egnn_launch_tp_backward(egnn_ctx*, const egnn_graph*, const int* col_ptr, const int* perm, const float* rhat_d,
                             const float* h, const float* w, const float* da, float* dh, float* dw, unsigned* dw_max,
-                            hipStream_t, bool shared_rows = false);
+                            hipStream_t, bool shared_rows = false, const int* route = nullptr);
 size_t egnn_radial_backward_ws_bytes(const egnn_ctx*, int which, int64_t n_edges);
 // dw_max_valid: the first word of ws (egnn_radial_backward_dw_max) holds the bit pattern of the largest |dw|; the
 // two large contractions then run on half-precision pieces, otherwise on bf16 pieces (which need no scaling)
 // len_ptr / len_perm (may be NULL): the edges grouped by length interval (egnn_length_bins), for the grid route
+// made (may be NULL): see egnn_launch_radial_grid; the route word is then already set (egnn_launch_radial_route)
 int egnn_launch_radial_backward(egnn_ctx*, int which, const float* rhat_d, int64_t n_edges, const float* W_r1,
                                 const float* W_r2, const float* dw, float* dW_r1, float* dW_r2, void* ws,
                                 bool dw_max_valid, hipStream_t, const int* len_ptr = nullptr,
-                                const int* len_perm = nullptr);
+                                const int* len_perm = nullptr, const TpBinsArgs* made = nullptr);
 static inline unsigned* egnn_radial_backward_dw_max(void* ws) { return reinterpret_cast<unsigned*>(ws); }
+static inline int* egnn_radial_backward_route(void* ws) { return reinterpret_cast<int*>((char*)ws + 384); }
 size_t egnn_readout_backward_partial_bytes(const egnn_ctx*, int64_t n_edges);
 size_t egnn_readout_backward_lds_bytes(const egnn_ctx*);
 void egnn_readout_backward_q_layout(const egnn_ctx*, int* q_off, int* nqp);   // q_off[EGNN_L_READOUT + 2]

@@ -395,7 +395,8 @@ static int rb_launch_hidden(egnn_ctx* ctx, const float* rhat_d, long n, const fl
 
 int egnn_launch_radial_backward(egnn_ctx* ctx, int which, const float* rhat_d, int64_t n_edges, const float* W_r1,
                                 const float* W_r2, const float* dw, float* dW_r1, float* dW_r2, void* ws,
-                                bool dw_max_valid, hipStream_t st, const int* len_ptr, const int* len_perm) {
+                                bool dw_max_valid, hipStream_t st, const int* len_ptr, const int* len_perm,
+                                const TpBinsArgs* made) {
   const int P = ctx->n_paths[which];
   const int PE = P * ctx->desc.channels, n_rbf = ctx->desc.n_rbf;
   int rc;
@@ -410,8 +411,8 @@ int egnn_launch_radial_backward(egnn_ctx* ctx, int which, const float* rhat_d, i
   float* scales = (float*)((char*)ws + 256);
   // Which route computes the gradients is decided on the device from W_r1 (or forced by EGNN_OPT_RADIAL_BWD): the
   // kernels of both are enqueued, those of the route that is not taken return at once.
-  int* route = (int*)((char*)ws + 384);
-  if ((rc = egnn_launch_radial_route(ctx, W_r1, route, st))) return rc;
+  int* route = egnn_radial_backward_route(ws);
+  if (!made && (rc = egnn_launch_radial_route(ctx, W_r1, route, st))) return rc;
   const int* skip = route;
   const bool half = dw_max_valid;
   char* base = (char*)ws + 512;
@@ -482,5 +483,5 @@ int egnn_launch_radial_backward(egnn_ctx* ctx, int which, const float* rhat_d, i
   if ((rc = egnn_launch_reduce_partials(ctx, part1, r1c, (long)EGNN_HIDDEN * n_rbf, dW_r1, 1.0f, st, skip))) return rc;
   // the grid route (its kernels run only if route[0] is 1)
   return egnn_launch_radial_grid(ctx, which, rhat_d, n_edges, len_ptr, len_perm, W_r1, W_r2, dw, dW_r1, dW_r2,
-                                 (char*)ws + rb_exact_ws_bytes(ctx, which, n_edges), route, rb_launch_hidden, st);
+                                 (char*)ws + rb_exact_ws_bytes(ctx, which, n_edges), route, rb_launch_hidden, st, made);
 }

@@ -23,10 +23,8 @@
 // has a fixed order, no floating-point atomics.
 #include <algorithm>
 #include "egnn_internal.h"
+#include "radial_grid.h"
 
-#define RG_BINS 2048
-#define RG_PTS 6
-#define RG_NODES (RG_BINS + RG_PTS - 1)
 #define RG_COLS 1024          // columns of dw per workgroup of the binning pass (256 threads x float4)
 #define RG_L1_LIMIT 256.0f    // largest absolute row sum of W_r1 this route accepts (at 16 radial bases; scaled with
                               // the inverse width of the Gaussians, n_rbf - 1, otherwise)
@@ -164,17 +162,6 @@ __global__ __launch_bounds__(64 * RG_WAVES) void rg_place_kernel(const int* __re
   }
 }
 static_assert(RG_BINS == 1 << 11, "rg_place_kernel ranks by 11 bits");
-
-// Lagrange weights of the six grid points -2 .. 3 around an interval, at position t in [0, 1) inside it
-__device__ __forceinline__ void rg_weights(float t, float (&phi)[RG_PTS]) {
-  const float a = t + 2.0f, b = t + 1.0f, c = t, d = t - 1.0f, e = t - 2.0f, f = t - 3.0f;
-  phi[0] = b * c * d * e * f * (-1.0f / 120.0f);
-  phi[1] = a * c * d * e * f * (1.0f / 24.0f);
-  phi[2] = a * b * d * e * f * (-1.0f / 12.0f);
-  phi[3] = a * b * c * e * f * (1.0f / 12.0f);
-  phi[4] = a * b * c * d * f * (-1.0f / 24.0f);
-  phi[5] = a * b * c * d * e * (1.0f / 120.0f);
-}
 
 // The binning pass.  grid = (interval, column tile); a thread owns four consecutive columns of dw and adds the rows
 // of the interval's edges, in ascending edge id, into six running sums (one per grid point the interval touches):
@@ -367,7 +354,7 @@ int egnn_launch_radial_grid(egnn_ctx* ctx, int which, const float* rhat_d, int64
                             const int* len_perm, const float* W_r1,
                             const float* W_r2, const float* dw, float* dW_r1, float* dW_r2, void* ws, const int* route,
                             int (*hidden_launch)(egnn_ctx*, const float*, long, const float*, float*, float*, hipStream_t),
-                            hipStream_t st) {
+                            hipStream_t st, const TpBinsArgs* made) {
   const int P = ctx->n_paths[which];
   const int PE = P * ctx->desc.channels, n_rbf = ctx->desc.n_rbf;
   PathAlpha al;
@@ -397,13 +384,17 @@ int egnn_launch_radial_grid(egnn_ctx* ctx, int which, const float* rhat_d, int64
   } else if ((rc = egnn_launch_length_bins(ctx, rd, n_edges, bin_ptr, perm, key, bucket, cursor, route, st))) {
     return rc;
   }
-  // the one pass over dw
-  // column tiles of equal width (a multiple of four columns, at most RG_COLS)
-  const int n_tiles = (PE + RG_COLS - 1) / RG_COLS;
-  const int cols_per_wg = ((PE + n_tiles - 1) / n_tiles + 3) & ~3;
-  hipLaunchKernelGGL(rg_bin_kernel, dim3(RG_BINS, n_tiles), b256, 0, st, dw, rd, bin_ptr, perm, Zp, (int)n_edges, PE,
-                     cols_per_wg, inv_h, route);
-  EGNN_LAUNCH_CHECK(ctx, "rg_bin_kernel");
+  if (made) {
+    if ((rc = egnn_launch_tp_bins(ctx, *made, rhat_d, n_edges, bin_ptr, perm, Zp, route, st))) return rc;
+  } else {
+    // the one pass over dw
+    // column tiles of equal width (a multiple of four columns, at most RG_COLS)
+    const int n_tiles = (PE + RG_COLS - 1) / RG_COLS;
+    const int cols_per_wg = ((PE + n_tiles - 1) / n_tiles + 3) & ~3;
+    hipLaunchKernelGGL(rg_bin_kernel, dim3(RG_BINS, n_tiles), b256, 0, st, dw, rd, bin_ptr, perm, Zp, (int)n_edges, PE,
+                       cols_per_wg, inv_h, route);
+    EGNN_LAUNCH_CHECK(ctx, "rg_bin_kernel");
+  }
   hipLaunchKernelGGL(rg_assemble_kernel, dim3(RG_NODES), b256, 0, st, Zp, Z, PE, ctx->log2_channels, al, route);
   EGNN_LAUNCH_CHECK(ctx, "rg_assemble_kernel");
   // G and S at the grid points

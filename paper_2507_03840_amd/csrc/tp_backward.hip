@@ -6,7 +6,8 @@
 // The sum over the outgoing edges of a source is what the forward pass does not have: edges are walked in
 // source-sorted order (col_ptr / perm from egnn_graph_transpose), one workgroup per source node, partial sums
 // in registers, slots added in fixed order -- the same shape as the forward kernel, no atomics.
-// dw_k is written per edge (it feeds the radial-MLP gradients).
+// dw_k feeds the radial-MLP gradients: written per edge, or not at all where tp_bins.hip makes it for itself (that route
+// reads 3.4 GB of w at 3,000 atoms, lmax 4, 32 channels and nothing bounds it but that: 1,350 -> 590 us).
 #include "egnn_internal.h"
 #include "bond_frame.h"
 
@@ -14,7 +15,7 @@
 // run of weights, so a run is loaded, turned into its part of the feature gradient and its own gradient, and stored
 // before the next one is touched -- at most ten weights and ten weight gradients are live at once instead of 42 + 42,
 // which is what lets two waves share a SIMD.
-template <int LMAX, int L1>
+template <int LMAX, int L1, bool DW>
 struct TpBwdDegree {
   using Mid = typename LayerMid<LMAX>::T;
   __device__ __forceinline__ static void run(const float* v, const float* go, float* gv, const float* wr,
@@ -23,16 +24,18 @@ struct TpBwdDegree {
     float gw[count];
     Mid::template run_bwd_l1<L1>(v + L1 * L1, wr + first, go, gv + L1 * L1, gw);
 #pragma unroll
-    for (int p = 0; p < count; ++p) {
+    for (int p = 0; p < (DW ? count : 0); ++p) {
       __builtin_nontemporal_store(gw[p], dwp + ((size_t)(first + p) << log2E));
       mx = fmaxf(mx, fabsf(gw[p]));
     }
-    if constexpr (L1 < LMAX) TpBwdDegree<LMAX, L1 + 1>::run(v, go, gv, wr, dwp, log2E, mx);
+    if constexpr (L1 < LMAX) TpBwdDegree<LMAX, L1 + 1, DW>::run(v, go, gv, wr, dwp, log2E, mx);
   }
 };
 
 // LE = log2(channels): a template parameter so that the row offsets of w, dw, h and da are immediates.
-template <int LMAX, int LE>
+// DW = false: the feature gradients alone (the weight gradients are made where they are summed, tp_bins.hip).
+// route (may be NULL): where it is 1 only the kernel without dw runs, else only the one with it.
+template <int LMAX, int LE, bool DW>
 __global__ __launch_bounds__(256, 2) void tp_backward_kernel(const int* __restrict__ col_ptr, const int* __restrict__ perm,
                                                              const int* __restrict__ dst,
                                                              const float4* __restrict__ rhat_d,
@@ -40,7 +43,9 @@ __global__ __launch_bounds__(256, 2) void tp_backward_kernel(const int* __restri
                                                              const int* __restrict__ w_row,
                                                              const float* __restrict__ da, float* __restrict__ dh,
                                                              float* __restrict__ dw, unsigned* __restrict__ dw_max,
-                                                             int n_total, int nodes_per_xcd, float scale) {
+                                                             int n_total, int nodes_per_xcd, float scale,
+                                                             const int* __restrict__ route) {
+  if (route && (route[0] != 0) == DW) return;
   constexpr int log2E = LE;
   using Mid = typename LayerMid<LMAX>::T;
   constexpr int D = (LMAX + 1) * (LMAX + 1);
@@ -102,13 +107,13 @@ __global__ __launch_bounds__(256, 2) void tp_backward_kernel(const int* __restri
     egnn_bond_trig<LMAX>(g.x, g.y, g.z, t);
     egnn_to_bond_frame<LMAX>(v, t);
     egnn_to_bond_frame<LMAX>(go, t);
-    TpBwdDegree<LMAX, 0>::run(v, go, gv, wr, dwp, log2E, mx);
+    TpBwdDegree<LMAX, 0, DW>::run(v, go, gv, wr, dwp, log2E, mx);
     egnn_from_bond_frame<LMAX>(gv, t);
 #pragma unroll
     for (int q = 0; q < D; ++q) acc[q] += gv[q];
   }
 
-  if (dw_max) {
+  if (DW && dw_max) {
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) mx = fmaxf(mx, __shfl_xor(mx, off));
     if ((tid & 63) == 0) egnn_raise_max(dw_max, mx);
@@ -127,7 +132,7 @@ __global__ __launch_bounds__(256, 2) void tp_backward_kernel(const int* __restri
 
 int egnn_launch_tp_backward(egnn_ctx* ctx, const egnn_graph* g, const int* col_ptr, const int* perm,
                             const float* rhat_d, const float* h, const float* w, const float* da, float* dh,
-                            float* dw, unsigned* dw_max, hipStream_t stream, bool shared_rows) {
+                            float* dw, unsigned* dw_max, hipStream_t stream, bool shared_rows, const int* route) {
   const int n = g->n_total;
   const int* w_row = shared_rows ? g->w_row : nullptr;
   if (n == 0) return EGNN_OK;
@@ -135,9 +140,14 @@ int egnn_launch_tp_backward(egnn_ctx* ctx, const egnn_graph* g, const int* col_p
   dim3 grid(per_xcd * 8), block(256);
   const float scale = 1.0f / sqrtf(ctx->desc.agg_norm);
   const float4* rd = reinterpret_cast<const float4*>(rhat_d);
-#define LAUNCH(L, LE_)                                                                                          \
-  hipLaunchKernelGGL((tp_backward_kernel<L, LE_>), grid, block, 0, stream, col_ptr, perm, g->dst, rd, h, w, w_row, da, \
-                     dh, dw, dw_max, n, per_xcd, scale)
+#define ONE(L, LE_, DW)                                                                                          \
+  hipLaunchKernelGGL((tp_backward_kernel<L, LE_, DW>), grid, block, 0, stream, col_ptr, perm, g->dst, rd, h, w, w_row, da, \
+                     dh, dw, dw_max, n, per_xcd, scale, route)
+#define LAUNCH(L, LE_)                     \
+  do {                                     \
+    if (route) ONE(L, LE_, false);         \
+    ONE(L, LE_, true);                     \
+  } while (0)
 #define CASES(L)                                                                        \
   switch (ctx->log2_channels) {                                                         \
     case 3: LAUNCH(L, 3); break;                                                        \
@@ -157,6 +167,7 @@ int egnn_launch_tp_backward(egnn_ctx* ctx, const egnn_graph* g, const int* col_p
   }
 #undef CASES
 #undef LAUNCH
+#undef ONE
   EGNN_LAUNCH_CHECK(ctx, "tp_backward_kernel");
   return EGNN_OK;
 }

@@ -230,6 +230,14 @@ def fused_route(B, m, which, n_edges, n_owned, n_total):
     return bool(f(m.ctx, C.byref(g)))
 
 
+def tp_bins_route(m, n_edges):
+    """Whether the adjoint of a layer on so many edges sums the radial weights' gradient as it is made: the library's own rule."""
+    import ctypes as C
+    f = m.lib._Z17egnn_tp_bins_fitsPK8egnn_ctxl
+    f.restype = C.c_bool
+    return bool(f(m.ctx, C.c_int64(n_edges)))
+
+
 def recorded_nodes(lib, call):
     """Number of nodes (kernels, here) that `call` leaves in a recorded graph."""
     import ctypes as C

@@ -1,6 +1,6 @@
 """The rules that send a call to the kernels with the radial weights in registers or through a weight tensor, at the sizes where they
 turn, asked of the library without a GPU.  Each line is one that measurements on both sides set; what they measured stands beside
-the rules in edge_fused.hip and readout_fused.hip."""
+the rules in edge_fused.hip, readout_fused.hip and tp_bins.hip."""
 import os
 
 import pytest
@@ -70,3 +70,11 @@ def test_readout(B, lmax, E, n_orb, n_edges, here, beyond):
 def test_readout_rows_of_v(B, orb):
     """Sets with more rows of V in a degree than the kernel has room for: the two kernels."""
     assert not U.fused_route(B, B.Egnn(3, 32, 16, 10.0, 20.0, orb_l=orb), "readout", 300000, 1200, 1200)
+
+
+@pytest.mark.parametrize("lmax,E,first", [(1, 8, 12000), (2, 16, 12000), (3, 32, 12000), (4, 128, 12000), (3, 16, 30000), (4, 16, 30000),
+                                          (3, 8, 60000), (4, 8, 60000)])
+def test_weight_gradient_summed_as_it_is_made(B, lmax, E, first):
+    m = B.Egnn(lmax, E, 16, 10.0, 20.0)
+    assert U.tp_bins_route(m, first) and not U.tp_bins_route(m, first - 1)
+    assert not U.tp_bins_route(B.Egnn(0, E, 16, 10.0, 20.0), 1000000)
