@@ -107,7 +107,8 @@ int egnn_workspace_bytes(const egnn_ctx* ctx, int64_t n_edges, int32_t n_owned, 
  * pointer is rejected with EGNN_EINVAL; a workspace overwritten in between gives a wrong list but no access outside
  * the buffers).  With ws == NULL
  * every destination sweeps all atoms (O(n_owned * n_total), fine for a few thousand atoms).  Both give the
- * same edge list.  count synchronises the stream (twice with a workspace: bounding box, edge count). */
+ * same edge list.  count synchronises the stream (edge count; with a workspace and more than 32,768 atoms that are not periodic along
+ * every axis a second time: bounding box). */
 int egnn_nlist_workspace_bytes(const egnn_ctx* ctx, int32_t n_total, size_t* bytes);
 int egnn_nlist_count(egnn_ctx* ctx, const float* pos, int32_t n_owned, int32_t n_total,
                      const float box[3], const uint8_t pbc[3], int32_t* row_ptr, int64_t* n_edges,

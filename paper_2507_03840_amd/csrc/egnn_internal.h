@@ -34,8 +34,8 @@ struct egnn_ctx {
   std::vector<hipEvent_t> ev;
   std::vector<int> ev_kind;              // per recorded call: 0 = layer, 1 = readout, 2 = layer adjoint, 3 = readout adjoint
   int ev_max_calls = 0;
-  CellGrid nl_grid;                      // grid of the last egnn_nlist_count that used the cell list
-  int nl_grid_atoms = -1;                //   and the atom count, workspace and positions it was built for
+  int nl_grid_atoms = -1;                // last egnn_nlist_count that used the cell list: atom counts, workspace and positions
+  int nl_grid_owned = 0;
   const void* nl_grid_ws = nullptr;
   const void* nl_grid_pos = nullptr;
   int use_fused = 0;                     // egnn_set_option(EGNN_OPT_FUSED): 0 by the rules of edge_fused.hip, 1 / 2 older kernels
@@ -118,8 +118,10 @@ int egnn_launch_reduce_partials(egnn_ctx*, float* partial /* scratch, may be ove
 // the radial MLP's reverse pass by interpolation on a grid of distances (radial_grid.hip)
 size_t egnn_radial_grid_ws_bytes(const egnn_ctx*, int which, int64_t n_edges);
 int egnn_launch_radial_route(egnn_ctx*, const float* W_r1, int* route, hipStream_t);
+// rd (may be NULL: then the lengths come from g, pos and box): edge records
 int egnn_launch_length_bins(egnn_ctx*, const float4* rd, int64_t n_edges, int* bin_ptr, int* perm, int* key, int* bucket,
-                            int* cursor, const int* route, hipStream_t);
+                            int* cursor, const int* route, hipStream_t, const egnn_graph* g = nullptr, const float* pos = nullptr,
+                            const float* box = nullptr);
 // made (may be NULL): the binned gradients come from these rows (tp_bins.hip), not from dw
 struct TpBinsArgs {
   const int *src, *dst;

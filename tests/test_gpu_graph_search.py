@@ -1,0 +1,78 @@
+"""GPU tests of the neighbour search (nlist.hip) where its parts change: cells along an axis from one to several, periodic or not; atoms
+far outside the box; pairs at the cutoff to the last bit; rows longer than what the counting pass keeps; more candidates than are put
+in order at a time; and the row scan at its block sizes."""
+import numpy as np
+import pytest
+
+from oracle import egnn_oracle as O
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    from paper_2507_03840_amd import binding
+    binding.load_library()
+    return binding
+
+
+def _check(B, pos, n_owned, box, pbc, r_cut):
+    pos, box, pbc = np.asarray(pos, np.float32), np.asarray(box, np.float32), np.asarray(pbc, np.uint8)
+    g = B.Egnn(1, 8, 8, r_cut, 1.0).egnn_nlist(B.to_device(pos), n_owned, box, pbc)
+    src, dst, shift, row_ptr = O.neighbour_list(pos, n_owned, box, pbc, r_cut)
+    print("  edges", len(src), "longest row", np.diff(row_ptr).max(), flush=True)
+    assert g.n_edges == len(src)
+    assert np.array_equal(g.row_ptr.cpu().numpy(), row_ptr)
+    assert np.array_equal(g.src.cpu().numpy(), src) and np.array_equal(g.dst.cpu().numpy(), dst)
+    assert np.array_equal(g.shift.cpu().numpy().reshape(-1, 3), shift)
+    return row_ptr
+
+
+@pytest.mark.parametrize("pbc", [(1, 1, 1), (1, 1, 0), (0, 1, 1), (0, 0, 0)])
+@pytest.mark.parametrize("cells", [(2, 2, 2), (3, 2, 4), (4, 3, 2), (2, 5, 3), (6, 4, 5)])
+def test_cells_along_an_axis(B, cells, pbc):
+    """Two cells an axis are the fewest of a periodic one; atoms are moved out of the box by up to 40 of its lengths."""
+    rng = np.random.default_rng([*cells, *pbc])
+    box = np.array([2.03 * c for c in cells], np.float32)
+    n = 700
+    pos = rng.random((n, 3)) * box
+    pos += rng.integers(-40, 41, (n, 3)) * box.astype(np.float64) * np.array(pbc)
+    print("case", cells, pbc, flush=True)
+    _check(B, pos, 611, box, pbc, 2.0)
+
+
+@pytest.mark.parametrize("scale", [1.0, 1e-3, 3e4])
+def test_pairs_at_the_cutoff(B, scale):
+    """A lattice whose third shell lies at the cutoff up to the rounding of the coordinates: half of it in, half of it out."""
+    rng = np.random.default_rng(4)
+    g = np.stack(np.meshgrid(*[np.arange(8)] * 3, indexing="ij"), -1).reshape(-1, 3) * 1.1
+    pos = (g + 5.0 + 3e-7 * rng.normal(size=g.shape)) * scale
+    _check(B, pos, len(pos), [8 * 1.1 * scale] * 3, [1, 1, 1], np.float32(1.1 * np.sqrt(3.0) * scale))
+    _check(B, pos, len(pos), [8 * 1.1 * scale] * 3, [0, 0, 0], np.float32(1.1 * np.sqrt(3.0) * scale))
+
+
+@pytest.mark.parametrize("n,n_owned", [(257, 257), (258, 258), (400, 300), (1024, 64), (1026, 300), (2100, 50), (2100, 1000)])
+def test_rows_and_candidate_lists(B, n, n_owned):
+    """All atoms in reach of each other: rows of n - 1 (256 sources an atom are kept), n candidates (1,024 are put in order at a time)."""
+    rng = np.random.default_rng(n)
+    row_ptr = _check(B, rng.random((n, 3)), n_owned, [1, 1, 1], [0, 0, 0], 3.0)
+    assert np.array_equal(np.diff(row_ptr), np.full(n_owned, n - 1))
+
+
+@pytest.mark.parametrize("n_total", [1, 7, 8191, 8193, 32767, 32768, 32769, 40960, 65537, 100000])
+def test_row_scan(B, n_total):
+    """The scan takes 32,768 rows at a time (through the index of the edges by source)."""
+    import torch
+    rng = np.random.default_rng(n_total)
+    n_edges = 30000
+    src = rng.integers(0, n_total, n_edges).astype(np.int32)
+    dst = np.sort(rng.integers(0, 40, n_edges)).astype(np.int32) % max(1, min(40, n_total))
+    dst = np.sort(dst).astype(np.int32)
+    n_owned = int(dst.max()) + 1
+    row_ptr = np.concatenate([[0], np.cumsum(np.bincount(dst, minlength=n_owned))]).astype(np.int32)
+    m = B.Egnn(1, 8, 4, 8.0, 1.0)
+    g = B.Graph(B.to_device(src), B.to_device(dst), B.to_device(row_ptr), None, n_owned, n_total)
+    ws = torch.empty(m.egnn_backward_workspace_bytes(n_edges, n_owned, n_total), dtype=torch.uint8, device="cuda")
+    col_ptr, perm = m.egnn_graph_transpose(g, ws)
+    assert np.array_equal(col_ptr.cpu().numpy(), np.concatenate([[0], np.cumsum(np.bincount(src, minlength=n_total))]))
+    assert np.array_equal(perm.cpu().numpy(), np.argsort(src, kind="stable"))
