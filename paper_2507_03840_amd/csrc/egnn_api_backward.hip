@@ -167,9 +167,11 @@ static int layer_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32_t
   unsigned* dw_max = egnn_radial_backward_dw_max(b.radial);
   if ((rc = egnn_launch_fill_int(ctx, (int*)dw_max, 64, 0, st))) return rc;
   // on the grid route the gradients of the weights are made where they are summed per length interval
-  const TpBinsArgs made = {g->src, g->dst, b.h, b.da};
   const bool bins = egnn_tp_bins_fits(ctx, g->n_edges);
   int* route = bins ? egnn_radial_backward_route(b.radial) : nullptr;
+  const EgnnBins made = [&](const int* bin_ptr, const int* len_perm, float* Zp) {
+    return egnn_launch_tp_bins(ctx, {g->src, g->dst, b.h, b.da}, b.rhat_d, g->n_edges, bin_ptr, len_perm, Zp, route, st);
+  };
   if (bins && (rc = egnn_launch_radial_route(ctx, W_r1, route, st))) return rc;
   if ((rc = egnn_launch_tp_backward(ctx, g, col_ptr, perm, b.rhat_d, b.h, w, b.da, b.dh, b.dw, dw_max, st, shared, route)))
     return rc;
@@ -285,9 +287,18 @@ static int readout_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32
   if ((rc = egnn_launch_node_mix(ctx, x, W_s, nullptr, nullptr, b.zs, n_t, st))) return rc;
   if ((rc = egnn_launch_node_mix(ctx, x, W_t, nullptr, nullptr, b.zt, n_t, st))) return rc;
   tm.mark(0);
+  // on the grid route the gradients of the weights are made where they are summed per length interval
+  const bool bins = egnn_readout_adjoint_fits(ctx, g->n_edges);
+  int* route = bins ? egnn_radial_backward_route(b.radial) : nullptr;
+  const ReadoutAdjoint adj = {b.rhat_d, b.zs, b.zt, w, V, b.dw, b.dz, b.dV_partial, route, shared};
+  const EgnnBins made = [&](const int* bin_ptr, const int* len_perm, float* Zp) {
+    return egnn_launch_readout_bins(ctx, g, adj, bin_ptr, len_perm, Zp, st);
+  };
+  if (bins && (rc = egnn_launch_radial_route(ctx, W_r1, route, st))) return rc;
   if ((rc = egnn_launch_readout_backward(ctx, g, b.rhat_d, b.zs, b.zt, w, V, b.tab_i, b.tab_f, dH, b.dz, b.dw, dV,
-                                         b.dV_partial, st, shared)))
+                                         b.dV_partial, st, shared, route)))
     return rc;
+  if (bins && (rc = egnn_launch_readout_adjoint(ctx, g, adj, dH, dV, st))) return rc;
   tm.mark(1);
   // dz_k feeds the source row (zs) and the destination row (zt, owned nodes only)
   if ((rc = egnn_launch_segsum_rows(ctx, b.dz, col_ptr, perm, b.dzs, n_t, row_len, st))) return rc;
@@ -302,7 +313,7 @@ static int readout_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32
   if ((rc = egnn_launch_mix_wgrad(ctx, b.dzt, x, dW_t, b.wgrad_partial, n_t, st))) return rc;
   tm.mark(2);
   rc = egnn_launch_radial_backward(ctx, 1, b.rhat_d, g->n_edges, W_r1, W_r2, b.dw, dW_r1, dW_r2, b.radial, false, st,
-                                   g->len_ptr, g->len_perm);   // (no running maximum of this dw: bf16 pieces on the exact route)
+                                   g->len_ptr, g->len_perm, bins ? &made : nullptr);   // (no running maximum of this dw: bf16 pieces on the exact route)
   tm.mark(3);
   tm.mark(4);
   return rc;

@@ -2,6 +2,7 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <functional>
 #include <string>
 #include <vector>
 #include "../../include/egnn.h"
@@ -122,7 +123,8 @@ int egnn_launch_radial_route(egnn_ctx*, const float* W_r1, int* route, hipStream
 int egnn_launch_length_bins(egnn_ctx*, const float4* rd, int64_t n_edges, int* bin_ptr, int* perm, int* key, int* bucket,
                             int* cursor, const int* route, hipStream_t, const egnn_graph* g = nullptr, const float* pos = nullptr,
                             const float* box = nullptr);
-// made (may be NULL): the binned gradients come from these rows (tp_bins.hip), not from dw
+// made (may be NULL): makes the gradients and bins them (tp_bins.hip, readout_adjoint.hip), instead of the pass over dw
+using EgnnBins = std::function<int(const int* bin_ptr, const int* perm, float* Zp)>;
 struct TpBinsArgs {
   const int *src, *dst;
   const float *h, *da;      // features [n_total][D][E], gradients of the summed messages [n_owned][D][E]
@@ -131,7 +133,7 @@ int egnn_launch_radial_grid(egnn_ctx*, int which, const float* rhat_d, int64_t n
                             const int* len_perm, const float* W_r1,
                             const float* W_r2, const float* dw, float* dW_r1, float* dW_r2, void* ws, const int* route,
                             int (*hidden_launch)(egnn_ctx*, const float*, long, const float*, float*, float*, hipStream_t),
-                            hipStream_t, const TpBinsArgs* made = nullptr);
+                            hipStream_t, const EgnnBins* made = nullptr);
 bool egnn_tp_bins_fits(const egnn_ctx*, int64_t n_edges);
 int egnn_launch_tp_bins(egnn_ctx*, const TpBinsArgs&, const float* rhat_d, int64_t n_edges, const int* bin_ptr, const int* perm,
                         float* Zp, const int* route, hipStream_t);
@@ -149,7 +151,7 @@ size_t egnn_radial_backward_ws_bytes(const egnn_ctx*, int which, int64_t n_edges
 int egnn_launch_radial_backward(egnn_ctx*, int which, const float* rhat_d, int64_t n_edges, const float* W_r1,
                                 const float* W_r2, const float* dw, float* dW_r1, float* dW_r2, void* ws,
                                 bool dw_max_valid, hipStream_t, const int* len_ptr = nullptr,
-                                const int* len_perm = nullptr, const TpBinsArgs* made = nullptr);
+                                const int* len_perm = nullptr, const EgnnBins* made = nullptr);
 static inline unsigned* egnn_radial_backward_dw_max(void* ws) { return reinterpret_cast<unsigned*>(ws); }
 static inline int* egnn_radial_backward_route(void* ws) { return reinterpret_cast<int*>((char*)ws + 384); }
 size_t egnn_readout_backward_partial_bytes(const egnn_ctx*, int64_t n_edges);
@@ -158,7 +160,18 @@ void egnn_readout_backward_q_layout(const egnn_ctx*, int* q_off, int* nqp);   //
 int egnn_launch_readout_backward(egnn_ctx*, const egnn_graph*, const float* rhat_d, const float* zs, const float* zt,
                                  const float* w, const float* V, const int* tab_i, const float* tab_f,
                                  const float* dH, float* dz, float* dw, float* dV, float* partial, hipStream_t,
-                                 bool shared_rows = false);
+                                 bool shared_rows = false, const int* skip = nullptr);
+// the reverse pass of the readout on the grid route (readout_adjoint.hip); dq: room of dw; route[1] = 1 - route[0]
+struct ReadoutAdjoint {
+  const float *rhat_d, *zs, *zt, *w, *V, *dq;
+  float *dz, *partial;
+  const int* route;
+  bool shared_rows;
+};
+bool egnn_readout_adjoint_fits(const egnn_ctx*, int64_t n_edges);
+int egnn_launch_readout_adjoint(egnn_ctx*, const egnn_graph*, const ReadoutAdjoint&, const float* dH, float* dV, hipStream_t);
+int egnn_launch_readout_bins(egnn_ctx*, const egnn_graph*, const ReadoutAdjoint&, const int* bin_ptr, const int* perm, float* Zp,
+                             hipStream_t);
 // half = true: `w` holds half-precision weights in the layout of w_half.h (egnn_w_bytes sizes it)
 // shared_rows = true: `w` has one row per entry of g->w_row (egnn_edge_pairs), else one per edge
 // h_half = true (needs half): `h` holds half-precision values

@@ -435,7 +435,7 @@ def generate():
 # ------------------------------------------------------------------ orbital blocks from coupled values
 def generate_uncouple():
     """Per pair of shell degrees (l_a, l_b <= 2) the block's coupled values, L after L, turned in place into the block
-    [m_a][m_b] (Eq. 1 read backwards): x[i] in registers, constants as literals."""
+    [m_a][m_b] (Eq. 1 read backwards), and the transpose: x[i] in registers, constants as literals."""
     out = ["// GENERATED by gen_tables.py -- do not edit.", "#pragma once", ""]
     for la in range(ORB_LMAX + 1):
         for lb in range(ORB_LMAX + 1):
@@ -446,6 +446,8 @@ def generate_uncouple():
                 at += 2 * L + 1
             assert at == na * nb and np.allclose(U.T @ U, np.eye(na * nb), atol=1e-12)
             out.append(emit_matvec(f"egnn_uncouple_{la}{lb}", U, f"({la},{lb}): coupled values -> block"))
+            out.append("")
+            out.append(emit_matvec(f"egnn_couple_{la}{lb}", U.T, f"({la},{lb}): block -> coupled values"))
             out.append("")
     return "\n".join(out) + "\n"
 

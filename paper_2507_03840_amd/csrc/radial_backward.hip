@@ -396,7 +396,7 @@ static int rb_launch_hidden(egnn_ctx* ctx, const float* rhat_d, long n, const fl
 int egnn_launch_radial_backward(egnn_ctx* ctx, int which, const float* rhat_d, int64_t n_edges, const float* W_r1,
                                 const float* W_r2, const float* dw, float* dW_r1, float* dW_r2, void* ws,
                                 bool dw_max_valid, hipStream_t st, const int* len_ptr, const int* len_perm,
-                                const TpBinsArgs* made) {
+                                const EgnnBins* made) {
   const int P = ctx->n_paths[which];
   const int PE = P * ctx->desc.channels, n_rbf = ctx->desc.n_rbf;
   int rc;

@@ -33,7 +33,7 @@ typedef float rg_f4 __attribute__((ext_vector_type(4)));
 
 static size_t rg_a256(size_t n) { return (n + 255) & ~(size_t)255; }
 
-// route[0] = 1: this route computes the gradients, 0: the exact route does.  forced: 0 decide from W_r1, 1 exact, 2 grid.
+// route[0] = 1: this route computes the gradients, 0: the exact route does; route[1] = 1 - route[0].  forced: 0 decide from W_r1, 1 exact, 2 grid.
 __global__ __launch_bounds__(64) void rg_route_kernel(const float* __restrict__ W_r1, int n_rbf, int forced,
                                                       int* __restrict__ route) {
   float s = 0.0f;
@@ -42,7 +42,10 @@ __global__ __launch_bounds__(64) void rg_route_kernel(const float* __restrict__ 
   for (int off = 32; off > 0; off >>= 1) s = fmaxf(s, __shfl_xor(s, off));
   // the hidden layer's input varies with d at a rate ~ (row sum) / (width of a Gaussian) = s (n_rbf - 1) / r_cut
   const bool smooth = s * (float)(n_rbf - 1) <= RG_L1_LIMIT * 15.0f;                                   // (NaN: exact route)
-  if (threadIdx.x == 0) route[0] = forced == 2 ? 1 : (forced == 1 ? 0 : (smooth ? 1 : 0));
+  if (threadIdx.x == 0) {
+    route[0] = forced == 2 ? 1 : (forced == 1 ? 0 : (smooth ? 1 : 0));
+    route[1] = 1 - route[0];
+  }
 }
 
 __device__ __forceinline__ int rg_bin(float d, float inv_h) {
@@ -363,7 +366,7 @@ int egnn_launch_radial_grid(egnn_ctx* ctx, int which, const float* rhat_d, int64
                             const int* len_perm, const float* W_r1,
                             const float* W_r2, const float* dw, float* dW_r1, float* dW_r2, void* ws, const int* route,
                             int (*hidden_launch)(egnn_ctx*, const float*, long, const float*, float*, float*, hipStream_t),
-                            hipStream_t st, const TpBinsArgs* made) {
+                            hipStream_t st, const EgnnBins* made) {
   const int P = ctx->n_paths[which];
   const int PE = P * ctx->desc.channels, n_rbf = ctx->desc.n_rbf;
   PathAlpha al;
@@ -394,7 +397,7 @@ int egnn_launch_radial_grid(egnn_ctx* ctx, int which, const float* rhat_d, int64
     return rc;
   }
   if (made) {
-    if ((rc = egnn_launch_tp_bins(ctx, *made, rhat_d, n_edges, bin_ptr, perm, Zp, route, st))) return rc;
+    if ((rc = (*made)(bin_ptr, perm, Zp))) return rc;
   } else {
     // the one pass over dw
     // column tiles of equal width (a multiple of four columns, at most RG_COLS)

@@ -1,4 +1,5 @@
-// Reverse pass of S6 (H_ij readout), per edge.
+// Reverse pass of S6 (H_ij readout), per edge, with the gradient of the weights in memory (the exact route, small calls and few orbitals;
+// readout_adjoint.hip otherwise).
 //
 // Forward (' = in the bond frame, rotated by D_k):  u = D^T Mid(D z ; w),  q[o][M] = sum_c V[o][c] u[(L,M)][c],
 // H = C q.  Given dH:
@@ -165,7 +166,8 @@ __global__ __launch_bounds__(256, 3) void readout_backward_kernel(
     const int* __restrict__ src, const int* __restrict__ dst, const float4* __restrict__ rhat_d,
     const float* __restrict__ zs, const float* __restrict__ zt, const float* __restrict__ w,
     const int* __restrict__ w_row, const float* __restrict__ V, ReadoutBwdTabs tb, const float* __restrict__ dH, float* __restrict__ dz,
-    float* __restrict__ dw, float* __restrict__ dV_partial, long n_edges, int iters) {
+    float* __restrict__ dw, float* __restrict__ dV_partial, long n_edges, int iters, const int* __restrict__ skip) {
+  if (skip && skip[0]) return;         // (readout_adjoint.hip has taken the call)
   constexpr int log2E = LE;
   using Mid = typename ReadoutMid<LMAX>::T;
   constexpr int D = (LMAX + 1) * (LMAX + 1);
@@ -316,7 +318,7 @@ size_t egnn_readout_backward_partial_bytes(const egnn_ctx* ctx, int64_t n_edges)
 int egnn_launch_readout_backward(egnn_ctx* ctx, const egnn_graph* g, const float* rhat_d, const float* zs,
                                  const float* zt, const float* w, const float* V, const int* tab_i,
                                  const float* tab_f, const float* dH, float* dz, float* dw, float* dV,
-                                 float* partial, hipStream_t stream, bool shared_rows) {
+                                 float* partial, hipStream_t stream, bool shared_rows, const int* skip) {
   const long n = g->n_edges;
   const int* w_row = shared_rows ? g->w_row : nullptr;
   const int E = ctx->desc.channels;
@@ -348,7 +350,7 @@ int egnn_launch_readout_backward(egnn_ctx* ctx, const egnn_graph* g, const float
       if (e != hipSuccess) return egnn_check_hip(ctx, e, "hipFuncSetAttribute(readout_backward_kernel)");         \
     }                                                                                                             \
     hipLaunchKernelGGL(kern, grid, block, shmem, stream, g->src, g->dst, rd, zs, zt, w, w_row, V, tb, dH, dz, dw, \
-                       partial, n, rob_iters(ctx, n));                                                            \
+                       partial, n, rob_iters(ctx, n), skip);                                                      \
   } while (0)
 #define CASES(L)                                                                \
   switch (ctx->log2_channels) {                                                 \
@@ -370,5 +372,5 @@ int egnn_launch_readout_backward(egnn_ctx* ctx, const egnn_graph* g, const float
 #undef CASES
 #undef LAUNCH
   EGNN_LAUNCH_CHECK(ctx, "readout_backward_kernel");
-  return egnn_launch_reduce_partials(ctx, partial, (int)grid_x, (long)n_vrows * E, dV, 1.0f, stream);
+  return egnn_launch_reduce_partials(ctx, partial, (int)grid_x, (long)n_vrows * E, dV, 1.0f, stream, skip);
 }

@@ -238,6 +238,14 @@ def tp_bins_route(m, n_edges):
     return bool(f(m.ctx, C.c_int64(n_edges)))
 
 
+def readout_adjoint_route(m, n_edges):
+    """The same for the adjoint of the readout."""
+    import ctypes as C
+    f = m.lib._Z25egnn_readout_adjoint_fitsPK8egnn_ctxl
+    f.restype = C.c_bool
+    return bool(f(m.ctx, C.c_int64(n_edges)))
+
+
 def recorded_nodes(lib, call):
     """Number of nodes (kernels, here) that `call` leaves in a recorded graph."""
     import ctypes as C

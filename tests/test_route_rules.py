@@ -1,6 +1,6 @@
 """The rules that send a call to the kernels with the radial weights in registers or through a weight tensor, at the sizes where they
 turn, asked of the library without a GPU.  Each line is one that measurements on both sides set; what they measured stands beside
-the rules in edge_fused.hip, readout_fused.hip and tp_bins.hip."""
+the rules in edge_fused.hip, readout_fused.hip, tp_bins.hip and readout_adjoint.hip."""
 import os
 
 import pytest
@@ -78,3 +78,19 @@ def test_weight_gradient_summed_as_it_is_made(B, lmax, E, first):
     m = B.Egnn(lmax, E, 16, 10.0, 20.0)
     assert U.tp_bins_route(m, first) and not U.tp_bins_route(m, first - 1)
     assert not U.tp_bins_route(B.Egnn(0, E, 16, 10.0, 20.0), 1000000)
+
+
+@pytest.mark.parametrize("lmax,E,orb,first", [
+    (1, 64, (0, 0, 1, 1, 2), 12000), (2, 32, (0, 0, 1, 1, 2), 12000), (3, 16, (0, 1, 1, 2), 12000), (4, 128, (0, 1, 1, 2), 12000),
+    (4, 64, (0, 1), 12000), (4, 32, (0, 1), 40000), (4, 16, (0, 1, 2), 40000), (3, 128, (0, 1), 18000), (3, 64, (0, 0, 1, 1), 18000),
+    (3, 32, (0, 1, 2), 40000), (3, 16, (0, 1), 40000)])
+def test_readout_adjoint(B, lmax, E, orb, first):
+    m = B.Egnn(lmax, E, 16, 10.0, 20.0, orb_l=orb)
+    assert U.readout_adjoint_route(m, first) and not U.readout_adjoint_route(m, first - 1)
+
+
+@pytest.mark.parametrize("lmax,E,orb", [(0, 32, (0, 0, 1, 1, 2)), (4, 8, (0, 0, 1, 1, 2)), (1, 32, (0, 0, 1, 1, 2)), (2, 16, (0, 0, 1, 1, 2)),
+                                        (2, 64, (0, 1, 2)), (3, 64, (0, 1)), (3, 32, (0, 1)), (4, 64, (0, 0, 0, 1, 1, 1)), (4, 32, (0, 0, 0, 1, 1, 1, 2, 2))])
+def test_readout_adjoint_never(B, lmax, E, orb):
+    """Too few channels, no room for its own gradients of the collapsed values, few orbitals, more rows of V than there is room for."""
+    assert not U.readout_adjoint_route(B.Egnn(lmax, E, 16, 10.0, 20.0, orb_l=orb), 1000000)
