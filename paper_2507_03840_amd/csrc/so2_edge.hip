@@ -1,44 +1,46 @@
-// The edge block's message transform without operands in memory: rotate, mix, rotate back and update per tile of 64 edges.
+// The edge block's message transform without operands in memory: rotate, mix, rotate back and update per tile of 32 edges.
 //
 // T_out[k] = T_in[k] + f_c D^T W (D x_src, D x_dst, D T_in[k]): what the separate kernels move through memory per edge (the
 // rotated rows, 9.6 KB at lmax 4 and 32 channels, written and read, and the products) stays in LDS and registers here, and
 // HBM sees T_in twice and T_out once.
 //
-// A workgroup takes 64 edges through stages of 16 channels of one group (edge, source, destination): threads (edge, channel)
-// rotate a row, scale it by a power of two of the edge's own and cut it into half-precision pieces in LDS; the 8 waves
-// contract it with the weights, which come from L2 (1 MB for 64 edges, 10 GB at 628,000, about 0.3 ms of L2's rate; larger
-// tiles do not fit LDS), into accumulators of [output channel][edge], 25 x 64 x 32 floats at lmax 4 = 100 registers a thread.
-// 628,000 edges, lmax 4, 32 channels: 3.45 ms, of which vector ALU 1.1 (rotations and pieces), matrix cores 0.7; the rest are
-// loads and barriers that one workgroup of 8 waves x 256 registers per compute unit cannot hide.  Separate kernels: 5.0
-// (gather 1.5, products 2.4, update 1.1).  Both blocks of 32 edges at a time in the inner loop: 4.1 ms (32 registers
-// spilled); 16 waves of 128 registers: 8.4 (47 spilled); rows of the next stage requested before the products: 3.8 to 4.2
-// (spills, or no registers left for the weights ahead).
+// A workgroup takes 32 edges through stages of 16 channels of one group (edge, source, destination): threads (edge, channel)
+// rotate a row, scale it by a power of two of the edge's own and cut it into half-precision pieces in LDS; the 4 waves
+// contract it with the weights, which come from L2 (1 MB for 32 edges), into accumulators of [output channel][edge], 25 x 32 x 32
+// floats at lmax 4 = 100 registers a thread.  Two workgroups share a compute unit, one rotating while the other contracts, whose
+// wavefronts go first where both could issue (s_setprio).
+// 628,000 edges, lmax 4, 32 channels: 3.11 ms.  Parts, by leaving the others out: rotations and pieces 1.05 ms, contraction 1.55 (matrix
+// cores 0.75, 20 GB of weights from L2, 20 GB of operands from LDS), rotating back and updating 0.65 (4 GB, 6 TB/s): they hardly
+// overlap.  Tiles of 64 edges and 8 waves, half the weights' traffic but one workgroup per compute unit: 3.45; without the priority 3.24;
+// weights two steps ahead 3.30, operands read one step ahead 3.34, rows to update asked for ahead 3.25: nothing waits for those.
+// Separate kernels: 5.0 (gather 1.5, products 2.4, update 1.1).  16 waves of 128 registers: 8.4 (47 spilled).
 #include "bond_frame.h"
 #include "egnn_internal.h"
 #include "so2_edge.h"
 #include "stream_gemm.h"
 
-#define SO2E_EDGES 64
-#define SO2E_THREADS 512
+#define SO2E_EDGES 32
+#define SO2E_WAVES 4
+#define SO2E_THREADS (64 * SO2E_WAVES)
 #define SO2E_CE 16           // channels of one group per stage: the contraction length of one matrix instruction
-// bytes of one component (l, m) of a stage's operand: two pieces of two half-waves of 64 x 16 bytes, each half-wave padded by 64
+// bytes of one component (l, m) of a stage's operand: two pieces of two half-waves of 32 x 16 bytes, each half-wave padded by 64
 // bytes, so that the pieces and halves that a wave writes together fall into different banks
-#define SO2E_HALF 1088
+#define SO2E_HALF (16 * SO2E_EDGES + 64)
 #define SO2E_PIECE (2 * SO2E_HALF)
 #define SO2E_COMP (2 * SO2E_PIECE)
-#define SO2E_LDY 72          // row pitch (floats) of the products on their way back: 16 channels x 64 edges per component
+#define SO2E_LDY 36          // row pitch (floats) of the products on their way back: 16 channels x 32 edges per component
 #define SO2E_INLINE __attribute__((always_inline))
 
 // Work units: outputs (lo, +m) and (lo, -m) of a pair share their weights Wr, Wi; of order 0, two degrees lo share their
-// operand.  Both are four 32 x 32 accumulators (two outputs x two blocks of 32 edges) and four operand registers of weights
-// per input degree.  Units are dealt to the 8 waves largest first, at most two each.
+// operand.  Both are two 32 x 32 accumulators (two outputs x 32 edges) and four operand registers of weights
+// per input degree.  Units are dealt to the 4 waves largest first, at most four each.
 template <int LMAX>
 struct So2eUnits {
   static constexpr int MAX = 16;
   int n, total_l;              // units; sum of their input degrees
   int m[MAX], lo[MAX], l0[MAX];
-  int slot[8][2];
-  constexpr So2eUnits() : n(0), total_l(0), m{}, lo{}, l0{}, slot{} {
+  int slot[SO2E_WAVES][4], most;    // units of a wave; largest number of them
+  constexpr So2eUnits() : n(0), total_l(0), m{}, lo{}, l0{}, slot{}, most(0) {
     for (int q = 0; q <= LMAX; ++q)
       for (int d = q; d <= LMAX; d += (q == 0 ? 2 : 1)) {
         m[n] = q;
@@ -47,9 +49,10 @@ struct So2eUnits {
         total_l += LMAX + 1 - q;
         ++n;
       }
-    int load[8] = {}, used[8] = {};
+    int load[SO2E_WAVES] = {}, used[SO2E_WAVES] = {};
     bool done[MAX] = {};
-    for (int w = 0; w < 8; ++w) slot[w][0] = slot[w][1] = -1;
+    for (int w = 0; w < SO2E_WAVES; ++w)
+      for (int q = 0; q < 4; ++q) slot[w][q] = -1;
     for (int t = 0; t < n; ++t) {
       int bu = -1, bc = -1;
       for (int u = 0; u < n; ++u) {
@@ -57,17 +60,15 @@ struct So2eUnits {
         if (!done[u] && cost > bc) { bu = u; bc = cost; }
       }
       int bw = -1;
-      for (int w = 0; w < 8; ++w)
-        if (used[w] < 2 && (bw < 0 || load[w] < load[bw])) bw = w;
+      for (int w = 0; w < SO2E_WAVES; ++w)
+        if (used[w] < 4 && (bw < 0 || load[w] < load[bw])) bw = w;
       slot[bw][used[bw]++] = bu;
+      if (used[bw] > most) most = used[bw];
       load[bw] += bc;
       done[bu] = true;
     }
   }
 };
-// slots a wave needs (8 waves)
-template <int LMAX>
-constexpr int so2e_slots() { return So2eUnits<LMAX>().n > 8 ? 2 : 1; }
 
 // ---------------------------------------------------------------------------------------------- weights
 // out[block of 32 output channels][stage][unit, input degree][weight 0 / 1][piece][lane]; a lane holds eight input channels of
@@ -128,7 +129,7 @@ __device__ __forceinline__ uint4 so2e_neg(uint4 a) {
 
 template <int LMAX>
 __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p) {
-  constexpr int D = (LMAX + 1) * (LMAX + 1), NS = so2e_slots<LMAX>();
+  constexpr int D = (LMAX + 1) * (LMAX + 1), NS = So2eUnits<LMAX>().most;
   static constexpr So2eUnits<LMAX> units{};
   typedef __amdgpu_buffer_rsrc_t rsrc;
   extern __shared__ uint4 so2e_smem[];
@@ -183,11 +184,11 @@ __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p)
 #pragma unroll
     for (int i = 0; i < D; ++i) v[i] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, o, (i << (log2E + 2)) + ch, 0));
   };
-  float16v acc[NS][4];
+  float16v acc[NS][2];
 #pragma unroll
   for (int u = 0; u < NS; ++u)
 #pragma unroll
-    for (int t = 0; t < 4; ++t)
+    for (int t = 0; t < 2; ++t)
 #pragma unroll
       for (int i = 0; i < 16; ++i) acc[u][t][i] = 0.0f;
   const char* frag = s_a + hh * SO2E_HALF + l32 * 16;
@@ -208,7 +209,7 @@ __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p)
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
       float v[D];
-      const int e = edge0 + it * 32;
+      const int e = edge0 + it * (SO2E_EDGES / 2);
       fetch(st, e, v);
       BondTrig t;
       trig(e, t);
@@ -234,22 +235,23 @@ __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p)
       }
     }
     __syncthreads();
-    const float r0 = s_ratio[l32], r1 = s_ratio[32 + l32];
-    const bool rescale = __any(r0 != 1.0f || r1 != 1.0f);
+    __builtin_amdgcn_s_setprio(2);
+    const float ratio = s_ratio[l32];
+    const bool rescale = __any(ratio != 1.0f);
 #pragma unroll
     for (int u = 0; u < NS; ++u) {
       const int unit = units.slot[wave][u];
       if (unit < 0) continue;
       if (rescale) {
 #pragma unroll
-        for (int t = 0; t < 4; ++t)
+        for (int t = 0; t < 2; ++t)
 #pragma unroll
-          for (int i = 0; i < 16; ++i) acc[u][t][i] *= (t & 1) ? r1 : r0;
+          for (int i = 0; i < 16; ++i) acc[u][t][i] *= ratio;
       }
       const int m = units.m[unit];
       const uint4* w = weights(st, u);
-      const uint4* after = u + 1 < NS && units.slot[wave][NS - 1] >= 0 ? weights(st, NS - 1) : weights(st + 1 < n_stages ? st + 1 : st, 0);
-#define SO2E_F(comp, piece, eb) (*reinterpret_cast<const uint4*>(frag + (comp) * SO2E_COMP + (piece) * SO2E_PIECE + (eb) * 512))
+      const uint4* after = u + 1 < NS && units.slot[wave][u + 1 < NS ? u + 1 : u] >= 0 ? weights(st, u + 1) : weights(st + 1 < n_stages ? st + 1 : st, 0);
+#define SO2E_F(comp, piece) (*reinterpret_cast<const uint4*>(frag + (comp) * SO2E_COMP + (piece) * SO2E_PIECE))
 #define SO2E_MMA(W, A, C) C = __builtin_amdgcn_mfma_f32_32x32x16_f16(sgh_as_h8(W), sgh_as_h8(A), C, 0, 0, 0)
       for (int l = m; l <= LMAX; ++l) {
         uint4 wc[4];
@@ -259,27 +261,25 @@ __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p)
 #pragma unroll
         for (int q = 0; q < 4; ++q) wn[q] = w[q * 64];
         const int cp = l * l + l + m, cm = l * l + l - m;
-#pragma unroll
-        for (int eb = 0; eb < 2; ++eb) {
-          const uint4 ph = SO2E_F(cp, 0, eb), pl = SO2E_F(cp, 1, eb);
-          float16v &a0 = acc[u][eb], &a1 = acc[u][2 + eb];
-          SO2E_MMA(wc[1], ph, a0); SO2E_MMA(wc[3], ph, a1);
-          SO2E_MMA(wc[0], pl, a0); SO2E_MMA(wc[2], pl, a1);
-          if (m == 0) {
-            SO2E_MMA(wc[0], ph, a0); SO2E_MMA(wc[2], ph, a1);
-          } else {
-            // y_+ = Wr x_+ - Wi x_-, y_- = Wi x_+ + Wr x_-
-            const uint4 mh = SO2E_F(cm, 0, eb), ml = SO2E_F(cm, 1, eb), nh = so2e_neg(mh), nl = so2e_neg(ml);
-            SO2E_MMA(wc[3], nh, a0); SO2E_MMA(wc[1], mh, a1);
-            SO2E_MMA(wc[2], nl, a0); SO2E_MMA(wc[0], ml, a1);
-            SO2E_MMA(wc[0], ph, a0); SO2E_MMA(wc[2], ph, a1);
-            SO2E_MMA(wc[2], nh, a0); SO2E_MMA(wc[0], mh, a1);
-          }
+        const uint4 ph = SO2E_F(cp, 0), pl = SO2E_F(cp, 1);
+        float16v &a0 = acc[u][0], &a1 = acc[u][1];
+        SO2E_MMA(wc[1], ph, a0); SO2E_MMA(wc[3], ph, a1);
+        SO2E_MMA(wc[0], pl, a0); SO2E_MMA(wc[2], pl, a1);
+        if (m == 0) {
+          SO2E_MMA(wc[0], ph, a0); SO2E_MMA(wc[2], ph, a1);
+        } else {
+          // y_+ = Wr x_+ - Wi x_-, y_- = Wi x_+ + Wr x_-
+          const uint4 mh = SO2E_F(cm, 0), ml = SO2E_F(cm, 1), nh = so2e_neg(mh), nl = so2e_neg(ml);
+          SO2E_MMA(wc[3], nh, a0); SO2E_MMA(wc[1], mh, a1);
+          SO2E_MMA(wc[2], nl, a0); SO2E_MMA(wc[0], ml, a1);
+          SO2E_MMA(wc[0], ph, a0); SO2E_MMA(wc[2], ph, a1);
+          SO2E_MMA(wc[2], nh, a0); SO2E_MMA(wc[0], mh, a1);
         }
       }
 #undef SO2E_MMA
 #undef SO2E_F
     }
+    __builtin_amdgcn_s_setprio(0);
     __syncthreads();
   }
 
@@ -287,9 +287,9 @@ __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p)
   const int eb = sgh_scale_exp(*p.w_max);
 #pragma unroll
   for (int it = 0; it < 2; ++it)
-    if (c == 0) s_ratio[edge0 + it * 32] = ldexpf(1.0f, -e_cur[it]) * ldexpf(1.0f, -eb);
+    if (c == 0) s_ratio[edge0 + it * (SO2E_EDGES / 2)] = ldexpf(1.0f, -e_cur[it]) * ldexpf(1.0f, -eb);
   __syncthreads();
-  const float u0 = s_ratio[l32], u1 = s_ratio[32 + l32];
+  const float unscale = s_ratio[l32];
 #pragma unroll
   for (int half = 0; half < 2; ++half) {
     if (half * 16 >= E) break;
@@ -300,18 +300,17 @@ __global__ __launch_bounds__(SO2E_THREADS, 2) void so2e_block_kernel(So2eArgs p)
       const int m = units.m[unit], lo = units.lo[unit];
       const int c0 = lo * lo + lo + m, c1 = m ? lo * lo + lo - m : (lo + 1) * (lo + 2);
 #pragma unroll
-      for (int t = 0; t < 4; ++t) {
-        if (t >= 2 && m == 0 && lo == LMAX) break;      // (no second degree)
-        float* y = s_y + ((t < 2 ? c0 : c1) * 16 + 4 * hh) * SO2E_LDY + (t & 1) * 32 + l32;
+      for (int t = 0; t < 2; ++t) {
+        if (t && m == 0 && lo == LMAX) break;      // (no second degree)
+        float* y = s_y + ((t ? c1 : c0) * 16 + 4 * hh) * SO2E_LDY + l32;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
-          y[(8 * (i >> 2) + (i & 3)) * SO2E_LDY] = acc[u][t][half * 8 + i] * ((t & 1) ? u1 : u0);
+        for (int i = 0; i < 8; ++i) y[(8 * (i >> 2) + (i & 3)) * SO2E_LDY] = acc[u][t][half * 8 + i] * unscale;
       }
     }
     __syncthreads();
 #pragma unroll
     for (int it = 0; it < 2; ++it) {
-      const int e = edge0 + it * 32;
+      const int e = edge0 + it * (SO2E_EDGES / 2);
       if (e < ne) {
         float o[D], ti[D];
         const int row = s_row[0][e] + 4 * c, ch = (cb * 32 + half * 16) * 4;

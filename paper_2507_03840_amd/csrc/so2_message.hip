@@ -652,11 +652,12 @@ static bool so2_block_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
              so2_ws(ctx, g->n_edges, true, false, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
-// Whether the edge block runs as one kernel over tiles of edges (so2_edge.hip).  us per call, per-edge kernels -> tiles: lmax
+// Whether the edge block runs as one kernel over tiles of edges (so2_edge.hip).  us per call, per-edge kernels -> tiles (of 64 edges;
+// those of 32 take 0.66 to 0.99 of their time at all of these sizes): lmax
 // 4, 32 channels, 3,000 nodes with 209 / 37.8 / 1.6 edges each 5,000 -> 3,450 / 985 -> 713 / 216 -> 98; lmax 4, 64 channels,
 // 37.8 2,528 -> 2,085; lmax 2, 16 channels 225 -> 128; 100 nodes 61 -> 30 to 346 -> 154.  With 128 channels every tile of edges
 // would be rotated four times (lmax 2, 37.8 edges 1,907 -> 2,957), and 8 are half a matrix instruction: both stay per edge. 
-// Few degrees have few units of work for a tile's eight waves (lmax 0 a single one), so there only calls that the per-edge
+// Few degrees have few units of work for a tile's waves (lmax 0 a single one), so there only calls that the per-edge
 // kernels spend on launches gain: lmax 0, 16 and 32 channels, 140,000 edges 137 -> 65 and 154 -> 110, 235,000 132 -> 109 and
 // 167 -> 184, 390,000 153 -> 172 and 218 -> 282; with 64 channels, whose rows are rotated twice, lmax 0, 13,600 136 -> 49,
 // 36,000 99 -> 104, 630,000 577 -> 1,609; lmax 1, 30,000 165 -> 140, 43,000 182 -> 195, 256,000 676 -> 978; lmax 2, 43,000 332
