@@ -7,7 +7,7 @@
 //     y_0 = W_0 x_0;    y_{+m} = Wr_m x_{+m} - Wi_m x_{-m},   y_{-m} = Wi_m x_{+m} + Wr_m x_{-m}    (3E -> E channels),
 // the result is rotated back, multiplied by the cutoff envelope and summed into the destination node (times
 // agg_norm^-1/2).  Unlike the tensor-product route of the layer (per-edge weights, no channel mixing) this is a
-// dense contraction shared by all edges, so it runs as five GEMMs, one per |m|:
+// dense contraction shared by all edges, so it runs as GEMMs, one per |m|, in one launch:
 //   1. so2_gather_kernel   lane = (edge, channel): both node rows rotated into the bond frame in registers, written
 //                          m-major: A_0[k] = (x_{l,0} of both nodes for all l, then e_k), A_m[k] = [x_{+m} | x_{-m}];
 //   2. so2_pack_kernel     the weights of order m as one matrix B_m = [[Wr^T, Wi^T], [-Wi^T, Wr^T]], scaled and cut
@@ -20,6 +20,7 @@
 // The sums of messages (plain and attention-weighted) mix their channels per node instead where nodes have enough edges
 // (so2_node.hip), and the edge block keeps its operands in LDS (so2_edge.hip); this per-edge form serves sparse graphs, the
 // channel counts those do not take and the adjoints of the two blocks.
+#include <algorithm>
 #include <type_traits>
 #include "egnn_internal.h"
 #include "bond_frame.h"
@@ -47,7 +48,7 @@ __host__ __device__ inline int so2_K(int lmax, int E, int m, bool full = false) 
 }
 __host__ __device__ inline int so2_N(int lmax, int E, int m) { return m == 0 ? (lmax + 1) * E : 2 * (lmax + 1 - m) * E; }
 // first float of order m in the packed weights: W_0, then (Wr_m, Wi_m) for m = 1..lmax
-static size_t so2_w_offset(int lmax, int E, int m) {
+__host__ __device__ static size_t so2_w_offset(int lmax, int E, int m) {
   size_t off = 0;
   for (int q = 0; q < m; ++q) {
     const size_t nl = lmax + 1 - q;
@@ -239,28 +240,40 @@ __device__ __forceinline__ float so2_b_value(const float* __restrict__ W, int m,
   return s_in == 0 ? W[sz + at] : -W[sz + at];         // x_{+m} -> y_{-m}: +Wi;  x_{-m} -> y_{+m}: -Wi
 }
 
-// T[ct][step][j][piece][64] halves (two pieces: see stream_gemm.h): thread -> (ct, step, j, pair of contraction indices)
-__global__ __launch_bounds__(256) void so2_pack_kernel(const float* __restrict__ W, uint16_t* __restrict__ T, int m, int lmax,
-                                                       int E, int K, int N, int n_steps, int n_ct, bool full,
-                                                       const unsigned* __restrict__ w_max, bool transposed) {
-  const long i = (long)blockIdx.x * 256 + threadIdx.x;
-  const long total = (long)n_ct * n_steps * 64 * 32;
-  if (i >= total) return;
+// T[ct][step][j][piece][64] halves (two pieces: see stream_gemm.h): thread -> (ct, step, j, pair of contraction indices); the
+// orders lie one behind the other in the grid (8 workgroups per packed tile and step)
+struct So2PackOrder {
+  const float* W;
+  uint16_t* T;
+  int m, K, N, n_steps, n_ct, first;   // first: first workgroup
+};
+struct So2PackArgs {
+  So2PackOrder o[5];
+  const unsigned* w_max;
+  int n, lmax, E;
+  bool full, transposed;
+};
+__global__ __launch_bounds__(256) void so2_pack_kernel(So2PackArgs p) {
+  int q = 0;
+  while (q + 1 < p.n && (int)blockIdx.x >= p.o[q + 1].first) ++q;
+  const So2PackOrder& o = p.o[q];
+  const long i = (long)((int)blockIdx.x - o.first) * 256 + threadIdx.x;
   const int rp = (int)(i & 31), j = (int)((i >> 5) & 63);
   const long blk = i >> 11;                    // ct * n_steps + step
-  const int step = (int)(blk % n_steps), ct = (int)(blk / n_steps);
+  const int step = (int)(blk % o.n_steps), ct = (int)(blk / o.n_steps);
   const int n = ct * 64 + j, k = step * 64 + 2 * rp;
-  const float sc = ldexpf(1.0f, sgh_scale_exp(*w_max));
+  const float sc = ldexpf(1.0f, sgh_scale_exp(*p.w_max));
   // transposed: the operand is B_m^T (contraction over the columns of Y_m, one output column per column of A_m)
-  const float xv[8] = {transposed ? so2_b_value(W, m, lmax, E, n, k, K, N, full) : so2_b_value(W, m, lmax, E, k, n, K, N, full),
-                       transposed ? so2_b_value(W, m, lmax, E, n, k + 1, K, N, full)
-                                  : so2_b_value(W, m, lmax, E, k + 1, n, K, N, full),
-                       0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  auto value = [&](int kk) {
+    return p.transposed ? so2_b_value(o.W, o.m, p.lmax, p.E, n, kk, o.K, o.N, p.full)
+                        : so2_b_value(o.W, o.m, p.lmax, p.E, kk, n, o.K, o.N, p.full);
+  };
+  const float xv[8] = {value(k), value(k + 1), 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
   uint4 hi, lo;
   sgh_split8(xv, sc, hi, lo);
-  uint32_t* o = reinterpret_cast<uint32_t*>(T) + blk * (64 * 64) + j * 64 + rp;
-  o[0] = hi.x;
-  o[32] = lo.x;
+  uint32_t* out = reinterpret_cast<uint32_t*>(o.T) + blk * (64 * 64) + j * 64 + rp;
+  out[0] = hi.x;
+  out[32] = lo.x;
 }
 
 // ---------------------------------------------------------------------------------------------- 3. GEMM
@@ -270,60 +283,120 @@ __global__ __launch_bounds__(256) void so2_pack_kernel(const float* __restrict__
 // all column blocks.  Workgroup ids go round-robin over the 8 XCDs, each with its own L2, so the id is decoded such
 // that the wide tiles of one block of rows (there is more than one only beyond 192 columns) sit on the same XCD with
 // consecutive dispatch slots: they read the same rows of A, once from HBM and then from that L2.
+// All orders run in one launch, those with the longest workgroups first: their LDS leaves one workgroup per compute unit at any
+// NCB, so a launch per order left much of the chip idle in its last round (73,000 edges, lmax 4, 32 channels, both blocks' adjoints:
+// 15 launches 1,215 us -> 3 of 995, their 15 launches to pack the weights 71 -> 18 us).
+struct So2GemmOrder {
+  const float* A;
+  const uint16_t* T;
+  float* C;
+  int K, lda, n_steps, N, ldc, n_ct, n_wt, nt, first;   // nt: 64-column tiles of a wide tile; first: first workgroup
+};
+struct So2GemmArgs {
+  So2GemmOrder o[5];
+  const unsigned *a_max, *w_max;
+  long M;
+  int n, n_row_blocks;
+};
+
 template <int NCB>
-__global__ __launch_bounds__(SG_THREADS) void so2_gemmw_kernel(const float* __restrict__ A, long M, int K, int lda,
-                                                               const uint16_t* __restrict__ T, int n_steps,
-                                                               float* __restrict__ C, int N, int ldc, int n_ct, int n_wt,
-                                                               int n_row_blocks, const unsigned* __restrict__ maxima) {
-  extern __shared__ uint4 so2_smem[];
+__device__ __forceinline__ void so2_gemm_tile(const So2GemmArgs& p, const So2GemmOrder& o, uint4* smem) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int xcd = blockIdx.x & 7, idx = blockIdx.x >> 3;
-  const int wt = idx % n_wt;
-  const int row_block = (idx / n_wt) * 8 + xcd;
-  if (row_block >= n_row_blocks) return;   // (whole workgroup: the grid is rounded up to a multiple of 8 row blocks)
+  const int local = (int)blockIdx.x - o.first, xcd = local & 7, idx = local >> 3;
+  const int wt = idx % o.n_wt;
+  const int row_block = (idx / o.n_wt) * 8 + xcd;
+  if (row_block >= p.n_row_blocks) return;   // (whole workgroup: an order's part of the grid is rounded up to 8 row blocks)
   const long e_base = ((long)row_block * SG_WAVES + wave) * 32;
   const int ct0 = wt * (NCB / 2);
-  const int ea = sgh_scale_exp(maxima[0]), eb = sgh_scale_exp(maxima[1]);
+  const int ea = sgh_scale_exp(*p.a_max), eb = sgh_scale_exp(*p.w_max);
   const float a_scale = ldexpf(1.0f, ea), unscale = ldexpf(1.0f, -ea - eb);
   float16v acc[NCB];
-  const long tile_stride = (long)n_steps * (64 * 16);
-  sghw_contract<NCB>(A, M, K, lda, reinterpret_cast<const uint4*>(T) + (long)ct0 * tile_stride, tile_stride, n_ct - ct0,
-                     n_steps, so2_smem, e_base, a_scale, acc);
+  const long tile_stride = (long)o.n_steps * (64 * 16);
+  sghw_contract<NCB>(o.A, p.M, o.K, o.lda, reinterpret_cast<const uint4*>(o.T) + (long)ct0 * tile_stride, tile_stride,
+                     o.n_ct - ct0, o.n_steps, smem, e_base, a_scale, acc);
   const int m = lane & 31, hh = lane >> 5;
 #pragma unroll
   for (int cb = 0; cb < NCB; ++cb) {
     const int col = ct0 * 64 + cb * 32 + m;
-    if (col < N) {
+    if (col < o.N) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
         const long e = e_base + 8 * (i >> 2) + 4 * hh + (i & 3);
-        if (e < M) C[(size_t)e * ldc + col] = unscale * acc[cb][i];
+        if (e < p.M) o.C[(size_t)e * o.ldc + col] = unscale * acc[cb][i];
       }
     }
   }
 }
 
-// launches the wide-tile product: NCB from the number of 64-column tiles (at most 6 column blocks per wave)
-static int so2_launch_gemm(egnn_ctx* ctx, const float* A, long n, int K, int lda, const uint16_t* T, float* C, int N,
-                           int ldc, const unsigned* maxima, hipStream_t st) {
-  const int n_steps = (K + 63) / 64, n_ct = (N + 63) / 64;
-  const int n_wt = (n_ct + 2) / 3;                // wide tiles of at most three 64-column tiles, evenly filled
-  const int nt = (n_ct + n_wt - 1) / n_wt;
-  const long rows_per_wg = 32L * SG_WAVES;
-  const int n_row_blocks = (int)((n + rows_per_wg - 1) / rows_per_wg);
-  const unsigned grid_x = (unsigned)(((n_row_blocks + 7) / 8) * 8 * n_wt);
-#define SO2_GEMMW(NCB)                                                                                               \
+// NT: most 64-column tiles of a wide tile among the orders
+template <int NT>
+__global__ __launch_bounds__(SG_THREADS) void so2_gemmw_kernel(So2GemmArgs p) {
+  extern __shared__ uint4 so2_smem[];
+  int q = 0;
+  while (q + 1 < p.n && (int)blockIdx.x >= p.o[q + 1].first) ++q;
+  const So2GemmOrder& o = p.o[q];
+  if constexpr (NT >= 3)
+    if (o.nt == 3) return so2_gemm_tile<6>(p, o, so2_smem);
+  if constexpr (NT >= 2)
+    if (o.nt == 2) return so2_gemm_tile<4>(p, o, so2_smem);
+  so2_gemm_tile<2>(p, o, so2_smem);
+}
+
+// Packs the weights of every order and multiplies: forward Y_m = A_m B_m, transposed dA_m = dY_m B_m^T over A_m.  maxima:
+// largest magnitudes of the large operand and of the weights.
+static int so2_products(egnn_ctx* ctx, const So2Bufs& b, uint16_t* const* T, const float* W_so2, long n, bool full,
+                        bool transposed, const unsigned* a_max, const unsigned* w_max, hipStream_t st) {
+  const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
+  So2PackArgs pk = {};
+  So2GemmArgs gm = {};
+  pk.w_max = gm.w_max = w_max;
+  gm.a_max = a_max;
+  pk.n = gm.n = lmax + 1;
+  pk.lmax = lmax; pk.E = E; pk.full = full; pk.transposed = transposed;
+  gm.M = n;
+  gm.n_row_blocks = (int)((n + 32L * SG_WAVES - 1) / (32L * SG_WAVES));
+  int pack_groups = 0, most = 1;
+  for (int m = 0; m <= lmax; ++m) {
+    So2PackOrder& k = pk.o[m];
+    So2GemmOrder& o = gm.o[m];
+    o.A = transposed ? b.Y[m] : b.A[m];
+    o.C = transposed ? b.A[m] : b.Y[m];
+    o.K = transposed ? b.N[m] : b.K[m];
+    o.N = transposed ? b.K[m] : b.N[m];
+    o.lda = transposed ? b.ldY[m] : b.ldA[m];
+    o.ldc = transposed ? b.ldA[m] : b.ldY[m];
+    o.T = T[m];
+    o.n_steps = (o.K + 63) / 64;
+    o.n_ct = (o.N + 63) / 64;
+    o.n_wt = (o.n_ct + 2) / 3;                // wide tiles of at most three 64-column tiles, evenly filled
+    o.nt = (o.n_ct + o.n_wt - 1) / o.n_wt;
+    most = std::max(most, o.nt);
+    k.W = W_so2 + so2_w_offset(lmax, E, m);
+    k.T = T[m];
+    k.m = m; k.K = b.K[m]; k.N = b.N[m]; k.n_steps = o.n_steps; k.n_ct = o.n_ct; k.first = pack_groups;
+    pack_groups += o.n_ct * o.n_steps * 8;
+  }
+  std::sort(gm.o, gm.o + gm.n,
+            [](const So2GemmOrder& x, const So2GemmOrder& y) { return x.n_steps * x.nt > y.n_steps * y.nt; });
+  long groups = 0;
+  for (int q = 0; q < gm.n; ++q) {
+    gm.o[q].first = (int)groups;
+    groups += (long)((gm.n_row_blocks + 7) / 8) * 8 * gm.o[q].n_wt;
+  }
+  if (groups > 2147483647L) return egnn_fail(ctx, EGNN_EINVAL, "so2 products: too many edges");
+  hipLaunchKernelGGL(so2_pack_kernel, dim3(pack_groups), dim3(256), 0, st, pk);
+  EGNN_LAUNCH_CHECK(ctx, "so2_pack_kernel");
+#define SO2_GEMMW(NT)                                                                                                \
   do {                                                                                                               \
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(so2_gemmw_kernel<NCB>),                         \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)SGHW_LDS_BYTES(NCB));        \
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(so2_gemmw_kernel<NT>),                          \
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)SGHW_LDS_BYTES(2 * NT));     \
     if (e != hipSuccess) return egnn_check_hip(ctx, e, "hipFuncSetAttribute(so2_gemmw_kernel)");                     \
-    hipLaunchKernelGGL(so2_gemmw_kernel<NCB>, dim3(grid_x), dim3(SG_THREADS), SGHW_LDS_BYTES(NCB), st, A, n, K, lda,  \
-                       T, n_steps, C, N, ldc, n_ct, n_wt, n_row_blocks, maxima);                                     \
+    hipLaunchKernelGGL(so2_gemmw_kernel<NT>, dim3((unsigned)groups), dim3(SG_THREADS), SGHW_LDS_BYTES(2 * NT), st, gm); \
   } while (0)
-  switch (nt) {
-    case 1: SO2_GEMMW(2); break;
-    case 2: SO2_GEMMW(4); break;
-    default: SO2_GEMMW(6); break;
+  switch (most) {
+    case 1: SO2_GEMMW(1); break;
+    case 2: SO2_GEMMW(2); break;
+    default: SO2_GEMMW(3); break;
   }
 #undef SO2_GEMMW
   EGNN_LAUNCH_CHECK(ctx, "so2_gemmw_kernel");
@@ -582,17 +655,7 @@ static int so2_transform(egnn_ctx* ctx, const egnn_graph* g, const float* pos, c
 #undef GATHER
   EGNN_LAUNCH_CHECK(ctx, "so2_gather_kernel");
   if ((rc = so2_launch_wmax(ctx, W_so2, call->maxima + 1, st))) return rc;
-  for (int m = 0; gemms && m <= lmax; ++m) {
-    const int K = call->b.K[m], N = call->b.N[m], n_steps = so2_steps(K), n_ct = so2_tiles(N);
-    const long total = (long)n_ct * n_steps * 64 * 32;
-    hipLaunchKernelGGL(so2_pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                       W_so2 + so2_w_offset(lmax, E, m), call->T[m], m, lmax, E, K, N, n_steps, n_ct, full, call->maxima + 1,
-                       false);
-    EGNN_LAUNCH_CHECK(ctx, "so2_pack_kernel");
-    if ((rc = so2_launch_gemm(ctx, call->b.A[m], n, K, call->b.ldA[m], call->T[m], call->b.Y[m], N, call->b.ldY[m],
-                              call->maxima, st)))
-      return rc;
-  }
+  if (gemms) return so2_products(ctx, call->b, call->T, W_so2, n, full, false, call->maxima, call->maxima + 1, st);
   return EGNN_OK;
 }
 
@@ -990,29 +1053,43 @@ __global__ __launch_bounds__(256) void so2_attention_adjoint_kernel(const int* _
 #define SW_BLOCK 16
 typedef float sw_f4 __attribute__((ext_vector_type(4)));
 typedef float sw_f2 __attribute__((ext_vector_type(2)));
-__global__ __launch_bounds__(256, 2) void so2_wgrad_kernel(const float* __restrict__ A, int K, int lda,
-                                                           const float* __restrict__ Y, int N, int ldy, long n_edges,
-                                                           long per_chunk, int quarters_n, float* __restrict__ partial,
-                                                           const unsigned* __restrict__ a_max,
-                                                           const unsigned* __restrict__ y_max) {
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+// The orders lie one behind the other in the grid, those with the longest chunks first; an order's (chunk, quarter) pairs are
+// numbered chunk by chunk and dealt out four to a workgroup.  73,000 edges, lmax 4, 32 channels, both blocks: a launch per order
+// 843 us, one for all 713; the sums of the partial results and their way into the weights' layout, 22 launches and 193 us, now 4 and 124
+// (6 TB/s).
+struct So2WgradOrder {
+  const float *A, *Y;
+  float *partial, *dB;
+  long per_chunk;
+  int K, lda, N, ldy, quarters_n, quarters, chunks, first, first_sum, m;   // first: first workgroup here, first_sum: of the sums
+};
+struct So2WgradArgs {
+  So2WgradOrder o[5];
+  const unsigned *a_max, *y_max;
+  long n_edges;
+  int n;
+};
+__global__ __launch_bounds__(256, 2) void so2_wgrad_kernel(So2WgradArgs p) {
+  int ord = 0;
+  while (ord + 1 < p.n && (int)blockIdx.x >= p.o[ord + 1].first) ++ord;
+  const So2WgradOrder& o = p.o[ord];
+  const float *A = o.A, *Y = o.Y;
+  const int K = o.K, lda = o.lda, N = o.N, ldy = o.ldy;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int i32 = lane & 31, hh = lane >> 5;
   // (tiles of one chunk of edges are neighbours in the grid and land on different XCDs: putting them on one XCD, so
   // that its L2 serves the rows they share, was measured slower)
-  const int chunk = blockIdx.y;
-  // the 128 x 64 quarters of the result are numbered row by row and dealt out four to a workgroup: only the last
-  // workgroup of a chunk can have waves without work (a wave that ends early does not make room for another one
-  // in practice)
-  const int quarter = blockIdx.x * (blockDim.x >> 6) + wave;   // (a result of fewer than four quarters: smaller workgroups)
-  const int kq = quarter / quarters_n, nq = quarter - kq * quarters_n;
+  const int unit = ((int)blockIdx.x - o.first) * 4 + wave;
+  const int chunk = unit / o.quarters, quarter = unit - chunk * o.quarters;
+  if (chunk >= o.chunks) return;             // (no barrier in this kernel)
+  const int kq = quarter / o.quarters_n, nq = quarter - kq * o.quarters_n;
   const int k0 = kq * 128, n0 = nq * 64;
-  if (k0 >= K) return;                       // (no barrier in this kernel)
-  const long e_begin = (long)chunk * per_chunk;
-  long e_end = e_begin + per_chunk;
-  if (e_end > n_edges) e_end = n_edges;
+  const long e_begin = (long)chunk * o.per_chunk;
+  long e_end = e_begin + o.per_chunk;
+  if (e_end > p.n_edges) e_end = p.n_edges;
   const int ca = k0 + 4 * i32, cy = n0 + 2 * i32;
   const bool a_ok = ca < K, y_ok = cy < N;
-  const int ea = sgh_scale_exp(*a_max), ey = sgh_scale_exp(*y_max);
+  const int ea = sgh_scale_exp(*p.a_max), ey = sgh_scale_exp(*p.y_max);
   const float a_scale = ldexpf(1.0f, ea), y_scale = ldexpf(1.0f, ey), unscale = ldexpf(1.0f, -ea - ey);
   // addresses: a row pointer that is the same for the whole wave (scalar arithmetic) plus a per-lane byte offset that
   // never changes (its half-wave's first row and its columns) -- no vector arithmetic per load
@@ -1100,7 +1177,7 @@ __global__ __launch_bounds__(256, 2) void so2_wgrad_kernel(const float* __restri
       products();
     }
   }
-  float* out = partial + (size_t)chunk * K * N;
+  float* out = o.partial + (size_t)chunk * K * N;
   if (y_ok) {
 #pragma unroll
     for (int a = 0; a < 4; ++a)
@@ -1115,12 +1192,44 @@ __global__ __launch_bounds__(256, 2) void so2_wgrad_kernel(const float* __restri
   }
 }
 
+// dB_m = sum of an order's partial results, in a fixed order: a workgroup takes 32 neighbouring elements, eight threads each, which
+// add every eighth chunk in eight running sums (eight loads in flight, 128 bytes a row).
+__global__ __launch_bounds__(256) void so2_wgrad_sum_kernel(So2WgradArgs p) {
+  __shared__ float red[8][32];
+  int ord = 0;
+  while (ord + 1 < p.n && (int)blockIdx.x >= p.o[ord + 1].first_sum) ++ord;
+  const So2WgradOrder& o = p.o[ord];
+  const int part = threadIdx.x >> 5, at = threadIdx.x & 31;
+  const long n = (long)o.K * o.N, i = (long)((int)blockIdx.x - o.first_sum) * 32 + at;   // (K and N are multiples of 8: n of 64)
+  float acc[8] = {0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f};
+  const float* from = o.partial + i;
+  int b = part;
+  for (; b + 56 < o.chunks; b += 64) {
+    float v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) v[u] = __builtin_nontemporal_load(from + (long)(b + 8 * u) * n);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) acc[u] += v[u];
+  }
+#pragma unroll
+  for (int u = 0; u < 7; ++u)
+    if (b + 8 * u < o.chunks) acc[u] += __builtin_nontemporal_load(from + (long)(b + 8 * u) * n);
+  red[part][at] = ((acc[0] + acc[1]) + (acc[2] + acc[3])) + ((acc[4] + acc[5]) + (acc[6] + acc[7]));
+  __syncthreads();
+  if (part == 0)
+    o.dB[i] = ((red[0][at] + red[1][at]) + (red[2][at] + red[3][at])) + ((red[4][at] + red[5][at]) + (red[6][at] + red[7][at]));
+}
+
 // dB_m [K][N] (column orders of A_m and Y_m) -> gradient of W_0 (m = 0) or of (Wr_m, Wi_m), row-major like the weights.
 // Without persistent edge embeddings (full = false) the weight columns that multiply the planes l > 0 of the edge
 // embedding, which are zero on that path, have gradient zero; with them the columns of A_m are in the column order of
-// the weights.  One thread per weight element of W_0 / Wr_m.
-__global__ __launch_bounds__(256) void so2_unpack_wgrad_kernel(const float* __restrict__ dB, float* __restrict__ dW, int m,
-                                                               int lmax, int E, int N, bool full) {
+// the weights.  One thread per weight element of W_0 / Wr_m; blockIdx.y: order.
+__global__ __launch_bounds__(256) void so2_unpack_wgrad_kernel(So2WgradArgs p, float* __restrict__ dW_so2, int lmax, int E,
+                                                               bool full) {
+  const So2WgradOrder& o = p.o[blockIdx.y];
+  const int m = o.m, N = o.N;
+  const float* dB = o.dB;
+  float* dW = dW_so2 + so2_w_offset(lmax, E, m);
   const int nl = lmax + 1 - m;
   const int rows = nl * E, cols = nl * 3 * E;
   const long idx = (long)blockIdx.x * 256 + threadIdx.x;
@@ -1303,20 +1412,18 @@ __global__ __launch_bounds__(256) void so2_dwe_kernel(const float4* __restrict__
 
 // chunks of edges of the weight gradient of one order.  All waves of a launch take the same time, so their number
 // should fill the chip's places once (256 compute units x 4 SIMDs x 2 waves, what the kernel's registers allow), not
-// one and a third times.  Every chunk is a multiple of 2 * SW_UNROLL edges.
-#define SW_UNROLL 8   // (chunks are multiples of 2 * SW_UNROLL = SW_BLOCK edges)
+// one and a third times.  Every chunk is a multiple of SW_BLOCK edges and at least `least`: SW_LEAST where the orders share
+// a launch (a chunk of one block would write 32 KB of partial results for the 12 KB it reads).
+#define SW_LEAST (4 * SW_BLOCK)
 #define SW_WAVE_SLOTS 2048
 static int so2_wgrad_quarters(int K, int N) { return ((K + 127) / 128) * ((N + 63) / 64); }
-static int so2_wgrad_waves(int K, int N) { const int q = so2_wgrad_quarters(K, N); return q < 4 ? q : 4; }   // per workgroup
-static int so2_wgrad_groups(int K, int N) {                                                                  // workgroups per chunk
-  return (so2_wgrad_quarters(K, N) + so2_wgrad_waves(K, N) - 1) / so2_wgrad_waves(K, N);
-}
-static void so2_wgrad_split(long n, int K, int N, int* chunks, long* per_chunk) {
-  long c = SW_WAVE_SLOTS / (so2_wgrad_waves(K, N) * so2_wgrad_groups(K, N));
+static void so2_wgrad_split(long n, int K, int N, int least, int* chunks, long* per_chunk) {
+  const int q = so2_wgrad_quarters(K, N);
+  long c = SW_WAVE_SLOTS / (q < 4 ? q : (q + 3) / 4 * 4);
   if (c < 1) c = 1;
   long per = (n + c - 1) / c;
-  per = (per + 2 * SW_UNROLL - 1) / (2 * SW_UNROLL) * (2 * SW_UNROLL);
-  if (per < 2 * SW_UNROLL) per = 2 * SW_UNROLL;
+  per = (per + SW_BLOCK - 1) / SW_BLOCK * SW_BLOCK;
+  if (per < least) per = least;
   *per_chunk = per;
   *chunks = (int)((n + per - 1) / per);
 }
@@ -1324,49 +1431,67 @@ static void so2_wgrad_split(long n, int K, int N, int* chunks, long* per_chunk) 
 struct So2Bwd {
   float* rows;      // [n_edges][D][E] source parts of dM
   float* dxd;       // [n_owned][D][E]
-  float* partial;   // partial weight gradients of one order
-  float* dB;        // [K_m][N_m] of one order
+  float* partial[5];   // partial weight gradients per order, and their sums [K_m][N_m]: of orders that share a launch apart,
+  float* dB[5];        // else in the same place
+  bool shared;         // every order in one launch
   float* dwe;       // [SO2_DWE_CHUNKS][E][n_rbf]   (message sum)
   float* tds;       // [n_edges] gradient of the attention weights, then of the scores   (node block)
   float* dwatt;     // [n_owned][E] per-node parts of dw_att                             (node block)
 };
 
-static size_t so2_bwd_ws(const egnn_ctx* ctx, int64_t n_edges, int32_t n_owned, bool full, bool carve, char* base,
+// With room for the partial results of every order (shared) the weight gradient is one launch; a workspace that only holds
+// those of the largest one, as much as has always been accepted, gets a launch per order.
+static size_t so2_bwd_ws(const egnn_ctx* ctx, int64_t n_edges, int32_t n_owned, bool full, bool shared, char* base,
                          So2Bwd* out) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels, D = (lmax + 1) * (lmax + 1);
   size_t used = so2_ws(ctx, n_edges, full, false, nullptr, nullptr, nullptr, nullptr, nullptr);
-  auto take = [&](size_t bytes) { char* p = carve ? base + used : nullptr; used += so2_a256(bytes); return p; };
-  size_t part = 0, db = 0;
+  auto take = [&](size_t bytes) { char* p = base ? base + used : nullptr; used += so2_a256(bytes); return p; };
+  size_t part[5], db[5], part_max = 0, db_max = 0;
   for (int m = 0; m <= lmax; ++m) {
     const int K = so2_K(lmax, E, m, full), N = so2_N(lmax, E, m);
     int chunks;
     long per;
-    so2_wgrad_split(n_edges > 0 ? n_edges : 1, K, N, &chunks, &per);
-    part = std::max(part, (size_t)chunks * K * N);
-    db = std::max(db, (size_t)K * N);
+    so2_wgrad_split(n_edges > 0 ? n_edges : 1, K, N, shared ? SW_LEAST : SW_BLOCK, &chunks, &per);
+    part[m] = (size_t)chunks * K * N;
+    db[m] = (size_t)K * N;
+    part_max = std::max(part_max, part[m]);
+    db_max = std::max(db_max, db[m]);
   }
-  So2Bwd w;
+  So2Bwd w = {};
+  w.shared = shared;
   w.rows = (float*)take((size_t)n_edges * D * E * sizeof(float));
   w.dxd = (float*)take((size_t)n_owned * D * E * sizeof(float));
-  w.partial = (float*)take(part * sizeof(float));
-  w.dB = (float*)take(db * sizeof(float));
+  for (int m = 0; m <= lmax; ++m) {
+    if (m > 0 && !shared) { w.partial[m] = w.partial[0]; w.dB[m] = w.dB[0]; continue; }
+    w.partial[m] = (float*)take((shared ? part[m] : part_max) * sizeof(float));
+    w.dB[m] = (float*)take((shared ? db[m] : db_max) * sizeof(float));
+  }
   w.dwe = full ? nullptr : (float*)take((size_t)SO2_DWE_CHUNKS * E * ctx->desc.n_rbf * sizeof(float));
   w.tds = full ? (float*)take((size_t)n_edges * sizeof(float)) : nullptr;
   w.dwatt = full ? (float*)take((size_t)n_owned * E * sizeof(float)) : nullptr;
   if (out) *out = w;
   return used;
 }
+static void so2_bwd_carve(const egnn_ctx* ctx, const egnn_graph* g, bool full, void* ws, size_t ws_bytes, So2Bwd* w) {
+  const bool shared = ws_bytes >= so2_bwd_ws(ctx, g->n_edges, g->n_owned, full, true, nullptr, nullptr);
+  so2_bwd_ws(ctx, g->n_edges, g->n_owned, full, shared, (char*)ws, w);
+}
+
+static size_t so2_bwd_ask(const egnn_ctx* ctx, int64_t n_edges, int32_t n_owned, bool full) {
+  return 256 + std::max(so2_bwd_ws(ctx, n_edges, n_owned, full, true, nullptr, nullptr),
+                        so2_bwd_ws(ctx, n_edges, n_owned, full, false, nullptr, nullptr));
+}
 
 extern "C" int egnn_so2_backward_workspace_bytes(const egnn_ctx* ctx, int64_t n_edges, int32_t n_owned, size_t* bytes) {
   if (!ctx || !bytes || n_edges < 0 || n_owned < 0) return EGNN_EINVAL;
-  *bytes = so2_bwd_ws(ctx, n_edges, n_owned, false, false, nullptr, nullptr) + 256;
+  *bytes = so2_bwd_ask(ctx, n_edges, n_owned, false);
   return EGNN_OK;
 }
 
 extern "C" int egnn_so2_blocks_backward_workspace_bytes(const egnn_ctx* ctx, int64_t n_edges, int32_t n_owned,
                                                         size_t* bytes) {
   if (!ctx || !bytes || n_edges < 0 || n_owned < 0) return EGNN_EINVAL;
-  *bytes = so2_bwd_ws(ctx, n_edges, n_owned, true, false, nullptr, nullptr) + 256;
+  *bytes = so2_bwd_ask(ctx, n_edges, n_owned, true);
   return EGNN_OK;
 }
 
@@ -1391,7 +1516,8 @@ struct So2Grad {
 
 // The part every reverse pass shares, after the operands A_m are in the workspace (so2_transform): dY_m over Y_m, then
 // per order the weight gradient and dA_m over A_m, then the rotation back with the sums over the two node roles.
-// dT / dT_add: gradient of the edge embeddings (full only).  maxima[2], [3] must be zero on entry.
+// dT / dT_add: gradient of the edge embeddings (full only).  maxima[2] must be zero on entry, [0] and [1]
+// hold the largest magnitudes of the operands and the weights.
 static int so2_backward_tail(egnn_ctx* ctx, const egnn_graph* g, const int32_t* col_ptr, const int32_t* perm, bool full,
                              const float* W_so2, const So2Grad& grad, So2Call& call, So2Bwd& w, float* dx,
                              float* dW_so2, float* dT, const float* dT_add, hipStream_t st) {
@@ -1401,38 +1527,46 @@ static int so2_backward_tail(egnn_ctx* ctx, const egnn_graph* g, const int32_t* 
   const float4* rd = reinterpret_cast<const float4*>(call.rhat_d);
   const int per_wg = 256 / E;
   const dim3 egrid((unsigned)((n + per_wg - 1) / per_wg)), block(256);
-  unsigned* bmax = call.maxima + 2;   // [0]: largest |dY| (operand of the GEMMs below), [1]: largest weight
+  unsigned* y_max = call.maxima + 2;   // largest |dY|
 #define DY(L)                                                                                                          \
   hipLaunchKernelGGL(so2_dy_kernel<L>, egrid, block, 0, st, g->dst, rd, grad.rows, grad.per_edge, grad.alpha, grad.ds, \
-                     grad.w_att, call.b, n, ctx->log2_channels, grad.scale, ctx->desc.r_cut, bmax)
+                     grad.w_att, call.b, n, ctx->log2_channels, grad.scale, ctx->desc.r_cut, y_max)
   SO2_BY_LMAX(lmax, DY)
 #undef DY
   EGNN_LAUNCH_CHECK(ctx, "so2_dy_kernel");
-  if ((rc = so2_launch_wmax(ctx, W_so2, bmax + 1, st))) return rc;
+  So2WgradOrder orders[5] = {};
   for (int m = 0; m <= lmax; ++m) {
-    const int K = call.b.K[m], N = call.b.N[m];
-    int chunks;
-    long per;
-    so2_wgrad_split(n, K, N, &chunks, &per);
-    hipLaunchKernelGGL(so2_wgrad_kernel, dim3(so2_wgrad_groups(K, N), chunks), dim3(64 * so2_wgrad_waves(K, N)), 0, st,
-                       call.b.A[m], K, call.b.ldA[m], call.b.Y[m], N, call.b.ldY[m], n, per, (N + 63) / 64, w.partial,
-                       call.maxima, bmax);
-    EGNN_LAUNCH_CHECK(ctx, "so2_wgrad_kernel");
-    if ((rc = egnn_launch_reduce_partials(ctx, w.partial, chunks, (long)K * N, w.dB, 1.0f, st))) return rc;
-    const int nl = lmax + 1 - m;
-    const long n_el = (long)nl * E * nl * 3 * E;
-    hipLaunchKernelGGL(so2_unpack_wgrad_kernel, dim3((unsigned)((n_el + 255) / 256)), dim3(256), 0, st, w.dB,
-                       dW_so2 + so2_w_offset(lmax, E, m), m, lmax, E, N, full);
-    EGNN_LAUNCH_CHECK(ctx, "so2_unpack_wgrad_kernel");
-    // dA_m = dY_m B_m^T over A_m: contraction over the N columns of Y_m, one output column per column of A_m
-    const int n_steps = so2_steps(N), n_ct = so2_tiles(K);
-    const long total = (long)n_ct * n_steps * 64 * 32;
-    hipLaunchKernelGGL(so2_pack_kernel, dim3((unsigned)((total + 255) / 256)), dim3(256), 0, st,
-                       W_so2 + so2_w_offset(lmax, E, m), call.T[m], m, lmax, E, K, N, n_steps, n_ct, full, bmax + 1, true);
-    EGNN_LAUNCH_CHECK(ctx, "so2_pack_kernel");
-    if ((rc = so2_launch_gemm(ctx, call.b.Y[m], n, N, call.b.ldY[m], call.T[m], call.b.A[m], K, call.b.ldA[m], bmax, st)))
-      return rc;
+    So2WgradOrder& o = orders[m];
+    o.A = call.b.A[m]; o.Y = call.b.Y[m]; o.partial = w.partial[m]; o.dB = w.dB[m];
+    o.K = call.b.K[m]; o.N = call.b.N[m]; o.lda = call.b.ldA[m]; o.ldy = call.b.ldY[m]; o.m = m;
+    o.quarters_n = (o.N + 63) / 64;
+    o.quarters = so2_wgrad_quarters(o.K, o.N);
+    so2_wgrad_split(n, o.K, o.N, w.shared ? SW_LEAST : SW_BLOCK, &o.chunks, &o.per_chunk);
   }
+  std::sort(orders, orders + lmax + 1, [](const So2WgradOrder& a, const So2WgradOrder& b) { return a.per_chunk > b.per_chunk; });
+  for (int first = 0; first <= lmax; first += w.shared ? lmax + 1 : 1) {
+    So2WgradArgs a = {};
+    a.a_max = call.maxima; a.y_max = y_max; a.n_edges = n;
+    a.n = w.shared ? lmax + 1 : 1;
+    int groups = 0, groups_sum = 0, most = 0;
+    for (int q = 0; q < a.n; ++q) {
+      So2WgradOrder& o = a.o[q] = orders[first + q];
+      o.first = groups;
+      o.first_sum = groups_sum;
+      groups += (o.quarters * o.chunks + 3) / 4;
+      groups_sum += o.K * o.N / 32;
+      const int nl = lmax + 1 - o.m;
+      most = std::max(most, nl * E * nl * 3 * E);
+    }
+    hipLaunchKernelGGL(so2_wgrad_kernel, dim3(groups), dim3(256), 0, st, a);
+    EGNN_LAUNCH_CHECK(ctx, "so2_wgrad_kernel");
+    hipLaunchKernelGGL(so2_wgrad_sum_kernel, dim3(groups_sum), dim3(256), 0, st, a);
+    EGNN_LAUNCH_CHECK(ctx, "so2_wgrad_sum_kernel");
+    hipLaunchKernelGGL(so2_unpack_wgrad_kernel, dim3((most + 255) / 256, a.n), dim3(256), 0, st, a, dW_so2, lmax, E, full);
+    EGNN_LAUNCH_CHECK(ctx, "so2_unpack_wgrad_kernel");
+  }
+  // dA_m = dY_m B_m^T over A_m: contraction over the N columns of Y_m, one output column per column of A_m
+  if ((rc = so2_products(ctx, call.b, call.T, W_so2, n, full, true, y_max, call.maxima + 1, st))) return rc;
   {
 #define DXE(L)                                                                                                       \
   do {                                                                                                               \
@@ -1538,7 +1672,7 @@ extern "C" int egnn_so2_message_sum_backward(egnn_ctx* ctx, const egnn_graph* g,
   So2Call call;
   if ((rc = so2_transform(ctx, g, pos, box, x, W_e, false, W_so2, ws, &call, st, false))) return rc;
   So2Bwd w;
-  so2_bwd_ws(ctx, n, g->n_owned, false, true, (char*)ws, &w);
+  so2_bwd_carve(ctx, g, false, ws, ws_bytes, &w);
   const So2Grad grad = {da, false, 1.0f / sqrtf(ctx->desc.agg_norm), nullptr, nullptr, nullptr};
   if ((rc = so2_backward_tail(ctx, g, col_ptr, perm, false, W_so2, grad, call, w, dx, dW_so2, nullptr, nullptr, st)))
     return rc;
@@ -1573,7 +1707,7 @@ extern "C" int egnn_so2_edge_block_backward(egnn_ctx* ctx, const egnn_graph* g, 
   So2Call call;
   if ((rc = so2_transform(ctx, g, pos, box, x, T_edge_in, true, W_so2, ws, &call, st, false))) return rc;
   So2Bwd w;
-  so2_bwd_ws(ctx, n, g->n_owned, true, true, (char*)ws, &w);
+  so2_bwd_carve(ctx, g, true, ws, ws_bytes, &w);
   // T' = T + f_c y: the message term has gradient f_c dT', the identity term passes dT' on (added by so2_dx_kernel)
   const So2Grad grad = {dT_out, true, 1.0f, nullptr, nullptr, nullptr};
   return so2_backward_tail(ctx, g, col_ptr, perm, true, W_so2, grad, call, w, dx, dW_so2, dT_in, dT_out, st);
@@ -1606,7 +1740,7 @@ extern "C" int egnn_so2_node_block_backward(egnn_ctx* ctx, const egnn_graph* g, 
                      call.b.ldY[0], w_att, call.alpha, g->n_owned, E);
   EGNN_LAUNCH_CHECK(ctx, "so2_attention_kernel");
   So2Bwd w;
-  so2_bwd_ws(ctx, n, g->n_owned, true, true, (char*)ws, &w);
+  so2_bwd_carve(ctx, g, true, ws, ws_bytes, &w);
   const float4* rd = reinterpret_cast<const float4*>(call.rhat_d);
 #define ATT(L)                                                                                                     \
   hipLaunchKernelGGL(so2_attention_adjoint_kernel<L>, dim3(g->n_owned), dim3(256), 0, st, g->row_ptr, rd, call.b,  \
