@@ -173,7 +173,9 @@ __device__ __forceinline__ double wg_sum(double v, double* red) {
   return r;
 }
 
-// number of entries that are not padding: per block popcount(rows) * popcount(columns)
+// number of entries that are not padding: per block popcount(rows) * popcount(columns); few blocks a thread, as each is two loads one
+// after the other (625,000 blocks: 16 a thread on 153 workgroups 19 us, 4 on 611 7.6)
+#define HL_COUNT_PER_WG 1024
 __global__ __launch_bounds__(256) void present_partial_kernel(long n_blocks, int n_orb,
                                                               const int* __restrict__ row_atom,
                                                               const int* __restrict__ col_atom,
@@ -183,8 +185,9 @@ __global__ __launch_bounds__(256) void present_partial_kernel(long n_blocks, int
   __shared__ double red[256];
   const uint32_t all = n_orb >= 32 ? 0xffffffffu : ((1u << n_orb) - 1u);
   double acc = 0.0;
-  for (int q = 0; q < HL_PER_WG / 256; ++q) {
-    const long blk = (long)blockIdx.x * HL_PER_WG + q * 256 + threadIdx.x;
+#pragma unroll
+  for (int q = 0; q < HL_COUNT_PER_WG / 256; ++q) {
+    const long blk = (long)blockIdx.x * HL_COUNT_PER_WG + q * 256 + threadIdx.x;
     if (blk < n_blocks) {
       const uint32_t rb = ham_bits(species, orb_bits, n_species, row_atom ? row_atom[blk] : (int)blk, all);
       const uint32_t cb = ham_bits(species, orb_bits, n_species, col_atom ? col_atom[blk] : (int)blk, all);
@@ -750,7 +753,7 @@ extern "C" int egnn_loss_l1l2(egnn_ctx* ctx, const float* H, const float* T, int
   if (((uintptr_t)ws & 255) != 0) return egnn_fail(ctx, EGNN_EINVAL, "loss_l1l2: workspace not 256-byte aligned");
   const int bpw = ham_bpw(ctx->n_orb * ctx->n_orb);
   const long nb_v = ((long)n_blocks + bpw - 1) / bpw;                       // workgroups of the loss kernel
-  const long nb_b = ((long)n_blocks + HL_PER_WG - 1) / HL_PER_WG;           // workgroups of the counting kernel (<= nb_v)
+  const long nb_b = ((long)n_blocks + HL_COUNT_PER_WG - 1) / HL_COUNT_PER_WG;   // workgroups of the counting kernel (<= nb_v: bpw <= 1024)
   const size_t need = h256(sizeof(double)) + 3 * h256((size_t)(nb_v + 1) * sizeof(double));
   if (ws_bytes < need) return egnn_fail(ctx, EGNN_EWS, "loss_l1l2: workspace too small");
   if (nb_v > 2147483647L) return egnn_fail(ctx, EGNN_EINVAL, "loss_l1l2: too many blocks");
