@@ -914,7 +914,7 @@ extern "C" int egnn_gate(egnn_ctx* ctx, const float* x, const float* W_g, float*
 //                                                              the edge update)
 // plus, for the node block (ds != NULL), ds_k w_att[c] LeakyReLU'(y_k[L = 0][c]) in the L = 0 plane -- the part that
 // reaches the messages through the attention scores; y_k[L = 0] is read from Y_0 before it is overwritten.  Ordinary stores: the
-// next kernels read the rows (73,000 edges, lmax 4, 32 channels, both blocks 253 us with nontemporal ones, 231 without).
+// next kernels read the rows (73,000 edges, lmax 4, 32 channels, both blocks 252 to 282 us with nontemporal ones, 231 to 253 without).
 template <int LMAX>
 __global__ __launch_bounds__(256) void so2_dy_kernel(const int* __restrict__ dst, const float4* __restrict__ rhat_d,
                                                      const float* __restrict__ rows, bool per_edge,
@@ -1056,7 +1056,7 @@ typedef float sw_f4 __attribute__((ext_vector_type(4)));
 typedef float sw_f2 __attribute__((ext_vector_type(2)));
 // The orders lie one behind the other in the grid, those with the longest chunks first; an order's (chunk, quarter) pairs are
 // numbered chunk by chunk and dealt out four to a workgroup.  73,000 edges, lmax 4, 32 channels, both blocks: a launch per order
-// 843 us, one for all 713; the sums of the partial results and their way into the weights' layout, 22 launches and 193 us, now 4 and 124
+// 843 us, one for all 713, pieces cut with sgh_cut8 675; the sums of the partial results and their way into the weights' layout, 22 launches and 193 us, now 4 and 124
 // (6 TB/s).
 struct So2WgradOrder {
   const float *A, *Y;
@@ -1118,12 +1118,12 @@ __global__ __launch_bounds__(256, 2) void so2_wgrad_kernel(So2WgradArgs p) {
 #pragma unroll
     for (int a = 0; a < 4; ++a) {
       const float x[8] = {ra[0][a], ra[1][a], ra[2][a], ra[3][a], ra[4][a], ra[5][a], ra[6][a], ra[7][a]};
-      sgh_split8(x, a_scale, ah[a], al[a]);
+      sgh_cut8(x, a_scale, ah[a], al[a]);
     }
 #pragma unroll
     for (int q = 0; q < 2; ++q) {
       const float x[8] = {ry[0][q], ry[1][q], ry[2][q], ry[3][q], ry[4][q], ry[5][q], ry[6][q], ry[7][q]};
-      sgh_split8(x, y_scale, yh[q], yl[q]);
+      sgh_cut8(x, y_scale, yh[q], yl[q]);
     }
   };
   auto products = [&]() {

@@ -228,6 +228,25 @@ __device__ __forceinline__ void sgh_split8(const float (&x)[8], float scale, uin
   lo = make_uint4(l[0], l[1], l[2], l[3]);
 }
 
+// The same with pairs as vectors, for a scale that is not known before the kernel runs: v_fma_mixhi_f16 leaves the second value of a
+// pair in the upper half of the first one's register, where pairs put together from bits take two more instructions per pair and piece
+// (so2_wgrad_kernel: 138 instead of 210 vector instructions beside 24 of the matrix cores).  Same bits.  Not for a constant scale of
+// one: that is compiled to v_cvt_pk_f16_f32, with which pieces came out less exact.
+__device__ __forceinline__ void sgh_cut8(const float (&x)[8], float scale, uint4& hi, uint4& lo) {
+  typedef _Float16 h2 __attribute__((ext_vector_type(2)));
+  uint32_t h[4], l[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float x0 = x[2 * q], x1 = x[2 * q + 1];
+    const h2 hp = {(_Float16)__builtin_fmaf(x0, scale, 0.0f), (_Float16)__builtin_fmaf(x1, scale, 0.0f)};
+    const h2 lp = {(_Float16)__builtin_fmaf(x0, scale, -(float)hp.x), (_Float16)__builtin_fmaf(x1, scale, -(float)hp.y)};
+    h[q] = __builtin_bit_cast(uint32_t, hp);
+    l[q] = __builtin_bit_cast(uint32_t, lp);
+  }
+  hi = make_uint4(h[0], h[1], h[2], h[3]);
+  lo = make_uint4(l[0], l[1], l[2], l[3]);
+}
+
 // acc0 / acc1 += A (pieces ah, al) x B (pieces b0 / b1) for one 16-wide contraction step, two column blocks, the two
 // accumulation chains interleaved; smallest terms first
 __device__ __forceinline__ void sgh_mma3x2(uint4 ah, uint4 al, const uint4 (&b0)[2], const uint4 (&b1)[2],
@@ -428,7 +447,7 @@ __device__ __forceinline__ void sghw_contract(const float* __restrict__ A, long 
         b0[0] = brow0[0]; b0[1] = brow0[8]; b1[0] = brow1[0]; b1[1] = brow1[8];
       }
       uint4 ah, al;
-      sgh_split8(xv, a_scale, ah, al);
+      sgh_cut8(xv, a_scale, ah, al);
 #pragma unroll
       for (int cb = 0; cb < NCB; cb += 2) {
         uint4 n0[2], n1[2];
