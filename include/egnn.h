@@ -105,7 +105,8 @@ int egnn_workspace_bytes(const egnn_ctx* ctx, int64_t n_edges, int32_t n_owned, 
  * goes through a cell list (cells of edge >= r_cut, at most 64 per axis); count builds the cells, fill reuses
  * them, so fill must follow count with the same atoms and the same, untouched workspace (a different pos or ws
  * pointer is rejected with EGNN_EINVAL; a workspace overwritten in between gives a wrong list but no access outside
- * the buffers).  With ws == NULL
+ * the buffers).  A workspace shorter than that serves down to the size of the cells alone (2 MB and 8 bytes per atom), the fill pass
+ * then searches again.  With ws == NULL, or one that is shorter still,
  * every destination sweeps all atoms (O(n_owned * n_total), fine for a few thousand atoms).  Both give the
  * same edge list.  count synchronises the stream (edge count; with a workspace and more than 32,768 atoms that are not periodic along
  * every axis a second time: bounding box). */

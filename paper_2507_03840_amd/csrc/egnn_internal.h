@@ -38,6 +38,7 @@ struct egnn_ctx {
   int nl_grid_atoms = -1;                // last egnn_nlist_count that used the cell list: atom counts, workspace and positions
   int nl_grid_owned = 0;
   const void* nl_grid_ws = nullptr;
+  size_t nl_grid_ws_bytes = 0;
   const void* nl_grid_pos = nullptr;
   int use_fused = 0;                     // egnn_set_option(EGNN_OPT_FUSED): 0 by the rules of edge_fused.hip, 1 / 2 older kernels
   bool w_half = false;                   // egnn_set_option(EGNN_OPT_W_FP16)

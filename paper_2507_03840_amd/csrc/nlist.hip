@@ -133,14 +133,29 @@ __global__ void cell_count_kernel(const float* __restrict__ pos, int n_total, Ce
   atomicAdd(&cell_ptr[cell + 1], 1);   // integer count: independent of order
 }
 
-// the atoms in the order of the cells: position and index (order inside a cell is irrelevant: bitmap)
+// The atoms in the order of the cells (order inside a cell is irrelevant: bitmap): position and index, or the index alone where the
+// workspace has no room for more.
+struct CellAtoms {
+  float4* at;
+  int* index;
+  __device__ __forceinline__ void put(int place, const float* __restrict__ pos, int i) const {
+    if (at) at[place] = make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], __int_as_float(i));
+    else index[place] = i;
+  }
+  template <bool PLACED>
+  __device__ __forceinline__ float4 get(int place, const float* __restrict__ pos, int n_total) const {
+    if (PLACED) return at[place];
+    const int i = index[place], r = min(max(i, 0), n_total - 1);
+    return make_float4(pos[3 * r], pos[3 * r + 1], pos[3 * r + 2], __int_as_float(i));
+  }
+};
+
 __global__ void cell_fill_kernel(const float* __restrict__ pos, int n_total, const int* __restrict__ cell_of,
-                                 const int* __restrict__ cell_ptr, int* __restrict__ cursor, float4* __restrict__ cell_atoms) {
+                                 const int* __restrict__ cell_ptr, int* __restrict__ cursor, CellAtoms cell_atoms) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_total) return;
   const int cell = cell_of[i];
-  cell_atoms[cell_ptr[cell] + atomicAdd(&cursor[cell], 1)] =
-      make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], __int_as_float(i));
+  cell_atoms.put(cell_ptr[cell] + atomicAdd(&cursor[cell], 1), pos, i);
 }
 
 // The grid: periodic axes span the box, open axes the bounding box of the atoms (bb: min xyz, max xyz); cell edge >= r_cut (1 + 1e-6), at
@@ -173,7 +188,7 @@ __host__ __device__ inline void cell_grid(const NlistGeom& g, const float* bb, d
 #define NL_BUILD_CELLS 8192
 __global__ __launch_bounds__(1024) void cells_build_kernel(const float* __restrict__ pos, int n_total, NlistGeom g, double rc_pad,
                                                            CellGrid* __restrict__ grid, int* __restrict__ cell_of,
-                                                           int* __restrict__ cell_ptr, float4* __restrict__ cell_atoms) {
+                                                           int* __restrict__ cell_ptr, CellAtoms cell_atoms) {
   __shared__ int s_count[NL_BUILD_CELLS];
   __shared__ float s_box[6][16];
   __shared__ int s_wave[16];
@@ -248,7 +263,7 @@ __global__ __launch_bounds__(1024) void cells_build_kernel(const float* __restri
   __syncthreads();
 #pragma unroll 4
   for (int i = tid; i < n_total; i += 1024)
-    cell_atoms[atomicAdd(&s_count[cell_of[i]], 1)] = make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], __int_as_float(i));
+    cell_atoms.put(atomicAdd(&s_count[cell_of[i]], 1), pos, i);
 }
 static_assert(NL_BUILD_CELLS == 8 * 1024, "eight cells a thread");
 
@@ -276,11 +291,11 @@ struct NlistKeep {
   int* list;       // [n_owned][row]
   int row;
 };
-template <bool FILL>
+template <bool FILL, bool PLACED>
 __global__ __launch_bounds__(256) void nlist_cells_kernel(const float* __restrict__ pos, int n_owned, int n_total,
                                                           NlistGeom g, const CellGrid* __restrict__ grid,
                                                           const int* __restrict__ cell_of, const int* __restrict__ cell_ptr,
-                                                          const float4* __restrict__ cell_atoms, int* __restrict__ row_ptr,
+                                                          CellAtoms cell_atoms, int* __restrict__ row_ptr,
                                                           int* __restrict__ src, int* __restrict__ dst,
                                                           int8_t* __restrict__ shift, NlistKeep keep, int words) {
   extern __shared__ unsigned int lds[];
@@ -376,7 +391,7 @@ __global__ __launch_bounds__(256) void nlist_cells_kernel(const float* __restric
   for (int run = 0; run < 18; ++run) {
     const int r0 = __builtin_amdgcn_readlane(a0, run), r1 = __builtin_amdgcn_readlane(a1, run);
     for (int b = r0; b < r1; b += 64) {
-      const float4 p = cell_atoms[min(b + lane, r1 - 1)];
+      const float4 p = cell_atoms.get<PLACED>(min(b + lane, r1 - 1), pos, n_total);
       const int i = __float_as_int(p.w);
       const float ex = p.x - fx, ey = p.y - fy, ez = p.z - fz;
       const float dx = __builtin_fmaf(-rintf(ex * vx), bx, ex), dy = __builtin_fmaf(-rintf(ey * vy), by, ey),
@@ -527,29 +542,45 @@ struct CellWs {
   int* cell_of;      // [n_total]
   int* cell_ptr;     // [max cells + 1]
   int* cursor;       // [max cells]
-  float4* cell_atoms;   // [n_total]
+  CellAtoms atoms;   // [n_total]
   int* kept;         // [kept_n] sources that the counting pass found
   size_t kept_n;
+  size_t need, need_kept;   // bytes up to the atoms' end, up to the end of what is kept
 };
 
-static size_t carve_cells(char* base, int n_total, CellWs* w) {
+// With room for the indices of the atoms alone (as much as has always been accepted) their positions are gathered, and what lies beyond
+// the positions is for the sources that are kept, down to none.
+static size_t least_cell_bytes(int n_total) {
+  return 256 + 2 * a256((size_t)n_total * sizeof(int)) + a256(((size_t)kMaxCells + 1) * sizeof(int)) + a256((size_t)kMaxCells * sizeof(int));
+}
+static size_t most_cell_bytes(int n_total) {
+  return least_cell_bytes(n_total) - a256((size_t)n_total * sizeof(int)) + a256((size_t)n_total * sizeof(float4)) +
+         a256(std::min<size_t>((size_t)n_total * NL_KEEP, NL_KEEP_MOST) * sizeof(int));
+}
+static CellWs carve_cells(void* ws, size_t ws_bytes, int n_total) {
+  CellWs w = {};
   size_t used = 0;
-  auto take = [&](size_t bytes) { char* p = base ? base + used : nullptr; used += a256(bytes); return p; };
-  w->bbox = (float*)take(6 * sizeof(float));
-  w->grid = (CellGrid*)take(sizeof(CellGrid));
-  w->cell_of = (int*)take((size_t)n_total * sizeof(int));
-  w->cell_ptr = (int*)take(((size_t)kMaxCells + 1) * sizeof(int));
-  w->cursor = (int*)take((size_t)kMaxCells * sizeof(int));
-  w->cell_atoms = (float4*)take((size_t)n_total * sizeof(float4));
-  w->kept_n = std::min<size_t>((size_t)n_total * NL_KEEP, NL_KEEP_MOST);
-  w->kept = (int*)take(w->kept_n * sizeof(int));
-  return used;
+  auto take = [&](size_t bytes) { char* p = (char*)ws + used; used += a256(bytes); return p; };
+  static_assert(128 + sizeof(CellGrid) <= 256, "bounding box and grid share 256 bytes");
+  w.bbox = (float*)take(256);
+  w.grid = (CellGrid*)((char*)w.bbox + 128);
+  w.cell_of = (int*)take((size_t)n_total * sizeof(int));
+  w.cell_ptr = (int*)take(((size_t)kMaxCells + 1) * sizeof(int));
+  w.cursor = (int*)take((size_t)kMaxCells * sizeof(int));
+  if (ws_bytes >= used + a256((size_t)n_total * sizeof(float4)))
+    w.atoms.at = (float4*)take((size_t)n_total * sizeof(float4));
+  else
+    w.atoms.index = (int*)take((size_t)n_total * sizeof(int));
+  w.need = used;
+  w.kept_n = std::min({(size_t)n_total * NL_KEEP, (size_t)NL_KEEP_MOST, (ws_bytes - used) / sizeof(int)});
+  w.kept = (int*)take(w.kept_n * sizeof(int));
+  w.need_kept = (size_t)((char*)(w.kept + w.kept_n) - (char*)ws);
+  return w;
 }
 
 extern "C" int egnn_nlist_workspace_bytes(const egnn_ctx* ctx, int32_t n_total, size_t* bytes) {
   if (!ctx || !bytes || n_total < 0) return EGNN_EINVAL;
-  CellWs w;
-  *bytes = carve_cells(nullptr, n_total, &w);
+  *bytes = most_cell_bytes(n_total);
   return EGNN_OK;
 }
 
@@ -569,25 +600,26 @@ static int nlist_geom(egnn_ctx* ctx, const float* pos, int32_t n_owned, int32_t 
 }
 
 static bool use_cells(const void* ws, size_t ws_bytes, int n_total) {
-  CellWs w;
-  return ws && n_total > 0 && n_total <= NL_MAX_BITMAP_ATOMS && ws_bytes >= carve_cells(nullptr, n_total, &w);
+  return ws && n_total > 0 && n_total <= NL_MAX_BITMAP_ATOMS && ws_bytes >= least_cell_bytes(n_total);
 }
+
+// sources kept per atom
+static int keep_row(const CellWs& w, int n_owned, int n_total) { return (int)std::min<size_t>(w.kept_n / n_owned, n_total); }
 
 template <bool FILL>
 static int launch_cells(egnn_ctx* ctx, const float* pos, int n_owned, int n_total, const NlistGeom& g,
-                        const CellWs& w, int* row_ptr, int* src, int* dst, int8_t* shift, hipStream_t st) {
+                        const CellWs& w, int keep_row, int* row_ptr, int* src, int* dst, int8_t* shift, hipStream_t st) {
   const int words = (n_total + 31) / 32;
   const int waves = words <= 1024 ? 4 : 1;
   const size_t shmem = (size_t)waves * (2 * words + NL_LIST) * sizeof(unsigned int);
+  const auto kernel = w.atoms.at ? nlist_cells_kernel<FILL, true> : nlist_cells_kernel<FILL, false>;
   if (shmem > 64 * 1024) {
-    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(nlist_cells_kernel<FILL>),
-                                             hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
+    const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)shmem);
     if (e != hipSuccess) return egnn_check_hip(ctx, e, "hipFuncSetAttribute(nlist_cells_kernel)");
   }
-  // (rows of sources lie as the counting pass laid them out: for another number of rows there are none)
-  const NlistKeep keep = {w.kept, ctx->nl_grid_owned == n_owned ? (int)std::min<size_t>(w.kept_n / n_owned, n_total) : 0};
-  hipLaunchKernelGGL(nlist_cells_kernel<FILL>, dim3((n_owned + waves - 1) / waves), dim3(64 * waves), shmem, st, pos, n_owned,
-                     n_total, g, w.grid, w.cell_of, w.cell_ptr, w.cell_atoms, row_ptr, src, dst, shift, keep, words);
+  const NlistKeep keep = {w.kept, keep_row};
+  hipLaunchKernelGGL(kernel, dim3((n_owned + waves - 1) / waves), dim3(64 * waves), shmem, st, pos, n_owned,
+                     n_total, g, w.grid, w.cell_of, w.cell_ptr, w.atoms, row_ptr, src, dst, shift, keep, words);
   EGNN_LAUNCH_CHECK(ctx, "nlist_cells_kernel");
   return EGNN_OK;
 }
@@ -603,16 +635,16 @@ extern "C" int egnn_nlist_count(egnn_ctx* ctx, const float* pos, int32_t n_owned
   if (ws && ((uintptr_t)ws & 255) != 0) return egnn_fail(ctx, EGNN_EINVAL, "nlist_count: workspace not 256-byte aligned");
   hipStream_t st = (hipStream_t)stream;
   if (n_owned > 0 && use_cells(ws, ws_bytes, n_total)) {
-    CellWs w;
-    carve_cells((char*)ws, n_total, &w);
+    const CellWs w = carve_cells(ws, ws_bytes, n_total);
     const double rc_pad = (double)ctx->desc.r_cut * (1.0 + 1e-6);
     ctx->nl_grid_atoms = n_total;   // egnn_nlist_fill walks the same cells
     ctx->nl_grid_owned = n_owned;
     ctx->nl_grid_ws = ws;
+    ctx->nl_grid_ws_bytes = ws_bytes;
     ctx->nl_grid_pos = pos;
     if (n_total <= NL_BUILD_ATOMS) {
       hipLaunchKernelGGL(cells_build_kernel, dim3(1), dim3(1024), 0, st, pos, n_total, g, rc_pad, w.grid, w.cell_of, w.cell_ptr,
-                         w.cell_atoms);
+                         w.atoms);
       EGNN_LAUNCH_CHECK(ctx, "cells_build_kernel");
     } else {
       float bb[6] = {};
@@ -630,10 +662,11 @@ extern "C" int egnn_nlist_count(egnn_ctx* ctx, const float* pos, int32_t n_owned
       hipLaunchKernelGGL(cell_count_kernel, ga, b, 0, st, pos, n_total, cg, w.grid, w.cell_of, w.cell_ptr);
       EGNN_LAUNCH_CHECK(ctx, "cell_count_kernel");
       if ((rc = egnn_launch_row_scan(ctx, w.cell_ptr, cg.n_cells, st))) return rc;
-      hipLaunchKernelGGL(cell_fill_kernel, ga, b, 0, st, pos, n_total, w.cell_of, w.cell_ptr, w.cursor, w.cell_atoms);
+      hipLaunchKernelGGL(cell_fill_kernel, ga, b, 0, st, pos, n_total, w.cell_of, w.cell_ptr, w.cursor, w.atoms);
       EGNN_LAUNCH_CHECK(ctx, "cell_fill_kernel");
     }
-    if ((rc = launch_cells<false>(ctx, pos, n_owned, n_total, g, w, row_ptr, nullptr, nullptr, nullptr, st))) return rc;
+    if ((rc = launch_cells<false>(ctx, pos, n_owned, n_total, g, w, keep_row(w, n_owned, n_total), row_ptr, nullptr, nullptr, nullptr, st)))
+      return rc;
   } else if (n_owned > 0) {
     hipLaunchKernelGGL(nlist_sweep_kernel<false>, dim3((n_owned + 3) / 4), dim3(256), 0, st, pos, n_owned, n_total,
                        g, row_ptr, (int*)nullptr, (int*)nullptr, (int8_t*)nullptr);
@@ -661,12 +694,14 @@ extern "C" int egnn_nlist_fill(egnn_ctx* ctx, const float* pos, int32_t n_owned,
   if (n_owned == 0 || n_edges == 0) return EGNN_OK;
   hipStream_t st = (hipStream_t)stream;
   if (use_cells(ws, ws_bytes, n_total)) {
-    // the cells built by egnn_nlist_count, their grid and the sources it found are still in the workspace
-    CellWs w;
-    carve_cells((char*)ws, n_total, &w);
+    // the cells built by egnn_nlist_count, their grid and the sources it found are still in the workspace, laid out for the size it had
     if (ctx->nl_grid_atoms != n_total || ctx->nl_grid_ws != ws || ctx->nl_grid_pos != pos)
       return egnn_fail(ctx, EGNN_EINVAL, "nlist_fill: call egnn_nlist_count with the same atoms and workspace first");
-    return launch_cells<true>(ctx, pos, n_owned, n_total, g, w, const_cast<int*>(row_ptr), src, dst, shift, st);
+    const CellWs w = carve_cells(ws, ctx->nl_grid_ws_bytes, n_total);
+    // (rows of sources lie as the counting pass laid them out: for another number of rows, or where the workspace is now shorter,
+    // there are none)
+    const int row = ctx->nl_grid_owned == n_owned && ws_bytes >= w.need_kept ? keep_row(w, n_owned, n_total) : 0;
+    if (ws_bytes >= w.need) return launch_cells<true>(ctx, pos, n_owned, n_total, g, w, row, const_cast<int*>(row_ptr), src, dst, shift, st);
   }
   hipLaunchKernelGGL(nlist_sweep_kernel<true>, dim3((n_owned + 3) / 4), dim3(256), 0, st, pos, n_owned, n_total, g,
                      const_cast<int*>(row_ptr), src, dst, shift);

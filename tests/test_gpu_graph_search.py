@@ -1,10 +1,13 @@
 """GPU tests of the neighbour search (nlist.hip) where its parts change: cells along an axis from one to several, periodic or not; atoms
 far outside the box; pairs at the cutoff to the last bit; rows longer than what the counting pass keeps; more candidates than are put
 in order at a time; and the row scan at its block sizes."""
+import ctypes as C
+
 import numpy as np
 import pytest
 
 from oracle import egnn_oracle as O
+from tests.test_nlist_workspace import cells_alone
 
 pytestmark = pytest.mark.gpu
 
@@ -57,6 +60,33 @@ def test_rows_and_candidate_lists(B, n, n_owned):
     rng = np.random.default_rng(n)
     row_ptr = _check(B, rng.random((n, 3)), n_owned, [1, 1, 1], [0, 0, 0], 3.0)
     assert np.array_equal(np.diff(row_ptr), np.full(n_owned, n - 1))
+
+
+@pytest.mark.parametrize("n,n_owned", [(700, 611), (33000, 70)])
+def test_shorter_workspaces(B, n, n_owned):
+    """Cells alone; positions in their order, but nothing kept; one source kept per atom; a workspace that is shorter in the filling pass."""
+    import torch
+    rng = np.random.default_rng(n)
+    pos = (rng.random((n, 3)) * 20.0).astype(np.float32)
+    box, pbc = np.array([20.0] * 3, np.float32), np.array([1, 0, 1], np.uint8)
+    r_cut = 3.0 * (700 / n) ** (1 / 3)
+    src, dst, _, row_ptr = O.neighbour_list(pos, n_owned, box, pbc, r_cut)
+    m = B.Egnn(1, 8, 8, r_cut, 1.0)
+    least, most = cells_alone(n), m.egnn_nlist_workspace_bytes(n)
+    positions = least + (16 * n + 255) // 256 * 256 - (4 * n + 255) // 256 * 256
+    p, bx, pb = B.to_device(pos), (C.c_float * 3)(*box), (C.c_uint8 * 3)(*[int(v) for v in pbc])
+    ws = torch.full((most,), -1, dtype=torch.int8, device="cuda").view(torch.uint8)
+    for first, second in ((least, least), (least - 1, least - 1), (positions, positions), (positions - 1, positions - 1),
+                          (positions + 4 * n_owned, positions + 4 * n_owned), (most, most), (most, most - 256), (most, positions),
+                          (most, least), (least, most)):
+        print("case", n, first, second, flush=True)
+        rp, ne = torch.empty(n_owned + 1, dtype=torch.int32, device="cuda"), C.c_int64()
+        m._check(m.lib.egnn_nlist_count(m.ctx, B._ptr(p), n_owned, n, bx, pb, B._ptr(rp), C.byref(ne), B._ptr(ws), C.c_size_t(first), None))
+        assert ne.value == len(src) and np.array_equal(rp.cpu().numpy(), row_ptr)
+        got = [torch.full((len(src),), -1, dtype=torch.int32, device="cuda") for _ in range(2)]
+        m._check(m.lib.egnn_nlist_fill(m.ctx, B._ptr(p), n_owned, n, bx, pb, B._ptr(rp), ne, B._ptr(got[0]), B._ptr(got[1]), None,
+                                       B._ptr(ws), C.c_size_t(second), None))
+        assert np.array_equal(got[0].cpu().numpy(), src) and np.array_equal(got[1].cpu().numpy(), dst)
 
 
 @pytest.mark.parametrize("n_total", [1, 7, 8191, 8193, 32767, 32768, 32769, 40960, 65537, 100000])
