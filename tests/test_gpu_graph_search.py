@@ -1,6 +1,6 @@
 """GPU tests of the neighbour search (nlist.hip) where its parts change: cells along an axis from one to several, periodic or not; atoms
 far outside the box; pairs at the cutoff to the last bit; rows longer than what the counting pass keeps; more candidates than are put
-in order at a time; and the row scan at its block sizes."""
+in order at a time; more atoms or cells than one workgroup builds; and the row scan at its block sizes."""
 import ctypes as C
 
 import numpy as np
@@ -60,6 +60,52 @@ def test_rows_and_candidate_lists(B, n, n_owned):
     rng = np.random.default_rng(n)
     row_ptr = _check(B, rng.random((n, 3)), n_owned, [1, 1, 1], [0, 0, 0], 3.0)
     assert np.array_equal(np.diff(row_ptr), np.full(n_owned, n - 1))
+
+
+@pytest.mark.parametrize("pbc", [(1, 1, 1), (1, 0, 1), (0, 0, 0)])
+@pytest.mark.parametrize("n,n_owned", [(32768, 50), (32769, 50), (70000, 40), (250000, 25), (262144, 20), (262145, 9)])
+def test_large_structures(B, n, n_owned, pbc):
+    """Above 32,768 atoms the cells come from kernels of their own and an atom's wavefront has a workgroup to itself, above 245,760 with more
+    than 64 KB of LDS; above 262,144 all atoms are swept."""
+    rng = np.random.default_rng([n, *pbc])
+    side = (n / 0.05) ** (1 / 3)
+    print("case", n, pbc, flush=True)
+    _check(B, rng.random((n, 3)) * side, n_owned, [side] * 3, pbc, 8.0)
+
+
+@pytest.mark.parametrize("pbc", [(1, 1, 1), (0, 0, 0)])
+@pytest.mark.parametrize("cells", [(32, 16, 16), (33, 16, 16), (64, 2, 64), (64, 64, 64), (17, 23, 41)])
+def test_more_cells_than_are_counted_at_once(B, cells, pbc):
+    """Few atoms in a large box: 8,192 cells are built by one workgroup, more are made coarser."""
+    rng = np.random.default_rng([*cells, *pbc])
+    box = np.array([2.001 * c for c in cells])
+    n = 2500
+    centres = rng.random((60, 3)) * box
+    pos = (centres[rng.integers(0, 60, n)] + rng.normal(size=(n, 3))) % box
+    pos[0], pos[1] = 0.0, np.nextafter(box.astype(np.float32), np.float32(0))       # (an open box is as large as its atoms)
+    print("case", cells, pbc, flush=True)
+    _check(B, pos, n, box, pbc, 2.0)
+
+
+def test_rows_kept_of_many_atoms(B):
+    """16,777,216 sources are kept in all, here 167 of an atom's 130 to 270; every 1,999th row against the oracle, all rows in order."""
+    rng = np.random.default_rng(8)
+    n, side = 100000, 126.0
+    pos, box, pbc = (rng.random((n, 3)) * side).astype(np.float32), np.array([side] * 3, np.float32), np.array([1, 1, 1], np.uint8)
+    m = B.Egnn(1, 8, 8, 10.0, 1.0)
+    g = m.egnn_nlist(B.to_device(pos), n, box, pbc)
+    src, dst, shift, row_ptr = (t.cpu().numpy() for t in (g.src, g.dst, g.shift, g.row_ptr))
+    lengths = np.diff(row_ptr)
+    print("edges", len(src), "rows of", lengths.min(), "to", lengths.max(), flush=True)
+    assert lengths.min() <= 167 < lengths.max() and row_ptr[0] == 0 and row_ptr[-1] == len(src)
+    assert np.array_equal(dst, np.repeat(np.arange(n), lengths))
+    assert (np.diff(src.astype(np.int64) + dst.astype(np.int64) * n) > 0).all()
+    for j in range(0, n, 1999):
+        order = np.concatenate([[j], np.delete(np.arange(n), j)])            # (the oracle's owned atom comes first)
+        s, _, sh, _ = O.neighbour_list(pos[order], 1, box, pbc, 10.0)
+        at = np.argsort(order[s])
+        rows = slice(row_ptr[j], row_ptr[j + 1])
+        assert np.array_equal(src[rows], order[s][at]) and np.array_equal(shift[rows], sh[at]), j
 
 
 @pytest.mark.parametrize("n,n_owned", [(700, 611), (33000, 70)])
