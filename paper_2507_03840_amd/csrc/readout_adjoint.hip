@@ -401,7 +401,9 @@ __global__ __launch_bounds__(256, 2) void ra_bins_kernel(RaArgs g) {
   if (begin < c1) {
     RaV V;
     ra_load_v<0, LE>(g, ch, e, V); ra_load_v<1, LE>(g, ch, e, V); ra_load_v<2, LE>(g, ch, e, V); ra_load_v<3, LE>(g, ch, e, V); ra_load_v<4, LE>(g, ch, e, V);
-    auto edge_at = [&](int at) { return min(max(g.perm[min(at + e, c1 - 1)], 0), (int)g.n_edges - 1); };
+    // (in range only where it becomes an index, a turn after its load: see tp_bins.hip)
+    auto edge_at = [&](int at) { return g.perm[min(at + e, c1 - 1)]; };
+    auto in_range = [&](int k) { return min(max(k, 0), (int)g.n_edges - 1); };
     auto load_q = [&](int k) {
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
@@ -409,7 +411,8 @@ __global__ __launch_bounds__(256, 2) void ra_bins_kernel(RaArgs g) {
         if (lane < RA_S / 4) __builtin_amdgcn_global_load_lds((ra_gp)(p + 4 * lane), (ra_lp)(myQ + i * RA_S), 16, 0, 0);
       }
     };
-    int k1 = edge_at(begin), k2 = edge_at(begin + step), k3 = edge_at(begin + 2 * step);
+    const int k1 = in_range(edge_at(begin));
+    int k2 = in_range(edge_at(begin + step)), k3 = edge_at(begin + 2 * step);
     int s2 = g.src[k2], d2 = g.dst[k2];
     float4 r1 = g.rhat_d[k1], r2 = g.rhat_d[k2];
     ra_load_rows<D, LE>(g.zs + ch0, g.src[k1], myS, lane);
@@ -433,10 +436,10 @@ __global__ __launch_bounds__(256, 2) void ra_bins_kernel(RaArgs g) {
       ra_load_rows<D, LE>(g.zt + ch0, d2, myT, lane);
       load_q(k2);
       r1 = r2;
-      k2 = k3;
-      s2 = g.src[k3];
-      d2 = g.dst[k3];
-      r2 = g.rhat_d[k3];
+      k2 = in_range(k3);
+      s2 = g.src[k2];
+      d2 = g.dst[k2];
+      r2 = g.rhat_d[k2];
       k3 = edge_at(at + 3 * step);
       __builtin_amdgcn_sched_barrier(0);
       BondTrig t;

@@ -11,7 +11,7 @@
 // The rows (2 x 3.2 KB an edge at lmax 4, 32 channels) go from memory to LDS one group ahead, as the rows of a gathered edge come
 // from an L2 at best and nothing else hides that; indices two groups ahead, edge numbers three.
 //
-// 627,000 edges, lmax 4, 32 channels: 590 us, in place of 640 for reading dw (3.4 GB) and 760 of the adjoint kernel's 1,350 for writing it.
+// 627,000 edges, lmax 4, 32 channels: 560 us (605 where an edge number was touched in the turn that loads it), in place of 640 for reading dw (3.4 GB) and 760 of the adjoint kernel's 1,350 for writing it.
 // What bounds it: issue of vector instructions (904 a group and wavefront, at 4.3 cycles of a SIMD each with two wavefronts on it; by the
 // counters waiting for memory takes 17 % of their time, 2.8 GB of the 4 GB of rows miss the L2s and come from the last-level cache).
 #include "egnn_internal.h"
@@ -80,7 +80,10 @@ __global__ __launch_bounds__(256, 2) void tp_bins_kernel(TpBins g) {
     const int row = D << g.log2E;
     float* const myX = sX[wave][0];
     float* const myG = sX[wave][1];
-    auto edge_at = [&](int at) { return min(max(g.perm[min(at + e, c1 - 1)], 0), g.n_edges - 1); };
+    // (a number is put in range only where it becomes an index, a turn after its load: loads return in order, so a touch in the turn of
+    // the load would wait for the rows asked for before it)
+    auto edge_at = [&](int at) { return g.perm[min(at + e, c1 - 1)]; };
+    auto in_range = [&](int k) { return min(max(k, 0), g.n_edges - 1); };
     // rows of the group's edges (j: the lane's own edge's node) to LDS
     auto load_rows = [&](const float* x, int j, float* to) {
 #pragma unroll
@@ -98,7 +101,8 @@ __global__ __launch_bounds__(256, 2) void tp_bins_kernel(TpBins g) {
       }
     };
     constexpr int STEP = 4 * EPW;
-    int k1 = edge_at(begin), k2 = edge_at(begin + STEP), k3 = edge_at(begin + 2 * STEP);
+    const int k1 = in_range(edge_at(begin)), k2 = in_range(edge_at(begin + STEP));
+    int k3 = edge_at(begin + 2 * STEP);
     int s1 = g.src[k1], j1 = g.dst[k1], s2 = g.src[k2], j2 = g.dst[k2];
     float4 r1 = g.rhat_d[k1], r2 = g.rhat_d[k2];
     load_rows(g.h, s1, myX);
@@ -118,9 +122,10 @@ __global__ __launch_bounds__(256, 2) void tp_bins_kernel(TpBins g) {
       load_rows(g.h, s2, myX);
       load_rows(g.da, j2, myG);
       r1 = r2;
-      s2 = g.src[k3];
-      j2 = g.dst[k3];
-      r2 = g.rhat_d[k3];
+      const int k = in_range(k3);
+      s2 = g.src[k];
+      j2 = g.dst[k];
+      r2 = g.rhat_d[k];
       k3 = edge_at(at + 3 * STEP);
       __builtin_amdgcn_sched_barrier(0);
       BondTrig t;
