@@ -9,9 +9,11 @@
 // 16 rows of V as rows, which gives dV; and du comes out of the products with (edge, order) as rows, V's rows contracted, in the
 // lane that goes on with it.
 //
-// 313,000 edges, lmax 4, 32 channels, 13 orbitals: 97 + 795 + 435 us, in place of 1,550 for the adjoint that wrote dw and 333 for reading it.
-// What bounds them: ra_edges the memory between L2 and last-level cache (4 GB: weights and dz), ra_bins the issue of vector instructions
-// (1,200 per four edges and 16 channels, two wavefronts a SIMD) and the hand-over from the matrix cores.
+// 313,000 edges, lmax 4, 32 channels, 13 orbitals: 95 + 705 + 410 us, in place of 1,550 for the adjoint that wrote dw and 333 for reading it.
+// What bounds them, by counters: ra_edges the memory beyond the L2s (3.7 GB of lines miss: weights twice, dz, dq; 5.3 TB/s), with vector
+// instructions issuing in 47 % of the SIMD-cycles, matrix cores busy in 17, 15 % of a wavefront's life in waits (775 us and 34 % where an entry of
+// w_row was touched in the turn that loads it and four registers were spilled); ra_bins the issue of vector instructions (85 %; 1,200 per
+// four edges and 16 channels, two wavefronts a SIMD) and the hand-over from the matrix cores.
 #include <algorithm>
 #include <type_traits>
 #include "egnn_internal.h"
@@ -216,7 +218,6 @@ struct RaDegree {
 };
 
 // ---------------------------------------------------------------------------------------------- dV and dz
-constexpr int ra_young(int P) { return P < 63 ? P : 63; }
 template <int LMAX, int LE>        // 2^LE channels
 __global__ __launch_bounds__(256, 2) void ra_edges_kernel(RaArgs g) {
   if (!g.route[0]) return;
@@ -254,36 +255,39 @@ __global__ __launch_bounds__(256, 2) void ra_edges_kernel(RaArgs g) {
   if (it < i1) {
     float w[P], v[D];
     const unsigned k1 = edge(it), k2 = edge(it + step);
-    auto weights = [&](unsigned row) { return g.w + ((size_t)row * P << LE) + ch; };
+    // (the entry of w_row is decoded only where it becomes an address, a turn after its load: see tp_bins.hip)
+    auto row_of = [&](unsigned k) { return g.w_row ? g.w_row[k] : (int)k; };
+    auto weights = [&](int row) { return g.w + ((size_t)(row < 0 ? ~row : row) * P << LE) + ch; };
     auto target = [&](int d) { return g.zt + ((size_t)d * D << LE) + ch; };
     float4 r1 = g.rhat_d[k1];
     ra_load_rows<D, LE>(g.zs + ch0, g.src[k1], myS, lane);
     load_q(it, myQ);
     {
       const float* const tp = target(g.dst[k1]);
-      const float* const wp = weights((unsigned)egnn_weight_row(g.w_row, k1));
+      const float* const wp = weights(row_of(k1));
 #pragma unroll
       for (int i = 0; i < D; ++i) v[i] = tp[i << LE];
 #pragma unroll
       for (int p = 0; p < P; ++p) w[p] = wp[p << LE];
     }
     int s2 = g.src[k2], d2 = g.dst[k2];
-    unsigned w2 = (unsigned)egnn_weight_row(g.w_row, k2);
+    int w2 = row_of(k2);
     float4 r2 = g.rhat_d[k2];
     float dz[D];
-    int k_done = -1, turn = 0;
-    auto store = [&]() {
-      float* out = g.dz + ((size_t)k_done * D << LE) + ch;
+    long done = -1;                    // first edge of the group whose dz is not stored yet
+    int turn = 0;
+    const int out_at = ((e * D << LE) + ch) * 4;
+    auto store = [&]() {               // (stores past the last edge are dropped; addresses per lane were spilled)
+      const auto out = __builtin_amdgcn_make_buffer_rsrc(g.dz + ((size_t)done * D << LE), 0,
+                                                         ((int)min(4L, g.n_edges - done) * D << LE) * 4, 0x00020000);
 #pragma unroll
-      for (int i = 0; i < D; ++i) __builtin_nontemporal_store(dz[i], out + (i << LE));
+      for (int i = 0; i < D; ++i) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(dz[i]), out, out_at, i << (LE + 2), 2 /* nt */);
     };
     ef_wait_arrived();
     for (; it < i1; it += step) {
-      // Everything but the youngest P loads has arrived: the rows on their way to LDS were asked for before the weights, which are
-      // the last loads of a turn.
-      __builtin_amdgcn_s_waitcnt(0x0F70 | (ra_young(P) & 15) | ((ra_young(P) >> 4) << 14));
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
-      __builtin_amdgcn_wave_barrier();
+      // (The one wait for loads of a turn, weights included, which were asked for in the middle of the turn before.  Leaving those in
+      // flight gains nothing: to copy them, or to use them past loads to LDS, the compiler waits for everything.)
+      ef_wait_arrived();
       float u[RA_D], wn[P];
 #pragma unroll
       for (int i = 0; i < D; ++i) v[i] += myS[e * ES + i * 16 + c];
@@ -292,7 +296,7 @@ __global__ __launch_bounds__(256, 2) void ra_edges_kernel(RaArgs g) {
       turn ^= 1;
       ef_wait_read();
       // (stored only now: a store in flight would hold up the wait above)
-      if (k_done >= 0) store();
+      if (done >= 0) store();
       ra_load_rows<D, LE>(g.zs + ch0, s2, myS, lane);                  // (past the last item: its edges once more, not used)
       load_q(it + step, myQ + turn * 4 * RA_S);
       const float *const tp = target(d2), *const wp = weights(w2);
@@ -300,7 +304,7 @@ __global__ __launch_bounds__(256, 2) void ra_edges_kernel(RaArgs g) {
       const unsigned k3 = edge(it + 2 * step);
       s2 = g.src[k3];
       d2 = g.dst[k3];
-      w2 = (unsigned)egnn_weight_row(g.w_row, k3);
+      w2 = row_of(k3);
       r2 = g.rhat_d[k3];
       __builtin_amdgcn_sched_barrier(0);
       BondTrig t;
@@ -312,8 +316,8 @@ __global__ __launch_bounds__(256, 2) void ra_edges_kernel(RaArgs g) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int i = 0; i < D; ++i) v[i] = tp[i << LE];
-      // (the wavefronts of the two halves of a 128-byte line of weights stay together: 835 -> 795 us; with loads that bypass the
-      // caches 1,020, every line fetched twice)
+      // (the wavefronts of the two halves of a 128-byte line of weights stay together: 40 us less of 835 with the former waits; with
+      // loads that bypass the caches 1,020, every line fetched twice)
       __builtin_amdgcn_s_barrier();
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
@@ -334,11 +338,11 @@ __global__ __launch_bounds__(256, 2) void ra_edges_kernel(RaArgs g) {
       egnn_to_bond_frame<4>(u, t);
       RaDegree<LMAX, 0>::feature(w, u, dz);
       egnn_from_bond_frame<LMAX>(dz, t);
-      k_done = first_edge(it) + e < g.n_edges ? (int)first_edge(it) + e : -1;
+      done = first_edge(it) < g.n_edges ? first_edge(it) : -1;
 #pragma unroll
       for (int p = 0; p < P; ++p) w[p] = wn[p];
     }
-    if (k_done >= 0) store();
+    if (done >= 0) store();
     ef_wait_arrived();                 // (nothing is on its way to LDS when it is used for the sums)
   }
   // one partial [n_vrows][channels] per workgroup: its wavefronts of the same channels added in fixed order

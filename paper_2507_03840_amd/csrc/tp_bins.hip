@@ -12,8 +12,8 @@
 // from an L2 at best and nothing else hides that; indices two groups ahead, edge numbers three.
 //
 // 627,000 edges, lmax 4, 32 channels: 560 us (605 where an edge number was touched in the turn that loads it), in place of 640 for reading dw (3.4 GB) and 760 of the adjoint kernel's 1,350 for writing it.
-// What bounds it: issue of vector instructions (904 a group and wavefront, at 4.3 cycles of a SIMD each with two wavefronts on it; by the
-// counters waiting for memory takes 17 % of their time, 2.8 GB of the 4 GB of rows miss the L2s and come from the last-level cache).
+// What bounds it: issue of vector instructions (945 a group and wavefront, at 3.6 cycles of a SIMD each with two wavefronts on it; by the
+// counters waits take 11 % of their time, 17 with the touch, 2.8 GB of the 4 GB of rows miss the L2s and come from the last-level cache).
 #include "egnn_internal.h"
 #include "bond_frame.h"
 #include "edge_fused.h"

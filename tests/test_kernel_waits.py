@@ -38,8 +38,9 @@ def arithmetic_before_wait(code):
     return n
 
 
-# an edge of lmax 1 takes more than 100 vector instructions in either kernel, one of lmax 4 about 1,000
-@pytest.mark.parametrize("source,kernel,instances", [("tp_bins.hip", "tp_bins_kernel", 12), ("readout_adjoint.hip", "ra_bins_kernel", 16)])
+# an edge of lmax 1 takes more than 100 vector instructions in any of the kernels, one of lmax 4 about 1,000
+@pytest.mark.parametrize("source,kernel,instances", [("tp_bins.hip", "tp_bins_kernel", 12), ("readout_adjoint.hip", "ra_bins_kernel", 16),
+                                                     ("readout_adjoint.hip", "ra_edges_kernel", 16)])
 def test_rows_of_the_next_turn(tmp_path, source, kernel, instances):
     code = {k: v for k, v in kernels(source, tmp_path).items() if kernel in k}
     assert len(code) == instances
