@@ -230,8 +230,10 @@ __device__ __forceinline__ void sgh_split8(const float (&x)[8], float scale, uin
 
 // The same with pairs as vectors, for a scale that is not known before the kernel runs: v_fma_mixhi_f16 leaves the second value of a
 // pair in the upper half of the first one's register, where pairs put together from bits take two more instructions per pair and piece
-// (so2_wgrad_kernel: 138 instead of 210 vector instructions beside 24 of the matrix cores).  Same bits.  Not for a constant scale of
-// one: that is compiled to v_cvt_pk_f16_f32, with which pieces came out less exact.
+// (so2_wgrad_kernel: 138 instead of 210 vector instructions beside 24 of the matrix cores).  Same bits.
+// The remainder is taken from the stored pair: without the empty asm the compiler makes a high piece a second time for it, and where x is a
+// product it may round one of the two once (v_fma_mixlo_f16) and the other twice (v_mul_f32, v_cvt_pk_f16_f32).  They then differ by 2^-11 of
+// the value near halfway cases.  (A power of two as the scale is exact either way.)
 __device__ __forceinline__ void sgh_cut8(const float (&x)[8], float scale, uint4& hi, uint4& lo) {
   typedef _Float16 h2 __attribute__((ext_vector_type(2)));
   uint32_t h[4], l[4];
@@ -239,8 +241,10 @@ __device__ __forceinline__ void sgh_cut8(const float (&x)[8], float scale, uint4
   for (int q = 0; q < 4; ++q) {
     const float x0 = x[2 * q], x1 = x[2 * q + 1];
     const h2 hp = {(_Float16)__builtin_fmaf(x0, scale, 0.0f), (_Float16)__builtin_fmaf(x1, scale, 0.0f)};
-    const h2 lp = {(_Float16)__builtin_fmaf(x0, scale, -(float)hp.x), (_Float16)__builtin_fmaf(x1, scale, -(float)hp.y)};
     h[q] = __builtin_bit_cast(uint32_t, hp);
+    asm("" : "+v"(h[q]));
+    const h2 kept = __builtin_bit_cast(h2, h[q]);
+    const h2 lp = {(_Float16)__builtin_fmaf(x0, scale, -(float)kept.x), (_Float16)__builtin_fmaf(x1, scale, -(float)kept.y)};
     l[q] = __builtin_bit_cast(uint32_t, lp);
   }
   hi = make_uint4(h[0], h[1], h[2], h[3]);

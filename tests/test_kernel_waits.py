@@ -1,5 +1,6 @@
-"""What the compiler makes of kernels that ask for the next turn's rows ahead: the turn's arithmetic lies between the loads and the first wait
-for them.  Loads return in order, so that one touch of a value loaded last would wait for all of them.  Compiled here to assembly (gfx950)."""
+"""What the compiler makes of kernels, read from their assembly (gfx950, compiled here).  Kernels that ask for the next turn's rows ahead: the
+turn's arithmetic lies between the loads and the first wait for them (loads return in order, so that one touch of a value loaded last would
+wait for all of them).  Half-precision pieces: every one made once."""
 import os
 import re
 import subprocess
@@ -12,7 +13,7 @@ pytestmark = pytest.mark.skipif(not os.path.exists(build.HIPCC), reason="no comp
 
 
 def kernels(source, tmp):
-    out = str(tmp / (source + ".s"))
+    out = str(tmp / (os.path.basename(source) + ".s"))
     subprocess.run([build.HIPCC, *build.FLAGS, "-w", "-S", "--cuda-device-only", source, "-o", out], cwd=build.CSRC, check=True,
                    stderr=subprocess.DEVNULL)
     found, name = {}, None
@@ -48,3 +49,24 @@ def test_rows_of_the_next_turn(tmp_path, source, kernel, instances):
         print(name, arithmetic_before_wait(lines))
         assert arithmetic_before_wait(lines) > 100, name
         assert not any(s.startswith("scratch_") for s in lines), name
+
+
+@pytest.mark.parametrize("values,scale", [("a[8 * i + q]", "s"), ("a[8 * i + q]", "1.0f"), ("a[8 * i + q] * b[8 * i + q]", "s"),
+                                          ("a[8 * i + q] * b[8 * i + q]", "1.0f")])
+def test_pieces_are_made_once(tmp_path, values, scale):
+    """sgh_cut8: eight values take sixteen roundings to half precision; one more, and a remainder is that of another high piece."""
+    source = tmp_path / "cut.hip"
+    source.write_text(f'''
+#include "{build.CSRC}/egnn_internal.h"
+#include "{build.CSRC}/stream_gemm.h"
+__global__ void cut(const float* a, const float* b, uint4* out, float s) {{
+  const int i = threadIdx.x;
+  float x[8];
+  for (int q = 0; q < 8; ++q) x[q] = {values};
+  sgh_cut8(x, {scale}, out[2 * i], out[2 * i + 1]);
+}}''')
+    (lines,) = kernels(str(source), tmp_path).values()
+    ops = [s.split()[0] for s in lines]
+    one = sum(o.startswith(("v_fma_mixlo_f16", "v_fma_mixhi_f16", "v_cvt_f16_f32")) for o in ops)
+    two = sum(o.startswith("v_cvt_pk") and "f16_f32" in o for o in ops)
+    assert one + 2 * two == 16
