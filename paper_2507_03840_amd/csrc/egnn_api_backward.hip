@@ -169,9 +169,10 @@ static int layer_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32_t
   // on the grid route the gradients of the weights are made where they are summed per length interval
   const bool bins = egnn_tp_bins_fits(ctx, g->n_edges);
   int* route = bins ? egnn_radial_backward_route(b.radial) : nullptr;
-  const EgnnBins made = [&](const int* bin_ptr, const int* len_perm, float* Zp) {
+  const auto make = [&](const int* bin_ptr, const int* len_perm, float* Zp) {
     return egnn_launch_tp_bins(ctx, {g->src, g->dst, b.h, b.da}, b.rhat_d, g->n_edges, bin_ptr, len_perm, Zp, route, st);
   };
+  const EgnnBins made(make);
   if (bins && (rc = egnn_launch_radial_route(ctx, W_r1, route, st))) return rc;
   if ((rc = egnn_launch_tp_backward(ctx, g, col_ptr, perm, b.rhat_d, b.h, w, b.da, b.dh, b.dw, dw_max, st, shared, route)))
     return rc;
@@ -291,9 +292,10 @@ static int readout_backward_impl(egnn_ctx* ctx, const egnn_graph* g, const int32
   const bool bins = egnn_readout_adjoint_fits(ctx, g->n_edges);
   int* route = bins ? egnn_radial_backward_route(b.radial) : nullptr;
   const ReadoutAdjoint adj = {b.rhat_d, b.zs, b.zt, w, V, b.dw, b.dz, b.dV_partial, route, shared};
-  const EgnnBins made = [&](const int* bin_ptr, const int* len_perm, float* Zp) {
+  const auto make = [&](const int* bin_ptr, const int* len_perm, float* Zp) {
     return egnn_launch_readout_bins(ctx, g, adj, bin_ptr, len_perm, Zp, st);
   };
+  const EgnnBins made(make);
   if (bins && (rc = egnn_launch_radial_route(ctx, W_r1, route, st))) return rc;
   if ((rc = egnn_launch_readout_backward(ctx, g, b.rhat_d, b.zs, b.zt, w, V, b.tab_i, b.tab_f, dH, b.dz, b.dw, dV,
                                          b.dV_partial, st, shared, route)))

@@ -2,7 +2,6 @@
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
-#include <functional>
 #include <string>
 #include <vector>
 #include "../../include/egnn.h"
@@ -125,7 +124,17 @@ int egnn_launch_length_bins(egnn_ctx*, const float4* rd, int64_t n_edges, int* b
                             int* cursor, const int* route, hipStream_t, const egnn_graph* g = nullptr, const float* pos = nullptr,
                             const float* box = nullptr);
 // made (may be NULL): makes the gradients and bins them (tp_bins.hip, readout_adjoint.hip), instead of the pass over dw
-using EgnnBins = std::function<int(const int* bin_ptr, const int* perm, float* Zp)>;
+// (refers to a callable that outlives the call: nothing is allocated, so nothing can be thrown through a C entry)
+struct EgnnBins {
+  const void* what;
+  int (*call)(const void* what, const int* bin_ptr, const int* perm, float* Zp);
+  template <class F>
+  explicit EgnnBins(const F& f)
+      : what(&f), call([](const void* w, const int* b, const int* p, float* Z) { return (*static_cast<const F*>(w))(b, p, Z); }) {}
+  template <class F>
+  explicit EgnnBins(const F&&) = delete;
+  int operator()(const int* bin_ptr, const int* perm, float* Zp) const { return call(what, bin_ptr, perm, Zp); }
+};
 struct TpBinsArgs {
   const int *src, *dst;
   const float *h, *da;      // features [n_total][D][E], gradients of the summed messages [n_owned][D][E]

@@ -230,7 +230,7 @@ __device__ __forceinline__ void sgh_split8(const float (&x)[8], float scale, uin
 
 // The same with pairs as vectors, for a scale that is not known before the kernel runs: v_fma_mixhi_f16 leaves the second value of a
 // pair in the upper half of the first one's register, where pairs put together from bits take two more instructions per pair and piece
-// (so2_wgrad_kernel: 138 instead of 210 vector instructions beside 24 of the matrix cores).  Same bits.
+// (so2_wgrad_kernel: 114 instead of 210 vector instructions beside 24 of the matrix cores).  Same bits.
 // The remainder is taken from the stored pair: without the empty asm the compiler makes a high piece a second time for it, and where x is a
 // product it may round one of the two once (v_fma_mixlo_f16) and the other twice (v_mul_f32, v_cvt_pk_f16_f32).  They then differ by 2^-11 of
 // the value near halfway cases.  (A power of two as the scale is exact either way.)

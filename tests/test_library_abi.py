@@ -31,6 +31,11 @@ def test_every_declared_symbol_is_exported(B):
         assert hasattr(lib, name), name
 
 
+def test_no_callback_that_allocates(B):
+    """std::function may allocate, and throw through a C entry."""
+    assert b"bad_function_call" not in open(B.LIB_PATH, "rb").read()
+
+
 @pytest.mark.parametrize("lmax", [0, 1, 2, 3, 4])
 def test_path_tables_match_definition(B, lmax):
     m = B.Egnn(lmax, 32, 16, 8.0, 50.0)
