@@ -159,7 +159,6 @@ __global__ __launch_bounds__(256) void padding_kernel(float* __restrict__ H, lon
 }
 
 // ------------------------------------------------------------------------------------------------ L1 + L2 loss
-#define HL_PER_WG 4096
 typedef float ham_f4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ double wg_sum(double v, double* red) {
   red[threadIdx.x] = v;
