@@ -93,7 +93,7 @@ extern "C" int egnn_backward_workspace_bytes(const egnn_ctx* ctx, int64_t n_edge
   ReadoutBwdBufs rb;
   size_t a = carve_layer_bwd(ctx, &g, nullptr, &lb);
   size_t b = ctx->n_orb > 0 ? carve_readout_bwd(ctx, &g, nullptr, &rb) : 0;
-  size_t c = egnn_transpose_ws_bytes(n_edges, n_total);
+  size_t c = egnn_transpose_ws_bytes(n_edges);
   size_t m = a > b ? a : b;
   *bytes = (m > c ? m : c) + 256;
   return EGNN_OK;

@@ -147,7 +147,7 @@ int egnn_launch_radial_grid(egnn_ctx*, int which, const float* rhat_d, int64_t n
 bool egnn_tp_bins_fits(const egnn_ctx*, int64_t n_edges);
 int egnn_launch_tp_bins(egnn_ctx*, const TpBinsArgs&, const float* rhat_d, int64_t n_edges, const int* bin_ptr, const int* perm,
                         float* Zp, const int* route, hipStream_t);
-size_t egnn_transpose_ws_bytes(int64_t n_edges, int32_t n_total);
+size_t egnn_transpose_ws_bytes(int64_t n_edges);
 // dw_max (may be NULL): a word the caller has set to zero; raised to the bit pattern of the largest |dw| written.
 // route (may be NULL): a device word; where it is 1, dw is left unwritten
 int egnn_launch_tp_backward(egnn_ctx*, const egnn_graph*, const int* col_ptr, const int* perm, const float* rhat_d,

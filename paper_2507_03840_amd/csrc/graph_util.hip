@@ -227,23 +227,21 @@ int egnn_launch_reduce_partials(egnn_ctx* ctx, float* partial, int n_partials, l
   return EGNN_OK;
 }
 
-size_t egnn_transpose_ws_bytes(int64_t n_edges, int32_t n_total) {
-  return (((size_t)n_total * sizeof(int) + 255) & ~(size_t)255) + (((size_t)n_edges * sizeof(int) + 255) & ~(size_t)255);
-}
+size_t egnn_transpose_ws_bytes(int64_t n_edges) { return ((size_t)n_edges * sizeof(int) + 255) & ~(size_t)255; }
 
 extern "C" int egnn_graph_transpose(egnn_ctx* ctx, const egnn_graph* g, int32_t* col_ptr, int32_t* perm, void* ws,
                                     size_t ws_bytes, void* stream) {
   if (!ctx) return EGNN_EINVAL;
   if (!g || !col_ptr || g->n_edges < 0 || g->n_total < 0 || (g->n_edges > 0 && (!g->src || !perm || !ws)))
     return egnn_fail(ctx, EGNN_EINVAL, "graph_transpose: null pointer or bad sizes");
-  if (g->n_edges > 0 && ws_bytes < egnn_transpose_ws_bytes(g->n_edges, g->n_total))
+  if (g->n_edges > 0 && ws_bytes < egnn_transpose_ws_bytes(g->n_edges))
     return egnn_fail(ctx, EGNN_EWS, "graph_transpose: workspace too small");
   hipStream_t st = (hipStream_t)stream;
   const long n_e = g->n_edges;
   int rc;
   if ((rc = egnn_launch_fill_int(ctx, col_ptr, (long)g->n_total + 1, 0, st))) return rc;
   if (n_e == 0) return EGNN_OK;
-  int* bucket = (int*)((char*)ws + (((size_t)g->n_total * sizeof(int) + 255) & ~(size_t)255));
+  int* bucket = (int*)ws;
   const dim3 ge((unsigned)((n_e + 255) / 256)), b(256);
   hipLaunchKernelGGL(count_src_kernel, ge, b, 0, st, g->src, n_e, col_ptr, perm);   // (perm is free until the sort)
   EGNN_LAUNCH_CHECK(ctx, "count_src_kernel");

@@ -56,6 +56,17 @@ def test_create_rejects_bad_descriptors(B):
         assert e.value.code == -1, kw
 
 
+def test_transpose_asks_for_one_word_per_edge(B):
+    """Nothing but the buckets lies in the workspace: whatever the number of atoms, a word per edge is not too small (EGNN_EWS), a byte less is."""
+    m = B.Egnn(1, 8, 8, 4.0, 1.0)
+    at, n_edges = ctypes.c_void_p(4096), 640
+    g = B.GraphDesc(4096, 4096, 4096, None, n_edges, 100, 50000, None, 0, None, None)
+    call = lambda n: m.lib.egnn_graph_transpose(m.ctx, ctypes.byref(g), at, at, at, ctypes.c_size_t(n), None)
+    if not os.path.exists("/dev/kfd"):                      # (without a GPU nothing is launched)
+        assert call(4 * n_edges) != -3
+    assert call(4 * n_edges - 1) == -3
+
+
 def test_workspace_bytes_cover_every_buffer(B):
     m = B.Egnn(4, 32, 16, 10.0, 200.0)
     n_e, n_o, n_t = 625_000, 3000, 3000
