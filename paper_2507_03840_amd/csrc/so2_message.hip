@@ -661,13 +661,14 @@ static int so2_transform(egnn_ctx* ctx, const egnn_graph* g, const float* pos, c
 
 // Whether the message sum mixes channels per node (so2_node.hip): what that costs per node, which depends on lmax and on
 // channels below a full tile of 32, has to be worth the edges' part of the per-edge products.  us per call, per edge -> per
-// node, at the degrees where it turns: 4,000 nodes, lmax 4: 8 channels, 30.5 edges a node 260 -> 296, 43.6 367 -> 305; 16
-// channels, 25.5 367 -> 372, 30.5 395 -> 376; 32 channels (10,000 nodes), 24.3 1,265 -> 1,332, 31.2 1,535 -> 1,345; 64
-// channels, 20.7 1,159 -> 1,189, 23.8 1,292 -> 1,188; 128 channels, 20.7 3,566 -> 2,670.  Lower lmax gains from 20 on (lmax 3:
-// 16 channels 214 -> 206, 64 714 -> 591; lmax 2: 32 channels 277 -> 123).  On few nodes the per-edge kernels, two per order,
-// are bound by their launches: 1,000 nodes, lmax 4, 20.6 edges: 16 channels 158 -> 120, 32 224 -> 154, 64 439 -> 350, but 8 100
-// -> 104 (25.3: 110 -> 105; 16 nodes 68 -> 42).  At lmax 0 there is only one order, and small calls gain nothing: 8 channels x
-// 7,000 edges 31 -> 33, x 13,600 44 -> 33; 32 x 1,200 31 -> 32, x 2,300 34 -> 33; 64 x 725 37 -> 34. Its buffers must fit the
+// node, at the degrees where it turns: 4,000 nodes, lmax 4: 8 channels, 32.2 edges a node 237 -> 295, 38.9 289 -> 309; 16
+// channels, 28.7 337 -> 376, 38.9 430 -> 389; 32 channels, 23.1 540 -> 555, 28.7 646 -> 557; 64 channels, 16.4 980 -> 1,139, 23.1
+// 1,331 -> 1,168; 128 channels, 20.1 3,503 -> 2,940.  Lower lmax gains from 20 on (lmax 3: 16 channels 187 -> 202, 25.8 227 -> 202,
+// 64 712 -> 587; lmax 2: 32 channels 264 -> 120).  On few nodes the per-edge kernels fill the chip no better: 1,000 nodes, lmax 4, 20.2 edges:
+// 32 channels 162 -> 152, 64 353 -> 342.  (With fewer channels they are the faster ones there since the orders share a launch, 16 channels 84 ->
+// 116, 32.1 128 -> 119, 8 at 28.7 72 -> 103; but their error against 64 bits is the larger one, 2.9e-7 -> 2.4e-7 at both, so the line stays.)
+// At lmax 0 there is only one order, and small calls gain nothing: 8 channels x 4,800 edges 32 -> 34, x 16,500 46 -> 33; 32 x 1,400 30 -> 32,
+// x 3,900 36 -> 33; 64 x 1,400 35 -> 35. Its buffers must fit the
 // workspace the caller was asked for (about 15 edges a node; many halo rows may not), and byte offsets of feature rows 32 bits.
 #define SO2N_FEW_NODES 1500
 static bool so2_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
@@ -684,13 +685,14 @@ static bool so2_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
 
 // The node block by the same means, with a pass over all edges for the attention scores first and a second gathering launch for
 // the edges' own rows, so it turns later.  us per call, per edge -> per node: from 32 edges a node: lmax 4, 64 channels, 4,000
-// nodes, 37.7 2,947 -> 2,585; lmax 3, 32 channels, 37.7 690 -> 651; lmax 2, 8 channels, 33.5 193 -> 168.  At lmax 4 with fewer
-// channels later: 32 channels, 37.7 1,144 -> 1,159, 50 1,528 -> 1,226 (1,000 nodes, 37.3 379 -> 343); 16, 43.6 750 -> 812, 64
-// 1,054 -> 922 (1,000 nodes, 43.2 245 -> 234); 8, 43.6 497 -> 622, 62 677 -> 661 (100 nodes, 36.2 88 -> 74); so too lmax 1 with
-// 8: 33.5 112 -> 133, 61 76 -> 69.  Small calls of lmax 0 and 1 are bound by launches, of which this has three more: 8
-// channels, lmax 1, 4,700 edges 45 -> 48, 13,600 56 -> 53; lmax 0, 16 channels, 4,700 39 -> 44, 13,600 67 -> 52; 32 channels,
-// 4,700 54 -> 50; 64 channels, 1,200 50 -> 57, 2,400 76 -> 58.  And lmax 0 with up to 16 channels is bound by the edges'
-// offsets from 300,000 edges on (134,000 131 -> 105, 387,000 163 -> 168, 632,000 223 -> 258).  128 channels stay per edge (the
+// nodes, 32.2 2,466 -> 2,405; lmax 3, 32 channels, 36.5 610 -> 641, 47 776 -> 685; lmax 2, 8 channels, 36.5 173 -> 172.  At lmax 4 with fewer
+// channels later: 32 channels, 36.5 1,015 -> 1,140, 47 1,278 -> 1,201; 16, 47 704 -> 812, 58 869 -> 869; 8, 58 580 -> 662, 67 679 -> 697;
+// so too lmax 1 with 8: 47 123 -> 144, 58 154 -> 153.  (Up to 1,000 nodes the per-edge kernels are faster to higher degrees since the orders share a
+// launch: lmax 4, 1,000 nodes, 32 channels, 36.2 290 -> 338, 57.7 438 -> 385; 100 nodes, 53 107 -> 131, 8 channels 48 -> 79; but their error
+// against 64 bits is the larger one, 5.8e-7 -> 4.2e-7 and 4.6e-7 -> 3.9e-7 there, so the lines stay.)
+// Small calls of lmax 0 and 1 are bound by launches: lmax 0, 32 channels, 2,200 edges 40 -> 45, 5,000 55 -> 47; 64 channels, 1,600 49 -> 55,
+// 3,400 76 -> 57; 16 channels, 16,500 74 -> 53.  And lmax 0 with up to 16 channels is bound by the edges'
+// offsets from 300,000 edges on (8 channels, 113,000 130 -> 95, 424,000 170 -> 156, 626,000 212 -> 198).  128 channels stay per edge (the
 // score kernel's sums are laid out for two blocks of 32).
 static size_t so2_block_nodes_ws(const egnn_ctx* ctx, const egnn_graph* g, char* base, float** rhat_d, float** alpha, So2nCall* c) {
   size_t used = 0;
@@ -715,26 +717,25 @@ static bool so2_block_use_nodes(const egnn_ctx* ctx, const egnn_graph* g) {
              so2_ws(ctx, g->n_edges, true, false, nullptr, nullptr, nullptr, nullptr, nullptr);
 }
 
-// Whether the edge block runs as one kernel over tiles of edges (so2_edge.hip).  us per call, per-edge kernels -> tiles (of 64 edges;
-// those of 32 take 0.66 to 0.99 of their time at all of these sizes): lmax
-// 4, 32 channels, 3,000 nodes with 209 / 37.8 / 1.6 edges each 5,000 -> 3,450 / 985 -> 713 / 216 -> 98; lmax 4, 64 channels,
-// 37.8 2,528 -> 2,085; lmax 2, 16 channels 225 -> 128; 100 nodes 61 -> 30 to 346 -> 154.  With 128 channels every tile of edges
-// would be rotated four times (lmax 2, 37.8 edges 1,907 -> 2,957), and 8 are half a matrix instruction: both stay per edge. 
-// Few degrees have few units of work for a tile's waves (lmax 0 a single one), so there only calls that the per-edge
-// kernels spend on launches gain: lmax 0, 16 and 32 channels, 140,000 edges 137 -> 65 and 154 -> 110, 235,000 132 -> 109 and
-// 167 -> 184, 390,000 153 -> 172 and 218 -> 282; with 64 channels, whose rows are rotated twice, lmax 0, 13,600 136 -> 49,
-// 36,000 99 -> 104, 630,000 577 -> 1,609; lmax 1, 30,000 165 -> 140, 43,000 182 -> 195, 256,000 676 -> 978; lmax 2, 43,000 332
-// -> 319, 64,000 401 -> 430, 256,000 1,523 -> 1,707. With 64 channels the two blocks of output channels are two workgroups that
-// both read the whole row, so an update in place is written to the workspace first (*in_place; the copy of 729 MB takes 0.24 of
-// 2.22 ms at 37.8 edges, per edge 2.32).
+// Whether the edge block runs as one kernel over tiles of edges (so2_edge.hip).  us per call, per-edge kernels -> tiles: lmax
+// 4, 32 channels, 626,000 / 85,700 / 13,000 edges 4,750 -> 2,990 / 656 -> 462 / 147 -> 92; lmax 4, 64 channels,
+// 85,700 1,720 -> 1,440; lmax 2, 16 channels 167 -> 88; 994 edges 27 -> 22 to 135 -> 119.  With 128 channels every tile of edges
+// would be rotated four times (tiles of 64 at lmax 2, 113,000 edges 1,907 -> 2,957), and 8 are half a matrix instruction: both stay per edge.
+// Few degrees have few units of work for a tile's waves (lmax 0 a single one), so there large calls are better off per edge: lmax 0, 16
+// channels 626,000 edges 211 -> 177, 1,890,000 550 -> 551; 32 channels 626,000 322 -> 282, 1,890,000 879 -> 906; with 64 channels, whose
+// rows are rotated twice, lmax 0, 85,700 155 -> 136, 256,000 281 -> 386; lmax 1, 85,700 260 -> 196, 626,000 1,405 -> 1,471. With 64
+// channels the two blocks of output channels are two workgroups that both read the whole row, so an update in place is written to the
+// workspace first (*in_place), and turns earlier: lmax 1, 85,700 259 -> 238, 256,000 631 -> 701; lmax 2, 28,700 213 -> 209, 85,700 516 -> 567
+// (out of place 516 -> 489).  One line for both, as their results are the same bits.  Error against 64 bits of either way 5e-8 to 1e-7, of the
+// tiles' no larger.
 static bool so2_block_use_tiles(const egnn_ctx* ctx, const egnn_graph* g, const float* T_in, const float* T_out, bool* in_place) {
   const int lmax = ctx->desc.lmax, E = ctx->desc.channels;
   const size_t row = (size_t)(lmax + 1) * (lmax + 1) * E * 4, all = (size_t)g->n_edges * row;
   const uintptr_t in = (uintptr_t)T_in, out = (uintptr_t)T_out;
   *in_place = E > 32 && in < out + all && out < in + all;
   int64_t most = INT64_MAX;
-  if (E == 64 && lmax <= 2) most = lmax == 2 ? 50000 : 32000;
-  else if (lmax == 0) most = E == 16 ? 300000 : 200000;
+  if (E == 64 && lmax <= 2) most = lmax == 2 ? 50000 : lmax == 1 ? 90000 : 100000;
+  else if (lmax == 0) most = E == 16 ? 1800000 : 1000000;
   return E >= 16 && E <= 64 && g->n_edges <= most && ((size_t)g->n_total + 1) * row < 0xFFFFFFFFu &&
          so2_a256((size_t)g->n_edges * 16) + 256 + so2_a256(so2e_weight_bytes(ctx)) + (*in_place ? all : 0) <=
              so2_ws(ctx, g->n_edges, true, false, nullptr, nullptr, nullptr, nullptr, nullptr);
@@ -1619,13 +1620,14 @@ static int so2_backward_check(egnn_ctx* ctx, const egnn_graph* g, const void* ws
 
 // As so2_use_nodes, per node of any kind: the sums over outgoing edges are taken for the halo nodes as well.  They are all that
 // is gathered, so the turn comes earlier than in the sum itself.  us per call, per edge -> per node.  Above 1,500 nodes: lmax 4,
-// 9,000 nodes, 32 channels 13.1 edges a node 1,719 -> 1,516 (4,000 nodes, 11.8 871 -> 726), 64 13.1 4,058 -> 3,420, 128 13.1
-// 11,945 -> 10,027; fewer channels leave the tiles of columns partly empty: 16, 13.1 982 -> 1,011, 14.8 1,101 -> 1,013 (20,000
-// nodes, 14.9 2,118 -> 2,086), 8, 14.8 741 -> 775, 19.2 886 -> 787 (20,000, 16.4 1,515 -> 1,604, 19.0 1,710 -> 1,620).  lmax 3,
-// 20,000 nodes: 32 channels 7.1 1,410 -> 1,548, 8.9 1,686 -> 1,551; 64 8.9 3,570 -> 3,479; 16 8.9 956 -> 1,118, 10.8 equal, 13.2
-// 1,309 -> 1,119.  lmax 2, 20,000 nodes: 64 channels 3.8 1,102 -> 1,355, 6.0 1,509 -> 1,357; 8 6.0 404 -> 391; 128 6.0 equal, 8.3
-// 4,816 -> 3,645.  Up to 1,500 nodes the per-edge route is bound by its launches: 1,000 nodes, lmax 4, 32 channels 9.3 395 ->
-// 215, 64 9.3 637 -> 473, 16 6.9 278 -> 166; lmax 3, 64 channels 4.7 368 -> 247; lmax 2, 32 channels 2.4 179 -> 102.  (At
+// 12,000 nodes, 32 channels 11.8 edges a node 1,802 -> 1,939, 13.1 1,984 -> 1,934, 64 11.8 4,535 -> 4,586, 13.1 4,960 -> 4,603, 128 11.8
+// 13,648 -> 13,401; fewer channels leave the tiles of columns partly empty: 16, 13.1 1,094 -> 1,291, 15.4 1,255 -> 1,299, 17.4 1,405 -> 1,309;
+// 8, 17.4 911 -> 1,004, 20 1,027 -> 1,009.  lmax 3: 32 channels 8.1 916 -> 985, 9.3 1,012 -> 982; 64 8.1 1,851 -> 2,050, 9.3 2,098 -> 2,050; 16
+// 10.5 661 -> 695, 11.8 713 -> 701.  lmax 2: 64 channels 3.6 702 -> 778, 5.8 914 -> 781; 8 5.8 279 -> 280; 128 5.8 2,001 -> 2,214, 6.9
+// 2,354 -> 2,219.  Up to 1,500 nodes the tiles of the per-edge products fill the chip less well: 1,000 nodes, lmax 4, 32 channels 8.0 248 ->
+// 210, 64 9.2 533 -> 466; lmax 3, 64 channels 5.8 302 -> 243; lmax 2, 32 channels 2.4 102 -> 99.  (With fewer channels at lmax 4 they are the
+// faster ones there since the orders share a launch, 16 channels 8.0 146 -> 160, 8 120 -> 143 at 10.4, but the error of the
+// features' gradient against 64 bits is theirs to lose, 3.3e-7 -> 2.9e-7 and 2.7e-7 -> 2.4e-7: the line stays.)  (At
 // lmax 0 and 1 it would pay from 2 edges a node on as well, but with so few products per element the weight gradient's error
 // against 64 bits would rise from 2.7e-7 to 3.0e-7: from 12 edges as ever.)
 static bool so2_use_nodes_backward(const egnn_ctx* ctx, const egnn_graph* g) {
