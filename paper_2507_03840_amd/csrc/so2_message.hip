@@ -1412,9 +1412,10 @@ __global__ __launch_bounds__(256) void so2_dwe_kernel(const float4* __restrict__
   }
 }
 
-// chunks of edges of the weight gradient of one order.  All waves of a launch take the same time, so their number
-// should fill the chip's places once (256 compute units x 4 SIMDs x 2 waves, what the kernel's registers allow), not
-// one and a third times.  Every chunk is a multiple of SW_BLOCK edges and at least `least`: SW_LEAST where the orders share
+// chunks of edges of the weight gradient of one order.  All waves of an order take the same time, so in a launch of its own their
+// number should fill the chip's places once (256 compute units x 4 SIMDs x 2 waves, what the kernel's registers allow), not
+// one and a third times.  Orders that share a launch keep that number each, the longest chunks first; one length for all would leave
+// fewer partial results to write and add (270 MB at 73,000 edges, lmax 4, 32 channels), which has not been measured.  Every chunk is a multiple of SW_BLOCK edges and at least `least`: SW_LEAST where the orders share
 // a launch (a chunk of one block would write 32 KB of partial results for the 12 KB it reads).
 #define SW_LEAST (4 * SW_BLOCK)
 #define SW_WAVE_SLOTS 2048
@@ -1803,7 +1804,7 @@ __global__ __launch_bounds__(256) void so2_gate_backward_kernel(const float* __r
 
 // partial[chunk][l-1][c][c'] = sum over the nodes n of the chunk of dz[n][l-1][c] x[n][L = 0][c'].  grid = (chunks, lmax);
 // a thread owns the S outputs o = tid + 256 s (c' = o mod E: neighbouring threads, neighbouring columns).  S = 64 for any E kept what 128
-// channels need, in scratch memory: 901 nodes, lmax 4, 32 channels 42 -> 5 us.
+// channels need, in scratch memory: 901 nodes, lmax 4, 32 channels 42 -> 5 us.  (128 channels still do: 587 registers spilled.)
 #define GATE_WGRAD_CHUNKS 64
 #define GATE_WGRAD_BATCH 8
 template <int S>
