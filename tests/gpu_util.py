@@ -1,4 +1,7 @@
 """Shared helpers of the GPU parity tests: build both sides from one seeded workload."""
+import re
+from functools import lru_cache
+
 import numpy as np
 from oracle import egnn_oracle as O
 from paper_2507_03840_amd import synth
@@ -218,32 +221,39 @@ def gpu_training_step(w, wt, agg, T, repeats=1, timing=None, keep=False, shared_
     return out
 
 
+@lru_cache(maxsize=None)
+def _internal_name(path, name):
+    """What the library calls a function of its own, whatever its arguments are."""
+    found = set(re.findall(rb"_Z%d%s[0-9A-Za-z_]*" % (len(name), name.encode()), open(path, "rb").read()))
+    assert len(found) == 1, (name, found)
+    return found.pop().decode()
+
+
+def _rule(m, name, *args):
+    import ctypes as C
+    f = getattr(m.lib, _internal_name(m.lib._name, name))
+    f.restype = C.c_bool
+    return bool(f(m.ctx, *args))
+
+
 def fused_route(B, m, which, n_edges, n_owned, n_total):
     """Whether a call on a graph of these sizes takes the kernel that keeps the radial weights in registers (which = "layer" or
     "readout"): the library's own rule, asked without a GPU."""
     import ctypes as C
-    names = dict(layer="_Z20egnn_edge_fused_fitsPK8egnn_ctxPK10egnn_graph",
-                 readout="_Z23egnn_readout_fused_fitsPK8egnn_ctxPK10egnn_graph")
-    f = getattr(m.lib, names[which])
-    f.restype = C.c_bool
     g = B.GraphDesc(None, None, None, None, n_edges, n_owned, n_total, None, 0, None, None)
-    return bool(f(m.ctx, C.byref(g)))
+    return _rule(m, dict(layer="egnn_edge_fused_fits", readout="egnn_readout_fused_fits")[which], C.byref(g))
 
 
 def tp_bins_route(m, n_edges):
     """Whether the adjoint of a layer on so many edges sums the radial weights' gradient as it is made: the library's own rule."""
     import ctypes as C
-    f = m.lib._Z17egnn_tp_bins_fitsPK8egnn_ctxl
-    f.restype = C.c_bool
-    return bool(f(m.ctx, C.c_int64(n_edges)))
+    return _rule(m, "egnn_tp_bins_fits", C.c_int64(n_edges))
 
 
 def readout_adjoint_route(m, n_edges):
     """The same for the adjoint of the readout."""
     import ctypes as C
-    f = m.lib._Z25egnn_readout_adjoint_fitsPK8egnn_ctxl
-    f.restype = C.c_bool
-    return bool(f(m.ctx, C.c_int64(n_edges)))
+    return _rule(m, "egnn_readout_adjoint_fits", C.c_int64(n_edges))
 
 
 def recorded_nodes(lib, call):
