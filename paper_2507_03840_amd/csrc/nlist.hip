@@ -138,8 +138,9 @@ __global__ void cell_count_kernel(const float* __restrict__ pos, int n_total, Ce
 struct CellAtoms {
   float4* at;
   int* index;
+  template <bool PLACED>
   __device__ __forceinline__ void put(int place, const float* __restrict__ pos, int i) const {
-    if (at) at[place] = make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], __int_as_float(i));
+    if (PLACED) at[place] = make_float4(pos[3 * i], pos[3 * i + 1], pos[3 * i + 2], __int_as_float(i));
     else index[place] = i;
   }
   template <bool PLACED>
@@ -150,12 +151,13 @@ struct CellAtoms {
   }
 };
 
+template <bool PLACED>
 __global__ void cell_fill_kernel(const float* __restrict__ pos, int n_total, const int* __restrict__ cell_of,
                                  const int* __restrict__ cell_ptr, int* __restrict__ cursor, CellAtoms cell_atoms) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n_total) return;
   const int cell = cell_of[i];
-  cell_atoms.put(cell_ptr[cell] + atomicAdd(&cursor[cell], 1), pos, i);
+  cell_atoms.put<PLACED>(cell_ptr[cell] + atomicAdd(&cursor[cell], 1), pos, i);
 }
 
 // The grid: periodic axes span the box, open axes the bounding box of the atoms (bb: min xyz, max xyz); cell edge >= r_cut (1 + 1e-6), at
@@ -186,6 +188,7 @@ __host__ __device__ inline void cell_grid(const NlistGeom& g, const float* bb, d
 // memory, scan) it took 52 us of kernels and a read-back at 20,000 atoms, now 26.
 #define NL_BUILD_ATOMS 32768
 #define NL_BUILD_CELLS 8192
+template <bool PLACED>
 __global__ __launch_bounds__(1024) void cells_build_kernel(const float* __restrict__ pos, int n_total, NlistGeom g, double rc_pad,
                                                            CellGrid* __restrict__ grid, int* __restrict__ cell_of,
                                                            int* __restrict__ cell_ptr, CellAtoms cell_atoms) {
@@ -263,7 +266,7 @@ __global__ __launch_bounds__(1024) void cells_build_kernel(const float* __restri
   __syncthreads();
 #pragma unroll 4
   for (int i = tid; i < n_total; i += 1024)
-    cell_atoms.put(atomicAdd(&s_count[cell_of[i]], 1), pos, i);
+    cell_atoms.put<PLACED>(atomicAdd(&s_count[cell_of[i]], 1), pos, i);
 }
 static_assert(NL_BUILD_CELLS == 8 * 1024, "eight cells a thread");
 
@@ -643,7 +646,7 @@ extern "C" int egnn_nlist_count(egnn_ctx* ctx, const float* pos, int32_t n_owned
     ctx->nl_grid_ws_bytes = ws_bytes;
     ctx->nl_grid_pos = pos;
     if (n_total <= NL_BUILD_ATOMS) {
-      hipLaunchKernelGGL(cells_build_kernel, dim3(1), dim3(1024), 0, st, pos, n_total, g, rc_pad, w.grid, w.cell_of, w.cell_ptr,
+      hipLaunchKernelGGL(w.atoms.at ? cells_build_kernel<true> : cells_build_kernel<false>, dim3(1), dim3(1024), 0, st, pos, n_total, g, rc_pad, w.grid, w.cell_of, w.cell_ptr,
                          w.atoms);
       EGNN_LAUNCH_CHECK(ctx, "cells_build_kernel");
     } else {
@@ -662,7 +665,7 @@ extern "C" int egnn_nlist_count(egnn_ctx* ctx, const float* pos, int32_t n_owned
       hipLaunchKernelGGL(cell_count_kernel, ga, b, 0, st, pos, n_total, cg, w.grid, w.cell_of, w.cell_ptr);
       EGNN_LAUNCH_CHECK(ctx, "cell_count_kernel");
       if ((rc = egnn_launch_row_scan(ctx, w.cell_ptr, cg.n_cells, st))) return rc;
-      hipLaunchKernelGGL(cell_fill_kernel, ga, b, 0, st, pos, n_total, w.cell_of, w.cell_ptr, w.cursor, w.atoms);
+      hipLaunchKernelGGL(w.atoms.at ? cell_fill_kernel<true> : cell_fill_kernel<false>, ga, b, 0, st, pos, n_total, w.cell_of, w.cell_ptr, w.cursor, w.atoms);
       EGNN_LAUNCH_CHECK(ctx, "cell_fill_kernel");
     }
     if ((rc = launch_cells<false>(ctx, pos, n_owned, n_total, g, w, keep_row(w, n_owned, n_total), row_ptr, nullptr, nullptr, nullptr, st)))
