@@ -376,21 +376,25 @@ def run_config(args, index, extras):
             ms_k, calls_k = m.egnn_timing_read()
             m.egnn_timing_enable(0)
             # stages of the reverse pass (HIP events of the library on the launch stream) with the bytes each one
-            # has to move at least: tp_backward reads w and writes dw; the readout adjoint reads w and dH and writes
-            # dw and dz; the radial MLP's reverse pass reads dw once (grid route; the exact route reads it twice)
+            # has to move at least: tp_backward reads w; the readout adjoint reads w and dH, writes dz, and writes and reads
+            # the collapsed gradients (248 words an edge); the radial MLP's reverse pass makes dw from node rows and moves
+            # little.  On small graphs (fewer than 12,000 edges at these channels) dw lies in memory: written by the first
+            # two, read once by the third.
+            made = n_edges >= 12000
             wbytes = 4 * n_edges * m.n_paths * w.channels
             wbytes_ro = 4 * n_edges * m.n_paths_readout * w.channels
             row = 4 * m.dim * w.channels
             adj = {n: ms_k[10 + i] / max(1, calls_k[2]) for i, n in enumerate(B.LAYER_ADJOINT_STAGES)}
             adj_ro = {n: ms_k[15 + i] / max(1, calls_k[3]) for i, n in enumerate(B.READOUT_ADJOINT_STAGES)}
-            stage_bytes = dict(tp_backward=2 * wbytes, radial_backward=wbytes,
-                               readout_backward=2 * wbytes_ro + n_edges * (row + 4 * w.n_orb * w.n_orb))
+            stage_bytes = dict(tp_backward=wbytes if made else 2 * wbytes, radial_backward=None if made else wbytes,
+                               readout_backward=(wbytes_ro if made else 2 * wbytes_ro)
+                               + n_edges * (row + 4 * w.n_orb * w.n_orb + (2 * 4 * 248 if made else 0)))
+            rate = lambda stage, ms: None if stage_bytes[stage] is None else stage_bytes[stage] / ms[stage] / 1e6
             reverse = dict(layer_ms=adj, readout_ms=adj_ro,
-                           tp_backward_GBs=stage_bytes["tp_backward"] / adj["tp_backward"] / 1e6,
-                           radial_backward_GBs=stage_bytes["radial_backward"] / adj["radial_backward"] / 1e6,
-                           readout_backward_GBs=stage_bytes["readout_backward"] / adj_ro["readout_backward"] / 1e6,
+                           tp_backward_GBs=rate("tp_backward", adj), radial_backward_GBs=rate("radial_backward", adj),
+                           readout_backward_GBs=rate("readout_backward", adj_ro),
                            note="per call, forward quantities kept; GB/s = the bytes the stage has to move at least "
-                                "(w, dw, dz, dH) over its time, against 8,000 GB/s")
+                                "(w, dz, dH, collapsed gradients; dw where it lies in memory) over its time, against 8,000 GB/s")
             training = dict(ms_per_step=1e3 * dt, steps=args.train_steps, loss=float(loss.cpu()[0]),
                             edge_layer_evaluations_per_s=n_edges * w.n_layers / dt,
                             step="layers fwd + readout + MSE + readout bwd + layers bwd (forward recomputed inside bwd)",
