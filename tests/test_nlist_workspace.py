@@ -5,6 +5,9 @@ import os
 
 import pytest
 
+# (the pointers are made up: a library that sweeps would launch kernels on them where there is a GPU)
+pytestmark = pytest.mark.skipif(os.path.exists("/dev/kfd"), reason="asked where nothing can be launched")
+
 
 @pytest.fixture(scope="module")
 def B():
